@@ -122,6 +122,7 @@ template <> struct Elem<GPUOS_F32> {
   template <int POL> static DEV void store1(void* p, uint32_t i, float f) { Mem<POL>::st4(p, i, __builtin_bit_cast(uint32_t, f)); }
   template <int POL> static DEV void copy1(void* o, const void* a, uint32_t i) { Mem<POL>::st4(o, i, Mem<POL>::ld4(a, i)); }
 };
+template <> struct Elem<GPUOS_I32> { static constexpr int V = 4, ES = 4; };      // moved and combined as words
 // 16-bit elements are taken out of and put into a 32-bit word as the halves of a two-element vector:
 // the compiler then reads a half with the conversion instruction's own operand selector and writes
 // two converted values with one pack (fp16) or one packed conversion (bf16), where shifts and
@@ -1022,9 +1023,16 @@ PATHFN void ew_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
 // ---------------------------------------------------------------------------
 // reductions over the last dim
 // ---------------------------------------------------------------------------
-template <int RIMPL> DEV float red_identity() {
-  return RIMPL == GPUOS_IMPL_SUM_LAST ? 0.0f : (RIMPL == GPUOS_IMPL_MAX_LAST ? -__builtin_inff() : __builtin_inff());
-}
+// The accumulator of a reduction over elements of dtype DT: fp32 for the float types, int32 for I32.
+template <int DT> struct RedAcc { typedef float T; };
+template <> struct RedAcc<GPUOS_I32> { typedef int32_t T; };
+template <int RIMPL, class T> DEV T red_identity();
+template <> DEV float red_identity<GPUOS_IMPL_SUM_LAST, float>() { return 0.0f; }
+template <> DEV float red_identity<GPUOS_IMPL_MAX_LAST, float>() { return -__builtin_inff(); }
+template <> DEV float red_identity<GPUOS_IMPL_MIN_LAST, float>() { return __builtin_inff(); }
+template <> DEV int32_t red_identity<GPUOS_IMPL_SUM_LAST, int32_t>() { return 0; }
+template <> DEV int32_t red_identity<GPUOS_IMPL_MAX_LAST, int32_t>() { return (int32_t)0x80000000; }
+template <> DEV int32_t red_identity<GPUOS_IMPL_MIN_LAST, int32_t>() { return 0x7fffffff; }
 template <int RIMPL> DEV float red_combine(float a, float b) {
   if (RIMPL == GPUOS_IMPL_SUM_LAST) return a + b;
   if (a != a) return a;                               // max / min propagate NaN
@@ -1032,10 +1040,7 @@ template <int RIMPL> DEV float red_combine(float a, float b) {
   if (RIMPL == GPUOS_IMPL_MAX_LAST) return a > b ? a : b;
   return a < b ? a : b;
 }
-template <int RIMPL> DEV int32_t red_identity_i() {
-  return RIMPL == GPUOS_IMPL_SUM_LAST ? 0 : (RIMPL == GPUOS_IMPL_MAX_LAST ? (int32_t)0x80000000 : 0x7fffffff);
-}
-template <int RIMPL> DEV int32_t red_combine_i(int32_t a, int32_t b) {
+template <int RIMPL> DEV int32_t red_combine(int32_t a, int32_t b) {
   if (RIMPL == GPUOS_IMPL_SUM_LAST) return (int32_t)((uint32_t)a + (uint32_t)b);
   if (RIMPL == GPUOS_IMPL_MAX_LAST) return a > b ? a : b;
   return a < b ? a : b;
@@ -1058,7 +1063,7 @@ template <int OFF> DEV float butterfly_partner(float v) {
 }
 
 // all-reduce over the `width` lanes (power of two <= 64, aligned) a lane belongs to
-template <int RIMPL> DEV float wave_reduce(float acc, uint32_t width) {
+template <int RIMPL, class T> DEV T wave_reduce(T acc, uint32_t width) {
   if (width > 32) acc = red_combine<RIMPL>(acc, butterfly_partner<32>(acc));
   if (width > 16) acc = red_combine<RIMPL>(acc, butterfly_partner<16>(acc));
   if (width > 8) acc = red_combine<RIMPL>(acc, butterfly_partner<8>(acc));
@@ -1067,20 +1072,16 @@ template <int RIMPL> DEV float wave_reduce(float acc, uint32_t width) {
   if (width > 1) acc = red_combine<RIMPL>(acc, butterfly_partner<1>(acc));
   return acc;
 }
-template <int RIMPL> DEV int32_t wave_reduce_i(int32_t acc, uint32_t width) {
-  if (width > 32) acc = red_combine_i<RIMPL>(acc, butterfly_partner<32>(acc));
-  if (width > 16) acc = red_combine_i<RIMPL>(acc, butterfly_partner<16>(acc));
-  if (width > 8) acc = red_combine_i<RIMPL>(acc, butterfly_partner<8>(acc));
-  if (width > 4) acc = red_combine_i<RIMPL>(acc, butterfly_partner<4>(acc));
-  if (width > 2) acc = red_combine_i<RIMPL>(acc, butterfly_partner<2>(acc));
-  if (width > 1) acc = red_combine_i<RIMPL>(acc, butterfly_partner<1>(acc));
-  return acc;
-}
 
 // PATH_RED_CONTIG: input is a contiguous [rows, n] matrix of dtype DT, output a
-// contiguous vector [rows] of any float dtype.  The rows of a chunk are read as one flat
-// run of 16-byte vectors aligned to the tensor base, whatever n is: a vector that straddles
-// a row boundary is loaded by both rows and masked per element.  Three shapes of work:
+// contiguous vector [rows] of any float dtype (I32 for I32).  The rows of a chunk are read as one
+// flat run of 16-byte vectors of the address space, whatever n and the base's alignment are: a
+// vector that straddles a row boundary is loaded by both rows and masked per element.  (The first
+// and the last vector of the run may hold bytes outside the tensor, in the same aligned 16 bytes as
+// one of its elements and so in the same page; they are masked like another row's.)  I32 rows take
+// the same way: with one wavefront per row and one word per lane and load, whatever the row length,
+// 24 integer operations of 0.1-50 MB took 529 us, a 13,946 x 22 maximum among them 505; now 95.
+// Three shapes of work:
 //   short rows  (span <= 64 vectors): P lanes per row, 64 / P rows per wavefront pass,
 //               four passes in flight;
 //   medium rows: one wavefront per row, RA rows at a time, UN loads per row in flight;
@@ -1089,6 +1090,8 @@ template <int RIMPL> DEV int32_t wave_reduce_i(int32_t acc, uint32_t width) {
 // Per-element accumulation.  SUM adds.  MAX / MIN must propagate NaN: the running value ignores
 // NaN (one compare + select) and `nan` remembers whether one was seen (one unordered compare,
 // or-ed into a wavefront-uniform mask register); red_finish folds the two before the lanes are combined.
+template <int RIMPL> DEV int32_t red_step(int32_t acc, int32_t x, bool&) { return red_combine<RIMPL>(acc, x); }
+template <int RIMPL> DEV int32_t red_finish(int32_t acc, bool) { return acc; }
 template <int RIMPL> DEV float red_step(float acc, float x, bool& nan) {
   if (RIMPL == GPUOS_IMPL_SUM_LAST) return acc + x;
   nan = nan || (x != x);
@@ -1113,14 +1116,17 @@ template <int RIMPL> DEV float red_step2(float acc, float x0, float x1, bool& na
   return r;
 }
 
+template <int DT> DEV typename RedAcc<DT>::T red_get(const v4i& q, int k) { return Elem<DT>::get(q, k); }
+template <> DEV int32_t red_get<GPUOS_I32>(const v4i& q, int k) { return q[k]; }
+
 template <int RIMPL, int DT>
-DEV float red_vector(const v4i& q, uint32_t f0, uint32_t lo, uint32_t hi, bool edge, float acc, bool& nan) {
+DEV typename RedAcc<DT>::T red_vector(const v4i& q, uint32_t f0, uint32_t lo, uint32_t hi, bool edge, typename RedAcc<DT>::T acc, bool& nan) {
   // q holds elements f0 .. f0+V-1 of the flat run; the row is [lo, hi)
   using E = Elem<DT>;
   if (!edge) {
-    if (RIMPL == GPUOS_IMPL_SUM_LAST) {
+    if constexpr (RIMPL == GPUOS_IMPL_SUM_LAST || DT == GPUOS_I32) {
 #pragma unroll
-      for (int k = 0; k < E::V; ++k) acc = red_step<RIMPL>(acc, E::get(q, k), nan);
+      for (int k = 0; k < E::V; ++k) acc = red_step<RIMPL>(acc, red_get<DT>(q, k), nan);
     } else {
 #pragma unroll
       for (int k = 0; k < E::V; k += 2) acc = red_step2<RIMPL>(acc, E::get(q, k), E::get(q, k + 1), nan);
@@ -1128,16 +1134,20 @@ DEV float red_vector(const v4i& q, uint32_t f0, uint32_t lo, uint32_t hi, bool e
   } else {
 #pragma unroll
     for (int k = 0; k < E::V; ++k)
-      if (f0 + k >= lo && f0 + k < hi) acc = red_step<RIMPL>(acc, E::get(q, k), nan);
+      if (f0 + k >= lo && f0 + k < hi) acc = red_step<RIMPL>(acc, red_get<DT>(q, k), nan);
   }
   return acc;
 }
 
+// the result of one row: of any float dtype, or the bits of an int32
+template <int POL> DEV void red_store(void* p, uint32_t i, uint32_t dt, float v) { store_rt<POL>(p, i, dt, v); }
+template <int POL> DEV void red_store(void* p, uint32_t i, uint32_t, int32_t v) { Mem<POL>::st4(p, i, (uint32_t)v); }
 
 struct RedArgs {       // what a row-reduction variant is called with (plain values: see lds_arg)
   const char* base;    // first byte of the run: the tensor base advanced to the chunk's first vector
   uint32_t bytes;      // length of the run, whole vectors
-  uint32_t base_elem;  // first element of the run (multiple of V), relative to the tensor
+  uint32_t base_elem;  // first element of the run (multiple of V), counted from the 16-byte block the tensor begins in
+  uint32_t lead;       // elements of that block in front of the tensor
   uint32_t n;
   char* po;
   uint32_t odt, row_begin, row_end, max_span;
@@ -1145,13 +1155,13 @@ struct RedArgs {       // what a row-reduction variant is called with (plain val
 };
 struct RedRun {        // the chunk's rows as a flat run of vectors
   rsrc_t rin;
-  uint32_t base_elem;
+  uint32_t skew;       // row r begins at element r * n + skew of the run (modulo 2^32)
   uint32_t n;
 };
 DEV RedRun red_run(const RedArgs& a) {
   RedRun run;
   run.rin = make_rsrc(uni_ptr((uint64_t)a.base), uni(a.bytes));
-  run.base_elem = uni(a.base_elem);
+  run.skew = uni(a.lead) - uni(a.base_elem);
   run.n = uni(a.n);
   return run;
 }
@@ -1162,22 +1172,23 @@ PATHFN void red_rows_wave(RedArgs a) {
   char* po = (char*)uni_ptr((uint64_t)a.po);
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end);
   using E = Elem<DT>;
+  using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
   constexpr uint32_t V = E::V;
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   const uint32_t n = run.n;
   // wave w takes rows row_begin + w, + 4, + 8, ... ; RA of them at a time
   for (uint32_t row0 = row_begin + wave; row0 < row_end; row0 += 4 * RA) {
-    float acc[RA];
+    A acc[RA];
     bool nan[RA];
     uint32_t lo[RA], hi[RA], j0[RA], j1[RA];
     uint32_t span = 0;
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
-      acc[i] = red_identity<RIMPL>();
+      acc[i] = red_identity<RIMPL, A>();
       nan[i] = false;
       const uint32_t row = row0 + 4 * i;
-      lo[i] = row * n - run.base_elem;
+      lo[i] = row * n + run.skew;
       hi[i] = lo[i] + n;
       j0[i] = lo[i] / V;
       j1[i] = (hi[i] - 1) / V;
@@ -1205,8 +1216,8 @@ PATHFN void red_rows_wave(RedArgs a) {
     }
 #pragma unroll
     for (int i = 0; i < RA; ++i) {
-      const float t = wave_reduce<RIMPL>(red_finish<RIMPL>(acc[i], nan[i]), 64);
-      if (lane == 0 && row0 + 4 * i < row_end) store_rt<POL>(po, row0 + 4 * i, odt, t);
+      const A t = wave_reduce<RIMPL>(red_finish<RIMPL>(acc[i], nan[i]), 64);
+      if (lane == 0 && row0 + 4 * i < row_end) red_store<POL>(po, row0 + 4 * i, odt, t);
     }
   }
 }
@@ -1220,18 +1231,19 @@ PATHFN void red_rows_quarter(RedArgs a) {
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end);
   float* s_part = lds_arg(a.s_part);
   using E = Elem<DT>;
+  using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
   constexpr uint32_t V = E::V;
   constexpr int UN = 8;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint32_t n = run.n;
   for (uint32_t row = row_begin; row < row_end; ++row) {
-    const uint32_t lo = row * n - run.base_elem, hi = lo + n;
+    const uint32_t lo = row * n + run.skew, hi = lo + n;
     const uint32_t j0 = lo / V, j1 = (hi - 1) / V;
     const uint32_t span = j1 - j0 + 1, sq = (span + 3u) / 4u;          // vectors per quarter
     const uint32_t q_begin = j0 + wave * sq;
     const uint32_t q_end = (q_begin + sq <= j1 + 1) ? q_begin + sq : j1 + 1;
-    float a0 = red_identity<RIMPL>(), a1 = a0;
+    A a0 = red_identity<RIMPL, A>(), a1 = a0;
     bool nan = false;
     for (uint32_t v = q_begin + lane; v < q_end; v += 64 * UN) {
       v4i q[UN];
@@ -1246,15 +1258,15 @@ PATHFN void red_rows_quarter(RedArgs a) {
         }
       }
     }
-    const float t = wave_reduce<RIMPL>(red_finish<RIMPL>(red_combine<RIMPL>(a0, a1), nan), 64);
-    if (lane == 0) s_part[(row - row_begin) * 4 + wave] = t;
+    const A t = wave_reduce<RIMPL>(red_finish<RIMPL>(red_combine<RIMPL>(a0, a1), nan), 64);
+    if (lane == 0) s_part[(row - row_begin) * 4 + wave] = __builtin_bit_cast(float, t);
   }
   __syncthreads();
   const uint32_t nrows = row_end - row_begin;
   if (tid < nrows) {
-    const float* p = s_part + tid * 4;
-    const float t = red_combine<RIMPL>(red_combine<RIMPL>(p[0], p[1]), red_combine<RIMPL>(p[2], p[3]));
-    store_rt<POL>(po, row_begin + tid, odt, t);
+    const A* p = (const A*)(s_part + tid * 4);
+    const A t = red_combine<RIMPL>(red_combine<RIMPL>(p[0], p[1]), red_combine<RIMPL>(p[2], p[3]));
+    red_store<POL>(po, row_begin + tid, odt, t);
   }
   __syncthreads();
 }
@@ -1265,6 +1277,7 @@ PATHFN void red_rows_short(RedArgs a) {
   char* po = (char*)uni_ptr((uint64_t)a.po);
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end), max_span = uni(a.max_span);
   using E = Elem<DT>;
+  using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
   constexpr uint32_t V = E::V;
   constexpr int UP = 8;
@@ -1281,32 +1294,32 @@ PATHFN void red_rows_short(RedArgs a) {
 #pragma unroll
     for (int u = 0; u < UP; ++u) {
       const uint32_t row = base + u * rpw + sub;
-      lo[u] = row * n - run.base_elem;
+      lo[u] = row * n + run.skew;
       hi[u] = lo[u] + n;
       j0[u] = lo[u] / V;
       j1[u] = (hi[u] - 1) / V;
       q[u] = M::ld16(run.rin, (row < row_end && j0[u] + j <= j1[u]) ? (j0[u] + j) * 16u : kNoLoad);
     }
-    float mine = 0.0f;                                // lane L ends up with the result of row base + L
+    A mine = 0;                                // lane L ends up with the result of row base + L
 #pragma unroll
     for (int u = 0; u < UP; ++u) {
       const uint32_t row = base + u * rpw + sub;
       const uint32_t jj = j0[u] + j;
-      float acc = red_identity<RIMPL>();
+      A acc = red_identity<RIMPL, A>();
       bool nan = false;
       if (row < row_end && jj <= j1[u])
         acc = red_vector<RIMPL, DT>(q[u], jj * V, lo[u], hi[u], jj == j0[u] || jj == j1[u], acc, nan);
       acc = wave_reduce<RIMPL>(red_finish<RIMPL>(acc, nan), P);
       // every lane of sub-group s now holds the result of row base + u * rpw + s
       if (gather) {
-        const float got = __shfl(acc, (int)((lane & (rpw - 1u)) * P), 64);
+        const A got = __shfl(acc, (int)((lane & (rpw - 1u)) * P), 64);
         if (lane / rpw == (uint32_t)u) mine = got;
       } else if (row < row_end && j == 0) {
-        store_rt<POL>(po, row, odt, acc);            // rows of one or two vectors: the owners are adjacent lanes already
+        red_store<POL>(po, row, odt, acc);            // rows of one or two vectors: the owners are adjacent lanes already
       }
     }
     // UP * rpw consecutive rows, one lane each: a coalesced store instead of one 4-byte store per row
-    if (gather && lane < UP * rpw && base + lane < row_end) store_rt<POL>(po, base + lane, odt, mine);
+    if (gather && lane < UP * rpw && base + lane < row_end) red_store<POL>(po, base + lane, odt, mine);
   }
 }
 
@@ -1318,6 +1331,7 @@ PATHFN void red_rows_short_aligned(RedArgs a) {
   const RedRun run = red_run(a);
   char* po = (char*)uni_ptr((uint64_t)a.po);
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end), vpr = uni(a.max_span);
+  using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
   constexpr int UP = 8;
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
@@ -1333,22 +1347,22 @@ PATHFN void red_rows_short_aligned(RedArgs a) {
       const uint32_t row = base + u * rpw + sub;
       q[u] = M::ld16(run.rin, (row < row_end && mine) ? ((row - row_begin) * vpr + j) * 16u : kNoLoad);
     }
-    float res = 0.0f;                                 // lane L ends up with the result of row base + L
+    A res = 0;                                 // lane L ends up with the result of row base + L
 #pragma unroll
     for (int u = 0; u < UP; ++u) {
       const uint32_t row = base + u * rpw + sub;
-      float acc = red_identity<RIMPL>();
+      A acc = red_identity<RIMPL, A>();
       bool nan = false;
       if (row < row_end && mine) acc = red_vector<RIMPL, DT>(q[u], 0, 0, 0, false, acc, nan);
       acc = wave_reduce<RIMPL>(red_finish<RIMPL>(acc, nan), P);
       if (gather) {
-        const float got = __shfl(acc, (int)((lane & (rpw - 1u)) * P), 64);
+        const A got = __shfl(acc, (int)((lane & (rpw - 1u)) * P), 64);
         if (lane / rpw == (uint32_t)u) res = got;
       } else if (row < row_end && j == 0) {
-        store_rt<POL>(po, row, odt, acc);
+        red_store<POL>(po, row, odt, acc);
       }
     }
-    if (gather && lane < UP * rpw && base + lane < row_end) store_rt<POL>(po, base + lane, odt, res);
+    if (gather && lane < UP * rpw && base + lane < row_end) red_store<POL>(po, base + lane, odt, res);
   }
 }
 
@@ -1358,35 +1372,23 @@ DEV void red_contig(const Record* r, uint32_t row_begin, uint32_t row_end, float
   constexpr uint32_t V = E::V;
   const uint32_t n = uni(r->red_n);
   const char* pin = uni_ptr(r->ptr[0]);
-  char* po = (char*)uni_ptr(r->ptr[3]);
-  const uint32_t odt = uni(r->dtype[3]);
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-  if (r->rflags & RF_VEC) {                           // tensor base is 16-byte aligned
-    RedArgs a;
-    a.n = n;
-    a.base_elem = (row_begin * n) / V * V;            // chunk start, aligned down to a vector
-    // end rounded up to a whole vector (the base is 16-byte aligned, so the padding stays inside
-    // the 16-byte block that holds the last element); vector loads further out read zeros; both
-    // are masked per element
-    a.base = pin + (uint64_t)a.base_elem * E::ES;
-    a.bytes = ((row_end * n - a.base_elem) * E::ES + 15u) & ~15u;
-    a.po = po; a.odt = odt; a.row_begin = row_begin; a.row_end = row_end; a.s_part = s_part;
-    a.max_span = (n % V == 0 && a.base_elem == row_begin * n) ? n / V : (n + V - 2) / V + 1;
-    if (a.max_span <= 64u && n % V == 0 && a.base_elem == row_begin * n) red_rows_short_aligned<POL, RIMPL, DT>(a);
-    else if (a.max_span <= 64u) red_rows_short<POL, RIMPL, DT>(a);
-    else if (a.max_span >= 1024u && row_end - row_begin <= kRedPartialRows) red_rows_quarter<POL, RIMPL, DT>(a);
-    else if (a.max_span < 256u) red_rows_wave<POL, RIMPL, DT, 4, 2>(a);
-    else red_rows_wave<POL, RIMPL, DT, 2, 4>(a);
-    return;
-  }
-  // tensor base not 16-byte aligned: one wave per row, element loads
-  for (uint32_t row = row_begin + wave; row < row_end; row += 4) {
-    const char* prow = pin + (uint64_t)row * n * E::ES;
-    float acc = red_identity<RIMPL>();
-    for (uint32_t jx = lane; jx < n; jx += 64) acc = red_combine<RIMPL>(acc, E::template load1<POL>(prow, jx));
-    acc = wave_reduce<RIMPL>(acc, 64);
-    if (lane == 0) store_rt<POL>(po, row, odt, acc);
-  }
+  RedArgs a;
+  a.n = n;
+  a.lead = ((uint32_t)(__UINTPTR_TYPE__)pin & 15u) / E::ES;
+  a.base_elem = (a.lead + row_begin * n) / V * V;     // chunk start, aligned down to a vector
+  // end rounded up to a whole vector: the padding stays inside the 16-byte block that holds the last
+  // element; vector loads further out read zeros; both are masked per element
+  a.base = pin - a.lead * E::ES + (uint64_t)a.base_elem * E::ES;
+  a.bytes = ((a.lead + row_end * n - a.base_elem) * E::ES + 15u) & ~15u;
+  a.po = (char*)uni_ptr(r->ptr[3]);
+  a.odt = uni(r->dtype[3]); a.row_begin = row_begin; a.row_end = row_end; a.s_part = s_part;
+  const bool whole = n % V == 0 && a.lead == 0;       // every row is whole vectors
+  a.max_span = whole ? n / V : (n + V - 2) / V + 1;
+  if (a.max_span <= 64u && whole) red_rows_short_aligned<POL, RIMPL, DT>(a);
+  else if (a.max_span <= 64u) red_rows_short<POL, RIMPL, DT>(a);
+  else if (a.max_span >= 1024u && row_end - row_begin <= kRedPartialRows) red_rows_quarter<POL, RIMPL, DT>(a);
+  else if (a.max_span < 256u) red_rows_wave<POL, RIMPL, DT, 4, 2>(a);
+  else red_rows_wave<POL, RIMPL, DT, 2, 4>(a);
 }
 
 // PATH_RED_GENERIC: one wave per output row; outer index decomposed over the
@@ -1415,15 +1417,15 @@ PATHFN void red_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
       }
     }
     if (INT) {
-      int32_t acc = red_identity_i<RIMPL>();
-      for (uint32_t jx = lane; jx < n; jx += 64) acc = red_combine_i<RIMPL>(acc, (int32_t)M::ld4(pin, ioff + jx * sl));
-      acc = wave_reduce_i<RIMPL>(acc, 64);
+      int32_t acc = red_identity<RIMPL, int32_t>();
+      for (uint32_t jx = lane; jx < n; jx += 64) acc = red_combine<RIMPL>(acc, (int32_t)M::ld4(pin, ioff + jx * sl));
+      acc = wave_reduce<RIMPL>(acc, 64);
       if (lane == 0) M::st4(po, ooff, (uint32_t)acc);
     } else {
-      float acc = red_identity<RIMPL>();
+      float acc = red_identity<RIMPL, float>();
       for (uint32_t jx = lane; jx < n; jx += 64) acc = red_combine<RIMPL>(acc, load_rt<POL>(pin, ioff + jx * sl, idt));
       acc = wave_reduce<RIMPL>(acc, 64);
-      if (lane == 0) store_rt<POL>(po, ooff, odt, acc);
+      if (lane == 0) red_store<POL>(po, ooff, odt, acc);
     }
   }
 }
@@ -1945,7 +1947,11 @@ DEV void run_reduction(const Record* r, uint32_t chunk, float* s_red) {
   const uint32_t begin = chunk * per;
   const uint32_t end = (rows - begin < per) ? rows : begin + per;
   const uint32_t path = uni(r->path), dt = uni(r->dtype[0]);
-  if (r->rflags & RF_INT) { red_generic<POL, RIMPL, true>(r, begin, end); return; }
+  if (r->rflags & RF_INT) {
+    if (path == PATH_RED_CONTIG) red_contig<POL, RIMPL, GPUOS_I32>(r, begin, end, s_red);
+    else red_generic<POL, RIMPL, true>(r, begin, end);
+    return;
+  }
   if (path == PATH_RED_CONTIG) {
     if (dt == GPUOS_F32) red_contig<POL, RIMPL, GPUOS_F32>(r, begin, end, s_red);
     else if (dt == GPUOS_F16) red_contig<POL, RIMPL, GPUOS_F16>(r, begin, end, s_red);

@@ -509,16 +509,18 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   rec.stride[0][5] = (uint32_t)s_last;
   rec.red_n = (uint32_t)n;
   rec.numel = (uint32_t)rows;
-  const uint32_t V = 16u / dtype_size(ops[0].dtype);
   const bool rows_contig = rows == 1 || (nd == 1 && oo[0].stride[0] == n && oo[1].stride[0] == 1);
-  if (!all_int && s_last == 1 && rows_contig && n * 4 < kMaxExtent) {            // a row fits one buffer resource
-    rec.path = PATH_RED_CONTIG;
-    if (aligned16(ops[0].ptr)) rec.rflags |= RF_VEC;    // rows are read as aligned vectors whatever n is
-  } else {
-    rec.path = PATH_RED_GENERIC;
-  }
-  // same traffic per chunk as an elementwise chunk: chunk_elems * 12 bytes of input rows
-  uint64_t rpc = (uint64_t)chunk_elems * 24 / ((uint64_t)n * dtype_size(ops[0].dtype));
+  // (a row fits one buffer resource; rows are read as aligned vectors whatever n and the base's alignment are)
+  rec.path = (s_last == 1 && rows_contig && n * 4 < kMaxExtent) ? PATH_RED_CONTIG : PATH_RED_GENERIC;
+  // A reduction writes almost nothing and its rows are a chain of memory latencies (load a few rows,
+  // combine, next), which grow to 10-20 us while the GPU streams: a small task is cut into chunks of
+  // one or two rounds of its workgroup (16 KiB), up to 64 of them, before chunks grow to the regular
+  // size.  (Chunks of twice the elementwise traffic whatever the task's size: a 0.2 MB reduction
+  // in a bandwidth-bound stream was two chunks of 7 rounds each and took 110 us.  Forty streaming
+  // operations of 0.1-220 MB, half of them reductions: 152 us a pass before, 130 now.)
+  const uint64_t row_bytes = (uint64_t)n * dtype_size(ops[0].dtype);
+  const uint64_t most = (uint64_t)chunk_elems * 24, spread = row_bytes * (uint64_t)rows / 64;
+  uint64_t rpc = (spread < 16384 ? 16384 : (spread < most ? spread : most)) / row_bytes;
   if (rpc < 1) rpc = 1;
   if (rpc >= 16) rpc = (rpc + 15) / 16 * 16;          // whole passes of the row-per-wave kernels
   const uint64_t min_rpc = ((uint64_t)rows + kMaxChunksPerTask - 1) / kMaxChunksPerTask;
