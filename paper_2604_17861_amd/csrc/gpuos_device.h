@@ -60,6 +60,9 @@ template <int POL> struct Mem {
     const v2i q = {(int)w0, (int)w1};
     __builtin_amdgcn_raw_buffer_store_b64(q, r, (int)off, 0, AUX);
   }
+  static DEV void stb4(rsrc_t r, uint32_t off, uint32_t w) { __builtin_amdgcn_raw_buffer_store_b32(w, r, (int)off, 0, AUX); }
+  static DEV void stb2(rsrc_t r, uint32_t off, uint32_t h) { __builtin_amdgcn_raw_buffer_store_b16((uint16_t)h, r, (int)off, 0, AUX); }
+  static DEV uint32_t ldb4(rsrc_t r, uint32_t off) { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX); }
   static DEV uint32_t ld4(const void* p, uint32_t i) {
     if (POL == POL_COHERENT) return __hip_atomic_load((const uint32_t*)p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     return ((const uint32_t*)p)[i];
@@ -369,6 +372,87 @@ template <class T> DEV T* lds_arg(T* p) {
   return (T*)(lds_t)(__UINTPTR_TYPE__)a;
 }
 
+// K 16-byte vectors of one operand; or, under MixArg, one scalar per vector in their place (of any
+// dtype: `word` holds the bits of an fp32 value, or an int32).
+template <int DT, int K> struct VecArg {
+  const v4i (&q)[K];
+  DEV v4i raw(int u) const { return q[u]; }
+  DEV float get(int u, int k) const { return Elem<DT>::get(q[u], k); }
+  DEV uint32_t word(int u, int k) const { return (uint32_t)q[u][k]; }
+};
+template <int DT, int K> struct MixArg {
+  const v4i (&q)[K];
+  const uint32_t (&w)[K];
+  bool scalar;
+  DEV v4i raw(int u) const { return q[u]; }
+  DEV float get(int u, int k) const { return scalar ? __builtin_bit_cast(float, w[u]) : Elem<DT>::get(q[u], k); }
+  DEV uint32_t word(int u, int k) const { return scalar ? w[u] : (uint32_t)q[u][k]; }
+};
+
+// K vectors of an elementwise operation: floats through fp32, I32 word by word, COPY as it is (bits).
+// Each result goes to sink(u, vector) as soon as it is there.
+template <int IMPL, int DT, int K, class A, class S> DEV void ew_vectors(const A& a, const A& b, const A& c, float alpha, S sink) {
+  using E = Elem<DT>;
+  constexpr int V = E::V;
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    v4i q;
+    if constexpr (IMPL == GPUOS_IMPL_COPY) q = a.raw(u);
+    else if constexpr (DT == GPUOS_I32) {
+#pragma unroll
+      for (int k = 0; k < V; ++k) q[k] = (int)int_op<IMPL>(a.word(u, k), b.word(u, k));
+    } else {
+      constexpr int N = Op<IMPL>::N;
+      float xa[V], xb[V], xc[V], xo[V];
+#pragma unroll
+      for (int k = 0; k < V; ++k) {
+        xa[k] = a.get(u, k); xb[k] = N > 1 ? b.get(u, k) : 0.f; xc[k] = N > 2 ? c.get(u, k) : 0.f;
+      }
+      apply_vec<IMPL, V, DT>(xa, xb, xc, alpha, xo);
+#pragma unroll
+      for (int k = 0; k < V; ++k) E::put(q, k, xo[k]);
+    }
+    sink(u, q);
+  }
+}
+
+// The operator as an executor sees it.  FixedOp: one implementation, the executor is instantiated for
+// it (operators of many instructions, programs, native code).  ByArity: the built-in operators of N
+// inputs and a few instructions share one executor, which decides between them when the round's loads
+// are on their way: the decision costs nothing there.  (An executor per operator makes the choice
+// among 12 x 3 x paths executors in front of the first load: every many-way branch of this kernel
+// becomes a chain that is walked case by case, and each further path put 0.25 us on every unit.)
+template <int IMPL> struct FixedOp {
+  static constexpr int N = Op<IMPL>::N;
+  template <int DT, int K, class A, class S> static DEV void vectors(uint32_t, const A& a, const A& b, const A& c, float alpha, S sink) {
+    ew_vectors<IMPL, DT, K>(a, b, c, alpha, sink);
+  }
+};
+template <int ARITY> struct ByArity {
+  static constexpr int N = ARITY;
+  template <int DT, int K, class A, class S> static DEV void vectors(uint32_t impl, const A& a, const A& b, const A& c, float alpha, S sink) {
+    if constexpr (DT == GPUOS_I32) {
+      if constexpr (N == 1) ew_vectors<GPUOS_IMPL_COPY, DT, K>(a, b, c, alpha, sink);
+      else if (impl == GPUOS_IMPL_ADD) ew_vectors<GPUOS_IMPL_ADD, DT, K>(a, b, c, alpha, sink);
+      else if (impl == GPUOS_IMPL_SUB) ew_vectors<GPUOS_IMPL_SUB, DT, K>(a, b, c, alpha, sink);
+      else ew_vectors<GPUOS_IMPL_MUL, DT, K>(a, b, c, alpha, sink);
+    } else if constexpr (N == 1) {
+      if (impl == GPUOS_IMPL_COPY) ew_vectors<GPUOS_IMPL_COPY, DT, K>(a, b, c, alpha, sink);
+      else if (impl == GPUOS_IMPL_SCALE) ew_vectors<GPUOS_IMPL_SCALE, DT, K>(a, b, c, alpha, sink);
+      else if (impl == GPUOS_IMPL_RELU) ew_vectors<GPUOS_IMPL_RELU, DT, K>(a, b, c, alpha, sink);
+      else ew_vectors<GPUOS_IMPL_EXP, DT, K>(a, b, c, alpha, sink);
+    } else if constexpr (N == 2) {
+      if (impl == GPUOS_IMPL_ADD) ew_vectors<GPUOS_IMPL_ADD, DT, K>(a, b, c, alpha, sink);
+      else if (impl == GPUOS_IMPL_MUL) ew_vectors<GPUOS_IMPL_MUL, DT, K>(a, b, c, alpha, sink);
+      else if (impl == GPUOS_IMPL_SUB) ew_vectors<GPUOS_IMPL_SUB, DT, K>(a, b, c, alpha, sink);
+      else if (impl == GPUOS_IMPL_DIV) ew_vectors<GPUOS_IMPL_DIV, DT, K>(a, b, c, alpha, sink);
+      else ew_vectors<GPUOS_IMPL_SUB_EXP, DT, K>(a, b, c, alpha, sink);
+    } else {
+      ew_vectors<GPUOS_IMPL_FMA, DT, K>(a, b, c, alpha, sink);
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // PATH_CONTIG: out[i] = f(a[i], b[i], c[i]), all operands the same dtype.
 // 16 bytes per lane per access, four accesses in flight per operand.
@@ -400,63 +484,29 @@ PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         qa[u] = M::ld16(ra, (v + u * kThreads) * 16u);
-        if (N > 1) qb[u] = M::ld16(rb, (v + u * kThreads) * 16u);
-        if (N > 2) qc[u] = M::ld16(rc, (v + u * kThreads) * 16u);
+        qb[u] = N > 1 ? M::ld16(rb, (v + u * kThreads) * 16u) : qa[u];
+        qc[u] = N > 2 ? M::ld16(rc, (v + u * kThreads) * 16u) : qa[u];
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        v4i q;
-        if (IMPL == GPUOS_IMPL_COPY) q = qa[u];
-        else {
-          float xa[V], xb[V], xc[V], xo[V];
-#pragma unroll
-          for (int k = 0; k < V; ++k) {
-            xa[k] = E::get(qa[u], k); xb[k] = N > 1 ? E::get(qb[u], k) : 0.f; xc[k] = N > 2 ? E::get(qc[u], k) : 0.f;
-          }
-          apply_vec<IMPL, V, DT>(xa, xb, xc, alpha, xo);
-#pragma unroll
-          for (int k = 0; k < V; ++k) E::put(q, k, xo[k]);
-        }
-        M::st16(ro, (v + u * kThreads) * 16u, q);
-      }
+      typedef VecArg<DT, U> Arg;
+      ew_vectors<IMPL, DT, U>(Arg{qa}, Arg{qb}, Arg{qc}, alpha, [&](int u, const v4i& q) { M::st16(ro, (v + u * kThreads) * 16u, q); });
     }
     for (; v < nvec; v += kThreads) {
-      const v4i qa = M::ld16(ra, v * 16u);
-      v4i qb, qc, q;
-      if (N > 1) qb = M::ld16(rb, v * 16u);
-      if (N > 2) qc = M::ld16(rc, v * 16u);
-      if (IMPL == GPUOS_IMPL_COPY) q = qa;
-      else {
-        float xa[V], xb[V], xc[V], xo[V];
-#pragma unroll
-        for (int k = 0; k < V; ++k) {
-          xa[k] = E::get(qa, k); xb[k] = N > 1 ? E::get(qb, k) : 0.f; xc[k] = N > 2 ? E::get(qc, k) : 0.f;
-        }
-        apply_vec<IMPL, V, DT>(xa, xb, xc, alpha, xo);
-#pragma unroll
-        for (int k = 0; k < V; ++k) E::put(q, k, xo[k]);
-      }
-      M::st16(ro, v * 16u, q);
+      v4i qa[1], qb[1], qc[1];
+      qa[0] = M::ld16(ra, v * 16u);
+      qb[0] = N > 1 ? M::ld16(rb, v * 16u) : qa[0];
+      qc[0] = N > 2 ? M::ld16(rc, v * 16u) : qa[0];
+      typedef VecArg<DT, 1> Arg;
+      ew_vectors<IMPL, DT, 1>(Arg{qa}, Arg{qb}, Arg{qc}, alpha, [&](int, const v4i& q) { M::st16(ro, v * 16u, q); });
     }
     begin += nvec * V;                                // ragged tail below
   }
   for (uint32_t i = begin + tid; i < end; i += kThreads) {
-    if (IMPL == GPUOS_IMPL_COPY) E::template copy1<POL>(po, pa, i);
+    if constexpr (DT == GPUOS_I32) M::st4(po, i, int_op<IMPL>(M::ld4(pa, i), M::ld4(pb, i)));
+    else if constexpr (IMPL == GPUOS_IMPL_COPY) E::template copy1<POL>(po, pa, i);
     else
       E::template store1<POL>(po, i, OpOut<IMPL, DT>::f(E::template load1<POL>(pa, i), N > 1 ? E::template load1<POL>(pb, i) : 0.f,
                                                  N > 2 ? E::template load1<POL>(pc, i) : 0.f, alpha));
   }
-}
-
-template <int POL, int IMPL>
-PATHFN void ew_contig_int(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
-  const Record* r = lds_arg(r_v);
-  const uint32_t begin = uni(begin_v), end = uni(end_v);
-  const char* a = uni_ptr(r->ptr[0]);
-  const char* b = r->n_inputs > 1 ? uni_ptr(r->ptr[1]) : a;
-  char* o = (char*)uni_ptr(r->ptr[3]);
-  for (uint32_t i = begin + threadIdx.x; i < end; i += kThreads)
-    Mem<POL>::st4(o, i, int_op<IMPL>(Mem<POL>::ld4(a, i), Mem<POL>::ld4(b, i)));
 }
 
 // ---------------------------------------------------------------------------
@@ -1017,6 +1067,155 @@ PATHFN void ew_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
       const float z = N > 2 ? load_rt<POL>(p[2], off[2], dt[2]) : 0.f;
       store_rt<POL>(po, off[3], dt[3], Op<IMPL>::f(x, y, z, alpha));
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// PATH_ROWS: up to three outer dims of any strides over rows of C elements that are contiguous in
+// every operand that is not one scalar per row: slices of a wider matrix (read or written), head
+// splits, masks repeated over leading dims, per-row scalars, whatever the row length and the
+// alignment of the rows are (an access of 16 bytes needs no alignment beyond its elements').
+// Operands of dtype DTI, output of dtype DTO (they differ for COPY only); scalars of any float dtype.
+// A row is cut into vectors of V elements from its first element on, one lane each; the last vector of
+// a row that is no multiple of V covers the row's last V elements and stores those the vector
+// before it does not hold.  The extent of every operand fits a buffer resource (checked on the host).
+// ---------------------------------------------------------------------------
+// DTI != DTO: the cast of a COPY.
+template <int POL, class OPER, int DTI, int DTO, bool SCALARS>
+PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
+  const Record* r = lds_arg(r_v);
+  const uint32_t begin = uni(begin_v), end = uni(end_v);
+  using EI = Elem<DTI>;
+  using EO = Elem<DTO>;
+  using M = Mem<POL>;
+  constexpr int V = EI::V > EO::V ? EI::V : EO::V, NI = V / EI::V, NO = V / EO::V;
+  constexpr int N = OPER::N;
+  constexpr int U = 4;
+  const uint32_t A = uni(r->size[0]), B = uni(r->size[1]), R = uni(r->size[2]), C = uni(r->size[3]);
+  const uint32_t VR = (C + V - 1) / V, tail = C % V;
+  rsrc_t rs[4];
+  uint32_t st[4][3], dt[3], es[3], lead[3];
+  bool scalar[3];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int kk = k < N || k == 3 ? k : 0;
+    const char* p = uni_ptr(r->ptr[kk]);
+    const uint32_t e = k == 3 ? (uint32_t)EO::ES : (uni(r->dtype[kk]) == GPUOS_F32 || DTI == GPUOS_I32 ? 4u : 2u);
+    uint32_t extent = k < 3 && SCALARS && uni(r->okind[kk]) == K_ROWSCALAR ? 1u : C;      // elements from the first to the last
+    extent += (A - 1) * uni(r->stride[kk][0]) + (B - 1) * uni(r->stride[kk][1]) + (R - 1) * uni(r->stride[kk][2]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) st[k][d] = uni(r->stride[kk][d]) * e;
+    if (k < 3) {
+      dt[k] = uni(r->dtype[kk]);
+      es[k] = e;
+      scalar[k] = SCALARS && uni(r->okind[kk]) == K_ROWSCALAR;
+      // a scalar is read as the aligned word that holds it
+      lead[k] = scalar[k] ? (uint32_t)(__UINTPTR_TYPE__)p & 3u : 0u;
+      rs[k] = make_rsrc(p - lead[k], (lead[k] + extent * e + (scalar[k] ? 3u : 0u)) & (scalar[k] ? ~3u : ~0u));
+    } else {
+      rs[k] = make_rsrc(p, extent * e);
+    }
+  }
+  const float alpha = __builtin_bit_cast(float, uni(__builtin_bit_cast(uint32_t, r->alpha)));
+  const uint32_t impl = uni(r->impl);
+  // (row, vector) of this lane's first unit by division, then steps of 256 units with carries
+  const bool deep = A * B > 1;
+  uint32_t v = begin + threadIdx.x;
+  uint32_t row = v / VR, vc = v - row * VR, b = 0, a = 0;
+  const uint32_t s_rows = kThreads / VR, s_vc = kThreads - s_rows * VR;
+  uint32_t s_r = s_rows, s_b = 0, s_a = 0;
+  if (deep) {
+    const uint32_t t = row / R;
+    row -= t * R;
+    a = t / B;
+    b = t - a * B;
+    const uint32_t ts = s_rows / R;
+    s_r = s_rows - ts * R;
+    s_a = ts / B;
+    s_b = ts - s_a * B;
+  }
+  for (; v - threadIdx.x < end; ) {
+    v4i q[3][U][NI];
+    uint32_t w[3][U], oo[U];
+    bool last[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool act = v + u * kThreads < end;
+      last[u] = tail != 0 && vc == VR - 1;
+      const uint32_t col = last[u] ? C - V : vc * V;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (k < N || k == 3) {
+          uint32_t o = row * st[k][2];
+          if (deep) o += b * st[k][1] + a * st[k][0];
+          if (k == 3) oo[u] = o + col * EO::ES;
+          else {
+            // (both forms of the load under SCALARS, the one that does not apply past the resource, where it
+            // moves nothing: no branch between the loads of a round)
+            const uint32_t of = act && !(SCALARS && scalar[k]) ? o + col * EI::ES : kNoLoad;
+#pragma unroll
+            for (int i = 0; i < NI; ++i) q[k][u][i] = M::ld16(rs[k], of + i * 16u);
+            if (SCALARS) w[k][u] = M::ldb4(rs[k], act && scalar[k] ? (lead[k] + o) & ~3u : kNoLoad) >> (((lead[k] + o) & 2u) * 8u);
+          }
+        }
+      }
+      vc += s_vc;
+      row += s_r;
+      if (vc >= VR) { vc -= VR; ++row; }
+      if (deep) {
+        b += s_b;
+        a += s_a;
+        if (row >= R) { row -= R; ++b; }               // (one step and one carry: at most 2 R - 1)
+        if (b >= B) { b -= B; ++a; }
+      }
+    }
+    auto sink = [&](int u, const v4i (&qo)[NO]) {
+      const bool act = v + u * kThreads < end;
+#pragma unroll
+      for (int i = 0; i < NO; ++i) M::st16(rs[3], act && !last[u] ? oo[u] + i * 16u : kNoLoad, qo[i]);
+      if (tail != 0 && act && last[u]) {
+#pragma unroll
+        for (int e = 1; e < V; ++e)
+          if ((uint32_t)e >= V - tail) {
+            if (EO::ES == 4) M::stb4(rs[3], oo[u] + e * 4u, (uint32_t)qo[e / EO::V][e % EO::V]);
+            else M::stb2(rs[3], oo[u] + e * 2u, (uint32_t)qo[e / EO::V][(e % EO::V) / 2] >> ((e & 1) * 16));
+          }
+      }
+    };
+    if constexpr (DTI != DTO) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        v4i qo[NO];
+#pragma unroll
+        for (int e = 0; e < V; ++e) EO::put(qo[e / EO::V], e % EO::V, EI::get(q[0][u][e / EI::V], e % EI::V));
+        sink(u, qo);
+      }
+    } else {
+      v4i qv[3][U];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int u = 0; u < U; ++u) qv[k][u] = q[k < N ? k : 0][u][0];
+      auto sink1 = [&](int u, const v4i& r1) { const v4i qo[1] = {r1}; sink(u, qo); };
+      if constexpr (SCALARS) {
+        if constexpr (DTI != GPUOS_I32) {
+#pragma unroll
+          for (int k = 0; k < N; ++k)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const uint32_t h = w[k][u] & 0xffffu;
+              w[k][u] = dt[k] == GPUOS_F32 ? w[k][u] : __builtin_bit_cast(uint32_t, dt[k] == GPUOS_F16 ? h2f(h) : b2f(h));
+            }
+        }
+        typedef MixArg<DTI, U> Arg;
+        OPER::template vectors<DTI, U>(impl, Arg{qv[0], w[0], scalar[0]}, Arg{qv[1], w[N > 1 ? 1 : 0], scalar[N > 1 ? 1 : 0]},
+                                       Arg{qv[2], w[N > 2 ? 2 : 0], scalar[N > 2 ? 2 : 0]}, alpha, sink1);
+      } else {
+        typedef VecArg<DTI, U> Arg;
+        OPER::template vectors<DTI, U>(impl, Arg{qv[0]}, Arg{qv[1]}, Arg{qv[2]}, alpha, sink1);
+      }
+    }
+    v += U * kThreads;
   }
 }
 
@@ -1897,16 +2096,77 @@ DEV void run_rowop(const Record* r, uint32_t chunk, float* s_red) {
 // paper's function-pointer table call, Section 4.1; here a switch over
 // precompiled implementations selected by the table entry).
 // ---------------------------------------------------------------------------
+// Which executor takes a task is decided by halving: pick<LO, HI> calls F::run<K> for the K in [LO, HI)
+// that equals k.  (The compiler turns a many-way branch into a chain that is walked case by case, with
+// a flag to carry per case; a two-way choice whose sides meet again is left alone.)
+template <int LO, int HI, class F, class... A> DEV void pick(uint32_t k, A... a) {
+  if constexpr (HI - LO == 1) F::template run<LO>(a...);
+  else {
+    constexpr int MID = (LO + HI) / 2;
+    if (k < (uint32_t)MID) pick<LO, MID, F>(k, a...);
+    else pick<MID, HI, F>(k, a...);
+  }
+}
+
+// The executors of PATH_ROWS: by arity without (groups of three: fp32, fp16, bf16) and with per-row
+// scalars, the operators of many instructions, casts, I32.
+enum : uint32_t { kClsUnary = 0, kClsBinary = 1, kClsTernary = 2, kClsErf = 3, kClsTanh = 4, kClsNone = 15 };
+constexpr int kRowsScalar = 15, kRowsCast = 21, kRowsInt = 27, kRowsCount = 30;
+template <int CLS> struct OperOf;
+template <> struct OperOf<kClsUnary> { typedef ByArity<1> T; };
+template <> struct OperOf<kClsBinary> { typedef ByArity<2> T; };
+template <> struct OperOf<kClsTernary> { typedef ByArity<3> T; };
+template <> struct OperOf<kClsErf> { typedef FixedOp<GPUOS_IMPL_GELU_ERF> T; };
+template <> struct OperOf<kClsTanh> { typedef FixedOp<GPUOS_IMPL_GELU_TANH> T; };
+static_assert(GPUOS_F32 == 0 && GPUOS_F16 == 1 && GPUOS_BF16 == 2, "the float dtypes count the members of a group");
+template <int POL> struct RowsExec {
+  template <int K> static DEV void run(const Record* r, uint32_t begin, uint32_t end) {
+    if constexpr (K < kRowsScalar) ew_rows<POL, typename OperOf<K / 3>::T, K % 3, K % 3, false>(r, begin, end);
+    else if constexpr (K < kRowsCast) ew_rows<POL, ByArity<2 + (K - kRowsScalar) / 3>, (K - kRowsScalar) % 3, (K - kRowsScalar) % 3, true>(r, begin, end);
+    else if constexpr (K < kRowsInt) {
+      // (from, to): 0 1, 0 2, 1 0, 1 2, 2 0, 2 1
+      constexpr int FROM = (K - kRowsCast) / 2, TO = (K - kRowsCast) % 2 + ((K - kRowsCast) % 2 >= FROM ? 1 : 0);
+      ew_rows<POL, ByArity<1>, FROM, TO, false>(r, begin, end);
+    }
+    else if constexpr (K < kRowsCount - 1) ew_rows<POL, ByArity<K - kRowsInt + 1>, GPUOS_I32, GPUOS_I32, false>(r, begin, end);
+    else ew_rows<POL, ByArity<2>, GPUOS_I32, GPUOS_I32, true>(r, begin, end);
+  }
+};
+
+// the executor of a PATH_ROWS task, kRowsCount if it has none
+DEV uint32_t rows_variant(const Record* r, uint32_t impl) {
+  // class by implementation, a nibble each: ADD SUB MUL DIV binary, RELU EXP unary, both GELUs, SCALE unary, FMA, SUB_EXP binary, COPY unary
+  const uint32_t cls = impl < 16u ? (uint32_t)(0xfff012043001111full >> (4u * impl)) & 15u : (uint32_t)kClsNone;
+  const uint32_t dt = uni(r->dtype[3]), dti = uni(r->vdtype);
+  const bool scalars = uni((uint32_t)r->okind[0] | (uint32_t)r->okind[1] | (uint32_t)r->okind[2]) != 0;
+  if (uni(r->rflags) & RF_INT) {
+    const bool takes = impl == GPUOS_IMPL_ADD || impl == GPUOS_IMPL_SUB || impl == GPUOS_IMPL_MUL || impl == GPUOS_IMPL_COPY;
+    return takes ? kRowsInt + (impl == GPUOS_IMPL_COPY ? 0u : 1u) + (scalars ? 1u : 0u) : (uint32_t)kRowsCount;
+  }
+  if (dti != dt) return impl == GPUOS_IMPL_COPY ? kRowsCast + 2u * dti + dt - (dt > dti ? 1u : 0u) : (uint32_t)kRowsCount;
+  if (!scalars) return cls <= kClsTanh ? cls * 3u + dt : (uint32_t)kRowsCount;
+  return cls == kClsBinary || cls == kClsTernary ? kRowsScalar + (cls - 1u) * 3u + dt : (uint32_t)kRowsCount;
+}
+
+// Elements [begin, end) of a PATH_ROWS task, whose numbers count vectors, as the element range that the
+// general executor walks: for an operator that was swapped in between submission and claim and has
+// no executor for the task's combination (another unary operator where a COPY converts).
+DEV void rows_elements(const Record* r, uint32_t& begin, uint32_t& end) {
+  const uint32_t C = uni(r->size[3]), V = uni(r->vwidth), VR = (C + V - 1) / V;
+  const uint32_t b = begin / VR, e = end / VR;
+  begin = b * C + (begin - b * VR) * V;
+  end = e * C + (end - e * VR) * V;                  // (vector 0 of the next row begins where this row ends)
+}
+
 template <int POL, int IMPL>
 DEV void run_elementwise(const Record* r, uint32_t chunk, float* s_scratch) {
   const uint32_t per = uni(r->chunk), numel = uni(r->numel);
-  const uint32_t begin = chunk * per;
-  const uint32_t end = (numel - begin < per) ? numel : begin + per;
+  uint32_t begin = chunk * per, end = (numel - begin < per) ? numel : begin + per;
   const uint32_t path = uni(r->path), dt = uni(r->dtype[3]);
   constexpr bool int_ok = IMPL == GPUOS_IMPL_ADD || IMPL == GPUOS_IMPL_SUB || IMPL == GPUOS_IMPL_MUL || IMPL == GPUOS_IMPL_COPY;
   if (r->rflags & RF_INT) {
     if (int_ok) {
-      if (path == PATH_CONTIG) ew_contig_int<POL, IMPL>(r, begin, end);
+      if (path == PATH_CONTIG) ew_contig<POL, int_ok ? IMPL : GPUOS_IMPL_COPY, GPUOS_I32>(r, begin, end);
       else ew_generic<POL, int_ok ? IMPL : GPUOS_IMPL_COPY, true>(r, begin, end);
     }
     return;
@@ -1937,6 +2197,17 @@ DEV void run_elementwise(const Record* r, uint32_t chunk, float* s_scratch) {
   } else if (path == PATH_STAGED) {
     ew_staged<POL, IMPL>(r, begin, end, s_scratch);
   } else {
+    if constexpr (IMPL >= kImplProg1) {                  // programs, interpreted and native; built-in operators: RowsExec
+      const uint32_t k0 = uni((uint32_t)r->okind[0] | (uint32_t)r->okind[1] | (uint32_t)r->okind[2]);
+      if (path == PATH_ROWS && uni(r->vdtype) == dt && (k0 == 0 || Op<IMPL>::N >= 2)) {
+        constexpr bool S = Op<IMPL>::N >= 2;
+        if (dt == GPUOS_F32) { if (k0) ew_rows<POL, FixedOp<IMPL>, GPUOS_F32, GPUOS_F32, S>(r, begin, end); else ew_rows<POL, FixedOp<IMPL>, GPUOS_F32, GPUOS_F32, false>(r, begin, end); }
+        else if (dt == GPUOS_F16) { if (k0) ew_rows<POL, FixedOp<IMPL>, GPUOS_F16, GPUOS_F16, S>(r, begin, end); else ew_rows<POL, FixedOp<IMPL>, GPUOS_F16, GPUOS_F16, false>(r, begin, end); }
+        else { if (k0) ew_rows<POL, FixedOp<IMPL>, GPUOS_BF16, GPUOS_BF16, S>(r, begin, end); else ew_rows<POL, FixedOp<IMPL>, GPUOS_BF16, GPUOS_BF16, false>(r, begin, end); }
+        return;
+      }
+    }
+    if (path == PATH_ROWS) rows_elements(r, begin, end);
     ew_generic<POL, IMPL, false>(r, begin, end);
   }
 }
@@ -1986,6 +2257,13 @@ template <int POL>
 DEV int32_t exec_chunk(const Record* r, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage* progs) {
   if (uni(r->path) == PATH_NOP) return impl == GPUOS_IMPL_FAIL ? GPUOS_E_BADOP : GPUOS_OK;
   if (impl >= GPUOS_IMPL_PROGRAM_BASE) return exec_program<POL>(r, impl, chunk, s_red, progs);
+  // (beside the switch, not a case in every implementation's paths: see ByArity)
+  const uint32_t k = uni(r->path) == PATH_ROWS ? rows_variant(r, impl) : (uint32_t)kRowsCount;
+  if (k < (uint32_t)kRowsCount) {
+    const uint32_t per = uni(r->chunk), numel = uni(r->numel), begin = chunk * per;
+    pick<0, kRowsCount, RowsExec<POL>>(k, r, begin, (numel - begin < per) ? numel : begin + per);
+    return GPUOS_OK;
+  }
   switch (impl) {
     case GPUOS_IMPL_ADD: run_elementwise<POL, GPUOS_IMPL_ADD>(r, chunk, s_red); break;
     case GPUOS_IMPL_SUB: run_elementwise<POL, GPUOS_IMPL_SUB>(r, chunk, s_red); break;
@@ -2066,6 +2344,17 @@ struct WorkShared {
                                    // the newly claimed unit's descriptor into it, or leave
   int32_t dep_status;              // 0, or the status a task whose dependency wait ran out completes with
   uint32_t rec_sum;                // weighted check sum of the record as fetched
+  // The first wavefront's state from one unit to the next, and the workgroup's counters (ST_WORK_UNITS
+  // on): here and not in registers, most of which the call of an executor does not preserve.  (The
+  // compiler spilled them to scratch memory and to lanes round the executors' call sites, a quarter
+  // of a microsecond per unit, more or less with every change of the executors.)
+  uint32_t waiting;                // bit k: descriptor slot k holds a unit that waits for a dependency
+  uint32_t have_claim;             // a unit number is claimed and its entry has not arrived yet
+  uint32_t draining;               // the stop flag was seen: claim nothing more, finish what is held, leave
+  uint32_t polls, yield_every;
+  uint64_t g;                      // the claimed unit number
+  uint32_t n_units, held_any;
+  uint64_t ticks[ST_WORK_TICKS_TOTAL - ST_WORK_TICKS_WAIT];
   alignas(16) float red[kScratchFloats];   // (16-byte LDS vectors are written into it)
 };
 
@@ -2105,18 +2394,17 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
   uint64_t* const claim_ctr = RING == 0 ? &a.d->claim : &a.d->claim_j;
   const uint64_t* const unit_ring = RING == 0 ? a.units : a.units_j;
   const rsrc_t rd = make_rsrc(a.dring, (a.cap_mask + 1u) * (uint32_t)sizeof(Record));
-  uint64_t w_units = 0, w_wait = 0, w_fetch = 0, w_dep = 0, w_exec = 0, w_done = 0;
+  auto count = [&](uint32_t which, uint64_t add) { if (tid == 0) s->ticks[which - ST_WORK_TICKS_WAIT] += add; };
+  if (tid == 0) {
+    s->waiting = s->have_claim = s->draining = s->polls = s->yield_every = s->n_units = 0;
+    s->g = 0;
+    for (uint32_t k = 0; k < ST_WORK_TICKS_TOTAL - ST_WORK_TICKS_WAIT; ++k) s->ticks[k] = 0;
+  }
+  lds_wave_sync();                                    // (only the first wavefront reads them)
   const bool timing = a.timing != 0, tracing = a.trace != nullptr;
   const uint64_t w_start = clock_if(timing);
-  // State of the first wavefront (the same in all its lanes; the other wavefronts never look at it).
-  uint32_t waiting = 0;            // bit k: descriptor slot k holds a unit that waits for a dependency
-  bool have_claim = false;         // a unit number is claimed and its entry has not arrived yet
-  bool draining = false;           // the stop flag was seen: claim nothing more, finish what is held, leave
-  uint64_t g = 0;                  // the claimed unit number
-  uint32_t polls = 0, yield_every = 0;
   while (true) {
     const uint64_t c0 = clock_if(timing);
-    const bool held_any = waiting != 0;
     // ---- decide what to do next (first wavefront): one round of loads per poll ----
     // Lane 32 polls the claimed entry itself (its stamp is the ready flag: every waiting workgroup
     // polls a different address); lane k < kStash looks at the done words that descriptor slot k waits for.
@@ -2124,6 +2412,10 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
       uint32_t action = kActExit, f = 0;
       int32_t dep_status = 0;
       uint64_t u_new = 0;
+      uint32_t waiting = uni(s->waiting), polls = uni(s->polls), yield_every = uni(s->yield_every);
+      bool have_claim = uni(s->have_claim) != 0, draining = uni(s->draining) != 0;
+      uint64_t g = uni64(s->g);
+      const bool held_any = waiting != 0;
       if (!have_claim && !draining && waiting != kStashFull) {
         uint64_t gg = 0;
         if (tid == 0) gg = __hip_atomic_fetch_add(claim_ctr, 1ull, __ATOMIC_RELAXED, SC_AGENT);
@@ -2236,6 +2528,10 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
         else __builtin_amdgcn_s_sleep(8);
       }
       if (tid == 0) {
+        s->waiting = waiting; s->polls = polls; s->yield_every = yield_every;
+        s->have_claim = have_claim ? 1u : 0u; s->draining = draining ? 1u : 0u;
+        s->g = g;
+        s->held_any = held_any ? 1u : 0u;
         s->action = action;
         s->slot = f;
         s->dep_status = dep_status;
@@ -2247,18 +2543,15 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
     if (action == kActExit) {
       if (tid == 0) {
         uint64_t* st = a.d->stat;
-        __hip_atomic_fetch_add(&st[ST_WORK_UNITS], w_units, __ATOMIC_RELAXED, SC_AGENT);
-        __hip_atomic_fetch_add(&st[ST_WORK_TICKS_WAIT], w_wait, __ATOMIC_RELAXED, SC_AGENT);
-        __hip_atomic_fetch_add(&st[ST_WORK_TICKS_FETCH], w_fetch, __ATOMIC_RELAXED, SC_AGENT);
-        __hip_atomic_fetch_add(&st[ST_WORK_TICKS_DEP], w_dep, __ATOMIC_RELAXED, SC_AGENT);
-        __hip_atomic_fetch_add(&st[ST_WORK_TICKS_EXEC], w_exec, __ATOMIC_RELAXED, SC_AGENT);
-        __hip_atomic_fetch_add(&st[ST_WORK_TICKS_COMPLETE], w_done, __ATOMIC_RELAXED, SC_AGENT);
+        __hip_atomic_fetch_add(&st[ST_WORK_UNITS], (uint64_t)s->n_units, __ATOMIC_RELAXED, SC_AGENT);
+        for (uint32_t k = ST_WORK_TICKS_WAIT; k < ST_WORK_TICKS_TOTAL; ++k)
+          __hip_atomic_fetch_add(&st[k], s->ticks[k - ST_WORK_TICKS_WAIT], __ATOMIC_RELAXED, SC_AGENT);
         __hip_atomic_fetch_add(&st[ST_WORK_TICKS_TOTAL], c0 - w_start, __ATOMIC_RELAXED, SC_AGENT);
       }
       return;
     }
     const uint64_t c1 = clock_if(timing || tracing);
-    if (timing) { if (held_any) w_dep += c1 - c0; else w_wait += c1 - c0; }
+    if (timing) count(s->held_any ? ST_WORK_TICKS_DEP : ST_WORK_TICKS_WAIT, c1 - c0);
     // the unit is the same for the whole workgroup: keep its fields in scalar registers
     const uint32_t unit_lo = uni((uint32_t)s->unit[f]), unit_hi = uni((uint32_t)(s->unit[f] >> 32));
     const uint64_t unit = ((uint64_t)unit_hi << 32) | unit_lo;
@@ -2283,7 +2576,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
         __syncthreads();
       }
       const uint64_t c2 = clock_if(timing);
-      if (timing) w_fetch += c2 - c1;
+      if (timing) count(ST_WORK_TICKS_FETCH, c2 - c1);
       if (!valid) {
         // never seen whole: nothing in it can be trusted, not even the ticket it would complete.  The
         // unit is dropped; the host's wait for the ticket runs into its time limit.
@@ -2293,17 +2586,18 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
       if ((r->dep[0] | r->dep[1] | r->dep[2]) != 0 && !(r->rflags & RF_DEPS_RESOLVED)) {
         // It names earlier tasks: it joins the units held, and the first wavefront looks at its done
         // words with the next poll (and runs it at once if they are all there).
-        if (tid < 64) {
-          waiting |= 1u << f;
-          if (tid == 0) s->since[f] = wall_clock64();
+        if (tid == 0) {
+          s->waiting |= 1u << f;
+          s->since[f] = wall_clock64();
         }
+        if (tid < 64) lds_wave_sync();
         continue;
       }
     }
-    int32_t status = r->status;
+    int32_t status = (int32_t)uni((uint32_t)r->status);
     const uint32_t impl = uni(r->impl);
-    if (status == GPUOS_OK && (s->entry[f] >> 32) != r->version) status = GPUOS_E_VERSION;
-    if (status == GPUOS_OK && s->dep_status != 0) status = s->dep_status;
+    if (status == GPUOS_OK && uni((uint32_t)(s->entry[f] >> 32)) != uni(r->version)) status = GPUOS_E_VERSION;
+    if (status == GPUOS_OK) status = (int32_t)uni((uint32_t)s->dep_status);
     const uint64_t c3 = clock_if(timing);
     // a task's start in the trace is the moment a workgroup took its descriptor (a unit that waited: when it began to)
     const uint64_t c_start = (tracing && action == kActRun) ? s->since[f] : c1;
@@ -2353,8 +2647,8 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
     }
     __syncthreads();                  // the descriptor in LDS may be overwritten after this
     const uint64_t c5 = clock_if(timing);
-    w_units += 1;
-    if (timing) { w_exec += c4 - c3; w_done += c5 - c4; }
+    if (tid == 0) s->n_units += 1;
+    if (timing) { count(ST_WORK_TICKS_EXEC, c4 - c3); count(ST_WORK_TICKS_COMPLETE, c5 - c4); }
   }
 }
 

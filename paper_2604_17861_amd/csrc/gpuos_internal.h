@@ -28,6 +28,8 @@ enum Path : uint8_t {
   PATH_ROW_FUSED = 7,    // row operation (softmax, layer norm): contiguous rows of whole
                          // 16-byte vectors, one dtype, a row lives in one wavefront's registers
   PATH_ROW_GENERIC = 8,  // row operation over any strides / dtypes: three passes over memory
+  PATH_ROWS = 10,        // <= 3 outer dims of any strides over rows that are contiguous in every operand
+                         // (or one scalar per row): slices, head splits, casts, any row length or alignment
   PATH_STAGED = 9        // contiguous [R, C] output, inputs with any row / column strides (stride-2
                          // slices, row and column vectors, mixed dtypes): gathered through LDS
 };
@@ -59,13 +61,14 @@ struct alignas(16) Record {
   uint8_t  rflags;
   uint8_t  okind[3];         // PATH_ROW2D / PATH_TILE2D: OperandKind per input
   uint8_t  sel;              // table slot the task claimed            (dispatcher)
-  uint16_t pad0;
+  uint8_t  vdtype;           // PATH_ROWS: dtype of the operands that are not one scalar per row
+  uint8_t  vwidth;           // PATH_ROWS: elements per vector (numel and chunk count vectors)
   uint32_t impl;             // implementation id                     (dispatcher)
   uint32_t version;          // table version the task claimed        (dispatcher)
   int32_t  status;           // 0, or the error the task completes with (dispatcher)
   uint32_t nchunks;
   uint32_t chunk;            // elements (elementwise) or rows (reduction, row operation) per chunk
-  uint32_t numel;            // elementwise: output elements; reduction / row operation: rows
+  uint32_t numel;            // elementwise: output elements (PATH_TILE2D: tiles, PATH_ROWS: vectors); reduction / row operation: rows
   uint32_t red_n;            // reduction / row length
   float    alpha;
   uint16_t dep[3];

@@ -141,6 +141,7 @@ bool impl_takes_int(uint32_t impl) {
 inline uint32_t dtype_size(uint32_t dt) { return (dt == GPUOS_F32 || dt == GPUOS_I32) ? 4u : 2u; }
 
 constexpr int64_t kMaxExtent = 2147483647LL;
+constexpr int64_t kRowsExtent = 0x7ffffff0LL - 64;   // bytes of an operand that PATH_ROWS addresses from one buffer resource, below the offset that loads nothing
 
 struct Operand {              // one tensor after masking broadcast dims
   uint64_t ptr;
@@ -384,8 +385,42 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
       }
       if (ok) { rec.path = PATH_ROW2D; rec.rflags |= RF_VEC; }
     }
-    // chunk_elems is quoted for 12 bytes of traffic per element (an fp32 binary op); scale it so
-    // that a chunk of any op moves about the same number of bytes
+    // Rows that are contiguous in every operand, or hold one scalar per row, under up to three outer
+    // dims of any strides: 16-byte accesses whatever the row length and alignment are, as long as a
+    // row holds a vector.  Operands of one dtype (a COPY may convert), scalars of any. 
+    if ((rec.path == PATH_GENERIC || (rec.path == PATH_CONTIG && !all_aligned)) && nd <= 4 &&
+        ops[ar].stride[nd - 1] == 1) {
+      bool ok = true;
+      int full = -1;                                             // the first operand that is not one scalar per row
+      uint8_t kinds[3] = {0, 0, 0};
+      for (int k = 0; k < ar && ok; ++k) {
+        const int64_t s1 = ops[k].stride[nd - 1];
+        if (s1 == 1) { if (full < 0) full = k; ok = ops[k].dtype == ops[full].dtype; kinds[k] = K_FULL; }
+        else if (s1 == 0 && ar >= 2) kinds[k] = K_ROWSCALAR;
+        else ok = false;
+      }
+      ok = ok && full >= 0 && (ops[full].dtype == ops[ar].dtype || impl == GPUOS_IMPL_COPY);
+      const int64_t C = size[nd - 1];
+      const uint32_t W = ok && (dtype_size(ops[full].dtype) == 2 || dtype_size(ops[ar].dtype) == 2) ? 8u : 4u;
+      for (int k = 0; k <= ar && ok; ++k) {                      // every operand's extent fits one buffer resource
+        int64_t extent = 1;
+        for (int d = 0; d < nd; ++d) extent += (size[d] - 1) * ops[k].stride[d];
+        ok = extent * (int64_t)dtype_size(ops[k].dtype) < kRowsExtent;
+      }
+      if (ok && C >= (int64_t)W) {
+        rec.path = PATH_ROWS;
+        rec.ndim = 4;
+        rec.vdtype = (uint8_t)ops[full].dtype;
+        rec.vwidth = (uint8_t)W;
+        const int lead = 4 - nd;                                 // leading dims of size 1
+        for (int d = 0; d < 4; ++d) {
+          rec.size[d] = d < lead ? 1u : (uint32_t)size[d - lead];
+          for (int k = 0; k < ar; ++k) rec.stride[k][d] = d < lead ? 0u : (uint32_t)ops[k].stride[d - lead];
+          rec.stride[3][d] = d < lead ? 0u : (uint32_t)ops[ar].stride[d - lead];
+        }
+        for (int k = 0; k < ar; ++k) rec.okind[k] = kinds[k];
+      }
+    }
     // [B, R, C] contiguous output with an input whose unit stride runs along R (a transposed
     // view): gathered through LDS tiles.  COPY between equal dtypes stays on the generic path,
     // which moves raw bits (NaN payloads survive).
@@ -456,6 +491,8 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
         }
       }
     }
+    // chunk_elems is quoted for 12 bytes of traffic per element (an fp32 binary op); scale it so
+    // that a chunk of any op moves about the same number of bytes
     uint64_t traffic = dtype_size(ops[ar].dtype);
     for (int k = 0; k < ar; ++k) traffic += dtype_size(ops[k].dtype);
     uint64_t base_per = ((uint64_t)chunk_elems * 12 / traffic + 1023) / 1024 * 1024;
@@ -479,6 +516,17 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
       }
       if (quarter < half) quarter = half;
       per = quarter < base_per ? quarter : base_per;
+    }
+    if (rec.path == PATH_ROWS) {                                 // counted in vectors, the partly filled last one of a row included
+      const uint64_t vectors = (uint64_t)numel / (uint64_t)size[nd - 1] * (((uint64_t)size[nd - 1] + rec.vwidth - 1) / rec.vwidth);
+      rec.numel = (uint32_t)vectors;
+      per /= rec.vwidth;
+      const uint64_t min_per = (vectors + kMaxChunksPerTask - 1) / kMaxChunksPerTask;
+      if (per < min_per) per = min_per;
+      rec.chunk = (uint32_t)per;
+      rec.nchunks = (uint32_t)((vectors + per - 1) / per);
+      *r = rec;
+      return GPUOS_OK;
     }
     rec.chunk = (uint32_t)per;
     rec.nchunks = (uint32_t)(((uint64_t)numel + per - 1) / per);

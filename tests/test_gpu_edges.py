@@ -12,3 +12,43 @@ pytestmark = pytest.mark.gpu
 def test_reductions_at_their_edges(code):
     stats, _ = _run_and_check(E.reduction_edges(code))
     print(stats, flush=True)
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16, S.I32])
+def test_rows_at_their_edges(code):
+    stats, _ = _run_and_check(E.rows_edges(code))
+    print(stats, flush=True)
+
+
+def test_an_operator_swapped_under_tasks_packed_as_rows():
+    """Tasks are packed for the operator bound when they are submitted and run with the one bound when
+    they are claimed: rows whose new operator has no executor of that kind (a program, another unary
+    operator on a converting copy) run element by element.  The swap falls between submission and
+    flush, so every task is claimed with the second binding."""
+    import numpy as np
+    from gpu_helpers import DevicePools, compare_with_oracle
+    from helpers import Builder
+    from paper_2604_17861_amd import runtime as R
+    rng = np.random.default_rng(3)
+    P = S.program
+    for op, new in (("COPY", "RELU"), ("SCALE", (P(("NEG", 0, 0)), 1)), ("SUB", (P(("SUB", 4, 1, 0), ("MOV", 0, 4)), 2))):
+        print("swap under", op, flush=True)
+        b = Builder()
+        prog = not isinstance(new, str)
+        impl = b.define_program(200, *new) if prog else S.IMPL[new]
+        for R_, C_ in ((5, 37), (90, 1001)):
+            x = b.pool(E.values(rng, (R_, C_ + 5), S.F32))[:, 2:C_ + 2]
+            y = b.pool(E.values(rng, (R_, C_), S.F32))
+            o = b.pool(np.zeros((R_, C_ + 1), np.float16 if op == "COPY" else np.float32))[:, 1:]
+            b.add(op, o, [x, y] if op == "SUB" else [x], alpha=2.0)
+        s = b.stream("swap_under_rows")
+        dp = DevicePools(s)
+        with R.Runtime(0, idle_exit_ms=20000, wait_timeout_ms=20000) as rt:
+            rt.register_table(s.table, s.programs)
+            t0 = rt.submit(dp.tasks, 0, len(s), flush=False)
+            rt.swap_op(S.OP[op], impl)
+            rt.wait()
+            comps = rt.completions(t0, len(s))
+        assert np.all(comps["status"] == 0) and np.all(comps["op_version"] == 2)
+        s.table[S.OP[op]] = impl
+        compare_with_oracle(s, dp.download())
