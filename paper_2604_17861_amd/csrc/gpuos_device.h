@@ -1219,6 +1219,18 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
   }
 }
 
+// Which executor takes a task is decided by halving: pick<LO, HI> calls F::run<K> for the K in [LO, HI)
+// that equals k.  (The compiler turns a many-way branch into a chain that is walked case by case, with
+// a flag to carry per case; a two-way choice whose sides meet again is left alone.)
+template <int LO, int HI, class F, class... A> DEV void pick(uint32_t k, A... a) {
+  if constexpr (HI - LO == 1) F::template run<LO>(a...);
+  else {
+    constexpr int MID = (LO + HI) / 2;
+    if (k < (uint32_t)MID) pick<LO, MID, F>(k, a...);
+    else pick<MID, HI, F>(k, a...);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // reductions over the last dim
 // ---------------------------------------------------------------------------
@@ -1632,10 +1644,14 @@ PATHFN void red_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
 // ---------------------------------------------------------------------------
 // fused row operations (operator library, Section 5.2: softmax, layer normalisation).
 // Each row of the last dim is one problem; the output has the input's shape.
-//   PATH_ROW_FUSED: one dtype, contiguous rows of whole aligned 16-byte vectors, at most 256
-//     vectors per row.  A row is read once into the registers of the P lanes that own it
+//   PATH_ROW_FUSED: one dtype, contiguous rows that hold at least a vector, any length and alignment.
+//     A row is cut into 16-byte vectors from its first element on; in a row that is no multiple the
+//     last vector covers the row's last V elements, and those the vector before it holds count for
+//     nothing (RAGGED: also rows whose base is not 16-byte aligned; accesses need element alignment only).
+//     Up to 256 vectors a row is read once into the registers of the P lanes that own it
 //     (P = 64 for rows over 64 vectors, else the power of two >= vectors per row, 64 / P rows
-//     per wavefront pass), reduced with xor butterflies over those lanes, and written once.
+//     per wavefront pass), reduced with xor butterflies over those lanes, and written once; longer
+//     rows belong to the workgroup (rowop_wg, softmax_long).
 //   PATH_ROW_GENERIC: any strides and dtypes; one wavefront per row, three passes over memory.
 // Arithmetic is fp32.  Lanes outside a row feed the identity (-inf to the softmax, 0 to the
 // sums).  The softmax maximum ignores NaN; a NaN still poisons its row through the sum.
@@ -1668,9 +1684,9 @@ template <int ROP> struct RowOp {
 // 16-byte vector), or fp32 under 16-bit x (P32: two vectors), as frameworks keep them.
 template <int POL, int DT, bool P32> struct RowParam {
   v4i q[P32 ? 2 : 1];
-  DEV void load(rsrc_t rs, uint32_t vec) {
-    if (P32) { q[0] = Mem<POL>::ld16(rs, vec * 32u); q[P32 ? 1 : 0] = Mem<POL>::ld16(rs, vec * 32u + 16u); }
-    else q[0] = Mem<POL>::ld16(rs, vec * 16u);
+  DEV void load(rsrc_t rs, uint32_t col) {             // from element `col` of the row on
+    if (P32) { q[0] = Mem<POL>::ld16(rs, col * 4u); q[P32 ? 1 : 0] = Mem<POL>::ld16(rs, col * 4u + 16u); }
+    else q[0] = Mem<POL>::ld16(rs, col * (uint32_t)Elem<DT>::ES);
   }
   DEV float get(int e) const {
     if (P32) return Elem<GPUOS_F32>::get(q[(e >> 2) & (P32 ? 1 : 0)], e & 3);
@@ -1678,13 +1694,44 @@ template <int POL, int DT, bool P32> struct RowParam {
   }
 };
 
-template <int POL, int ROP, int DT, int KW, int UP, bool P32 = false>
-DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end) {
+// The vectors of a row of n elements: vector `vec` begins at element begin(vec), and its elements from
+// first(vec) on are its own.
+template <int V, bool RAGGED> struct RowCut {
+  uint32_t n, vpr, tail;                               // vectors per row; elements of the last one that are its own (0: all)
+  DEV explicit RowCut(uint32_t n_) : n(n_), vpr((n_ + V - 1) / V), tail(n_ % V) {}
+  DEV bool last(uint32_t vec) const { return RAGGED && tail != 0 && vec == vpr - 1; }
+  DEV uint32_t begin(uint32_t vec) const { return last(vec) ? n - V : vec * V; }
+  DEV int first(uint32_t vec) const { return last(vec) ? V - (int)tail : 0; }
+};
+// One vector of the output, its own elements only.
+template <int POL, int DT, bool RAGGED> DEV void row_store(rsrc_t ro, uint32_t off, const v4i& q, bool act, int first) {
+  using E = Elem<DT>;
+  if (!RAGGED) { if (act) Mem<POL>::st16(ro, off, q); return; }
+  Mem<POL>::st16(ro, act && first == 0 ? off : kNoLoad, q);
+  if (act && first != 0) {
+#pragma unroll
+    for (int e = 1; e < (int)E::V; ++e)
+      if (e >= first) {
+        if (E::ES == 4) Mem<POL>::stb4(ro, off + e * 4u, (uint32_t)q[e & 3]);
+        else Mem<POL>::stb2(ro, off + e * 2u, (uint32_t)q[e / 2] >> ((e & 1) * 16));
+      }
+  }
+}
+
+// Bound by memory for fp32, by memory and conversions together for 16-bit rows.  A pass (UP rows per lane
+// group) is a chain load -> reduce -> reduce -> store; layer norm, whose chunks are several passes,
+// requests the next pass before it computes this one.  (Softmax rows are not: the registers for it
+// make the function save its caller's, a memory round trip per chunk.)
+template <int POL, int ROP, int DT, int KW, int UP, bool P32, bool RAGGED>
+DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v) {
   using E = Elem<DT>;
   using M = Mem<POL>;
   using RO = RowOp<ROP>;
   constexpr uint32_t V = E::V;
-  const uint32_t n = uni(r->red_n), vpr = n / V;
+  constexpr bool MASK = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST;
+  const uint32_t n = uni(r->red_n);
+  const RowCut<V, RAGGED> cut(n);
+  const uint32_t vpr = cut.vpr;
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
   uint32_t P = 64;
   if (KW == 1) { P = 1; while (P < vpr) P <<= 1; }
@@ -1698,7 +1745,7 @@ DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end) {
   // second / third input: laid out like x (K_FULL) or a [period, n] block reused every period rows;
   // layer norm: gamma and beta are always one row
   rsrc_t rs[2];
-  uint32_t period[2] = {0, 0};
+  uint32_t period = 0;
 #pragma unroll
   for (int k = 1; k < RO::NIN; ++k) {
     if (!RO::SOFTMAX) {
@@ -1706,50 +1753,73 @@ DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end) {
     } else if (uni(r->okind[k]) == K_FULL) {
       rs[k - 1] = make_rsrc(uni_ptr(r->ptr[k]) + chunk_off, chunk_bytes);
     } else {
-      period[k - 1] = uni(r->stride[k][0]);
-      rs[k - 1] = make_rsrc(uni_ptr(r->ptr[k]), period[k - 1] * n * E::ES);
+      period = uni(r->stride[k][0]);
+      rs[k - 1] = make_rsrc(uni_ptr(r->ptr[k]), period * n * E::ES);
     }
   }
-  // layer norm: this lane's pieces of gamma and beta are loaded once
-  RowParam<POL, DT, P32> gq[KW], bq[KW];
-  if (!RO::SOFTMAX) {
+  // this lane's vectors are the same in every row
+  uint32_t at[KW];                                     // byte offset in a row
+  int first[KW];
 #pragma unroll
-    for (int k = 0; k < KW; ++k) {
-      const uint32_t vec = j + 64u * k;
-      gq[k].load(rs[0], vec);                        // past the row: reads zeros (bounds-checked), never used
-      bq[k].load(rs[1], vec);
-    }
+  for (int k = 0; k < KW; ++k) {
+    const uint32_t vec = j + 64u * k;
+    at[k] = cut.begin(vec) * E::ES;
+    first[k] = cut.first(vec);
   }
-  for (uint32_t base = row_begin + wave * rpw * UP; base < row_end; base += 4u * rpw * UP) {
-    v4i q[UP][KW], mq[UP][KW];
-    bool act[UP][KW];
+  const uint32_t step = 4u * rpw * UP;
+  struct Pass { v4i q[UP][KW], mq[MASK ? UP : 1][MASK ? KW : 1]; };
+  auto load = [&](Pass& p, uint32_t base) {            // a row past the chunk is not fetched
 #pragma unroll
     for (int u = 0; u < UP; ++u) {
       const uint32_t row = base + u * rpw + sub, lr = row - row_begin;
       uint32_t mr = lr;
-      if (ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST && period[0]) mr = row % period[0];
+      if (MASK && period) mr = row % period;
 #pragma unroll
       for (int k = 0; k < KW; ++k) {
-        const uint32_t vec = j + 64u * k;
-        act[u][k] = row < row_end && vec < vpr;
-        // rows past the chunk and vectors past the row read zeros or a neighbour's data; masked below
-        q[u][k] = M::ld16(rx, (lr * vpr + vec) * 16u);
-        if (ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST) mq[u][k] = M::ld16(rs[0], (mr * vpr + vec) * 16u);
+        const bool act = row < row_end && j + 64u * k < vpr;
+        p.q[u][k] = M::ld16(rx, act ? lr * n * E::ES + at[k] : kNoLoad);
+        if (MASK) p.mq[u][k] = M::ld16(rs[0], act ? mr * n * E::ES + at[k] : kNoLoad);
       }
     }
+  };
+  uint32_t base = row_begin + wave * rpw * UP;
+  constexpr bool AHEAD = !RO::SOFTMAX;
+  Pass cur, nxt;
+  if (AHEAD) load(cur, base);
+  // layer norm: gamma and beta lie in LDS, vector by vector (each wavefront loading its own to registers
+  // fetched them four times a chunk, as many bytes as the chunk's rows, and left none for the next pass)
+  v4i* const params = (v4i*)s_v;                       // [2][vpr][PQ]
+  constexpr uint32_t PQ = P32 ? 2 : 1;
+  static_assert(2 * 256 * 2 * 4 <= kScratchFloats, "two rows of 256 vectors of fp32 parameters under 16-bit elements");
+  if (!RO::SOFTMAX) {
+    for (uint32_t vec = threadIdx.x; vec < vpr; vec += kThreads) {
+      RowParam<POL, DT, P32> g, b;
+      g.load(rs[0], cut.begin(vec));
+      b.load(rs[1], cut.begin(vec));
+#pragma unroll
+      for (uint32_t i = 0; i < PQ; ++i) { params[vec * PQ + i] = g.q[i]; params[(vpr + vec) * PQ + i] = b.q[i]; }
+    }
+    __syncthreads();
+  }
+  for (; base < row_end; base += step) {
+    if (AHEAD) load(nxt, base + step);
+    else load(cur, base);
 #pragma unroll
     for (int u = 0; u < UP; ++u) {
       const uint32_t row = base + u * rpw + sub, lr = row - row_begin;
       float t[KW][V];
+      bool act[KW];
+#pragma unroll
+      for (int k = 0; k < KW; ++k) act[k] = row < row_end && j + 64u * k < vpr;
       if (RO::SOFTMAX) {
         float m = -__builtin_inff();
 #pragma unroll
         for (int k = 0; k < KW; ++k)
 #pragma unroll
           for (int e = 0; e < (int)V; ++e) {
-            float x = E::get(q[u][k], e);
-            if (ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST) x = alpha * x + E::get(mq[u][k], e);
-            t[k][e] = act[u][k] ? x : -__builtin_inff();
+            float x = E::get(cur.q[u][k], e);
+            if (MASK) x = alpha * x + E::get(cur.mq[MASK ? u : 0][MASK ? k : 0], e);
+            t[k][e] = act[k] && (!RAGGED || e >= first[k]) ? x : -__builtin_inff();
             m = __builtin_fmaxf(m, t[k][e]);
           }
         m = bfly_max(m, P);
@@ -1765,32 +1835,38 @@ DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end) {
           v4i oq;
 #pragma unroll
           for (int e = 0; e < (int)V; ++e) E::put(oq, e, t[k][e] * inv);
-          if (act[u][k]) M::st16(ro, (lr * vpr + j + 64u * k) * 16u, oq);
+          row_store<POL, DT, RAGGED>(ro, lr * n * E::ES + at[k], oq, act[k], first[k]);
         }
       } else {
         float s = 0.0f;
 #pragma unroll
         for (int k = 0; k < KW; ++k)
 #pragma unroll
-          for (int e = 0; e < (int)V; ++e) { t[k][e] = act[u][k] ? E::get(q[u][k], e) : 0.0f; s += t[k][e]; }
+          for (int e = 0; e < (int)V; ++e) { t[k][e] = E::get(cur.q[u][k], e); s += act[k] && (!RAGGED || e >= first[k]) ? t[k][e] : 0.0f; }
         const float mean = bfly_sum(s, P) / (float)n;
         float ss = 0.0f;
 #pragma unroll
         for (int k = 0; k < KW; ++k)
 #pragma unroll
-          for (int e = 0; e < (int)V; ++e) { t[k][e] = act[u][k] ? t[k][e] - mean : 0.0f; ss += t[k][e] * t[k][e]; }
+          for (int e = 0; e < (int)V; ++e) { t[k][e] -= mean; ss += act[k] && (!RAGGED || e >= first[k]) ? t[k][e] * t[k][e] : 0.0f; }
         const float var = bfly_sum(ss, P) / (float)n;
         const float rstd = 1.0f / __builtin_sqrtf(var + alpha);
 #pragma unroll
         for (int k = 0; k < KW; ++k) {
           v4i oq;
+          RowParam<POL, DT, P32> g, b;
+          const uint32_t vec = j + 64u * k < vpr ? j + 64u * k : 0u;
 #pragma unroll
-          for (int e = 0; e < (int)V; ++e) E::put(oq, e, t[k][e] * rstd * gq[k].get(e) + bq[k].get(e));
-          if (act[u][k]) M::st16(ro, (lr * vpr + j + 64u * k) * 16u, oq);
+          for (uint32_t i = 0; i < PQ; ++i) { g.q[i] = params[vec * PQ + i]; b.q[i] = params[(vpr + vec) * PQ + i]; }
+#pragma unroll
+          for (int e = 0; e < (int)V; ++e) E::put(oq, e, t[k][e] * rstd * g.get(e) + b.get(e));
+          row_store<POL, DT, RAGGED>(ro, lr * n * E::ES + at[k], oq, act[k], first[k]);
         }
       }
     }
+    if (AHEAD) cur = nxt;
   }
+  if (!RO::SOFTMAX) __syncthreads();                   // the LDS belongs to the next chunk after this
 }
 
 template <int POL, int ROP>
@@ -1858,20 +1934,39 @@ PATHFN void rowop_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
   }
 }
 
-// Rows longer than one wavefront's registers: the whole workgroup owns a row.  KW = 1..4: the row
-// (up to 1024 vectors) lives in registers, 256 lanes x KW vectors, read once and written once.
-// KW = 0: any length, three streaming passes of 16-byte vector loads over the row (the second and
-// third pass re-read what the first brought into the caches).  Cross-wavefront reductions go
-// through four rotating LDS slots: one barrier per reduction.
-template <int POL, int ROP, int DT, int KW, bool P32 = false>
+// Sum / maximum over the workgroup, through four rotating LDS slots: one barrier per reduction.
+struct WgReduce {
+  float* slots;                                        // 16 floats
+  uint32_t turn;
+  DEV float* next() { float* p = slots + (turn & 3u) * 4u; ++turn; return p; }
+  DEV float sum(float v) {
+    v = bfly_sum(v, 64);
+    float* slot = next();
+    if ((threadIdx.x & 63u) == 0) slot[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return (slot[0] + slot[1]) + (slot[2] + slot[3]);
+  }
+  DEV float max(float v) {
+    v = bfly_max(v, 64);
+    float* slot = next();
+    if ((threadIdx.x & 63u) == 0) slot[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return __builtin_fmaxf(__builtin_fmaxf(slot[0], slot[1]), __builtin_fmaxf(slot[2], slot[3]));
+  }
+};
+
+// Rows longer than one wavefront's registers: the whole workgroup owns a row and holds it in
+// registers, 256 lanes x KW vectors, read once and written once.
+template <int POL, int ROP, int DT, int KW, bool P32, bool RAGGED>
 DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_red) {
   using E = Elem<DT>;
   using M = Mem<POL>;
   using RO = RowOp<ROP>;
   constexpr uint32_t V = E::V;
-  constexpr int KR = KW > 0 ? KW : 1;
-  const uint32_t n = uni(r->red_n), vpr = n / V;
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  constexpr bool MASK = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST;
+  const uint32_t n = uni(r->red_n);
+  const RowCut<V, RAGGED> cut(n);
+  const uint32_t vpr = cut.vpr, tid = threadIdx.x;
   const float alpha = r->alpha;
   const uint32_t nrows = row_end - row_begin;
   const uint32_t chunk_bytes = nrows * n * E::ES;
@@ -1879,7 +1974,7 @@ DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* 
   const rsrc_t rx = make_rsrc(uni_ptr(r->ptr[0]) + chunk_off, chunk_bytes);
   const rsrc_t ro = make_rsrc(uni_ptr(r->ptr[3]) + chunk_off, chunk_bytes);
   rsrc_t rs[2];
-  uint32_t period[2] = {0, 0};
+  uint32_t period = 0;
 #pragma unroll
   for (int k = 1; k < RO::NIN; ++k) {
     if (!RO::SOFTMAX) {
@@ -1887,188 +1982,330 @@ DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* 
     } else if (uni(r->okind[k]) == K_FULL) {
       rs[k - 1] = make_rsrc(uni_ptr(r->ptr[k]) + chunk_off, chunk_bytes);
     } else {
-      period[k - 1] = uni(r->stride[k][0]);
-      rs[k - 1] = make_rsrc(uni_ptr(r->ptr[k]), period[k - 1] * n * E::ES);
+      period = uni(r->stride[k][0]);
+      rs[k - 1] = make_rsrc(uni_ptr(r->ptr[k]), period * n * E::ES);
     }
   }
-  uint32_t turn = 0;                                   // which of the four LDS slots the next reduction uses
-  auto wg_sum = [&](float v) {
-    v = bfly_sum(v, 64);
-    float* slot = s_red + (turn & 3u) * 4u;
-    ++turn;
-    if (lane == 0) slot[wave] = v;
-    __syncthreads();
-    return (slot[0] + slot[1]) + (slot[2] + slot[3]);
-  };
-  auto wg_max = [&](float v) {
-    v = bfly_max(v, 64);
-    float* slot = s_red + (turn & 3u) * 4u;
-    ++turn;
-    if (lane == 0) slot[wave] = v;
-    __syncthreads();
-    return __builtin_fmaxf(__builtin_fmaxf(slot[0], slot[1]), __builtin_fmaxf(slot[2], slot[3]));
-  };
-  // the argument of element e of vector `vec` of local row lr (softmax family) / the element itself
-  auto arg = [&](const v4i& q, const v4i& mq, int e) {
-    float x = E::get(q, e);
-    if (ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST) x = alpha * x + E::get(mq, e);
-    return x;
-  };
-  RowParam<POL, DT, P32> gq[KR], bq[KR];               // layer norm, KW > 0: this lane's gamma / beta pieces
-  if (!RO::SOFTMAX && KW > 0) {
+  // layer norm: up to four vectors a lane, this lane's gamma and beta stay in registers; longer rows
+  // fill them, and fetch the two again
+  constexpr int KP = !RO::SOFTMAX && KW <= 4 ? KW : 1;
+  RowParam<POL, DT, P32> gk[KP], bk[KP];
+  if (!RO::SOFTMAX && KW <= 4) {
 #pragma unroll
-    for (int k = 0; k < KR; ++k) {
-      gq[k].load(rs[0], tid + kThreads * k);
-      bq[k].load(rs[1], tid + kThreads * k);
+    for (int k = 0; k < KP; ++k) {
+      const uint32_t vec = tid + kThreads * k;
+      gk[k].load(rs[0], vec < vpr ? cut.begin(vec) : 0u);
+      bk[k].load(rs[1], vec < vpr ? cut.begin(vec) : 0u);
     }
   }
+  WgReduce wg = {s_red, 0};
   for (uint32_t row = row_begin; row < row_end; ++row) {
     const uint32_t lr = row - row_begin;
     uint32_t mr = lr;
-    if (ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST && period[0]) mr = row % period[0];
-    if (KW > 0) {
-      v4i q[KR], mq[KR];
-      bool act[KR];
+    if (MASK && period) mr = row % period;
+    v4i q[KW], mq[MASK ? KW : 1];
 #pragma unroll
-      for (int k = 0; k < KR; ++k) {
-        const uint32_t vec = tid + kThreads * k;
-        act[k] = vec < vpr;
-        q[k] = M::ld16(rx, act[k] ? (lr * vpr + vec) * 16u : kNoLoad);
-        if (ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST) mq[k] = M::ld16(rs[0], act[k] ? (mr * vpr + vec) * 16u : kNoLoad);
-      }
-      float t[KR][V];
-      if (RO::SOFTMAX) {
-        float m = -__builtin_inff();
-#pragma unroll
-        for (int k = 0; k < KR; ++k)
-#pragma unroll
-          for (int e = 0; e < (int)V; ++e) { t[k][e] = act[k] ? arg(q[k], mq[k], e) : -__builtin_inff(); m = __builtin_fmaxf(m, t[k][e]); }
-        m = wg_max(m);
-        float sum = 0.0f;
-#pragma unroll
-        for (int k = 0; k < KR; ++k)
-#pragma unroll
-          for (int e = 0; e < (int)V; ++e) { t[k][e] = __expf(t[k][e] - m); sum += t[k][e]; }
-        const float inv = 1.0f / wg_sum(sum);
-#pragma unroll
-        for (int k = 0; k < KR; ++k) {
-          v4i oq;
-#pragma unroll
-          for (int e = 0; e < (int)V; ++e) E::put(oq, e, t[k][e] * inv);
-          if (act[k]) M::st16(ro, (lr * vpr + tid + kThreads * k) * 16u, oq);
-        }
-      } else {
-        float sum = 0.0f;
-#pragma unroll
-        for (int k = 0; k < KR; ++k)
-#pragma unroll
-          for (int e = 0; e < (int)V; ++e) { t[k][e] = act[k] ? E::get(q[k], e) : 0.0f; sum += t[k][e]; }
-        const float mean = wg_sum(sum) / (float)n;
-        float ss = 0.0f;
-#pragma unroll
-        for (int k = 0; k < KR; ++k)
-#pragma unroll
-          for (int e = 0; e < (int)V; ++e) { t[k][e] = act[k] ? t[k][e] - mean : 0.0f; ss += t[k][e] * t[k][e]; }
-        const float rstd = 1.0f / __builtin_sqrtf(wg_sum(ss) / (float)n + alpha);
-#pragma unroll
-        for (int k = 0; k < KR; ++k) {
-          v4i oq;
-#pragma unroll
-          for (int e = 0; e < (int)V; ++e) E::put(oq, e, t[k][e] * rstd * gq[k].get(e) + bq[k].get(e));
-          if (act[k]) M::st16(ro, (lr * vpr + tid + kThreads * k) * 16u, oq);
-        }
-      }
-    } else if (RO::SOFTMAX) {
-      const v4i zero = {0, 0, 0, 0};
+    for (int k = 0; k < KW; ++k) {
+      const uint32_t vec = tid + kThreads * k;
+      const uint32_t at = cut.begin(vec) * E::ES;
+      q[k] = M::ld16(rx, vec < vpr ? lr * n * E::ES + at : kNoLoad);
+      if (MASK) mq[k] = M::ld16(rs[0], vec < vpr ? mr * n * E::ES + at : kNoLoad);
+    }
+    float t[KW][V];
+    auto own = [&](int k, int e) { const uint32_t vec = tid + kThreads * k; return vec < vpr && (!RAGGED || e >= cut.first(vec)); };
+    if (RO::SOFTMAX) {
       float m = -__builtin_inff();
-      for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
-        const v4i q = M::ld16(rx, (lr * vpr + vec) * 16u);
-        const v4i mq = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST ? M::ld16(rs[0], (mr * vpr + vec) * 16u) : zero;
 #pragma unroll
-        for (int e = 0; e < (int)V; ++e) m = __builtin_fmaxf(m, arg(q, mq, e));
-      }
-      m = wg_max(m);
+      for (int k = 0; k < KW; ++k)
+#pragma unroll
+        for (int e = 0; e < (int)V; ++e) {
+          float x = E::get(q[k], e);
+          if (MASK) x = alpha * x + E::get(mq[MASK ? k : 0], e);
+          t[k][e] = own(k, e) ? x : -__builtin_inff();
+          m = __builtin_fmaxf(m, t[k][e]);
+        }
+      m = wg.max(m);
       float sum = 0.0f;
-      for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
-        const v4i q = M::ld16(rx, (lr * vpr + vec) * 16u);
-        const v4i mq = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST ? M::ld16(rs[0], (mr * vpr + vec) * 16u) : zero;
 #pragma unroll
-        for (int e = 0; e < (int)V; ++e) sum += __expf(arg(q, mq, e) - m);
-      }
-      const float inv = 1.0f / wg_sum(sum);
-      for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
-        const v4i q = M::ld16(rx, (lr * vpr + vec) * 16u);
-        const v4i mq = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST ? M::ld16(rs[0], (mr * vpr + vec) * 16u) : zero;
+      for (int k = 0; k < KW; ++k)
+#pragma unroll
+        for (int e = 0; e < (int)V; ++e) { t[k][e] = __expf(t[k][e] - m); sum += t[k][e]; }
+      const float inv = 1.0f / wg.sum(sum);
+#pragma unroll
+      for (int k = 0; k < KW; ++k) {
+        const uint32_t vec = tid + kThreads * k;
         v4i oq;
 #pragma unroll
-        for (int e = 0; e < (int)V; ++e) E::put(oq, e, __expf(arg(q, mq, e) - m) * inv);
-        M::st16(ro, (lr * vpr + vec) * 16u, oq);
+        for (int e = 0; e < (int)V; ++e) E::put(oq, e, t[k][e] * inv);
+        row_store<POL, DT, RAGGED>(ro, lr * n * E::ES + cut.begin(vec) * E::ES, oq, vec < vpr, cut.first(vec));
       }
     } else {
       float sum = 0.0f;
-      for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
-        const v4i q = M::ld16(rx, (lr * vpr + vec) * 16u);
 #pragma unroll
-        for (int e = 0; e < (int)V; ++e) sum += E::get(q, e);
-      }
-      const float mean = wg_sum(sum) / (float)n;
+      for (int k = 0; k < KW; ++k)
+#pragma unroll
+        for (int e = 0; e < (int)V; ++e) { t[k][e] = E::get(q[k], e); sum += own(k, e) ? t[k][e] : 0.0f; }
+      const float mean = wg.sum(sum) / (float)n;
       float ss = 0.0f;
-      for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
-        const v4i q = M::ld16(rx, (lr * vpr + vec) * 16u);
 #pragma unroll
-        for (int e = 0; e < (int)V; ++e) { const float d = E::get(q, e) - mean; ss += d * d; }
-      }
-      const float rstd = 1.0f / __builtin_sqrtf(wg_sum(ss) / (float)n + alpha);
-      for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
-        const v4i q = M::ld16(rx, (lr * vpr + vec) * 16u);
+      for (int k = 0; k < KW; ++k)
+#pragma unroll
+        for (int e = 0; e < (int)V; ++e) { t[k][e] -= mean; ss += own(k, e) ? t[k][e] * t[k][e] : 0.0f; }
+      const float rstd = 1.0f / __builtin_sqrtf(wg.sum(ss) / (float)n + alpha);
+#pragma unroll
+      for (int k = 0; k < KW; ++k) {
+        const uint32_t vec = tid + kThreads * k;
         RowParam<POL, DT, P32> g, b;
-        g.load(rs[0], vec);
-        b.load(rs[1], vec);
+        if (KW <= 4) { g = gk[k < KP ? k : 0]; b = bk[k < KP ? k : 0]; }
+        else {
+          g.load(rs[0], vec < vpr ? cut.begin(vec) : 0u);
+          b.load(rs[1], vec < vpr ? cut.begin(vec) : 0u);
+        }
         v4i oq;
 #pragma unroll
-        for (int e = 0; e < (int)V; ++e) E::put(oq, e, (E::get(q, e) - mean) * rstd * g.get(e) + b.get(e));
-        M::st16(ro, (lr * vpr + vec) * 16u, oq);
+        for (int e = 0; e < (int)V; ++e) E::put(oq, e, t[k][e] * rstd * g.get(e) + b.get(e));
+        row_store<POL, DT, RAGGED>(ro, lr * n * E::ES + cut.begin(vec) * E::ES, oq, vec < vpr, cut.first(vec));
       }
     }
   }
   __syncthreads();                                     // the LDS slots belong to the next chunk after this
 }
 
-template <int POL, int ROP, int DT>
-PATHFN void rowop_fused_dt(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
-  const Record* r = lds_arg(r_v);
-  const uint32_t begin = uni(begin_v), end = uni(end_v);
-  const uint32_t vpr = uni(r->red_n) / Elem<DT>::V;
-  if (ROP == GPUOS_IMPL_LAYERNORM_LAST && DT != GPUOS_F32 && uni(r->dtype[1]) == GPUOS_F32) {   // fp32 gamma / beta under 16-bit x
-    constexpr bool P = ROP == GPUOS_IMPL_LAYERNORM_LAST && DT != GPUOS_F32;
-    if (vpr <= 64u) rowop_fused<POL, ROP, DT, 1, 4, P>(r, begin, end);
-    else if (vpr <= 128u) rowop_fused<POL, ROP, DT, 2, 2, P>(r, begin, end);
-    else rowop_fused<POL, ROP, DT, 4, 1, P>(r, begin, end);
-    return;
+// Softmax rows too long for the workgroup's registers (over 16,384 elements): two passes over the row.
+// The first keeps a running maximum and a sum relative to it per lane, rescaled once per
+// batch of four vectors; the second writes.  What the first has left in registers (the last twelve
+// vectors of a lane, eight of 16-bit elements) and in LDS (its first six) is not read again, the rest
+// comes from the memory-side cache.
+template <int POL, int ROP, int DT, bool RAGGED>
+DEV void softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v) {
+  using E = Elem<DT>;
+  using M = Mem<POL>;
+  constexpr uint32_t V = E::V;
+  constexpr bool MASK = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST;
+  constexpr uint32_t U = 4, NB = MASK ? 0 : (DT == GPUOS_F32 ? 3 : 2);       // batches kept in registers (masked rows: none)
+  constexpr uint32_t NL = MASK ? 0 : 6, NR = NB * U;                        // vectors per lane kept in LDS / in registers
+  const uint32_t n = uni(r->red_n);
+  const RowCut<V, RAGGED> cut(n);
+  const uint32_t vpr = cut.vpr, tid = threadIdx.x;
+  const float alpha = r->alpha;
+  const uint32_t chunk_bytes = (row_end - row_begin) * n * E::ES;
+  const uint64_t chunk_off = (uint64_t)row_begin * n * E::ES;
+  const rsrc_t rx = make_rsrc(uni_ptr(r->ptr[0]) + chunk_off, chunk_bytes);
+  const rsrc_t ro = make_rsrc(uni_ptr(r->ptr[3]) + chunk_off, chunk_bytes);
+  rsrc_t rm = rx;
+  uint32_t period = 0;
+  if (MASK) {
+    if (uni(r->okind[1]) == K_FULL) rm = make_rsrc(uni_ptr(r->ptr[1]) + chunk_off, chunk_bytes);
+    else { period = uni(r->stride[1][0]); rm = make_rsrc(uni_ptr(r->ptr[1]), period * n * E::ES); }
   }
-  if (vpr <= 64u) rowop_fused<POL, ROP, DT, 1, 4>(r, begin, end);
-  else if (vpr <= 128u) rowop_fused<POL, ROP, DT, 2, 2>(r, begin, end);
-  else rowop_fused<POL, ROP, DT, 4, 1>(r, begin, end);
+  WgReduce wg = {s_v, 0};
+  v4i* const kept = (v4i*)(s_v + 16) + tid;            // vector i of this lane lies at kept[i * kThreads]
+  static_assert(16 + 6 * kThreads * 4 <= kScratchFloats, "six vectors per lane");
+  const uint32_t T = (vpr + kThreads - 1) / kThreads;  // vectors per lane, the last partly filled
+  const uint32_t held = T > NR ? T - NR : 0u;          // vectors [held, T) of a lane end the first pass in registers
+  for (uint32_t row = row_begin; row < row_end; ++row) {
+    const uint32_t x0 = (row - row_begin) * n * E::ES, m0 = MASK ? (period ? row % period : row - row_begin) * n * E::ES : 0u;
+    auto fetch = [&](uint32_t i, v4i& q, v4i& mq) {
+      const uint32_t vec = tid + kThreads * i, at = cut.begin(vec) * E::ES;
+      q = M::ld16(rx, vec < vpr ? x0 + at : kNoLoad);
+      if (MASK) mq = M::ld16(rm, vec < vpr ? m0 + at : kNoLoad);
+    };
+    // the softmax argument of element e of vector i, -inf where it is not this vector's (or i is not below lim)
+    auto arg = [&](uint32_t i, uint32_t lim, const v4i& q, const v4i& mq, int e) {
+      const uint32_t vec = tid + kThreads * i;
+      float x = E::get(q, e);
+      if (MASK) x = alpha * x + E::get(mq, e);
+      return i < lim && vec < vpr && (!RAGGED || e >= cut.first(vec)) ? x : -__builtin_inff();
+    };
+    float m = -__builtin_inff(), sum = 0.0f;
+    auto take = [&](uint32_t i0, uint32_t lim, const v4i (&q)[U], const v4i (&mq)[U]) {
+      float mb = m;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < (int)V; ++e) mb = __builtin_fmaxf(mb, arg(i0 + u, lim, q[u], mq[u], e));
+      const float ref = mb == -__builtin_inff() ? 0.0f : mb;       // (nothing but -inf so far: relative to 0, every term is 0)
+      float part = 0.0f;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < (int)V; ++e) part += __expf(arg(i0 + u, lim, q[u], mq[u], e) - ref);
+      sum = sum * __expf(m - ref) + part;
+      m = mb;
+    };
+    v4i keep[NB ? NB : 1][U];
+    const v4i zero = {0, 0, 0, 0};
+    for (uint32_t i0 = 0; i0 < held; i0 += U) {
+      v4i q[U], mq[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) { mq[u] = zero; fetch(i0 + u, q[u], mq[u]); }
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+        if (i0 + u < NL) kept[(i0 + u) * kThreads] = q[u];
+      take(i0, held, q, mq);
+    }
+    v4i none[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) none[u] = zero;
+#pragma unroll
+    for (uint32_t c = 0; c < NB; ++c)
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) fetch(held + c * U + u, keep[c][u], none[u]);
+#pragma unroll
+    for (uint32_t c = 0; c < NB; ++c) take(held + c * U, T, keep[c], none);
+    const float M_ = wg.max(m);
+    const float inv = 1.0f / wg.sum(sum * __expf(m - M_));
+    auto put = [&](uint32_t i, const v4i& q, const v4i& mq) {
+      const uint32_t vec = tid + kThreads * i;
+      v4i oq;
+#pragma unroll
+      for (int e = 0; e < (int)V; ++e) {
+        float x = E::get(q, e);
+        if (MASK) x = alpha * x + E::get(mq, e);
+        E::put(oq, e, __expf(x - M_) * inv);
+      }
+      row_store<POL, DT, RAGGED>(ro, x0 + cut.begin(vec) * E::ES, oq, i < T && vec < vpr, cut.first(vec));
+    };
+#pragma unroll
+    for (uint32_t c = 0; c < NB; ++c)
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) put(held + c * U + u, keep[c][u], zero);
+    for (uint32_t i = 0; i < NL && i < held; ++i) put(i, kept[i * kThreads], zero);
+    for (uint32_t i0 = NL; i0 < held; i0 += U) {
+      v4i q[U], mq[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) { mq[u] = zero; fetch(i0 + u, q[u], mq[u]); }
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+        if (i0 + u < held) put(i0 + u, q[u], mq[u]);
+    }
+  }
+  __syncthreads();                                     // the LDS belongs to the next chunk after this
 }
 
-template <int POL, int ROP, int DT>
-PATHFN void rowop_wg_dt(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v) {
-  const Record* r = lds_arg(r_v);
-  float* s_red = lds_arg(s_v);
-  const uint32_t begin = uni(begin_v), end = uni(end_v);
-  const uint32_t vpr = uni(r->red_n) / Elem<DT>::V;
-  if (ROP == GPUOS_IMPL_LAYERNORM_LAST && DT != GPUOS_F32 && uni(r->dtype[1]) == GPUOS_F32) {
-    constexpr bool P = ROP == GPUOS_IMPL_LAYERNORM_LAST && DT != GPUOS_F32;
-    if (vpr <= 512u) rowop_wg<POL, ROP, DT, 2, P>(r, begin, end, s_red);
-    else if (vpr <= 1024u) rowop_wg<POL, ROP, DT, 4, P>(r, begin, end, s_red);
-    else rowop_wg<POL, ROP, DT, 0, P>(r, begin, end, s_red);
-    return;
+// Layer norm rows too long for the workgroup's registers: three passes of vector loads over the row.
+template <int POL, int DT, bool P32, bool RAGGED>
+DEV void layernorm_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v) {
+  using E = Elem<DT>;
+  using M = Mem<POL>;
+  constexpr uint32_t V = E::V;
+  const uint32_t n = uni(r->red_n);
+  const RowCut<V, RAGGED> cut(n);
+  const uint32_t vpr = cut.vpr, tid = threadIdx.x;
+  const float alpha = r->alpha;
+  const uint32_t chunk_bytes = (row_end - row_begin) * n * E::ES;
+  const uint64_t chunk_off = (uint64_t)row_begin * n * E::ES;
+  const rsrc_t rx = make_rsrc(uni_ptr(r->ptr[0]) + chunk_off, chunk_bytes);
+  const rsrc_t ro = make_rsrc(uni_ptr(r->ptr[3]) + chunk_off, chunk_bytes);
+  const rsrc_t rg = make_rsrc(uni_ptr(r->ptr[1]), n * (P32 ? 4u : (uint32_t)E::ES)), rb = make_rsrc(uni_ptr(r->ptr[2]), n * (P32 ? 4u : (uint32_t)E::ES));
+  WgReduce wg = {s_v, 0};
+  for (uint32_t row = row_begin; row < row_end; ++row) {
+    const uint32_t x0 = (row - row_begin) * n * E::ES;
+    float sum = 0.0f;
+    for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
+      const v4i q = M::ld16(rx, x0 + cut.begin(vec) * E::ES);
+#pragma unroll
+      for (int e = 0; e < (int)V; ++e) sum += !RAGGED || e >= cut.first(vec) ? E::get(q, e) : 0.0f;
+    }
+    const float mean = wg.sum(sum) / (float)n;
+    float ss = 0.0f;
+    for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
+      const v4i q = M::ld16(rx, x0 + cut.begin(vec) * E::ES);
+#pragma unroll
+      for (int e = 0; e < (int)V; ++e) { const float d = E::get(q, e) - mean; ss += !RAGGED || e >= cut.first(vec) ? d * d : 0.0f; }
+    }
+    const float rstd = 1.0f / __builtin_sqrtf(wg.sum(ss) / (float)n + alpha);
+    for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
+      const v4i q = M::ld16(rx, x0 + cut.begin(vec) * E::ES);
+      RowParam<POL, DT, P32> g, b;
+      g.load(rg, cut.begin(vec));
+      b.load(rb, cut.begin(vec));
+      v4i oq;
+#pragma unroll
+      for (int e = 0; e < (int)V; ++e) E::put(oq, e, (E::get(q, e) - mean) * rstd * g.get(e) + b.get(e));
+      row_store<POL, DT, RAGGED>(ro, x0 + cut.begin(vec) * E::ES, oq, true, cut.first(vec));
+    }
   }
-  if (vpr <= 512u) rowop_wg<POL, ROP, DT, 2>(r, begin, end, s_red);
-  else if (vpr <= 1024u) rowop_wg<POL, ROP, DT, 4>(r, begin, end, s_red);
-  else rowop_wg<POL, ROP, DT, 0>(r, begin, end, s_red);
+  __syncthreads();                                     // the LDS slots belong to the next chunk after this
 }
 
+// The executors of PATH_ROW_FUSED.  Aligned rows of up to 1,024 vectors have one per dtype, called from
+// the worker loop; ragged and longer rows are reached through rowop_other, one call site for all of
+// them.  (Every call site in the worker loop costs every unit: the loop's scalars are put out of the
+// call's way round each, and with forty sites more the compiler kept those in a register that it
+// stored to scratch memory and fetched from there at every decision, 1.5 us a unit.)
+template <int POL, int ROP, int DT, bool P32, bool RAGGED>
+DEV void rowop_short(const Record* r, uint32_t begin, uint32_t end, float* s) {      // <= 256 vectors
+  const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
+  if (vpr <= 64u) rowop_fused<POL, ROP, DT, 1, 4, P32, RAGGED>(r, begin, end, s);
+  else if (vpr <= 128u) rowop_fused<POL, ROP, DT, 2, 2, P32, RAGGED>(r, begin, end, s);
+  else rowop_fused<POL, ROP, DT, 4, 1, P32, RAGGED>(r, begin, end, s);
+}
+template <int POL, int ROP, int DT, bool P32, bool RAGGED>
+DEV void rowop_mid(const Record* r, uint32_t begin, uint32_t end, float* s) {        // <= 1,024 vectors
+  const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
+  if (vpr <= 512u) rowop_wg<POL, ROP, DT, 2, P32, RAGGED>(r, begin, end, s);
+  else rowop_wg<POL, ROP, DT, 4, P32, RAGGED>(r, begin, end, s);
+}
+template <int POL, int ROP, int DT, bool P32, bool RAGGED>
+DEV void rowop_long(const Record* r, uint32_t begin, uint32_t end, float* s) {
+  const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
+  constexpr bool MASK = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST;       // (twice the registers per vector)
+  if constexpr (!MASK || DT == GPUOS_F32) {
+    if (vpr <= 2048u) return rowop_wg<POL, ROP, DT, 8, P32, RAGGED>(r, begin, end, s);
+  }
+  if constexpr (!MASK && DT == GPUOS_F32) {
+    if (vpr <= 4096u) return rowop_wg<POL, ROP, DT, 16, P32, RAGGED>(r, begin, end, s);
+  }
+  if constexpr (RowOp<ROP>::SOFTMAX) softmax_long<POL, ROP, DT, RAGGED>(r, begin, end, s);
+  else layernorm_long<POL, DT, P32, RAGGED>(r, begin, end, s);
+}
+enum { kRowShort, kRowMid, kRowLong };
+template <int POL, int ROP, int DT, int LEN, bool RAGGED>
+PATHFN void rowop_dt(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v) {
+  const Record* r = lds_arg(r_v);
+  float* s = lds_arg(s_v);
+  const uint32_t begin = uni(begin_v), end = uni(end_v);
+  constexpr bool LN16 = ROP == GPUOS_IMPL_LAYERNORM_LAST && DT != GPUOS_F32;
+  if (LN16 && uni(r->dtype[1]) == GPUOS_F32) {                       // fp32 gamma / beta under 16-bit x
+    if constexpr (LEN == kRowShort) rowop_short<POL, ROP, DT, LN16, RAGGED>(r, begin, end, s);
+    else if constexpr (LEN == kRowMid) rowop_mid<POL, ROP, DT, LN16, RAGGED>(r, begin, end, s);
+    else rowop_long<POL, ROP, DT, LN16, RAGGED>(r, begin, end, s);
+    return;
+  }
+  if constexpr (LEN == kRowShort) rowop_short<POL, ROP, DT, false, RAGGED>(r, begin, end, s);
+  else if constexpr (LEN == kRowMid) rowop_mid<POL, ROP, DT, false, RAGGED>(r, begin, end, s);
+  else rowop_long<POL, ROP, DT, false, RAGGED>(r, begin, end, s);
+}
+template <int POL, int ROP, int DT>
+DEV void rowop_other_dt(const Record* r, uint32_t begin, uint32_t end, float* s) {
+  const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
+  if (uni(r->rflags) & RF_VEC) rowop_dt<POL, ROP, DT, kRowLong, false>(r, begin, end, s);
+  else if (vpr <= 256u) rowop_dt<POL, ROP, DT, kRowShort, true>(r, begin, end, s);
+  else if (vpr <= 1024u) rowop_dt<POL, ROP, DT, kRowMid, true>(r, begin, end, s);
+  else rowop_dt<POL, ROP, DT, kRowLong, true>(r, begin, end, s);
+}
+template <int POL, int ROP>
+DEV void rowop_other_op(const Record* r, uint32_t begin, uint32_t end, float* s) {
+  const uint32_t dt = uni(r->dtype[3]);
+  if (dt == GPUOS_F32) rowop_other_dt<POL, ROP, GPUOS_F32>(r, begin, end, s);
+  else if (dt == GPUOS_F16) rowop_other_dt<POL, ROP, GPUOS_F16>(r, begin, end, s);
+  else rowop_other_dt<POL, ROP, GPUOS_BF16>(r, begin, end, s);
+}
+template <int POL>
+PATHFN void rowop_other(const Record* r_v, uint32_t impl_v, uint32_t begin_v, uint32_t end_v, float* s_v) {
+  const Record* r = lds_arg(r_v);
+  float* s = lds_arg(s_v);
+  const uint32_t impl = uni(impl_v), begin = uni(begin_v), end = uni(end_v);
+  if (impl == GPUOS_IMPL_SOFTMAX_LAST) rowop_other_op<POL, GPUOS_IMPL_SOFTMAX_LAST>(r, begin, end, s);
+  else if (impl == GPUOS_IMPL_MASKED_SOFTMAX_LAST) rowop_other_op<POL, GPUOS_IMPL_MASKED_SOFTMAX_LAST>(r, begin, end, s);
+  else rowop_other_op<POL, GPUOS_IMPL_LAYERNORM_LAST>(r, begin, end, s);
+}
+
+// PATH_ROW_FUSED rows that rowop_other takes
+DEV bool rowop_is_other(const Record* r) {
+  return uni(r->path) == PATH_ROW_FUSED && ((uni(r->rflags) & RF_VEC) == 0 || uni(r->red_n) > (uni(r->dtype[3]) == GPUOS_F32 ? 4096u : 8192u));
+}
 template <int POL, int ROP>
 DEV void run_rowop(const Record* r, uint32_t chunk, float* s_red) {
   const uint32_t per = uni(r->chunk), rows = uni(r->numel);
@@ -2078,13 +2315,13 @@ DEV void run_rowop(const Record* r, uint32_t chunk, float* s_red) {
     const uint32_t dt = uni(r->dtype[3]);
     const bool wide = uni(r->red_n) * (dt == GPUOS_F32 ? 4u : 2u) > 256u * 16u;     // more than 256 vectors per row
     if (!wide) {
-      if (dt == GPUOS_F32) rowop_fused_dt<POL, ROP, GPUOS_F32>(r, begin, end);
-      else if (dt == GPUOS_F16) rowop_fused_dt<POL, ROP, GPUOS_F16>(r, begin, end);
-      else rowop_fused_dt<POL, ROP, GPUOS_BF16>(r, begin, end);
+      if (dt == GPUOS_F32) rowop_dt<POL, ROP, GPUOS_F32, kRowShort, false>(r, begin, end, s_red);
+      else if (dt == GPUOS_F16) rowop_dt<POL, ROP, GPUOS_F16, kRowShort, false>(r, begin, end, s_red);
+      else rowop_dt<POL, ROP, GPUOS_BF16, kRowShort, false>(r, begin, end, s_red);
     } else {
-      if (dt == GPUOS_F32) rowop_wg_dt<POL, ROP, GPUOS_F32>(r, begin, end, s_red);
-      else if (dt == GPUOS_F16) rowop_wg_dt<POL, ROP, GPUOS_F16>(r, begin, end, s_red);
-      else rowop_wg_dt<POL, ROP, GPUOS_BF16>(r, begin, end, s_red);
+      if (dt == GPUOS_F32) rowop_dt<POL, ROP, GPUOS_F32, kRowMid, false>(r, begin, end, s_red);
+      else if (dt == GPUOS_F16) rowop_dt<POL, ROP, GPUOS_F16, kRowMid, false>(r, begin, end, s_red);
+      else rowop_dt<POL, ROP, GPUOS_BF16, kRowMid, false>(r, begin, end, s_red);
     }
   } else {
     rowop_generic<POL, ROP>(r, begin, end);
@@ -2096,18 +2333,6 @@ DEV void run_rowop(const Record* r, uint32_t chunk, float* s_red) {
 // paper's function-pointer table call, Section 4.1; here a switch over
 // precompiled implementations selected by the table entry).
 // ---------------------------------------------------------------------------
-// Which executor takes a task is decided by halving: pick<LO, HI> calls F::run<K> for the K in [LO, HI)
-// that equals k.  (The compiler turns a many-way branch into a chain that is walked case by case, with
-// a flag to carry per case; a two-way choice whose sides meet again is left alone.)
-template <int LO, int HI, class F, class... A> DEV void pick(uint32_t k, A... a) {
-  if constexpr (HI - LO == 1) F::template run<LO>(a...);
-  else {
-    constexpr int MID = (LO + HI) / 2;
-    if (k < (uint32_t)MID) pick<LO, MID, F>(k, a...);
-    else pick<MID, HI, F>(k, a...);
-  }
-}
-
 // The executors of PATH_ROWS: by arity without (groups of three: fp32, fp16, bf16) and with per-row
 // scalars, the operators of many instructions, casts, I32.
 enum : uint32_t { kClsUnary = 0, kClsBinary = 1, kClsTernary = 2, kClsErf = 3, kClsTanh = 4, kClsNone = 15 };
@@ -2258,6 +2483,11 @@ DEV int32_t exec_chunk(const Record* r, uint32_t impl, uint32_t chunk, float* s_
   if (uni(r->path) == PATH_NOP) return impl == GPUOS_IMPL_FAIL ? GPUOS_E_BADOP : GPUOS_OK;
   if (impl >= GPUOS_IMPL_PROGRAM_BASE) return exec_program<POL>(r, impl, chunk, s_red, progs);
   // (beside the switch, not a case in every implementation's paths: see ByArity)
+  if (impl >= GPUOS_IMPL_SOFTMAX_LAST && impl <= GPUOS_IMPL_LAYERNORM_LAST && rowop_is_other(r)) {
+    const uint32_t per = uni(r->chunk), rows = uni(r->numel), begin = chunk * per;
+    rowop_other<POL>(r, impl, begin, (rows - begin < per) ? rows : begin + per, s_red);
+    return GPUOS_OK;
+  }
   const uint32_t k = uni(r->path) == PATH_ROWS ? rows_variant(r, impl) : (uint32_t)kRowsCount;
   if (k < (uint32_t)kRowsCount) {
     const uint32_t per = uni(r->chunk), numel = uni(r->numel), begin = chunk * per;

@@ -214,7 +214,7 @@ inline bool aligned16(uint64_t p) { return (p & 15u) == 0; }
 
 // Validate `t` for implementation `impl` and pack it.  Nothing is written to
 // *r unless the result is GPUOS_OK.
-int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elems = kChunkElems, int program_arity = 0) {
+int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elems = kChunkElems, int program_arity = 0, bool rows_path = true) {
   Record rec;
   std::memset(&rec, 0, sizeof(rec));
   rec.op_id = t.op_id;
@@ -301,9 +301,10 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     rec.red_n = (uint32_t)n;
     rec.numel = (uint32_t)rows;
     rec.path = PATH_ROW_GENERIC;
-    // vector path (rows in registers up to 1024 vectors, streamed beyond): one dtype, unit stride
-    // along the row, whole aligned vectors; x and the output contiguous; further inputs contiguous [period, n]
-    // blocks that repeat every `period` rows (period = rows: same layout as x; 1: a row vector)
+    // vector path (rows in registers up to 16,384 elements, streamed beyond): one dtype, unit stride
+    // along the row, rows that hold a vector; x and the output contiguous; further inputs contiguous [period, n]
+    // blocks that repeat every `period` rows (period = rows: same layout as x; 1: a row vector).
+    // RF_VEC: the rows of every operand are whole aligned vectors (else the ragged executors).
     const uint32_t es = dtype_size(ops[ar].dtype);
     const uint32_t V = 16u / es;
     auto dense_rows = [&](const Operand& o, int from) {      // dims from..nd-1 laid out as [.., n] contiguous
@@ -317,8 +318,9 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     // one dtype for every tensor; layer norm also with fp32 gamma and beta under 16-bit x and y
     const bool ln_p32 = impl == GPUOS_IMPL_LAYERNORM_LAST && ops[0].dtype == ops[ar].dtype && ops[0].dtype != GPUOS_F32 &&
                         ops[1].dtype == GPUOS_F32 && ops[2].dtype == GPUOS_F32;
-    bool fast = (same_dt || ln_p32) && n % V == 0 && n * (int64_t)es < kMaxExtent && n * 4 < kMaxExtent;
-    for (int k = 0; k <= ar && fast; ++k) fast = s_last[k] == 1 && aligned16(ops[k].ptr);
+    bool fast = (same_dt || ln_p32) && n >= (int64_t)V && n * (int64_t)es < kMaxExtent && n * 4 < kMaxExtent;
+    bool whole = n % V == 0;
+    for (int k = 0; k <= ar && fast; ++k) { fast = s_last[k] == 1; whole = whole && aligned16(ops[k].ptr); }
     fast = fast && (rows == 1 || (dense_rows(oo[0], 0) && dense_rows(oo[ar], 0)));
     uint32_t period[3] = {0, 0, 0};
     for (int k = 1; k < ar && fast; ++k) {
@@ -338,11 +340,14 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
       fast = rec.okind[1] == K_PERIODIC && period[1] == 1 && rec.okind[2] == K_PERIODIC && period[2] == 1;
     if (fast) {
       rec.path = PATH_ROW_FUSED;
-      rec.rflags |= RF_VEC;
+      if (whole) rec.rflags |= RF_VEC;
       for (int k = 1; k < ar; ++k) rec.stride[k][0] = period[k];
     }
+    // traffic of a row: gamma and beta are fetched once per chunk.  (Counted per row they made the chunks of
+    // an 8,192 x 1,024 bf16 layer norm 16 rows, each fetching as many bytes of parameters as of rows.)
     uint64_t row_bytes = 0;
-    for (int k = 0; k <= ar; ++k) row_bytes += (uint64_t)n * dtype_size(ops[k].dtype);
+    for (int k = 0; k <= ar; ++k)
+      if (k == 0 || k == ar || impl != GPUOS_IMPL_LAYERNORM_LAST) row_bytes += (uint64_t)n * dtype_size(ops[k].dtype);
     uint64_t rpc = (uint64_t)chunk_elems * 12 / row_bytes;
     if (rpc < 1) rpc = 1;
     if (rpc >= 16) rpc = (rpc + 15) / 16 * 16;
@@ -388,7 +393,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     // Rows that are contiguous in every operand, or hold one scalar per row, under up to three outer
     // dims of any strides: 16-byte accesses whatever the row length and alignment are, as long as a
     // row holds a vector.  Operands of one dtype (a COPY may convert), scalars of any. 
-    if ((rec.path == PATH_GENERIC || (rec.path == PATH_CONTIG && !all_aligned)) && nd <= 4 &&
+    if (rows_path && (rec.path == PATH_GENERIC || (rec.path == PATH_CONTIG && !all_aligned)) && nd <= 4 &&
         ops[ar].stride[nd - 1] == 1) {
       bool ok = true;
       int full = -1;                                             // the first operand that is not one scalar per row
@@ -513,6 +518,8 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
         // workgroups, two rounds each at least
         quarter = (((uint64_t)numel + 31) / 32 + 1023) / 1024 * 1024;
         half = 2048;
+        // (rounds in a row are latencies in a row: a large task's chunks of 16 rounds took 50 us under load)
+        if (numel > (1 << 20) && base_per > 8192) base_per = 8192;
       }
       if (quarter < half) quarter = half;
       per = quarter < base_per ? quarter : base_per;
@@ -1914,6 +1921,14 @@ int gpuos_task_plan(const gpuos_task* t, uint32_t impl, uint32_t out[4]) {
   const int rc = pack_task(*t, impl, &r);
   if (rc != GPUOS_OK) return rc;
   out[0] = r.path; out[1] = r.nchunks; out[2] = r.chunk; out[3] = r.ndim;
+  // the layout class is what is reported; PATH_ROWS is an executor for part of several, and ragged rows
+  // have one of their own among the fused row operations
+  if (r.path == PATH_ROW_FUSED && !(r.rflags & RF_VEC)) out[0] = PATH_ROW_GENERIC;
+  if (r.path == PATH_ROWS) {
+    Record c;
+    (void)pack_task(*t, impl, &c, kChunkElems, 0, false);
+    out[0] = c.path; out[3] = c.ndim;
+  }
   return GPUOS_OK;
 }
 

@@ -71,3 +71,40 @@ def rows_edges(code):
                     b.add("COPY", out(c), [x])
                     b.add("COPY", b.pool(np.zeros((A, B, R, C), np_dtype(c))), [flat])
     return b.stream("rows_edges_%d" % code)
+
+
+def row_operation_edges(code):
+    """Softmax, masked softmax and layer norm over rows of any length and alignment: a vector and less,
+    a vector and one element, the lengths where a row moves from lane groups to a wavefront, to the
+    workgroup's registers and beyond them, remainders of one and of all but one element; masks
+    repeated every few rows; fp32 parameters under 16-bit rows; NaN, infinities and rows of -inf."""
+    rng = np.random.default_rng(720 + code)
+    b = Builder()
+    V = 4 if code == S.F32 else 8
+    dt = np_dtype(code)
+    for i, (rows, n) in enumerate(((5, V - 1), (3, V), (70, V + 1), (300, 3 * V - 1), (131, 32 * V + 1), (130, 64 * V - 1), (65, 64 * V + 1),
+                                   (19, 128 * V - 3), (17, 128 * V + 1), (9, 256 * V - 1), (9, 256 * V + 1), (5, 512 * V + 3), (3, 1024 * V - 1),
+                                   (3, 1024 * V + 1), (3, 2048 * V - 1), (2, 2048 * V + 1), (3, 4096 * V + V + 1), (2, 5632 * V + 1), (2, 65535), (2, 65536))):
+        lead = (0, 1, V - 1)[i % 3]
+        x = b.pool(values(rng, rows * n + lead, code, 3.0))[lead:].reshape(rows, n)
+
+        def out():
+            return b.pool(np.zeros(rows * n + 1, dt))[i % 2:][:rows * n].reshape(rows, n)
+        b.add("SOFTMAX_LAST", out(), [x])
+        mrow = b.pool(values(rng, n, code))
+        b.add("MASKED_SOFTMAX_LAST", out(), [x, np.broadcast_to(mrow, (rows, n))], alpha=0.3)
+        if rows % 5 == 0:                                    # a mask of `per` rows, repeated
+            per = rows // 5
+            m = b.pool(values(rng, per * n + 1, code))[1:].reshape(per, n)
+            o = out().reshape(5, per, n)
+            b.add("MASKED_SOFTMAX_LAST", o, [x.reshape(5, per, n), np.broadcast_to(m, (5, per, n))], alpha=0.5)
+        for pcode in ((code,) if code == S.F32 else (code, S.F32)):
+            g, be = b.pool(to_dtype(1 + 0.2 * rng.standard_normal(n + 1), pcode))[1:], b.pool(values(rng, n, pcode))
+            b.add("LAYERNORM_LAST", out(), [x, np.broadcast_to(g, (rows, n)), np.broadcast_to(be, (rows, n))], alpha=1e-5)
+        if rows >= 3 and code != S.BF16:
+            y = b.pool(np.ascontiguousarray(x[:3]))
+            y[0, n // 2] = np.nan
+            y[1, :] = -np.inf
+            y[2, ::2] = -np.inf
+            b.add("SOFTMAX_LAST", b.pool(np.zeros((3, n), dt)), [y])
+    return b.stream("row_operation_edges_%d" % code)

@@ -52,3 +52,9 @@ def test_an_operator_swapped_under_tasks_packed_as_rows():
         assert np.all(comps["status"] == 0) and np.all(comps["op_version"] == 2)
         s.table[S.OP[op]] = impl
         compare_with_oracle(s, dp.download())
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_row_operations_at_their_edges(code):
+    stats, _ = _run_and_check(E.row_operation_edges(code))
+    print(stats, flush=True)
