@@ -171,43 +171,42 @@ int check_operand(const gpuos_tensor& t, int ndim, const int64_t* size, bool is_
   return GPUOS_OK;
 }
 
-// Merge adjacent dims that every operand walks as one: outer stride == inner
-// stride * inner size for all operands.  Size-1 dims are dropped first.
-int coalesce(int nd, int64_t* size, Operand* ops, int nops) {
-  int64_t sz[GPUOS_MAX_DIMS];
-  int64_t st[5][GPUOS_MAX_DIMS];
-  int m = 0;
-  for (int d = 0; d < nd; ++d) {
-    if (size[d] == 1) continue;
-    sz[m] = size[d];
-    for (int k = 0; k < nops; ++k) st[k][m] = ops[k].stride[d];
-    ++m;
-  }
-  if (m == 0) {                                   // a single element
-    sz[0] = 1;
-    for (int k = 0; k < nops; ++k) st[k][0] = 1;
-    m = 1;
-  }
-  int w = 0;                                      // index of the dim being grown (outermost so far)
-  for (int d = 1; d < m; ++d) {
-    bool merge = true;
-    for (int k = 0; k < nops; ++k)
-      if (st[k][w] != st[k][d] * sz[d]) { merge = false; break; }
-    if (merge) {
-      sz[w] *= sz[d];
-      for (int k = 0; k < nops; ++k) st[k][w] = st[k][d];
-    } else {
-      ++w;
-      sz[w] = sz[d];
-      for (int k = 0; k < nops; ++k) st[k][w] = st[k][d];
+// Every operand dense in the iteration's order: one run of `numel` elements.  (Most tasks of a stream
+// are; deciding it takes a third of what merging dims does.)
+bool all_dense(int nd, const int64_t* size, const Operand* ops, int nops) {
+  int64_t want = 1;
+  for (int d = nd - 1; d >= 0; --d) {
+    if (size[d] != 1) {
+      for (int k = 0; k < nops; ++k)
+        if (ops[k].stride[d] != want) return false;
+      want *= size[d];
     }
   }
-  m = w + 1;
-  for (int d = 0; d < GPUOS_MAX_DIMS; ++d) {
-    size[d] = d < m ? sz[d] : 1;
-    for (int k = 0; k < nops; ++k) ops[k].stride[d] = d < m ? st[k][d] : 0;
+  return true;
+}
+
+// a / b rounded up, both below 2^32: a 32-bit division (a 64-bit one costs 10 ns, and a task needs several)
+inline uint64_t div_up(uint64_t a, uint64_t b) { return a < (1ull << 31) && b < (1ull << 31) ? ((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b : (a + b - 1) / b; }
+
+// Merge adjacent dims that every operand walks as one: outer stride == inner
+// stride * inner size for all operands.  Size-1 dims are dropped first.  In place:
+// entries from the returned count on are left as they are.
+int coalesce(int nd, int64_t* size, Operand* ops, int nops) {
+  int w = -1;                                     // index of the dim being grown (outermost so far)
+  for (int d = 0; d < nd; ++d) {
+    if (size[d] == 1) continue;
+    bool merge = w >= 0;
+    for (int k = 0; k < nops && merge; ++k) merge = ops[k].stride[w] == ops[k].stride[d] * size[d];
+    if (merge) size[w] *= size[d];
+    else size[++w] = size[d];
+    for (int k = 0; k < nops; ++k) ops[k].stride[w] = ops[k].stride[d];
   }
-  return m;
+  if (w < 0) {                                    // a single element
+    size[0] = 1;
+    for (int k = 0; k < nops; ++k) ops[k].stride[0] = 1;
+    w = 0;
+  }
+  return w + 1;
 }
 
 inline bool aligned16(uint64_t p) { return (p & 15u) == 0; }
@@ -361,7 +360,13 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
 
   if (!red) {
     if (numel == 0) { rec.path = PATH_NOP; rec.nchunks = 1; *r = rec; return GPUOS_OK; }
-    const int nd = coalesce(t.ndim, size, ops, ar + 1);
+    int nd = 1;
+    if (numel > 1 && all_dense(t.ndim, size, ops, ar + 1)) {
+      size[0] = numel;
+      for (int k = 0; k <= ar; ++k) ops[k].stride[0] = 1;
+    } else {
+      nd = coalesce(t.ndim, size, ops, ar + 1);
+    }
     rec.ndim = (uint8_t)nd;
     for (int d = 0; d < nd; ++d) {
       rec.size[d] = (uint32_t)size[d];
@@ -500,7 +505,8 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     // that a chunk of any op moves about the same number of bytes
     uint64_t traffic = dtype_size(ops[ar].dtype);
     for (int k = 0; k < ar; ++k) traffic += dtype_size(ops[k].dtype);
-    uint64_t base_per = ((uint64_t)chunk_elems * 12 / traffic + 1023) / 1024 * 1024;
+    uint64_t base_per = chunk_elems < (1u << 28) ? chunk_elems * 12u / (uint32_t)traffic : (uint64_t)chunk_elems * 12 / traffic;
+    base_per = (base_per + 1023) / 1024 * 1024;
     uint64_t per = ((uint64_t)numel + kMaxChunksPerTask - 1) / kMaxChunksPerTask;
     per = (per + 1023) / 1024 * 1024;
     if (per < base_per) {
@@ -525,18 +531,19 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
       per = quarter < base_per ? quarter : base_per;
     }
     if (rec.path == PATH_ROWS) {                                 // counted in vectors, the partly filled last one of a row included
-      const uint64_t vectors = (uint64_t)numel / (uint64_t)size[nd - 1] * (((uint64_t)size[nd - 1] + rec.vwidth - 1) / rec.vwidth);
+      const uint32_t row = (uint32_t)size[nd - 1];
+      const uint64_t vectors = (uint64_t)((uint32_t)numel / row) * ((row + rec.vwidth - 1u) / rec.vwidth);
       rec.numel = (uint32_t)vectors;
       per /= rec.vwidth;
       const uint64_t min_per = (vectors + kMaxChunksPerTask - 1) / kMaxChunksPerTask;
       if (per < min_per) per = min_per;
       rec.chunk = (uint32_t)per;
-      rec.nchunks = (uint32_t)((vectors + per - 1) / per);
+      rec.nchunks = (uint32_t)div_up(vectors, per);
       *r = rec;
       return GPUOS_OK;
     }
     rec.chunk = (uint32_t)per;
-    rec.nchunks = (uint32_t)(((uint64_t)numel + per - 1) / per);
+    rec.nchunks = (uint32_t)div_up((uint64_t)numel, per);
     *r = rec;
     return GPUOS_OK;
   }
