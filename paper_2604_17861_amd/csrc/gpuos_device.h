@@ -2759,7 +2759,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
         for (int k = 0; k < 3; ++k) {
           const uint32_t back = r->dep[k];
           if (back != 0 && back <= ticket) {
-            need[k] = ticket - back + 1;
+            need[k] = done_target(ticket - back, a.cap_shift);
             done_word[k] = &a.st[(ticket - back) & a.cap_mask].done_seq;
           }
         }
@@ -2932,11 +2932,11 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
     // ---- complete ----
     if (tid == 0) {
       const uint32_t nchunks = r->nchunks;
+      const uint64_t target = done_target(r->ticket, a.cap_shift);
       bool last = true;
       if (nchunks > 1) {
-        const uint32_t prev = __hip_atomic_fetch_add(&a.st[slot].chunks_done, 1u, __ATOMIC_RELAXED, SC_AGENT);
-        last = (prev + 1 == nchunks);
-        if (last) __hip_atomic_store(&a.st[slot].chunks_done, 0u, __ATOMIC_RELAXED, SC_SYSTEM);
+        const uint64_t share = chunk + 1 == nchunks ? kDoneTask - (nchunks - 1) : 1ull;
+        last = __hip_atomic_fetch_add(&a.st[slot].done_seq, share, __ATOMIC_RELAXED, SC_AGENT) + share == target;
       }
       if (last) {
         const uint64_t ticket = r->ticket;
@@ -2960,7 +2960,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
           __hip_atomic_store(&tr->ticket, ticket, __ATOMIC_RELAXED, SC_SYSTEM);
           drain_stores();
         }
-        __hip_atomic_store(&a.st[slot].done_seq, ticket + 1, __ATOMIC_RELAXED, SC_SYSTEM);
+        if (nchunks <= 1) __hip_atomic_store(&a.st[slot].done_seq, target, __ATOMIC_RELAXED, SC_SYSTEM);
         __hip_atomic_store(&a.hcomp[slot], pack_completion(ticket, status, r->version), __ATOMIC_RELAXED, SC_SYSTEM);
         __hip_atomic_fetch_add(&a.d->done_count, 1ull, __ATOMIC_RELAXED, SC_AGENT);
       }

@@ -166,10 +166,18 @@ enum StatIndex {
   ST_WORK_TICKS_COMPLETE, ST_WORK_TICKS_TOTAL, ST_DISP_DEFERRED
 };
 
+// A task's done word counts its chunks for the task's own completion and for those that wait for it at
+// once: every chunk adds its share of kDoneTask (1, and the last-numbered chunk the rest), so the
+// word reaches done_target(ticket) with the add of whichever chunk finishes last.  That add tells its
+// workgroup that it was the last, and a task that polls the word sees it the moment it lands.  (With a
+// counter beside the word the last finisher had to hear back from the counter before it could write the
+// word, one more trip to memory between a task and the next.)
+constexpr uint64_t kDoneTask = 1ull << 20;               // more than a task has chunks
+GPUOS_HD inline uint64_t done_target(uint64_t ticket, uint32_t cap_shift) { return ((ticket >> cap_shift) + 1) * kDoneTask; }
+
 struct SlotState {                   // device memory, one per ring slot
-  uint64_t done_seq;                 // ticket+1 of the last task completed in this slot
-  uint32_t chunks_done;
-  uint32_t pad;
+  uint64_t done_seq;                 // grows by kDoneTask per task that completes in this slot, a chunk at a time (done_target)
+  uint64_t pad;
   uint64_t t_first;                  // tracing: device clock when chunk 0 of the current task was claimed
 };
 

@@ -138,7 +138,7 @@ DEV bool deps_complete(const WorkerArgs& a, uint64_t ticket, const uint16_t* dep
   for (int k = 0; k < 3; ++k) {
     const uint32_t back = dep[k];
     if (back != 0 && back <= ticket) {
-      const uint64_t want = ticket - back + 1;
+      const uint64_t want = done_target(ticket - back, a.cap_shift);
       ok = ok && __hip_atomic_load(&a.st[(ticket - back) & a.cap_mask].done_seq, __ATOMIC_RELAXED, SC_SYSTEM) >= want;
     }
   }
