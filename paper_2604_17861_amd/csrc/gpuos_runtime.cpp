@@ -342,12 +342,19 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
       if (whole) rec.rflags |= RF_VEC;
       for (int k = 1; k < ar; ++k) rec.stride[k][0] = period[k];
     }
-    // traffic of a row: gamma and beta are fetched once per chunk.  (Counted per row they made the chunks of
-    // an 8,192 x 1,024 bf16 layer norm 16 rows, each fetching as many bytes of parameters as of rows.)
     uint64_t row_bytes = 0;
-    for (int k = 0; k <= ar; ++k)
-      if (k == 0 || k == ar || impl != GPUOS_IMPL_LAYERNORM_LAST) row_bytes += (uint64_t)n * dtype_size(ops[k].dtype);
+    for (int k = 0; k <= ar; ++k) row_bytes += (uint64_t)n * dtype_size(ops[k].dtype);
     uint64_t rpc = (uint64_t)chunk_elems * 12 / row_bytes;
+    if (impl == GPUOS_IMPL_LAYERNORM_LAST) {
+      // Gamma and beta are fetched once per chunk and are no traffic of a row: counted as such they made the
+      // chunks of an 8,192 x 1,024 bf16 layer norm 16 rows, each fetching as many bytes of
+      // parameters as of rows (68 us for four of them, 46 with 48 rows).  But a task that has not
+      // rows for 192 such chunks keeps the smaller ones: 2M elements in 86 chunks took 30-43 us
+      // where 171 chunks took 21-27.
+      const uint64_t most = (uint64_t)chunk_elems * 12 / ((uint64_t)n * 2 * dtype_size(ops[0].dtype)), spread = (uint64_t)rows / 192;
+      if (rpc < spread) rpc = spread;
+      if (rpc > most) rpc = most;
+    }
     if (rpc < 1) rpc = 1;
     if (rpc >= 16) rpc = (rpc + 15) / 16 * 16;
     const uint64_t min_rpc = ((uint64_t)rows + kMaxChunksPerTask - 1) / kMaxChunksPerTask;
