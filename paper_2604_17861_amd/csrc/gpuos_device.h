@@ -1809,8 +1809,8 @@ template <int POL, int DT, bool RAGGED> DEV void row_store(rsrc_t ro, uint32_t o
 }
 
 // Bound by memory for fp32, by memory and conversions together for 16-bit rows.  A pass (UP rows per lane
-// group) is a chain load -> reduce -> reduce -> store; layer norm, whose chunks are several passes,
-// requests the next pass before it computes this one.  (Softmax rows are not: the registers for it
+// group) is a chain load -> reduce -> reduce -> store; layer norm over 16-bit rows, whose chunks are
+// several passes, requests the next pass before it computes this one.  (Softmax rows are not: the registers for it
 // make the function save its caller's, a memory round trip per chunk.)
 template <int POL, int ROP, int DT, int KW, int UP, bool P32, bool RAGGED>
 DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v) {
@@ -1873,15 +1873,27 @@ DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, floa
     }
   };
   uint32_t base = row_begin + wave * rpw * UP;
-  constexpr bool AHEAD = !RO::SOFTMAX;
+  constexpr bool AHEAD = !RO::SOFTMAX && DT != GPUOS_F32;
   Pass cur, nxt;
   if (AHEAD) load(cur, base);
   // layer norm: gamma and beta lie in LDS, vector by vector (each wavefront loading its own to registers
   // fetched them four times a chunk, as many bytes as the chunk's rows, and left none for the next pass)
   v4i* const params = (v4i*)s_v;                       // [2][vpr][PQ]
+  // Not for fp32 rows, which are short of neither registers nor arithmetic: there the staging, its
+  // barrier and the registers of the next pass cost 3 us of 22 on 2M elements.
   constexpr uint32_t PQ = P32 ? 2 : 1;
+  constexpr int KP = AHEAD || RO::SOFTMAX ? 1 : KW;
+  RowParam<POL, DT, P32> gk[KP], bk[KP];
+  if (!RO::SOFTMAX && !AHEAD) {
+#pragma unroll
+    for (int k = 0; k < KP; ++k) {
+      const uint32_t col = j + 64u * k < vpr ? cut.begin(j + 64u * k) : 0u;
+      gk[k].load(rs[0], col);
+      bk[k].load(rs[1], col);
+    }
+  }
   static_assert(2 * 256 * 2 * 4 <= kScratchFloats, "two rows of 256 vectors of fp32 parameters under 16-bit elements");
-  if (!RO::SOFTMAX) {
+  if (AHEAD) {
     for (uint32_t vec = threadIdx.x; vec < vpr; vec += kThreads) {
       RowParam<POL, DT, P32> g, b;
       g.load(rs[0], cut.begin(vec));
@@ -1945,9 +1957,14 @@ DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, floa
         for (int k = 0; k < KW; ++k) {
           v4i oq;
           RowParam<POL, DT, P32> g, b;
-          const uint32_t vec = j + 64u * k < vpr ? j + 64u * k : 0u;
+          if (AHEAD) {
+            const uint32_t vec = j + 64u * k < vpr ? j + 64u * k : 0u;
 #pragma unroll
-          for (uint32_t i = 0; i < PQ; ++i) { g.q[i] = params[vec * PQ + i]; b.q[i] = params[(vpr + vec) * PQ + i]; }
+            for (uint32_t i = 0; i < PQ; ++i) { g.q[i] = params[vec * PQ + i]; b.q[i] = params[(vpr + vec) * PQ + i]; }
+          } else {
+            g = gk[k < KP ? k : 0];
+            b = bk[k < KP ? k : 0];
+          }
 #pragma unroll
           for (int e = 0; e < (int)V; ++e) E::put(oq, e, t[k][e] * rstd * g.get(e) + b.get(e));
           row_store<POL, DT, RAGGED>(ro, lr * n * E::ES + at[k], oq, act[k], first[k]);
@@ -1956,7 +1973,7 @@ DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, floa
     }
     if (AHEAD) cur = nxt;
   }
-  if (!RO::SOFTMAX) __syncthreads();                   // the LDS belongs to the next chunk after this
+  if (AHEAD) __syncthreads();                          // the LDS belongs to the next chunk after this
 }
 
 template <int POL, int ROP>
