@@ -211,6 +211,14 @@ int coalesce(int nd, int64_t* size, Operand* ops, int nops) {
 
 inline bool aligned16(uint64_t p) { return (p & 15u) == 0; }
 
+// A packed record leaves pack_task through here.  A work unit has ten bits for its chunk: one past them
+// would run a low chunk again and never complete the task, so it is refused, whatever rule made it.
+inline int packed(const Record& rec, Record* r) {
+  if (rec.nchunks > kMaxChunksPerTask) return GPUOS_E_INVAL;
+  *r = rec;
+  return GPUOS_OK;
+}
+
 // Validate `t` for implementation `impl` and pack it.  Nothing is written to
 // *r unless the result is GPUOS_OK.
 int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elems = kChunkElems, int program_arity = 0, bool rows_path = true) {
@@ -225,8 +233,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   if (impl == GPUOS_IMPL_FAIL) {                   // executes nothing; one unit reports it
     rec.path = PATH_NOP;
     rec.nchunks = 1;
-    *r = rec;
-    return GPUOS_OK;
+    return packed(rec, r);
   }
   // an operator program: elementwise, float-only, the arity it was defined with
   const int ar = impl >= GPUOS_IMPL_PROGRAM_BASE ? (program_arity > 0 ? program_arity : -1) : impl_arity(impl);
@@ -274,7 +281,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
 
   if (impl_is_rowop(impl)) {
     // ---- fused row operation: rows of the last dim, every operand has the full rank ----
-    if (numel == 0) { rec.path = PATH_NOP; rec.nchunks = 1; *r = rec; return GPUOS_OK; }
+    if (numel == 0) { rec.path = PATH_NOP; rec.nchunks = 1; return packed(rec, r); }
     const int64_t n = size[t.ndim - 1];
     const int64_t rows = numel / n;
     int64_t osz[GPUOS_MAX_DIMS];
@@ -361,12 +368,11 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     if (rpc < min_rpc) rpc = min_rpc;
     rec.chunk = (uint32_t)rpc;
     rec.nchunks = (uint32_t)(((uint64_t)rows + rpc - 1) / rpc);
-    *r = rec;
-    return GPUOS_OK;
+    return packed(rec, r);
   }
 
   if (!red) {
-    if (numel == 0) { rec.path = PATH_NOP; rec.nchunks = 1; *r = rec; return GPUOS_OK; }
+    if (numel == 0) { rec.path = PATH_NOP; rec.nchunks = 1; return packed(rec, r); }
     int nd = 1;
     if (numel > 1 && all_dense(t.ndim, size, ops, ar + 1)) {
       size[0] = numel;
@@ -481,8 +487,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
         rec.numel = (uint32_t)tiles;
         rec.chunk = (uint32_t)per_t;
         rec.nchunks = (uint32_t)((tiles + per_t - 1) / per_t);
-        *r = rec;
-        return GPUOS_OK;
+        return packed(rec, r);
       }
     }
     // Contiguous output of at most three merged dims whose inputs are strided, broadcast or of another
@@ -514,8 +519,8 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     for (int k = 0; k < ar; ++k) traffic += dtype_size(ops[k].dtype);
     uint64_t base_per = chunk_elems < (1u << 28) ? chunk_elems * 12u / (uint32_t)traffic : (uint64_t)chunk_elems * 12 / traffic;
     base_per = (base_per + 1023) / 1024 * 1024;
-    uint64_t per = ((uint64_t)numel + kMaxChunksPerTask - 1) / kMaxChunksPerTask;
-    per = (per + 1023) / 1024 * 1024;
+    const uint64_t least = (((uint64_t)numel + kMaxChunksPerTask - 1) / kMaxChunksPerTask + 1023) / 1024 * 1024;
+    uint64_t per = least;
     if (per < base_per) {
       // A task of at most four regular chunks is cut into (up to) four chunks of at least half the
       // regular size.  One workgroup streams a chunk at 50-60 GB/s, so a task of 8K-32K elements that
@@ -536,6 +541,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
       }
       if (quarter < half) quarter = half;
       per = quarter < base_per ? quarter : base_per;
+      if (per < least) per = least;                                // (the gather path's own base_per may be below it)
     }
     if (rec.path == PATH_ROWS) {                                 // counted in vectors, the partly filled last one of a row included
       const uint32_t row = (uint32_t)size[nd - 1];
@@ -546,13 +552,11 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
       if (per < min_per) per = min_per;
       rec.chunk = (uint32_t)per;
       rec.nchunks = (uint32_t)div_up(vectors, per);
-      *r = rec;
-      return GPUOS_OK;
+      return packed(rec, r);
     }
     rec.chunk = (uint32_t)per;
     rec.nchunks = (uint32_t)div_up((uint64_t)numel, per);
-    *r = rec;
-    return GPUOS_OK;
+    return packed(rec, r);
   }
 
   // ---- reduction over the last dim ----
@@ -560,7 +564,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   int64_t rows = 1;
   for (int d = 0; d + 1 < t.ndim; ++d) rows *= size[d];
   if (n == 0 && rows != 0) return GPUOS_E_INVAL;    // empty reduced dim: no defined result
-  if (rows == 0 || n == 0) { rec.path = PATH_NOP; rec.nchunks = 1; *r = rec; return GPUOS_OK; }
+  if (rows == 0 || n == 0) { rec.path = PATH_NOP; rec.nchunks = 1; return packed(rec, r); }
   const int64_t s_last = n > 1 ? ops[0].stride[t.ndim - 1] : 1;
   int64_t osz[GPUOS_MAX_DIMS];
   Operand oo[2] = {ops[0], ops[1]};
@@ -596,8 +600,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   if (rpc < min_rpc) rpc = min_rpc;
   rec.chunk = (uint32_t)rpc;
   rec.nchunks = (uint32_t)(((uint64_t)rows + rpc - 1) / rpc);
-  *r = rec;
-  return GPUOS_OK;
+  return packed(rec, r);
 }
 
 struct OpInfo {

@@ -108,3 +108,19 @@ def row_operation_edges(code):
             y[2, ::2] = -np.inf
             b.add("SOFTMAX_LAST", b.pool(np.zeros((3, n), dt)), [y])
     return b.stream("row_operation_edges_%d" % code)
+
+
+def large_gathers():
+    """Gathered tasks of more elements than 1,024 of the gather path's regular chunks hold: a product
+    with every other column of a matrix, and a stride-2 slice of 16-bit elements.  (A chunk never run
+    leaves zeros.  Not in place: the comparison takes its inputs from what the GPU left.)"""
+    rng = np.random.default_rng(730)
+    b = Builder()
+    R, C = 3000, 3072
+    x = b.pool(rng.standard_normal((R, 2 * C), dtype=np.float32))
+    y = b.pool(rng.standard_normal((R, C), dtype=np.float32))
+    b.add("MUL", b.pool(np.zeros((R, C), np.float32)), [x[:, ::2], y])
+    n = (8 << 20) + 5003
+    h = b.pool(rng.integers(0, 0x7f00, size=2 * n, dtype=np.uint16))
+    b.add("SCALE", b.pool(np.zeros(n, np.uint16)), [h[1::2]], alpha=0.5)
+    return b.stream("large_gathers")

@@ -52,6 +52,14 @@ def test_rows_edges(code):
     assert counted_in_vectors > 0.8 * len(s)
 
 
+def test_large_gathers():
+    s = E.large_gathers()
+    assert not stream_extent_violations(s)
+    for (path, chunks, per, _), size, nd in zip(plans(s), s.tasks["size"], s.tasks["ndim"]):
+        numel = int(np.prod(size[:nd]))
+        assert path == "STAGED" and chunks <= 1024 and (chunks - 1) * per < numel <= chunks * per and per > 8192
+
+
 @pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
 def test_row_operation_edges(code):
     s = E.row_operation_edges(code)
@@ -87,3 +95,45 @@ def test_what_rows_leaves_to_the_other_paths():
         assert path == "GENERIC"
         counts_vectors.append(chunks != -(-numel // per) and chunks == -(-(numel // C * -(-C // 4)) // per))
     assert counts_vectors == [False] * 5 + [True], counts_vectors
+
+
+def plan_of(op, shape, ins, out, alpha=0.0, dep=(0, 0, 0)):
+    """The plan of one task from (address, strides in elements, dtype) of its operands; nothing is read."""
+    tasks, pool_of = S.new_tasks(1)
+    S.set_head(tasks, 0, S.OP[op], shape, len(ins), alpha=alpha, dep=dep)
+    for k, (ptr, st, dt) in enumerate(ins):
+        S.set_tensor(tasks, pool_of, 0, k, 0, ptr, st, dt)
+    S.set_tensor(tasks, pool_of, 0, 3, 0, *out)
+    return R.task_plan(tasks, 0, S.IMPL[op])
+
+
+@pytest.mark.parametrize("layout", ["contiguous", "unaligned", "gathered", "gathered beside a dense input", "generic", "transposed", "slice"])
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16, S.I32])
+def test_no_task_is_more_than_1024_chunks(layout, code):
+    """A work unit names its chunk in ten bits: however large a task is and whatever the regular chunk of
+    its path, it is at most 1,024 chunks, and they cover it exactly."""
+    at = [(k + 1) << 36 for k in range(4)]
+    ops = {1: "COPY", 2: "MUL"} if code == S.I32 else {1: "SCALE", 2: "MUL", 3: "FMA"}
+    for numel in (1 << 20, (1 << 20) + 4096, 8 << 20, (8 << 20) + 4096, 9 << 20, 12 << 20, 14 << 20, (16 << 20) + 4096, 24 << 20, 32 << 20, 48 << 20, 64 << 20,
+                  (64 << 20) + 4096, 256 << 20):
+        for arity, op in ops.items():
+            n, C = numel, 4096
+            dense, out, shape = [1], (at[3], [1], code), [n]
+            ins = [(at[k], [1], code) for k in range(arity)]
+            if layout == "unaligned":
+                ins[0] = (at[0] + 4, [1], code)
+            elif layout == "gathered":                       # every input a stride-2 slice
+                ins = [(at[k], [2], code) for k in range(arity)]
+            elif layout == "gathered beside a dense input":
+                ins[0] = (at[0], [2], code)
+            elif layout == "generic":
+                ins[0], out = (at[0], [3], code), (at[3], [2], code)
+            elif layout == "transposed":
+                shape, ins, out = [C, n // C], [(at[k], [1, C], code) for k in range(arity)], (at[3], [n // C, 1], code)
+            elif layout == "slice":
+                shape, ins, out = [n // C, C], [(at[k], [C + 3, 1], code) for k in range(arity)], (at[3], [C + 1, 1], code)
+            path, chunks, per, _ = plan_of(op, shape, ins, out)
+            what = (layout, op, numel, path, chunks, per)
+            assert 1 <= chunks <= 1024, what
+            if path in ("CONTIG", "STAGED", "GENERIC") and layout not in ("unaligned", "slice"):
+                assert (chunks - 1) * per < n <= chunks * per, what

@@ -58,3 +58,8 @@ def test_an_operator_swapped_under_tasks_packed_as_rows():
 def test_row_operations_at_their_edges(code):
     stats, _ = _run_and_check(E.row_operation_edges(code))
     print(stats, flush=True)
+
+
+def test_gathers_larger_than_1024_regular_chunks():
+    stats, _ = _run_and_check(E.large_gathers())
+    print(stats, flush=True)
