@@ -563,11 +563,15 @@ int gpuos_audit_log(gpuos_ctx* ctx, uint64_t first, uint32_t n, gpuos_audit_reco
  * execution path (0 nothing to do, 1 contiguous vector, 2 [rows, cols]
  * with row-vector / per-row-scalar operands, 3 generic strided walk,
  * 4 contiguous-row reduction, 5 generic reduction, 6 LDS-tiled transposed
- * gather, 7 row operation with rows in registers, 8 row operation over any
- * strides, 9 contiguous output with strided / broadcast / mixed-dtype inputs
- * gathered through LDS),
+ * gather, 7 row operation over contiguous rows of whole aligned 16-byte
+ * vectors, 8 row operation over any strides, 9 contiguous output with strided
+ * / broadcast / mixed-dtype inputs gathered through LDS, 10 rows that are
+ * contiguous in every operand, or one scalar each, under outer dims of any
+ * strides, 11 as 7 with rows of any length and alignment),
  * out[1] = work units (chunks) the task is split into, out[2] = size of one
- * unit in the path's own unit (elements, rows or 32 x 32 tiles), out[3] =
+ * unit in the path's own unit (elements; 4, 5, 7, 8, 11: rows; 6: 32 x 32
+ * tiles; 10: pieces of a row of 4 elements, 8 where a tensor is 16 bits, the
+ * partly filled last one of a row included), out[3] =
  * dims left after merging adjacent dims.  For tests and for sizing. */
 int gpuos_task_plan(const gpuos_task* task, uint32_t impl_id, uint32_t out[4]);
 

@@ -1734,7 +1734,8 @@ PATHFN void red_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
 // ---------------------------------------------------------------------------
 // fused row operations (operator library, Section 5.2: softmax, layer normalisation).
 // Each row of the last dim is one problem; the output has the input's shape.
-//   PATH_ROW_FUSED: one dtype, contiguous rows that hold at least a vector, any length and alignment.
+//   PATH_ROW_FUSED, PATH_ROW_RAGGED: one dtype, contiguous rows that hold at least a vector; whole aligned
+//     vectors, or any length and alignment.
 //     A row is cut into 16-byte vectors from its first element on; in a row that is no multiple the
 //     last vector covers the row's last V elements, and those the vector before it holds count for
 //     nothing (RAGGED: also rows whose base is not 16-byte aligned; accesses need element alignment only).
@@ -2336,7 +2337,7 @@ DEV void layernorm_long(const Record* r, uint32_t row_begin, uint32_t row_end, f
   __syncthreads();                                     // the LDS slots belong to the next chunk after this
 }
 
-// The executors of PATH_ROW_FUSED.  Aligned rows of up to 1,024 vectors have one per dtype, called from
+// The executors of PATH_ROW_FUSED and PATH_ROW_RAGGED.  Aligned rows of up to 1,024 vectors have one per dtype, called from
 // the worker loop; ragged and longer rows are reached through rowop_other, one call site for all of
 // them.  (Every call site in the worker loop costs every unit: the loop's scalars are put out of the
 // call's way round each, and with forty sites more the compiler kept those in a register that it
@@ -2387,7 +2388,7 @@ PATHFN void rowop_dt(const Record* r_v, uint32_t begin_v, uint32_t end_v, float*
 template <int POL, int ROP, int DT>
 DEV void rowop_other_dt(const Record* r, uint32_t begin, uint32_t end, float* s) {
   const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
-  if (uni(r->rflags) & RF_VEC) rowop_dt<POL, ROP, DT, kRowLong, false>(r, begin, end, s);
+  if (uni(r->path) == PATH_ROW_FUSED) rowop_dt<POL, ROP, DT, kRowLong, false>(r, begin, end, s);
   else if (vpr <= 256u) rowop_dt<POL, ROP, DT, kRowShort, true>(r, begin, end, s);
   else if (vpr <= 1024u) rowop_dt<POL, ROP, DT, kRowMid, true>(r, begin, end, s);
   else rowop_dt<POL, ROP, DT, kRowLong, true>(r, begin, end, s);
@@ -2409,9 +2410,10 @@ PATHFN void rowop_other(const Record* r_v, uint32_t impl_v, uint32_t begin_v, ui
   else rowop_other_op<POL, GPUOS_IMPL_LAYERNORM_LAST>(r, begin, end, s);
 }
 
-// PATH_ROW_FUSED rows that rowop_other takes
+// the rows that rowop_other takes
 DEV bool rowop_is_other(const Record* r) {
-  return uni(r->path) == PATH_ROW_FUSED && ((uni(r->rflags) & RF_VEC) == 0 || uni(r->red_n) > (uni(r->dtype[3]) == GPUOS_F32 ? 4096u : 8192u));
+  const uint32_t path = uni(r->path);
+  return path == PATH_ROW_RAGGED || (path == PATH_ROW_FUSED && uni(r->red_n) > (uni(r->dtype[3]) == GPUOS_F32 ? 4096u : 8192u));
 }
 template <int POL, int ROP>
 DEV void run_rowop(const Record* r, uint32_t chunk, float* s_red) {

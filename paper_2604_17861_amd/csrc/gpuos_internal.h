@@ -25,13 +25,15 @@ enum Path : uint8_t {
   PATH_RED_GENERIC = 5,  // last-dim reduction, any strides
   PATH_TILE2D = 6,       // [R, C] contiguous output, >= 1 input stored transposed:
                          // gathered through an LDS tile
-  PATH_ROW_FUSED = 7,    // row operation (softmax, layer norm): contiguous rows of whole
-                         // 16-byte vectors, one dtype, a row lives in one wavefront's registers
+  PATH_ROW_FUSED = 7,    // row operation (softmax, layer norm): one dtype (layer norm: or fp32 parameters), contiguous
+                         // rows of whole aligned 16-byte vectors, read once into the registers of a part
+                         // of a wavefront, a wavefront or the workgroup; the longest in two or three passes
   PATH_ROW_GENERIC = 8,  // row operation over any strides / dtypes: three passes over memory
+  PATH_STAGED = 9,       // contiguous [R, C] output, inputs with any row / column strides (stride-2
+                         // slices, row and column vectors, mixed dtypes): gathered through LDS
   PATH_ROWS = 10,        // <= 3 outer dims of any strides over rows that are contiguous in every operand
                          // (or one scalar per row): slices, head splits, casts, any row length or alignment
-  PATH_STAGED = 9        // contiguous [R, C] output, inputs with any row / column strides (stride-2
-                         // slices, row and column vectors, mixed dtypes): gathered through LDS
+  PATH_ROW_RAGGED = 11   // as PATH_ROW_FUSED, rows of any length from one vector on and any alignment
 };
 
 enum RecFlag : uint8_t {
@@ -42,7 +44,7 @@ enum RecFlag : uint8_t {
 };
 
 enum OperandKind : uint8_t { K_FULL = 0, K_ROWVEC = 1, K_ROWSCALAR = 2, K_TRANSPOSED = 3,
-                             K_PERIODIC = 4 };   // PATH_ROW_FUSED: contiguous [period, n] block reused every `period` rows
+                             K_PERIODIC = 4 };   // PATH_ROW_FUSED / _RAGGED: contiguous [period, n] block reused every `period` rows
 
 constexpr uint32_t kMaxChunksPerTask = 1024;   // unit ring holds capacity * this entries
 constexpr uint32_t kChunkElems = 16384;        // minimum elements per chunk

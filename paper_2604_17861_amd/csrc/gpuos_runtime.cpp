@@ -221,7 +221,7 @@ inline int packed(const Record& rec, Record* r) {
 
 // Validate `t` for implementation `impl` and pack it.  Nothing is written to
 // *r unless the result is GPUOS_OK.
-int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elems = kChunkElems, int program_arity = 0, bool rows_path = true) {
+int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elems = kChunkElems, int program_arity = 0) {
   Record rec;
   std::memset(&rec, 0, sizeof(rec));
   rec.op_id = t.op_id;
@@ -310,7 +310,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     // vector path (rows in registers up to 16,384 elements, streamed beyond): one dtype, unit stride
     // along the row, rows that hold a vector; x and the output contiguous; further inputs contiguous [period, n]
     // blocks that repeat every `period` rows (period = rows: same layout as x; 1: a row vector).
-    // RF_VEC: the rows of every operand are whole aligned vectors (else the ragged executors).
+    // Where the rows of some operand are not whole aligned vectors: the ragged executors.
     const uint32_t es = dtype_size(ops[ar].dtype);
     const uint32_t V = 16u / es;
     auto dense_rows = [&](const Operand& o, int from) {      // dims from..nd-1 laid out as [.., n] contiguous
@@ -345,8 +345,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     if (impl == GPUOS_IMPL_LAYERNORM_LAST && fast && rows > 1)    // gamma, beta: row vectors, loaded once per lane
       fast = rec.okind[1] == K_PERIODIC && period[1] == 1 && rec.okind[2] == K_PERIODIC && period[2] == 1;
     if (fast) {
-      rec.path = PATH_ROW_FUSED;
-      if (whole) rec.rflags |= RF_VEC;
+      rec.path = whole ? PATH_ROW_FUSED : PATH_ROW_RAGGED;
       for (int k = 1; k < ar; ++k) rec.stride[k][0] = period[k];
     }
     uint64_t row_bytes = 0;
@@ -411,7 +410,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     // Rows that are contiguous in every operand, or hold one scalar per row, under up to three outer
     // dims of any strides: 16-byte accesses whatever the row length and alignment are, as long as a
     // row holds a vector.  Operands of one dtype (a COPY may convert), scalars of any. 
-    if (rows_path && (rec.path == PATH_GENERIC || (rec.path == PATH_CONTIG && !all_aligned)) && nd <= 4 &&
+    if ((rec.path == PATH_GENERIC || (rec.path == PATH_CONTIG && !all_aligned)) && nd <= 4 &&
         ops[ar].stride[nd - 1] == 1) {
       bool ok = true;
       int full = -1;                                             // the first operand that is not one scalar per row
@@ -1938,13 +1937,10 @@ int gpuos_task_plan(const gpuos_task* t, uint32_t impl, uint32_t out[4]) {
   const int rc = pack_task(*t, impl, &r);
   if (rc != GPUOS_OK) return rc;
   out[0] = r.path; out[1] = r.nchunks; out[2] = r.chunk; out[3] = r.ndim;
-  // the layout class is what is reported; PATH_ROWS is an executor for part of several, and ragged rows
-  // have one of their own among the fused row operations
-  if (r.path == PATH_ROW_FUSED && !(r.rflags & RF_VEC)) out[0] = PATH_ROW_GENERIC;
-  if (r.path == PATH_ROWS) {
-    Record c;
-    (void)pack_task(*t, impl, &c, kChunkElems, 0, false);
-    out[0] = c.path; out[3] = c.ndim;
+  if (r.path == PATH_ROWS) {                    // (the record's leading dims of size 1 are none of the task's)
+    uint32_t lead = 0;
+    while (lead < 3 && r.size[lead] == 1) ++lead;
+    out[3] = 4 - lead;
   }
   return GPUOS_OK;
 }

@@ -420,11 +420,13 @@ def task_bytes(tasks, impls):
     return out
 
 
-PATHS = ("NOP", "CONTIG", "ROW2D", "GENERIC", "RED_CONTIG", "RED_GENERIC", "TILE2D", "ROW_FUSED", "ROW_GENERIC", "STAGED")
+PATHS = ("NOP", "CONTIG", "ROW2D", "GENERIC", "RED_CONTIG", "RED_GENERIC", "TILE2D", "ROW_FUSED", "ROW_GENERIC", "STAGED",
+         "ROWS", "ROW_RAGGED")
 
 
 def task_plan(tasks, i, impl):
-    """(path name, chunks, chunk size, merged dims) the host packs task i into (gpuos_task_plan)."""
+    """(path name, chunks, chunk size, merged dims) the host packs task i into (gpuos_task_plan, which
+    says what a chunk's size counts on each path)."""
     out = (ctypes.c_uint32 * 4)()
     _check(lib().gpuos_task_plan(_tasks_ptr(tasks, i), int(impl), out), "gpuos_task_plan")
     return PATHS[out[0]], int(out[1]), int(out[2]), int(out[3])

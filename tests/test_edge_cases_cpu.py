@@ -10,13 +10,18 @@ from helpers import run_oracle
 from parity_cases import stream_extent_violations
 
 
-def plans(stream):
-    """(path, chunks, chunk, dims) of every task, packed with its pools at 256-byte aligned addresses."""
+def aligned_tasks(stream):
+    """The stream's descriptors with its pools at 256-byte aligned addresses (nothing lies there)."""
     bases, at = [], 1 << 20
     for p in stream.pools:
         bases.append(at)
         at += (p.nbytes + 511) // 256 * 256
-    tasks = stream.materialize(bases)
+    return stream.materialize(bases)
+
+
+def plans(stream):
+    """(path, chunks, chunk, dims) of every task, packed with its pools at 256-byte aligned addresses."""
+    tasks = aligned_tasks(stream)
     impls = stream.impl_for(None)
     return [R.task_plan(tasks, i, int(impls[i])) for i in range(len(stream))]
 
@@ -40,16 +45,20 @@ def test_rows_edges(code):
     assert not stream_extent_violations(s)
     run_oracle(s)
     V = 4 if code in (S.F32, S.I32) else 8
-    # the chunks cover every element once; a rows task counts vectors of V (8 with a 16-bit operand), the
-    # partly filled last one of a row included
-    counted_in_vectors = 0
-    for (path, chunks, per, _), size, nd, dts in zip(plans(s), s.tasks["size"], s.tasks["ndim"], s.tasks["out"]["dtype"]):
+    # a rows task counts pieces of V elements (8 with a 16-bit operand), the partly filled last one of a row
+    # included.  Others: an aligned matrix with one scalar per row is ROW2D, and a row shorter than a
+    # piece (a cast's, four or five fp32 elements) is gathered or walked.
+    taken = {"ROWS": 0, "ROW2D": 0, "STAGED": 0, "GENERIC": 0}
+    for (path, chunks, per, dims), size, nd, dts in zip(plans(s), s.tasks["size"], s.tasks["ndim"], s.tasks["out"]["dtype"]):
         numel, C = int(np.prod(size[:nd])), int(size[nd - 1])
         W = 8 if V == 8 or dts not in (S.F32, S.I32) else 4
-        vectors = numel // C * -(-C // W)
-        assert chunks <= 1024 and (chunks == -(-numel // per) or chunks == -(-vectors // per) or C < W or path == "CONTIG")
-        counted_in_vectors += chunks == -(-vectors // per)
-    assert counted_in_vectors > 0.8 * len(s)
+        taken[path] += 1
+        assert path == "ROWS" or (path == "ROW2D" and C % V == 0) or C < W, (path, size, W)
+        assert chunks <= 1024 and dims <= 4
+        if path == "ROWS":
+            vectors = {numel // c * -(-c // W) for c in (C, numel)}              # rows of the last dim, or one flat run
+            assert any((chunks - 1) * per < v <= chunks * per for v in vectors)
+    assert taken["ROWS"] > 0.85 * len(s) and taken["STAGED"] + taken["GENERIC"] <= 8, taken
 
 
 def test_large_gathers():
@@ -66,15 +75,23 @@ def test_row_operation_edges(code):
     assert not stream_extent_violations(s)
     run_oracle(s)
     V = 4 if code == S.F32 else 8
+    paths = []
     for (path, chunks, per, _), size, nd in zip(plans(s), s.tasks["size"], s.tasks["ndim"]):
         n, rows = int(size[nd - 1]), int(np.prod(size[:nd - 1]))
-        assert path in ("ROW_FUSED", "ROW_GENERIC") and (n >= V or path == "ROW_GENERIC")
+        paths.append((path, n))
         assert chunks == -(-rows // per)
+    # shorter than a vector: any strides; whole vectors at aligned addresses: fused; every other one ragged
+    t = aligned_tasks(s)
+    ptrs = [[int(p) for p in ins[:k]] + [int(out)] for ins, out, k in zip(t["inp"]["ptr"], t["out"]["ptr"], t["n_inputs"])]
+    for (path, n), ptr in zip(paths, ptrs):
+        want = "ROW_GENERIC" if n < V else "ROW_FUSED" if n % V == 0 and all(p % 16 == 0 for p in ptr) else "ROW_RAGGED"
+        assert path == want, (path, want, n, ptr)
+    assert {p for p, _ in paths} >= {"ROW_GENERIC", "ROW_RAGGED"}
 
 
 def test_what_rows_leaves_to_the_other_paths():
-    """Rows shorter than a vector, strided elements, transposed views, more outer dims than three and
-    mixed dtypes keep their chunks, which count elements in thousands; rows count vectors."""
+    """Rows shorter than a vector, strided elements, transposed views, mixed dtypes and more outer dims
+    than three are walked, also where the output is no contiguous tensor."""
     from helpers import Builder
     b = Builder()
     x = b.pool(np.zeros((640, 64), np.float32))
@@ -88,13 +105,7 @@ def test_what_rows_leaves_to_the_other_paths():
     b.add("MUL", o[:, 1:33], [h[:, :32], x[:, :32]])
     b.add("COPY", b.pool(np.zeros((2, 3, 2, 3, 3, 129), np.float32))[..., :128], [six[:2, 1:, 1:, 1:, :, :128]])
     b.add("ADD", o[:, 1:33], [x[:, :32], x[:, 32:]])                    # ... and this one is rows
-    s = b.stream()
-    counts_vectors = []
-    for (path, chunks, per, _), size, nd in zip(plans(s), s.tasks["size"], s.tasks["ndim"]):
-        numel, C = int(np.prod(size[:nd])), int(size[nd - 1])
-        assert path == "GENERIC"
-        counts_vectors.append(chunks != -(-numel // per) and chunks == -(-(numel // C * -(-C // 4)) // per))
-    assert counts_vectors == [False] * 5 + [True], counts_vectors
+    assert [p[0] for p in plans(b.stream())] == ["GENERIC"] * 5 + ["ROWS"]
 
 
 def plan_of(op, shape, ins, out, alpha=0.0, dep=(0, 0, 0)):
@@ -135,5 +146,10 @@ def test_no_task_is_more_than_1024_chunks(layout, code):
             path, chunks, per, _ = plan_of(op, shape, ins, out)
             what = (layout, op, numel, path, chunks, per)
             assert 1 <= chunks <= 1024, what
-            if path in ("CONTIG", "STAGED", "GENERIC") and layout not in ("unaligned", "slice"):
-                assert (chunks - 1) * per < n <= chunks * per, what
+            V = 4 if code in (S.F32, S.I32) else 8
+            units = {"ROWS": numel // V, "TILE2D": (C // 32) * -(-(n // C) // 32)}.get(path, n)
+            assert (chunks - 1) * per < units <= chunks * per, what
+            want = {"contiguous": "CONTIG", "unaligned": "ROWS", "slice": "ROWS", "generic": "GENERIC", "transposed": "TILE2D"}.get(layout, "STAGED")
+            if code == S.I32 and want in ("TILE2D", "STAGED"):
+                want = "GENERIC"
+            assert path == want, what

@@ -100,8 +100,9 @@ def test_task_bytes_counts_each_distinct_element_once():
 
 def test_task_plan_picks_the_execution_path_the_layout_calls_for():
     """The host classifies each task by the strides left after merging dims: contiguous ->
-    vector path, row vector / per-row scalar -> 2-D path, a transposed input under a contiguous
-    output -> LDS tiles, anything else -> the generic walk; reductions by row contiguity."""
+    vector path, row vector / per-row scalar -> 2-D path, contiguous rows of any pitch, length or
+    alignment -> rows, a transposed input under a contiguous output -> LDS tiles, anything else -> the
+    generic walk; reductions by row contiguity."""
     from helpers import Builder
     b = Builder()
     f = lambda *shape: b.pool(np.zeros(shape, np.float32))
@@ -116,7 +117,7 @@ def test_task_plan_picks_the_execution_path_the_layout_calls_for():
     b.add("MUL", o[0, :4, :4], [at[0, :4, :4], c[0, :4, :4]])            # 5 output not contiguous
     b.add("COPY", o.transpose(0, 2, 1), [f(4, 80, 96)])                  # 6 transposed OUTPUT: generic
     b.add("COPY", o, [at])                                               # 7 same-dtype copy keeps raw bits: generic
-    b.add("RELU", o[:, ::2, :], [a[:, ::2, :]])                          # 8 gapped rows: generic
+    b.add("RELU", o[:, ::2, :], [a[:, ::2, :]])                          # 8 gapped rows
     b.add("SUM_LAST", f(4, 96), [a])                                     # 9 contiguous rows
     b.add("MAX_LAST", f(4, 96), [at])                                    # 10 strided rows
     b.add("ADD", f(4, 5)[:0], [f(4, 5)[:0], f(4, 5)[:0]])                # 11 empty
@@ -125,29 +126,29 @@ def test_task_plan_picks_the_execution_path_the_layout_calls_for():
     impl = s.impl_for()
     got = [R.task_plan(hp.tasks, i, impl[i]) for i in range(len(s))]
     paths = [g[0] for g in got]
-    assert paths == ["CONTIG", "ROW2D", "ROW2D", "TILE2D", "TILE2D", "GENERIC", "GENERIC", "GENERIC", "GENERIC",
+    assert paths == ["CONTIG", "ROW2D", "ROW2D", "TILE2D", "TILE2D", "GENERIC", "GENERIC", "GENERIC", "ROWS",
                      "RED_CONTIG", "RED_GENERIC", "NOP"], paths
     assert got[0][3] == 1                                  # [4, 96, 80] contiguous merges to one dim
     assert got[3][1] * got[3][2] >= 4 * 3 * 3 and got[3][3] == 3      # 4 batches of 3 x 3 tiles
-    # contiguous output, inputs strided / broadcast / of another dtype: gathered through LDS
+    # contiguous output, inputs strided / of another dtype: gathered through LDS
     g = Builder()
     f = lambda *shape: g.pool(np.zeros(shape, np.float32))
     h = lambda *shape: g.pool(np.zeros(shape, np.float16))
     x2 = f(2 * 5000 + 1)
     g.add("RELU", f(5000), [x2[1::2]])                                   # 0 a stride-2 slice that starts at element 1
-    g.add("ADD", f(33, 77), [f(33, 77), np.broadcast_to(f(77), (33, 77))])          # 1 row vector, 77 is no multiple of the vector width
-    g.add("MUL", f(33, 77), [f(33, 77), np.broadcast_to(f(33)[:, None], (33, 77))]) # 2 column vector: read along the rows through LDS tiles
+    g.add("ADD", f(33, 77), [f(33, 77), np.broadcast_to(f(77), (33, 77))])          # 1 row vector, 77 is no multiple of the vector width: rows
+    g.add("MUL", f(33, 77), [f(33, 77), np.broadcast_to(f(33)[:, None], (33, 77))]) # 2 column vector: one scalar per row
     g.add("ADD", f(6, 9, 5), [f(6, 5, 9).transpose(0, 2, 1), f(6, 9, 5)])           # 3 small transposes (5 columns: no LDS tiles)
     g.add("SUB", h(400), [f(400), h(400)])                               # 4 mixed dtypes
     g.add("COPY", f(5000), [x2[::2]])                                    # 5 same-dtype copy keeps raw bits: generic
     g.add("RELU", f(5001)[1:], [x2[: 10000: 2]])                         # 6 output not 16-byte aligned: generic
     i32 = g.pool(np.zeros(200, np.int32))
     g.add("ADD", g.pool(np.zeros(100, np.int32)), [i32[::2], i32[1::2]]) # 7 integers: generic
-    g.add("ADD", f(3, 4, 5, 6), [f(3, 4, 5, 6), np.broadcast_to(f(4, 1, 6)[None], (3, 4, 5, 6))])   # 8 four dims that do not merge: generic
+    g.add("ADD", f(3, 4, 5, 6), [f(3, 4, 5, 6), np.broadcast_to(f(4, 1, 6)[None], (3, 4, 5, 6))])   # 8 four dims that do not merge: rows
     sg = g.stream()
     hg = HostPools(sg)
     got = [R.task_plan(hg.tasks, i, sg.impl_for()[i])[0] for i in range(len(sg))]
-    assert got == ["STAGED", "STAGED", "TILE2D", "STAGED", "STAGED"] + ["GENERIC"] * 4, got
+    assert got == ["STAGED", "ROWS", "ROWS", "STAGED", "STAGED"] + ["GENERIC"] * 3 + ["ROWS"], got
     # a large transposed task splits into at most 1024 units that cover every tile
     big = Builder()
     src = big.pool(np.zeros((3000, 2100), np.float16)).T
@@ -198,9 +199,9 @@ def test_small_tasks_are_cut_into_more_chunks_than_their_size_alone_would_give()
 
 
 def test_task_plan_for_row_operations():
-    """Rows of whole aligned vectors (at most 256 of them), one dtype, contiguous -> rows in
-    registers, with further inputs laid out like x, repeated every `period` rows, or one row;
-    everything else takes the three-pass path."""
+    """Rows of whole aligned vectors, one dtype, contiguous -> the fused executors, with further inputs
+    laid out like x, repeated every `period` rows, or one row; rows of any other length from a vector
+    on -> their ragged forms; everything else takes the three-pass path."""
     from helpers import Builder
     b = Builder()
     f = lambda *shape: b.pool(np.zeros(shape, np.float32))
@@ -214,7 +215,7 @@ def test_task_plan_for_row_operations():
     b.add("LAYERNORM_LAST", f(50, 1024), [f(50, 1024), np.broadcast_to(f(1024), (50, 1024)), np.broadcast_to(f(1024), (50, 1024))])  # 5
     b.add("LAYERNORM_LAST", f(50, 1024), [f(50, 1024), f(50, 1024), np.broadcast_to(f(1024), (50, 1024))])   # 6 per-element gamma
     b.add("SOFTMAX_LAST", f(10, 1028), [f(10, 1028)])                                        # 7 257 vectors: a workgroup per row
-    b.add("SOFTMAX_LAST", f(10, 30), [f(10, 30)])                                            # 8 not whole vectors
+    b.add("SOFTMAX_LAST", f(10, 30), [f(10, 30)])                                            # 8 not whole vectors: ragged
     b.add("SOFTMAX_LAST", f(10, 32), [h(10, 32)])                                            # 9 mixed dtypes
     b.add("SOFTMAX_LAST", f(10, 32), [f(10, 64)[:, ::2]])                                    # 10 strided
     b.add("SOFTMAX_LAST", f(10, 32), [f(10, 36)[:, :32]])                                    # 11 row pitch
@@ -226,7 +227,7 @@ def test_task_plan_for_row_operations():
     hp = HostPools(s)
     impl = s.impl_for()
     got = [R.task_plan(hp.tasks, i, impl[i]) for i in range(len(s))]
-    want = ["ROW_FUSED"] * 4 + ["ROW_GENERIC", "ROW_FUSED", "ROW_GENERIC", "ROW_FUSED", "ROW_GENERIC", "ROW_GENERIC",
+    want = ["ROW_FUSED"] * 4 + ["ROW_GENERIC", "ROW_FUSED", "ROW_GENERIC", "ROW_FUSED", "ROW_RAGGED", "ROW_GENERIC",
                                 "ROW_GENERIC", "ROW_GENERIC", "ROW_FUSED", "ROW_FUSED", "ROW_FUSED", "ROW_GENERIC"]
     assert [g[0] for g in got] == want, [g[0] for g in got]
     rows = 2 * 3 * 64
