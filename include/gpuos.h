@@ -281,7 +281,7 @@ typedef struct gpuos_config {
   uint32_t chunk_elems;             /* elements of a large task one workgroup takes at a time,
                                        quoted for 12 bytes of traffic per element and scaled for
                                        other operators (0 => 16384; rounded up to a multiple of
-                                       1024).  Tasks of up to 2^20 elements and links of a chain
+                                       1024, 2^24 at most).  Tasks of up to 2^20 elements and links of a chain
                                        take half of it; a task of at most four such chunks is cut
                                        into up to four; gathered and transposed inputs are spread
                                        over up to 32 resp. 64 workgroups (gpuos_task_plan tells) */

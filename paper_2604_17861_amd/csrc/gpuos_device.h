@@ -196,8 +196,6 @@ template <int POL> DEV void store_rt(void* p, uint32_t i, uint32_t dt, float f) 
 // cancellation-free form and rounded once: an fp32 evaluation cannot hold 2 ulp
 // for x < 0, where 1 + tanh(u) and 1 + erf(u) cancel.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kNoLoad = 0x7ffffff0u;   // a buffer offset past every resource: the load returns 0 and moves no data
-
 template <int IMPL> struct Op;
 template <> struct Op<GPUOS_IMPL_ADD> { static constexpr int N = 2; static DEV float f(float x, float y, float, float) { return x + y; } };
 template <> struct Op<GPUOS_IMPL_SUB> { static constexpr int N = 2; static DEV float f(float x, float y, float, float) { return x - y; } };

@@ -48,6 +48,8 @@ enum OperandKind : uint8_t { K_FULL = 0, K_ROWVEC = 1, K_ROWSCALAR = 2, K_TRANSP
 
 constexpr uint32_t kMaxChunksPerTask = 1024;   // unit ring holds capacity * this entries
 constexpr uint32_t kChunkElems = 16384;        // minimum elements per chunk
+constexpr uint32_t kMostChunkElems = 1u << 24; // ... and the most a context may ask for: a chunk of any path is addressed through one buffer resource
+constexpr uint32_t kNoLoad = 0x7ffffff0u;      // a buffer offset past every resource: a load there returns 0 and a store does nothing
 constexpr uint32_t kDispatchBatch = 64;        // records mirrored per dispatcher pass
 constexpr uint32_t kThreads = 256;             // threads per workgroup of the worker
 

@@ -141,7 +141,7 @@ bool impl_takes_int(uint32_t impl) {
 inline uint32_t dtype_size(uint32_t dt) { return (dt == GPUOS_F32 || dt == GPUOS_I32) ? 4u : 2u; }
 
 constexpr int64_t kMaxExtent = 2147483647LL;
-constexpr int64_t kRowsExtent = 0x7ffffff0LL - 64;   // bytes of an operand that PATH_ROWS addresses from one buffer resource, below the offset that loads nothing
+constexpr int64_t kRowsExtent = (int64_t)kNoLoad - 64;   // bytes of an operand that PATH_ROWS addresses from one buffer resource, below the offset that loads nothing
 
 struct Operand {              // one tensor after masking broadcast dims
   uint64_t ptr;
@@ -324,7 +324,8 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     // one dtype for every tensor; layer norm also with fp32 gamma and beta under 16-bit x and y
     const bool ln_p32 = impl == GPUOS_IMPL_LAYERNORM_LAST && ops[0].dtype == ops[ar].dtype && ops[0].dtype != GPUOS_F32 &&
                         ops[1].dtype == GPUOS_F32 && ops[2].dtype == GPUOS_F32;
-    bool fast = (same_dt || ln_p32) && n >= (int64_t)V && n * (int64_t)es < kMaxExtent && n * 4 < kMaxExtent;
+    // (a row ends at or below kNoLoad, where the ragged executors put the stores that are to do nothing)
+    bool fast = (same_dt || ln_p32) && n >= (int64_t)V && n * (int64_t)es <= (int64_t)kNoLoad && n * 4 < kMaxExtent;
     bool whole = n % V == 0;
     for (int k = 0; k <= ar && fast; ++k) { fast = s_last[k] == 1; whole = whole && aligned16(ops[k].ptr); }
     fast = fast && (rows == 1 || (dense_rows(oo[0], 0) && dense_rows(oo[ar], 0)));
@@ -1040,7 +1041,7 @@ int gpuos_init(gpuos_ctx** out, uint32_t queue_capacity, const gpuos_config* use
   if (cfg.wait_timeout_ms == 0) cfg.wait_timeout_ms = 30000;
   if (cfg.completion_log == 0) cfg.completion_log = 1u << 20;
   if (cfg.chunk_elems == 0) cfg.chunk_elems = kChunkElems;
-  cfg.chunk_elems = (cfg.chunk_elems + 1023u) / 1024u * 1024u;
+  cfg.chunk_elems = cfg.chunk_elems < kMostChunkElems ? (cfg.chunk_elems + 1023u) / 1024u * 1024u : kMostChunkElems;
   uint32_t cap = queue_capacity ? queue_capacity : 4096u;
   if (cap < 2 || cap > 65536 || (cap & (cap - 1)) != 0) return GPUOS_E_INVAL;
   const char* env_jit = std::getenv("GPUOS_JIT");                 // GPUOS_JIT=0: operator programs stay interpreted
@@ -1187,7 +1188,7 @@ int gpuos_init_static(gpuos_ctx** out, uint32_t queue_capacity, const gpuos_conf
   if (cfg.workgroups_per_cu == 0) cfg.workgroups_per_cu = 3;
   if (cfg.wait_timeout_ms == 0) cfg.wait_timeout_ms = 30000;
   if (cfg.chunk_elems == 0) cfg.chunk_elems = kChunkElems;
-  cfg.chunk_elems = (cfg.chunk_elems + 1023u) / 1024u * 1024u;
+  cfg.chunk_elems = cfg.chunk_elems < kMostChunkElems ? (cfg.chunk_elems + 1023u) / 1024u * 1024u : kMostChunkElems;
   const uint32_t cap = queue_capacity ? queue_capacity : kStaticMaxCapacity;
   auto reject = [](const char* why) { g_hip_error = std::string("gpuos_init_static: ") + why; return GPUOS_E_INVAL; };
   if (cfg.threads_per_workgroup != kThreads) return reject("only 256 threads per workgroup are built");

@@ -89,6 +89,11 @@ void consumer(gpuos::WorkerArgs a, Worker* w) {
           version = table[rec.op_id].version;
           if (table[rec.op_id].impl == GPUOS_IMPL_FAIL) status = GPUOS_E_BADOP;
           if (rec.nchunks == 0 || rec.nchunks > kMaxChunksPerTask) g_errors.fetch_add(1);
+          // a chunk's elements are addressed by 32-bit byte offsets below kNoLoad
+          const uint64_t es = rec.dtype[3] == GPUOS_F32 || rec.dtype[3] == GPUOS_I32 ? 4 : 2;
+          const uint64_t units = rec.chunk < rec.numel ? rec.chunk : rec.numel;
+          const uint64_t per = rec.path == PATH_ROW_FUSED || rec.path == PATH_ROW_RAGGED ? rec.red_n : 1;
+          if ((rec.path == PATH_CONTIG || per > 1) && units * per * es > kNoLoad) g_errors.fetch_add(1);
         }
         comp[i] = pack_completion(ticket, status, version);
         g_records.fetch_add(1);

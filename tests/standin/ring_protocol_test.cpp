@@ -86,8 +86,41 @@ static void check_word_rejects_mixtures() {
   std::printf("ok: check word rejects every old/new mixture of a slot's records\n");
 }
 
+// However large the chunks a context asks for, every chunk lies within what 32-bit byte offsets reach
+// (the stand-in looks at each record): integer and float tensors, rows of whole vectors and ragged ones.
+static void chunks_stay_addressable() {
+  for (uint32_t elems : {1u << 24, 1u << 29, 800000000u, 0xffffffffu}) {
+    gpuos_config cfg;
+    gpuos_default_config(&cfg);
+    cfg.chunk_elems = elems;
+    cfg.wait_timeout_ms = 20000;
+    gpuos_ctx* c = nullptr;
+    CHECK(gpuos_init(&c, 64, &cfg) == GPUOS_OK);
+    CHECK(gpuos_register_op(c, 7, GPUOS_IMPL_ADD, nullptr) == GPUOS_OK);
+    CHECK(gpuos_register_op(c, 8, GPUOS_IMPL_SOFTMAX_LAST, nullptr) == GPUOS_OK);
+    for (uint32_t dt : {GPUOS_F32, GPUOS_I32}) {
+      gpuos_task t = add_task(7, 2147483647u - 1024u);
+      t.in[0].dtype = t.in[1].dtype = t.out.dtype = (uint8_t)dt;
+      CHECK(gpuos_submit(c, &t, 1, nullptr) == GPUOS_OK);
+    }
+    for (uint32_t n : {1024u, 1021u, 536870908u}) {
+      gpuos_task t = add_task(8, 0);
+      t.ndim = 2; t.n_inputs = 1;
+      t.size[0] = 2147483647u / n; t.size[1] = n;
+      t.in[0].stride[0] = t.out.stride[0] = n;
+      t.in[0].stride[1] = t.out.stride[1] = 1;
+      CHECK(gpuos_submit(c, &t, 1, nullptr) == GPUOS_OK);
+    }
+    CHECK(gpuos_flush(c) == GPUOS_OK && gpuos_wait(c, GPUOS_ALL, 0) == GPUOS_OK);
+    CHECK(gpuos_shutdown(c) == GPUOS_OK);
+  }
+  CHECK(standin_errors() == 0);
+  std::printf("chunks within 32-bit offsets: ok\n");
+}
+
 int main() {
   check_word_rejects_mixtures();
+  chunks_stay_addressable();
   // 1. many producers, tiny rings: every ticket exactly once, consecutive inside a call, in-order log
   for (uint32_t cap : {2u, 8u, 64u}) {
     for (int harv = 0; harv < 2; ++harv) {

@@ -153,3 +153,17 @@ def test_no_task_is_more_than_1024_chunks(layout, code):
             if code == S.I32 and want in ("TILE2D", "STAGED"):
                 want = "GENERIC"
             assert path == want, what
+
+
+@pytest.mark.parametrize("op", ["SOFTMAX_LAST", "MASKED_SOFTMAX_LAST", "LAYERNORM_LAST"])
+def test_rows_up_to_the_last_addressable_byte(op):
+    """The executors of contiguous rows address a row by byte offsets below 0x7ffffff0, the offset that is
+    given to the stores that are to do nothing: longer rows are walked."""
+    at = [(k + 1) << 40 for k in range(4)]
+    most = 0x7ffffff0 // 4                                       # fp32 elements
+    for n, want in ((1000, "ROW_FUSED"), (1001, "ROW_RAGGED"), (most - 4, "ROW_FUSED"), (most - 1, "ROW_RAGGED"), (most, "ROW_FUSED"),
+                    (most + 1, "ROW_GENERIC"), (most + 2, "ROW_GENERIC"), (most + 3, "ROW_GENERIC")):
+        for rows in (1, 3) if n > 2000 else (1, 3, 100000):
+            st = {"SOFTMAX_LAST": [[n, 1]], "MASKED_SOFTMAX_LAST": [[n, 1], [0, 1]], "LAYERNORM_LAST": [[n, 1], [0, 1], [0, 1]]}[op]
+            path = plan_of(op, [rows, n], [(at[k], s, S.F32) for k, s in enumerate(st)], (at[3], [n, 1], S.F32), alpha=1.0)[0]
+            assert path == want, (op, rows, n, path)
