@@ -124,3 +124,20 @@ def large_gathers():
     h = b.pool(rng.integers(0, 0x7f00, size=2 * n, dtype=np.uint16))
     b.add("SCALE", b.pool(np.zeros(n, np.uint16)), [h[1::2]], alpha=0.5)
     return b.stream("large_gathers")
+
+
+def gelu_values(code):
+    """Both GELUs over every value of a 16-bit format, or over fp32 values of both signs from 2^-20 to 16
+    and the special ones: once contiguous and aligned, once as rows of an odd length."""
+    rng = np.random.default_rng(740)
+    b = Builder()
+    if code == S.F32:
+        v = np.ldexp(rng.uniform(0.5, 1.0, 1 << 19), rng.integers(-20, 5, 1 << 19)).astype(np.float32)
+        v = np.concatenate([v, -v, np.array([0.0, -0.0, np.inf, -np.inf, np.nan, 3e38, -3e38, 1e-42, -1e-42, 14.3, -14.3, -14.5, -14.6], np.float32)])
+    else:
+        v = np.arange(65536, dtype=np.uint16).view(np_dtype(code))
+    x, y = b.pool(v), b.pool(np.append(v[:1], v[:v.size // 7 * 7]))[1:].reshape(7, -1)
+    for name in ("GELU_ERF", "GELU_TANH"):
+        b.add(name, b.pool(np.zeros_like(v)), [x])
+        b.add(name, b.pool(np.zeros((7, y.shape[1] + 1), v.dtype))[:, 1:], [y])
+    return b.stream("gelu_values_%d" % code)

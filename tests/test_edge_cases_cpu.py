@@ -61,6 +61,13 @@ def test_rows_edges(code):
     assert taken["ROWS"] > 0.85 * len(s) and taken["STAGED"] + taken["GENERIC"] <= 8, taken
 
 
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_gelu_values(code):
+    s = E.gelu_values(code)
+    assert not stream_extent_violations(s)
+    assert [p[0] for p in plans(s)] == ["CONTIG", "ROWS"] * 2
+
+
 def test_large_gathers():
     s = E.large_gathers()
     assert not stream_extent_violations(s)
