@@ -2657,7 +2657,8 @@ struct WorkShared {
   uint32_t draining;               // the stop flag was seen: claim nothing more, finish what is held, leave
   uint32_t polls, yield_every;
   uint64_t g;                      // the claimed unit number
-  uint32_t n_units, held_any;
+  uint64_t n_units;
+  uint32_t held_any;
   uint64_t ticks[ST_WORK_TICKS_TOTAL - ST_WORK_TICKS_WAIT];
   alignas(16) float red[kScratchFloats];   // (16-byte LDS vectors are written into it)
 };
@@ -2847,7 +2848,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
     if (action == kActExit) {
       if (tid == 0) {
         uint64_t* st = a.d->stat;
-        __hip_atomic_fetch_add(&st[ST_WORK_UNITS], (uint64_t)s->n_units, __ATOMIC_RELAXED, SC_AGENT);
+        __hip_atomic_fetch_add(&st[ST_WORK_UNITS], s->n_units, __ATOMIC_RELAXED, SC_AGENT);
         for (uint32_t k = ST_WORK_TICKS_WAIT; k < ST_WORK_TICKS_TOTAL; ++k)
           __hip_atomic_fetch_add(&st[k], s->ticks[k - ST_WORK_TICKS_WAIT], __ATOMIC_RELAXED, SC_AGENT);
         __hip_atomic_fetch_add(&st[ST_WORK_TICKS_TOTAL], c0 - w_start, __ATOMIC_RELAXED, SC_AGENT);
