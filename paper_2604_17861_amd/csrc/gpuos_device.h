@@ -426,6 +426,17 @@ template <class T> DEV T* lds_arg(T* p) {
   const uint32_t a = uni((uint32_t)(__UINTPTR_TYPE__)(lds_t)p);
   return (T*)(lds_t)(__UINTPTR_TYPE__)a;
 }
+// This thread's index in the workgroup, from its wavefront's index (a scalar).  The executors get it as an
+// argument, and the worker finds it anew for each unit (the empty asm keeps it from being carried over).
+// threadIdx.x in an executor would make every call hand over the work-item id, and the worker kernel,
+// which has to keep that across calls that preserve few vector registers, kept it in scratch
+// memory: three loads from there in a row on every unit, 0.3 us, with one set of executors, none with another.
+DEV uint32_t lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+DEV uint32_t thread_index(uint32_t wave) {
+  uint32_t zero = 0;
+  asm volatile("" : "+v"(zero));
+  return wave * 64u + __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
 
 // K 16-byte vectors of one operand; or, under MixArg, one scalar per vector in their place (of any
 // dtype: `word` holds the bits of an fp32 value, or an int32).
@@ -513,7 +524,7 @@ template <int ARITY> struct ByArity {
 // 16 bytes per lane per access, four accesses in flight per operand.
 // ---------------------------------------------------------------------------
 template <int POL, int IMPL, int DT>
-PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
+PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   uint32_t begin = uni(begin_v);
   const uint32_t end = uni(end_v);
@@ -525,7 +536,6 @@ PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
   const char* pc = N > 2 ? uni_ptr(r->ptr[2]) : pa;
   char* po = (char*)uni_ptr(r->ptr[3]);
   const float alpha = r->alpha;
-  const uint32_t tid = threadIdx.x;
   if (r->rflags & RF_VEC) {
     // buffer resources rebased to this chunk; begin is a multiple of V
     const uint32_t nvec = (end - begin) / V;
@@ -577,7 +587,7 @@ constexpr uint32_t kScratchFloats = 7168;   // LDS scratch per workgroup (gather
 // compile-time facts and the selects and branches on them disappear.  KIND1 < 0: kinds read from
 // the descriptor.
 template <int POL, int IMPL, int DT, int KIND1>
-PATHFN void ew_row2d(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v) {
+PATHFN void ew_row2d(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   const uint32_t begin = uni(begin_v), end = uni(end_v);
   float* s_scratch = lds_arg(s_v);
@@ -619,7 +629,7 @@ PATHFN void ew_row2d(const Record* r_v, uint32_t begin_v, uint32_t end_v, float*
   const uint32_t step_rows = step / C, step_cols = step - step_rows * C;
   uint32_t row, col;
   {
-    const uint32_t i = begin + threadIdx.x * V;
+    const uint32_t i = begin + tid * V;
     row = i / C;
     col = i - row * C;
   }
@@ -667,20 +677,20 @@ PATHFN void ew_row2d(const Record* r_v, uint32_t begin_v, uint32_t end_v, float*
       }
     }
   };
-  load_round(threadIdx.x);                           // (every thread, whatever nvec: the barrier below is for all)
+  load_round(tid);                           // (every thread, whatever nvec: the barrier below is for all)
   if (staged) {
     uint32_t region = 0;
 #pragma unroll
     for (int k = 0; k < N; ++k)
       if (kind[k] == K_ROWSCALAR) {
-        for (uint32_t t = threadIdx.x; t < row_cnt; t += kThreads)
+        for (uint32_t t = tid; t < row_cnt; t += kThreads)
           s_scratch[region + t] = load_rt<POL>(p[k], (row_first + t) * st0[k], dt[k]);
         region += row_cnt;
       }
     __syncthreads();
   }
-  compute_round(threadIdx.x);
-  for (uint32_t v0 = threadIdx.x + kThreads * UN; v0 < nvec; v0 += kThreads * UN) {
+  compute_round(tid);
+  for (uint32_t v0 = tid + kThreads * UN; v0 < nvec; v0 += kThreads * UN) {
     load_round(v0);
     compute_round(v0);
   }
@@ -698,7 +708,7 @@ PATHFN void ew_row2d(const Record* r_v, uint32_t begin_v, uint32_t end_v, float*
 constexpr uint32_t kTile = 32, kTilePitch = 33;
 
 template <int POL, int IMPL>
-PATHFN void ew_tile2d(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v) {
+PATHFN void ew_tile2d(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   const uint32_t tile_begin = uni(begin_v), tile_end = uni(end_v);
   float* s_scratch = lds_arg(s_v);
@@ -718,7 +728,6 @@ PATHFN void ew_tile2d(const Record* r_v, uint32_t begin_v, uint32_t end_v, float
   char* po = (char*)uni_ptr(r->ptr[3]);
   const uint32_t odt = uni(r->dtype[3]);
   const float alpha = r->alpha;
-  const uint32_t tid = threadIdx.x;
   uint32_t m_f32[3], m_f16[3], m_bf16[3];                  // all ones for the input's dtype
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -853,10 +862,10 @@ template <int IMPL> DEV void staged_ctx(StagedCtx& c, const Record* r, uint32_t 
 // every input is in LDS, and the round holds no memory load at all.
 template <int POL, int IMPL, bool FULL, bool ALL_STAGED>
 DEV void staged_round(const StagedCtx& c, uint32_t c0, uint32_t c1, const uint32_t (&g_lo)[3], const uint32_t (&g_region)[3],
-                      const bool (&g_staged)[3]) {
+                      const bool (&g_staged)[3], uint32_t tid) {
   using M = Mem<POL>;
   constexpr int N = Op<IMPL>::N;
-  const uint32_t i = c0 + 4u * threadIdx.x;
+  const uint32_t i = c0 + 4u * tid;
   if (!FULL && i >= c1) return;
   uint32_t b = i / c.RC;
   const uint32_t j = i - b * c.RC;
@@ -934,18 +943,18 @@ DEV void staged_round(const StagedCtx& c, uint32_t c0, uint32_t c1, const uint32
 // common round's code.
 template <int POL, int IMPL>
 PATHFN void ew_staged_slow_round(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v, uint32_t c0_v, uint32_t c1_v,
-                                 uint32_t lo0, uint32_t lo1, uint32_t lo2, uint32_t rg0, uint32_t rg1, uint32_t rg2, uint32_t staged_mask_v) {
+                                 uint32_t lo0, uint32_t lo1, uint32_t lo2, uint32_t rg0, uint32_t rg1, uint32_t rg2, uint32_t staged_mask_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   StagedCtx c;
   staged_ctx<IMPL>(c, r, uni(begin_v), uni(end_v), (char*)lds_arg(s_v));
   const uint32_t g_lo[3] = {uni(lo0), uni(lo1), uni(lo2)}, g_region[3] = {uni(rg0), uni(rg1), uni(rg2)};
   const uint32_t mask = uni(staged_mask_v);
   const bool g_staged[3] = {(mask & 1u) != 0, (mask & 2u) != 0, (mask & 4u) != 0};
-  staged_round<POL, IMPL, false, false>(c, uni(c0_v), uni(c1_v), g_lo, g_region, g_staged);
+  staged_round<POL, IMPL, false, false>(c, uni(c0_v), uni(c1_v), g_lo, g_region, g_staged, tid);
 }
 
 template <int POL, int IMPL>
-PATHFN void ew_staged(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v) {
+PATHFN void ew_staged(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   const uint32_t begin = uni(begin_v), end = uni(end_v);
   char* lds = (char*)lds_arg(s_v);
@@ -953,7 +962,6 @@ PATHFN void ew_staged(const Record* r_v, uint32_t begin_v, uint32_t end_v, float
   constexpr int N = Op<IMPL>::N;
   StagedCtx c;
   staged_ctx<IMPL>(c, r, begin, end, lds);
-  const uint32_t tid = threadIdx.x;
   constexpr uint32_t kLdsBytes = kScratchFloats * 4u;
   constexpr uint32_t kBatchBytes = kStageLoads * kThreads * 16u;
   static_assert(kStageLoads == 4, "the pin in stash() names four vectors");
@@ -1038,7 +1046,7 @@ PATHFN void ew_staged(const Record* r_v, uint32_t begin_v, uint32_t end_v, float
   };
   auto slow_round = [&]() {
     const uint32_t mask = (g_staged[0] ? 1u : 0u) | (g_staged[1] ? 2u : 0u) | (g_staged[2] ? 4u : 0u);
-    ew_staged_slow_round<POL, IMPL>(r_v, begin, end, s_v, c0, c1, g_lo[0], g_lo[1], g_lo[2], g_region[0], g_region[1], g_region[2], mask);
+    ew_staged_slow_round<POL, IMPL>(r_v, begin, end, s_v, c0, c1, g_lo[0], g_lo[1], g_lo[2], g_region[0], g_region[1], g_region[2], mask, tid);
   };
   while (i1 < end) {                  // a round with a successor
     take();
@@ -1047,7 +1055,7 @@ PATHFN void ew_staged(const Record* r_v, uint32_t begin_v, uint32_t end_v, float
     i1 = (end - i0 < kStageRound) ? end : i0 + kStageRound;
     plan(i0, i1);
     issue(0);
-    staged_round<POL, IMPL, true, true>(c, c0, c1, g_lo, g_region, g_staged);
+    staged_round<POL, IMPL, true, true>(c, c0, c1, g_lo, g_region, g_staged, tid);
     __syncthreads();                  // the staged windows may be overwritten now
     stash(0);
     for (uint32_t b0 = kBatchBytes; b0 < most; b0 += kBatchBytes) { issue(b0); stash(b0); }
@@ -1057,7 +1065,7 @@ PATHFN void ew_staged(const Record* r_v, uint32_t begin_v, uint32_t end_v, float
   // stage: one after the other.
   for (;;) {
     take();
-    if (all_staged) staged_round<POL, IMPL, false, true>(c, c0, c1, g_lo, g_region, g_staged);
+    if (all_staged) staged_round<POL, IMPL, false, true>(c, c0, c1, g_lo, g_region, g_staged, tid);
     else slow_round();
     __syncthreads();                  // the scratch may be reused (by the next round, by the next chunk)
     if (i1 >= end) break;
@@ -1076,7 +1084,7 @@ PATHFN void ew_staged(const Record* r_v, uint32_t begin_v, uint32_t end_v, float
 // operand strides (0 on broadcast dims), per operand dtype.
 // ---------------------------------------------------------------------------
 template <int POL, int IMPL, bool INT>
-PATHFN void ew_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
+PATHFN void ew_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   const uint32_t begin = uni(begin_v), end = uni(end_v);
   using M = Mem<POL>;
@@ -1097,7 +1105,7 @@ PATHFN void ew_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
   dt[3] = uni(r->dtype[3]);
   char* po = (char*)uni_ptr(r->ptr[3]);
   const float alpha = r->alpha;
-  for (uint32_t i = begin + threadIdx.x; i < end; i += kThreads) {
+  for (uint32_t i = begin + tid; i < end; i += kThreads) {
     uint32_t rem = i, off[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int d = GPUOS_MAX_DIMS - 1; d >= 0; --d) {
@@ -1137,7 +1145,7 @@ PATHFN void ew_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
 // ---------------------------------------------------------------------------
 // DTI != DTO: the cast of a COPY.
 template <int POL, class OPER, int DTI, int DTO, bool SCALARS>
-PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
+PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   const uint32_t begin = uni(begin_v), end = uni(end_v);
   using EI = Elem<DTI>;
@@ -1175,7 +1183,7 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
   const uint32_t impl = uni(r->impl);
   // (row, vector) of this lane's first unit by division, then steps of 256 units with carries
   const bool deep = A * B > 1;
-  uint32_t v = begin + threadIdx.x;
+  uint32_t v = begin + tid;
   uint32_t row = v / VR, vc = v - row * VR, b = 0, a = 0;
   const uint32_t s_rows = kThreads / VR, s_vc = kThreads - s_rows * VR;
   uint32_t s_r = s_rows, s_b = 0, s_a = 0;
@@ -1189,7 +1197,7 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
     s_a = ts / B;
     s_b = ts - s_a * B;
   }
-  for (; v - threadIdx.x < end; ) {
+  for (; v - tid < end; ) {
     v4i q[3][U][NI];
     uint32_t w[3][U], oo[U];
     bool last[U];
@@ -1417,6 +1425,7 @@ struct RedArgs {       // what a row-reduction variant is called with (plain val
   uint32_t n;
   char* po;
   uint32_t odt, row_begin, row_end, max_span;
+  uint32_t tid;
   float* s_part;       // LDS
 };
 struct RedRun {        // the chunk's rows as a flat run of vectors
@@ -1435,13 +1444,14 @@ DEV RedRun red_run(const RedArgs& a) {
 template <int POL, int RIMPL, int DT, int RA, int UN>
 PATHFN void red_rows_wave(RedArgs a) {
   const RedRun run = red_run(a);
+  const uint32_t tid = a.tid;
   char* po = (char*)uni_ptr((uint64_t)a.po);
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end);
   using E = Elem<DT>;
   using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
   constexpr uint32_t V = E::V;
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t lane = tid & 63u, wave = tid >> 6;
   const uint32_t n = run.n;
   // wave w takes rows row_begin + w, + 4, + 8, ... ; RA of them at a time
   for (uint32_t row0 = row_begin + wave; row0 < row_end; row0 += 4 * RA) {
@@ -1493,6 +1503,7 @@ constexpr uint32_t kRedPartialRows = 64;   // rows of partial results the LDS sc
 template <int POL, int RIMPL, int DT>
 PATHFN void red_rows_quarter(RedArgs a) {
   const RedRun run = red_run(a);
+  const uint32_t tid = a.tid;
   char* po = (char*)uni_ptr((uint64_t)a.po);
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end);
   float* s_part = lds_arg(a.s_part);
@@ -1501,7 +1512,7 @@ PATHFN void red_rows_quarter(RedArgs a) {
   using M = Mem<POL>;
   constexpr uint32_t V = E::V;
   constexpr int UN = 8;
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t lane = tid & 63u, wave = tid >> 6;
   const uint32_t n = run.n;
   for (uint32_t row = row_begin; row < row_end; ++row) {
     const uint32_t lo = row * n + run.skew, hi = lo + n;
@@ -1540,6 +1551,7 @@ PATHFN void red_rows_quarter(RedArgs a) {
 template <int POL, int RIMPL, int DT>
 PATHFN void red_rows_short(RedArgs a) {
   const RedRun run = red_run(a);
+  const uint32_t tid = a.tid;
   char* po = (char*)uni_ptr((uint64_t)a.po);
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end), max_span = uni(a.max_span);
   using E = Elem<DT>;
@@ -1547,7 +1559,7 @@ PATHFN void red_rows_short(RedArgs a) {
   using M = Mem<POL>;
   constexpr uint32_t V = E::V;
   constexpr int UP = 8;
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t lane = tid & 63u, wave = tid >> 6;
   const uint32_t n = run.n;
   uint32_t P = 1;                                     // lanes per row: power of two >= the widest span
   while (P < max_span) P <<= 1;
@@ -1595,12 +1607,13 @@ PATHFN void red_rows_short(RedArgs a) {
 template <int POL, int RIMPL, int DT>
 PATHFN void red_rows_short_aligned(RedArgs a) {
   const RedRun run = red_run(a);
+  const uint32_t tid = a.tid;
   char* po = (char*)uni_ptr((uint64_t)a.po);
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end), vpr = uni(a.max_span);
   using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
   constexpr int UP = 8;
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t lane = tid & 63u, wave = tid >> 6;
   uint32_t P = 1;                                     // lanes per row: power of two >= vectors per row
   while (P < vpr) P <<= 1;
   const uint32_t rpw = 64u / P, sub = lane / P, j = lane & (P - 1u);
@@ -1633,7 +1646,7 @@ PATHFN void red_rows_short_aligned(RedArgs a) {
 }
 
 template <int POL, int RIMPL, int DT>
-DEV void red_contig(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_part) {
+DEV void red_contig(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_part, uint32_t tid) {
   using E = Elem<DT>;
   constexpr uint32_t V = E::V;
   const uint32_t n = uni(r->red_n);
@@ -1647,7 +1660,7 @@ DEV void red_contig(const Record* r, uint32_t row_begin, uint32_t row_end, float
   a.base = pin - a.lead * E::ES + (uint64_t)a.base_elem * E::ES;
   a.bytes = ((a.lead + row_end * n - a.base_elem) * E::ES + 15u) & ~15u;
   a.po = (char*)uni_ptr(r->ptr[3]);
-  a.odt = uni(r->dtype[3]); a.row_begin = row_begin; a.row_end = row_end; a.s_part = s_part;
+  a.odt = uni(r->dtype[3]); a.row_begin = row_begin; a.row_end = row_end; a.s_part = s_part; a.tid = tid;
   const bool whole = n % V == 0 && a.lead == 0;       // every row is whole vectors
   a.max_span = whole ? n / V : (n + V - 2) / V + 1;
   if (a.max_span <= 64u && whole) red_rows_short_aligned<POL, RIMPL, DT>(a);
@@ -1660,7 +1673,7 @@ DEV void red_contig(const Record* r, uint32_t row_begin, uint32_t row_end, float
 // PATH_RED_GENERIC: one wave per output row; outer index decomposed over the
 // coalesced outer dims; stride[0][5] walks the reduced dim.
 template <int POL, int RIMPL, bool INT>
-PATHFN void red_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
+PATHFN void red_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   const uint32_t row_begin = uni(begin_v), row_end = uni(end_v);
   using M = Mem<POL>;
@@ -1669,7 +1682,7 @@ PATHFN void red_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
   const char* pin = uni_ptr(r->ptr[0]);
   char* po = (char*)uni_ptr(r->ptr[3]);
   const uint32_t idt = uni(r->dtype[0]), odt = uni(r->dtype[3]);
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t lane = tid & 63u, wave = tid >> 6;
   for (uint32_t row = row_begin + wave; row < row_end; row += 4) {
     uint32_t rem = row, ioff = 0, ooff = 0;
 #pragma unroll
@@ -1779,7 +1792,7 @@ template <int POL, int DT, bool RAGGED> DEV void row_store(rsrc_t ro, uint32_t o
 // several passes, requests the next pass before it computes this one.  (Softmax rows are not: the registers for it
 // make the function save its caller's, a memory round trip per chunk.)
 template <int POL, int ROP, int DT, int KW, int UP, bool P32, bool RAGGED>
-DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v) {
+DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
   using E = Elem<DT>;
   using M = Mem<POL>;
   using RO = RowOp<ROP>;
@@ -1788,7 +1801,7 @@ DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, floa
   const uint32_t n = uni(r->red_n);
   const RowCut<V, RAGGED> cut(n);
   const uint32_t vpr = cut.vpr;
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t lane = tid & 63u, wave = tid >> 6;
   uint32_t P = 64;
   if (KW == 1) { P = 1; while (P < vpr) P <<= 1; }
   const uint32_t rpw = 64u / P, sub = lane / P, j = lane & (P - 1u);
@@ -1860,7 +1873,7 @@ DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, floa
   }
   static_assert(2 * 256 * 2 * 4 <= kScratchFloats, "two rows of 256 vectors of fp32 parameters under 16-bit elements");
   if (AHEAD) {
-    for (uint32_t vec = threadIdx.x; vec < vpr; vec += kThreads) {
+    for (uint32_t vec = tid; vec < vpr; vec += kThreads) {
       RowParam<POL, DT, P32> g, b;
       g.load(rs[0], cut.begin(vec));
       b.load(rs[1], cut.begin(vec));
@@ -1943,7 +1956,7 @@ DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, floa
 }
 
 template <int POL, int ROP>
-PATHFN void rowop_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
+PATHFN void rowop_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   const uint32_t row_begin = uni(begin_v), row_end = uni(end_v);
   using RO = RowOp<ROP>;
@@ -1959,7 +1972,7 @@ PATHFN void rowop_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
   }
   char* po = (char*)uni_ptr(r->ptr[3]);
   const uint32_t odt = uni(r->dtype[3]), slo = uni(r->stride[3][5]);
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t lane = tid & 63u, wave = tid >> 6;
   for (uint32_t row = row_begin + wave; row < row_end; row += 4) {
     uint32_t rem = row, off[3] = {0, 0, 0}, ooff = 0;
 #pragma unroll
@@ -2010,19 +2023,19 @@ PATHFN void rowop_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v) {
 // Sum / maximum over the workgroup, through four rotating LDS slots: one barrier per reduction.
 struct WgReduce {
   float* slots;                                        // 16 floats
-  uint32_t turn;
+  uint32_t turn, tid;
   DEV float* next() { float* p = slots + (turn & 3u) * 4u; ++turn; return p; }
   DEV float sum(float v) {
     v = bfly_sum(v, 64);
     float* slot = next();
-    if ((threadIdx.x & 63u) == 0) slot[threadIdx.x >> 6] = v;
+    if ((tid & 63u) == 0) slot[tid >> 6] = v;
     __syncthreads();
     return (slot[0] + slot[1]) + (slot[2] + slot[3]);
   }
   DEV float max(float v) {
     v = bfly_max(v, 64);
     float* slot = next();
-    if ((threadIdx.x & 63u) == 0) slot[threadIdx.x >> 6] = v;
+    if ((tid & 63u) == 0) slot[tid >> 6] = v;
     __syncthreads();
     return __builtin_fmaxf(__builtin_fmaxf(slot[0], slot[1]), __builtin_fmaxf(slot[2], slot[3]));
   }
@@ -2031,7 +2044,7 @@ struct WgReduce {
 // Rows longer than one wavefront's registers: the whole workgroup owns a row and holds it in
 // registers, 256 lanes x KW vectors, read once and written once.
 template <int POL, int ROP, int DT, int KW, bool P32, bool RAGGED>
-DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_red) {
+DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_red, uint32_t tid) {
   using E = Elem<DT>;
   using M = Mem<POL>;
   using RO = RowOp<ROP>;
@@ -2039,7 +2052,7 @@ DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* 
   constexpr bool MASK = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST;
   const uint32_t n = uni(r->red_n);
   const RowCut<V, RAGGED> cut(n);
-  const uint32_t vpr = cut.vpr, tid = threadIdx.x;
+  const uint32_t vpr = cut.vpr;
   const float alpha = r->alpha;
   const uint32_t nrows = row_end - row_begin;
   const uint32_t chunk_bytes = nrows * n * E::ES;
@@ -2071,7 +2084,7 @@ DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* 
       bk[k].load(rs[1], vec < vpr ? cut.begin(vec) : 0u);
     }
   }
-  WgReduce wg = {s_red, 0};
+  WgReduce wg = {s_red, 0, tid};
   for (uint32_t row = row_begin; row < row_end; ++row) {
     const uint32_t lr = row - row_begin;
     uint32_t mr = lr;
@@ -2150,7 +2163,7 @@ DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* 
 // vectors of a lane, eight of 16-bit elements) and in LDS (its first six) is not read again, the rest
 // comes from the memory-side cache.
 template <int POL, int ROP, int DT, bool RAGGED>
-DEV void softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v) {
+DEV void softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
   using E = Elem<DT>;
   using M = Mem<POL>;
   constexpr uint32_t V = E::V;
@@ -2159,7 +2172,7 @@ DEV void softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, flo
   constexpr uint32_t NL = MASK ? 0 : 6, NR = NB * U;                        // vectors per lane kept in LDS / in registers
   const uint32_t n = uni(r->red_n);
   const RowCut<V, RAGGED> cut(n);
-  const uint32_t vpr = cut.vpr, tid = threadIdx.x;
+  const uint32_t vpr = cut.vpr;
   const float alpha = r->alpha;
   const uint32_t chunk_bytes = (row_end - row_begin) * n * E::ES;
   const uint64_t chunk_off = (uint64_t)row_begin * n * E::ES;
@@ -2171,7 +2184,7 @@ DEV void softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, flo
     if (uni(r->okind[1]) == K_FULL) rm = make_rsrc(uni_ptr(r->ptr[1]) + chunk_off, chunk_bytes);
     else { period = uni(r->stride[1][0]); rm = make_rsrc(uni_ptr(r->ptr[1]), period * n * E::ES); }
   }
-  WgReduce wg = {s_v, 0};
+  WgReduce wg = {s_v, 0, tid};
   v4i* const kept = (v4i*)(s_v + 16) + tid;            // vector i of this lane lies at kept[i * kThreads]
   static_assert(16 + 6 * kThreads * 4 <= kScratchFloats, "six vectors per lane");
   const uint32_t T = (vpr + kThreads - 1) / kThreads;  // vectors per lane, the last partly filled
@@ -2258,20 +2271,20 @@ DEV void softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, flo
 
 // Layer norm rows too long for the workgroup's registers: three passes of vector loads over the row.
 template <int POL, int DT, bool P32, bool RAGGED>
-DEV void layernorm_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v) {
+DEV void layernorm_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
   using E = Elem<DT>;
   using M = Mem<POL>;
   constexpr uint32_t V = E::V;
   const uint32_t n = uni(r->red_n);
   const RowCut<V, RAGGED> cut(n);
-  const uint32_t vpr = cut.vpr, tid = threadIdx.x;
+  const uint32_t vpr = cut.vpr;
   const float alpha = r->alpha;
   const uint32_t chunk_bytes = (row_end - row_begin) * n * E::ES;
   const uint64_t chunk_off = (uint64_t)row_begin * n * E::ES;
   const rsrc_t rx = make_rsrc(uni_ptr(r->ptr[0]) + chunk_off, chunk_bytes);
   const rsrc_t ro = make_rsrc(uni_ptr(r->ptr[3]) + chunk_off, chunk_bytes);
   const rsrc_t rg = make_rsrc(uni_ptr(r->ptr[1]), n * (P32 ? 4u : (uint32_t)E::ES)), rb = make_rsrc(uni_ptr(r->ptr[2]), n * (P32 ? 4u : (uint32_t)E::ES));
-  WgReduce wg = {s_v, 0};
+  WgReduce wg = {s_v, 0, tid};
   for (uint32_t row = row_begin; row < row_end; ++row) {
     const uint32_t x0 = (row - row_begin) * n * E::ES;
     float sum = 0.0f;
@@ -2308,97 +2321,113 @@ DEV void layernorm_long(const Record* r, uint32_t row_begin, uint32_t row_end, f
 // call's way round each, and with forty sites more the compiler kept those in a register that it
 // stored to scratch memory and fetched from there at every decision, 1.5 us a unit.)
 template <int POL, int ROP, int DT, bool P32, bool RAGGED>
-DEV void rowop_short(const Record* r, uint32_t begin, uint32_t end, float* s) {      // <= 256 vectors
+DEV void rowop_short(const Record* r, uint32_t begin, uint32_t end, float* s, uint32_t tid) {      // <= 256 vectors
   const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
-  if (vpr <= 64u) rowop_fused<POL, ROP, DT, 1, 4, P32, RAGGED>(r, begin, end, s);
-  else if (vpr <= 128u) rowop_fused<POL, ROP, DT, 2, 2, P32, RAGGED>(r, begin, end, s);
-  else rowop_fused<POL, ROP, DT, 4, 1, P32, RAGGED>(r, begin, end, s);
+  if (vpr <= 64u) rowop_fused<POL, ROP, DT, 1, 4, P32, RAGGED>(r, begin, end, s, tid);
+  else if (vpr <= 128u) rowop_fused<POL, ROP, DT, 2, 2, P32, RAGGED>(r, begin, end, s, tid);
+  else rowop_fused<POL, ROP, DT, 4, 1, P32, RAGGED>(r, begin, end, s, tid);
 }
 template <int POL, int ROP, int DT, bool P32, bool RAGGED>
-DEV void rowop_mid(const Record* r, uint32_t begin, uint32_t end, float* s) {        // <= 1,024 vectors
+DEV void rowop_mid(const Record* r, uint32_t begin, uint32_t end, float* s, uint32_t tid) {        // <= 1,024 vectors
   const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
-  if (vpr <= 512u) rowop_wg<POL, ROP, DT, 2, P32, RAGGED>(r, begin, end, s);
-  else rowop_wg<POL, ROP, DT, 4, P32, RAGGED>(r, begin, end, s);
+  if (vpr <= 512u) rowop_wg<POL, ROP, DT, 2, P32, RAGGED>(r, begin, end, s, tid);
+  else rowop_wg<POL, ROP, DT, 4, P32, RAGGED>(r, begin, end, s, tid);
 }
 template <int POL, int ROP, int DT, bool P32, bool RAGGED>
-DEV void rowop_long(const Record* r, uint32_t begin, uint32_t end, float* s) {
+DEV void rowop_long(const Record* r, uint32_t begin, uint32_t end, float* s, uint32_t tid) {
   const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
   constexpr bool MASK = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST;       // (twice the registers per vector)
   if constexpr (!MASK || DT == GPUOS_F32) {
-    if (vpr <= 2048u) return rowop_wg<POL, ROP, DT, 8, P32, RAGGED>(r, begin, end, s);
+    if (vpr <= 2048u) return rowop_wg<POL, ROP, DT, 8, P32, RAGGED>(r, begin, end, s, tid);
   }
   if constexpr (!MASK && DT == GPUOS_F32) {
-    if (vpr <= 4096u) return rowop_wg<POL, ROP, DT, 16, P32, RAGGED>(r, begin, end, s);
+    if (vpr <= 4096u) return rowop_wg<POL, ROP, DT, 16, P32, RAGGED>(r, begin, end, s, tid);
   }
-  if constexpr (RowOp<ROP>::SOFTMAX) softmax_long<POL, ROP, DT, RAGGED>(r, begin, end, s);
-  else layernorm_long<POL, DT, P32, RAGGED>(r, begin, end, s);
+  if constexpr (RowOp<ROP>::SOFTMAX) softmax_long<POL, ROP, DT, RAGGED>(r, begin, end, s, tid);
+  else layernorm_long<POL, DT, P32, RAGGED>(r, begin, end, s, tid);
 }
 enum { kRowShort, kRowMid, kRowLong };
 template <int POL, int ROP, int DT, int LEN, bool RAGGED>
-PATHFN void rowop_dt(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v) {
+PATHFN void rowop_dt(const Record* r_v, uint32_t begin_v, uint32_t end_v, float* s_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   float* s = lds_arg(s_v);
   const uint32_t begin = uni(begin_v), end = uni(end_v);
   constexpr bool LN16 = ROP == GPUOS_IMPL_LAYERNORM_LAST && DT != GPUOS_F32;
   if (LN16 && uni(r->dtype[1]) == GPUOS_F32) {                       // fp32 gamma / beta under 16-bit x
-    if constexpr (LEN == kRowShort) rowop_short<POL, ROP, DT, LN16, RAGGED>(r, begin, end, s);
-    else if constexpr (LEN == kRowMid) rowop_mid<POL, ROP, DT, LN16, RAGGED>(r, begin, end, s);
-    else rowop_long<POL, ROP, DT, LN16, RAGGED>(r, begin, end, s);
+    if constexpr (LEN == kRowShort) rowop_short<POL, ROP, DT, LN16, RAGGED>(r, begin, end, s, tid);
+    else if constexpr (LEN == kRowMid) rowop_mid<POL, ROP, DT, LN16, RAGGED>(r, begin, end, s, tid);
+    else rowop_long<POL, ROP, DT, LN16, RAGGED>(r, begin, end, s, tid);
     return;
   }
-  if constexpr (LEN == kRowShort) rowop_short<POL, ROP, DT, false, RAGGED>(r, begin, end, s);
-  else if constexpr (LEN == kRowMid) rowop_mid<POL, ROP, DT, false, RAGGED>(r, begin, end, s);
-  else rowop_long<POL, ROP, DT, false, RAGGED>(r, begin, end, s);
+  if constexpr (LEN == kRowShort) rowop_short<POL, ROP, DT, false, RAGGED>(r, begin, end, s, tid);
+  else if constexpr (LEN == kRowMid) rowop_mid<POL, ROP, DT, false, RAGGED>(r, begin, end, s, tid);
+  else rowop_long<POL, ROP, DT, false, RAGGED>(r, begin, end, s, tid);
 }
 template <int POL, int ROP, int DT>
-DEV void rowop_other_dt(const Record* r, uint32_t begin, uint32_t end, float* s) {
+DEV void rowop_other_dt(const Record* r, uint32_t begin, uint32_t end, float* s, uint32_t tid) {
   const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
-  if (uni(r->path) == PATH_ROW_FUSED) rowop_dt<POL, ROP, DT, kRowLong, false>(r, begin, end, s);
-  else if (vpr <= 256u) rowop_dt<POL, ROP, DT, kRowShort, true>(r, begin, end, s);
-  else if (vpr <= 1024u) rowop_dt<POL, ROP, DT, kRowMid, true>(r, begin, end, s);
-  else rowop_dt<POL, ROP, DT, kRowLong, true>(r, begin, end, s);
+  if (uni(r->path) == PATH_ROW_FUSED) rowop_dt<POL, ROP, DT, kRowLong, false>(r, begin, end, s, tid);
+  else if (vpr <= 256u) rowop_dt<POL, ROP, DT, kRowShort, true>(r, begin, end, s, tid);
+  else if (vpr <= 1024u) rowop_dt<POL, ROP, DT, kRowMid, true>(r, begin, end, s, tid);
+  else rowop_dt<POL, ROP, DT, kRowLong, true>(r, begin, end, s, tid);
 }
 template <int POL, int ROP>
-DEV void rowop_other_op(const Record* r, uint32_t begin, uint32_t end, float* s) {
+DEV void rowop_other_op(const Record* r, uint32_t begin, uint32_t end, float* s, uint32_t tid) {
   const uint32_t dt = uni(r->dtype[3]);
-  if (dt == GPUOS_F32) rowop_other_dt<POL, ROP, GPUOS_F32>(r, begin, end, s);
-  else if (dt == GPUOS_F16) rowop_other_dt<POL, ROP, GPUOS_F16>(r, begin, end, s);
-  else rowop_other_dt<POL, ROP, GPUOS_BF16>(r, begin, end, s);
+  if (dt == GPUOS_F32) rowop_other_dt<POL, ROP, GPUOS_F32>(r, begin, end, s, tid);
+  else if (dt == GPUOS_F16) rowop_other_dt<POL, ROP, GPUOS_F16>(r, begin, end, s, tid);
+  else rowop_other_dt<POL, ROP, GPUOS_BF16>(r, begin, end, s, tid);
 }
 template <int POL>
-PATHFN void rowop_other(const Record* r_v, uint32_t impl_v, uint32_t begin_v, uint32_t end_v, float* s_v) {
+PATHFN void rowop_other(const Record* r_v, uint32_t impl_v, uint32_t begin_v, uint32_t end_v, float* s_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   float* s = lds_arg(s_v);
   const uint32_t impl = uni(impl_v), begin = uni(begin_v), end = uni(end_v);
-  if (impl == GPUOS_IMPL_SOFTMAX_LAST) rowop_other_op<POL, GPUOS_IMPL_SOFTMAX_LAST>(r, begin, end, s);
-  else if (impl == GPUOS_IMPL_MASKED_SOFTMAX_LAST) rowop_other_op<POL, GPUOS_IMPL_MASKED_SOFTMAX_LAST>(r, begin, end, s);
-  else rowop_other_op<POL, GPUOS_IMPL_LAYERNORM_LAST>(r, begin, end, s);
+  if (impl == GPUOS_IMPL_SOFTMAX_LAST) rowop_other_op<POL, GPUOS_IMPL_SOFTMAX_LAST>(r, begin, end, s, tid);
+  else if (impl == GPUOS_IMPL_MASKED_SOFTMAX_LAST) rowop_other_op<POL, GPUOS_IMPL_MASKED_SOFTMAX_LAST>(r, begin, end, s, tid);
+  else rowop_other_op<POL, GPUOS_IMPL_LAYERNORM_LAST>(r, begin, end, s, tid);
 }
 
+// What the choice of an executor asks of a record, in registers: the worker reads it with the rest of the
+// record's head, in one go (field by field it was two more LDS latencies in a row on every unit).
+struct RecHead {
+  v4i op, dims;                                        // bytes 0-15 and 32-47 of the record
+  static DEV RecHead of(const Record* r) { const v4i* h = (const v4i*)r; return {h[0], h[2]}; }
+  DEV uint32_t path() const { return (uni((uint32_t)op[0]) >> 16) & 0xffu; }
+  DEV uint32_t dtype_in0() const { return (uni((uint32_t)op[1]) >> 8) & 0xffu; }
+  DEV uint32_t dtype_out() const { return uni((uint32_t)op[2]) & 0xffu; }
+  DEV uint32_t rflags() const { return (uni((uint32_t)op[2]) >> 8) & 0xffu; }
+  DEV uint32_t chunk() const { return uni((uint32_t)dims[0]); }
+  DEV uint32_t numel() const { return uni((uint32_t)dims[1]); }
+  DEV uint32_t red_n() const { return uni((uint32_t)dims[2]); }
+};
+static_assert(__builtin_offsetof(Record, path) == 2 && __builtin_offsetof(Record, dtype) == 5 && __builtin_offsetof(Record, rflags) == 9 &&
+              __builtin_offsetof(Record, chunk) == 32 && __builtin_offsetof(Record, numel) == 36 && __builtin_offsetof(Record, red_n) == 40, "the words of RecHead");
+
 // the rows that rowop_other takes
-DEV bool rowop_is_other(const Record* r) {
-  const uint32_t path = uni(r->path);
-  return path == PATH_ROW_RAGGED || (path == PATH_ROW_FUSED && uni(r->red_n) > (uni(r->dtype[3]) == GPUOS_F32 ? 4096u : 8192u));
+DEV bool rowop_is_other(const RecHead& h) {
+  const uint32_t path = h.path();
+  return path == PATH_ROW_RAGGED || (path == PATH_ROW_FUSED && h.red_n() > (h.dtype_out() == GPUOS_F32 ? 4096u : 8192u));
 }
 template <int POL, int ROP>
-DEV void run_rowop(const Record* r, uint32_t chunk, float* s_red) {
-  const uint32_t per = uni(r->chunk), rows = uni(r->numel);
+DEV void run_rowop(const Record* r, const RecHead& h, uint32_t chunk, float* s_red, uint32_t tid) {
+  const uint32_t per = h.chunk(), rows = h.numel();
   const uint32_t begin = chunk * per;
   const uint32_t end = (rows - begin < per) ? rows : begin + per;
-  if (uni(r->path) == PATH_ROW_FUSED) {
-    const uint32_t dt = uni(r->dtype[3]);
-    const bool wide = uni(r->red_n) * (dt == GPUOS_F32 ? 4u : 2u) > 256u * 16u;     // more than 256 vectors per row
+  if (h.path() == PATH_ROW_FUSED) {
+    const uint32_t dt = h.dtype_out();
+    const bool wide = h.red_n() * (dt == GPUOS_F32 ? 4u : 2u) > 256u * 16u;     // more than 256 vectors per row
     if (!wide) {
-      if (dt == GPUOS_F32) rowop_dt<POL, ROP, GPUOS_F32, kRowShort, false>(r, begin, end, s_red);
-      else if (dt == GPUOS_F16) rowop_dt<POL, ROP, GPUOS_F16, kRowShort, false>(r, begin, end, s_red);
-      else rowop_dt<POL, ROP, GPUOS_BF16, kRowShort, false>(r, begin, end, s_red);
+      if (dt == GPUOS_F32) rowop_dt<POL, ROP, GPUOS_F32, kRowShort, false>(r, begin, end, s_red, tid);
+      else if (dt == GPUOS_F16) rowop_dt<POL, ROP, GPUOS_F16, kRowShort, false>(r, begin, end, s_red, tid);
+      else rowop_dt<POL, ROP, GPUOS_BF16, kRowShort, false>(r, begin, end, s_red, tid);
     } else {
-      if (dt == GPUOS_F32) rowop_dt<POL, ROP, GPUOS_F32, kRowMid, false>(r, begin, end, s_red);
-      else if (dt == GPUOS_F16) rowop_dt<POL, ROP, GPUOS_F16, kRowMid, false>(r, begin, end, s_red);
-      else rowop_dt<POL, ROP, GPUOS_BF16, kRowMid, false>(r, begin, end, s_red);
+      if (dt == GPUOS_F32) rowop_dt<POL, ROP, GPUOS_F32, kRowMid, false>(r, begin, end, s_red, tid);
+      else if (dt == GPUOS_F16) rowop_dt<POL, ROP, GPUOS_F16, kRowMid, false>(r, begin, end, s_red, tid);
+      else rowop_dt<POL, ROP, GPUOS_BF16, kRowMid, false>(r, begin, end, s_red, tid);
     }
   } else {
-    rowop_generic<POL, ROP>(r, begin, end);
+    rowop_generic<POL, ROP>(r, begin, end, tid);
   }
 }
 
@@ -2419,16 +2448,16 @@ template <> struct OperOf<kClsErf> { typedef FixedOp<GPUOS_IMPL_GELU_ERF> T; };
 template <> struct OperOf<kClsTanh> { typedef FixedOp<GPUOS_IMPL_GELU_TANH> T; };
 static_assert(GPUOS_F32 == 0 && GPUOS_F16 == 1 && GPUOS_BF16 == 2, "the float dtypes count the members of a group");
 template <int POL> struct RowsExec {
-  template <int K> static DEV void run(const Record* r, uint32_t begin, uint32_t end) {
-    if constexpr (K < kRowsScalar) ew_rows<POL, typename OperOf<K / 3>::T, K % 3, K % 3, false>(r, begin, end);
-    else if constexpr (K < kRowsCast) ew_rows<POL, ByArity<2 + (K - kRowsScalar) / 3>, (K - kRowsScalar) % 3, (K - kRowsScalar) % 3, true>(r, begin, end);
+  template <int K> static DEV void run(const Record* r, uint32_t begin, uint32_t end, uint32_t tid) {
+    if constexpr (K < kRowsScalar) ew_rows<POL, typename OperOf<K / 3>::T, K % 3, K % 3, false>(r, begin, end, tid);
+    else if constexpr (K < kRowsCast) ew_rows<POL, ByArity<2 + (K - kRowsScalar) / 3>, (K - kRowsScalar) % 3, (K - kRowsScalar) % 3, true>(r, begin, end, tid);
     else if constexpr (K < kRowsInt) {
       // (from, to): 0 1, 0 2, 1 0, 1 2, 2 0, 2 1
       constexpr int FROM = (K - kRowsCast) / 2, TO = (K - kRowsCast) % 2 + ((K - kRowsCast) % 2 >= FROM ? 1 : 0);
-      ew_rows<POL, ByArity<1>, FROM, TO, false>(r, begin, end);
+      ew_rows<POL, ByArity<1>, FROM, TO, false>(r, begin, end, tid);
     }
-    else if constexpr (K < kRowsCount - 1) ew_rows<POL, ByArity<K - kRowsInt + 1>, GPUOS_I32, GPUOS_I32, false>(r, begin, end);
-    else ew_rows<POL, ByArity<2>, GPUOS_I32, GPUOS_I32, true>(r, begin, end);
+    else if constexpr (K < kRowsCount - 1) ew_rows<POL, ByArity<K - kRowsInt + 1>, GPUOS_I32, GPUOS_I32, false>(r, begin, end, tid);
+    else ew_rows<POL, ByArity<2>, GPUOS_I32, GPUOS_I32, true>(r, begin, end, tid);
   }
 };
 
@@ -2458,135 +2487,135 @@ DEV void rows_elements(const Record* r, uint32_t& begin, uint32_t& end) {
 }
 
 template <int POL, int IMPL>
-DEV void run_elementwise(const Record* r, uint32_t chunk, float* s_scratch) {
-  const uint32_t per = uni(r->chunk), numel = uni(r->numel);
+DEV void run_elementwise(const Record* r, const RecHead& h, uint32_t chunk, float* s_scratch, uint32_t tid) {
+  const uint32_t per = h.chunk(), numel = h.numel();
   uint32_t begin = chunk * per, end = (numel - begin < per) ? numel : begin + per;
-  const uint32_t path = uni(r->path), dt = uni(r->dtype[3]);
+  const uint32_t path = h.path(), dt = h.dtype_out();
   constexpr bool int_ok = IMPL == GPUOS_IMPL_ADD || IMPL == GPUOS_IMPL_SUB || IMPL == GPUOS_IMPL_MUL || IMPL == GPUOS_IMPL_COPY;
-  if (r->rflags & RF_INT) {
+  if (h.rflags() & RF_INT) {
     if (int_ok) {
-      if (path == PATH_CONTIG) ew_contig<POL, int_ok ? IMPL : GPUOS_IMPL_COPY, GPUOS_I32>(r, begin, end);
-      else ew_generic<POL, int_ok ? IMPL : GPUOS_IMPL_COPY, true>(r, begin, end);
+      if (path == PATH_CONTIG) ew_contig<POL, int_ok ? IMPL : GPUOS_IMPL_COPY, GPUOS_I32>(r, begin, end, tid);
+      else ew_generic<POL, int_ok ? IMPL : GPUOS_IMPL_COPY, true>(r, begin, end, tid);
     }
     return;
   }
   if (path == PATH_CONTIG) {
-    if (dt == GPUOS_F32) ew_contig<POL, IMPL, GPUOS_F32>(r, begin, end);
-    else if (dt == GPUOS_F16) ew_contig<POL, IMPL, GPUOS_F16>(r, begin, end);
-    else ew_contig<POL, IMPL, GPUOS_BF16>(r, begin, end);
+    if (dt == GPUOS_F32) ew_contig<POL, IMPL, GPUOS_F32>(r, begin, end, tid);
+    else if (dt == GPUOS_F16) ew_contig<POL, IMPL, GPUOS_F16>(r, begin, end, tid);
+    else ew_contig<POL, IMPL, GPUOS_BF16>(r, begin, end, tid);
   } else if (path == PATH_ROW2D && Op<IMPL>::N >= 2) {
     constexpr int I2 = Op<IMPL>::N >= 2 ? IMPL : GPUOS_IMPL_ADD;
     const uint32_t k0 = uni(r->okind[0]), k1 = uni(r->okind[1]);
     const int spec = (Op<I2>::N == 2 && k0 == K_FULL) ? (k1 == K_ROWSCALAR ? 1 : (k1 == K_ROWVEC ? 2 : 0)) : 0;
     if (dt == GPUOS_F32) {
-      if (spec == 1) ew_row2d<POL, I2, GPUOS_F32, K_ROWSCALAR>(r, begin, end, s_scratch);
-      else if (spec == 2) ew_row2d<POL, I2, GPUOS_F32, K_ROWVEC>(r, begin, end, s_scratch);
-      else ew_row2d<POL, I2, GPUOS_F32, -1>(r, begin, end, s_scratch);
+      if (spec == 1) ew_row2d<POL, I2, GPUOS_F32, K_ROWSCALAR>(r, begin, end, s_scratch, tid);
+      else if (spec == 2) ew_row2d<POL, I2, GPUOS_F32, K_ROWVEC>(r, begin, end, s_scratch, tid);
+      else ew_row2d<POL, I2, GPUOS_F32, -1>(r, begin, end, s_scratch, tid);
     } else if (dt == GPUOS_F16) {
-      if (spec == 1) ew_row2d<POL, I2, GPUOS_F16, K_ROWSCALAR>(r, begin, end, s_scratch);
-      else if (spec == 2) ew_row2d<POL, I2, GPUOS_F16, K_ROWVEC>(r, begin, end, s_scratch);
-      else ew_row2d<POL, I2, GPUOS_F16, -1>(r, begin, end, s_scratch);
+      if (spec == 1) ew_row2d<POL, I2, GPUOS_F16, K_ROWSCALAR>(r, begin, end, s_scratch, tid);
+      else if (spec == 2) ew_row2d<POL, I2, GPUOS_F16, K_ROWVEC>(r, begin, end, s_scratch, tid);
+      else ew_row2d<POL, I2, GPUOS_F16, -1>(r, begin, end, s_scratch, tid);
     } else {
-      if (spec == 1) ew_row2d<POL, I2, GPUOS_BF16, K_ROWSCALAR>(r, begin, end, s_scratch);
-      else if (spec == 2) ew_row2d<POL, I2, GPUOS_BF16, K_ROWVEC>(r, begin, end, s_scratch);
-      else ew_row2d<POL, I2, GPUOS_BF16, -1>(r, begin, end, s_scratch);
+      if (spec == 1) ew_row2d<POL, I2, GPUOS_BF16, K_ROWSCALAR>(r, begin, end, s_scratch, tid);
+      else if (spec == 2) ew_row2d<POL, I2, GPUOS_BF16, K_ROWVEC>(r, begin, end, s_scratch, tid);
+      else ew_row2d<POL, I2, GPUOS_BF16, -1>(r, begin, end, s_scratch, tid);
     }
   } else if (path == PATH_TILE2D) {
-    ew_tile2d<POL, IMPL>(r, begin, end, s_scratch);      // begin / end count tiles here
+    ew_tile2d<POL, IMPL>(r, begin, end, s_scratch, tid);      // begin / end count tiles here
   } else if (path == PATH_STAGED) {
-    ew_staged<POL, IMPL>(r, begin, end, s_scratch);
+    ew_staged<POL, IMPL>(r, begin, end, s_scratch, tid);
   } else {
     if constexpr (IMPL >= kImplProg1) {                  // programs, interpreted and native; built-in operators: RowsExec
       const uint32_t k0 = uni((uint32_t)r->okind[0] | (uint32_t)r->okind[1] | (uint32_t)r->okind[2]);
       if (path == PATH_ROWS && uni(r->vdtype) == dt && (k0 == 0 || Op<IMPL>::N >= 2)) {
         constexpr bool S = Op<IMPL>::N >= 2;
-        if (dt == GPUOS_F32) { if (k0) ew_rows<POL, FixedOp<IMPL>, GPUOS_F32, GPUOS_F32, S>(r, begin, end); else ew_rows<POL, FixedOp<IMPL>, GPUOS_F32, GPUOS_F32, false>(r, begin, end); }
-        else if (dt == GPUOS_F16) { if (k0) ew_rows<POL, FixedOp<IMPL>, GPUOS_F16, GPUOS_F16, S>(r, begin, end); else ew_rows<POL, FixedOp<IMPL>, GPUOS_F16, GPUOS_F16, false>(r, begin, end); }
-        else { if (k0) ew_rows<POL, FixedOp<IMPL>, GPUOS_BF16, GPUOS_BF16, S>(r, begin, end); else ew_rows<POL, FixedOp<IMPL>, GPUOS_BF16, GPUOS_BF16, false>(r, begin, end); }
+        if (dt == GPUOS_F32) { if (k0) ew_rows<POL, FixedOp<IMPL>, GPUOS_F32, GPUOS_F32, S>(r, begin, end, tid); else ew_rows<POL, FixedOp<IMPL>, GPUOS_F32, GPUOS_F32, false>(r, begin, end, tid); }
+        else if (dt == GPUOS_F16) { if (k0) ew_rows<POL, FixedOp<IMPL>, GPUOS_F16, GPUOS_F16, S>(r, begin, end, tid); else ew_rows<POL, FixedOp<IMPL>, GPUOS_F16, GPUOS_F16, false>(r, begin, end, tid); }
+        else { if (k0) ew_rows<POL, FixedOp<IMPL>, GPUOS_BF16, GPUOS_BF16, S>(r, begin, end, tid); else ew_rows<POL, FixedOp<IMPL>, GPUOS_BF16, GPUOS_BF16, false>(r, begin, end, tid); }
         return;
       }
     }
     if (path == PATH_ROWS) rows_elements(r, begin, end);
-    ew_generic<POL, IMPL, false>(r, begin, end);
+    ew_generic<POL, IMPL, false>(r, begin, end, tid);
   }
 }
 
 template <int POL, int RIMPL>
-DEV void run_reduction(const Record* r, uint32_t chunk, float* s_red) {
-  const uint32_t per = uni(r->chunk), rows = uni(r->numel);
+DEV void run_reduction(const Record* r, const RecHead& h, uint32_t chunk, float* s_red, uint32_t tid) {
+  const uint32_t per = h.chunk(), rows = h.numel();
   const uint32_t begin = chunk * per;
   const uint32_t end = (rows - begin < per) ? rows : begin + per;
-  const uint32_t path = uni(r->path), dt = uni(r->dtype[0]);
-  if (r->rflags & RF_INT) {
-    if (path == PATH_RED_CONTIG) red_contig<POL, RIMPL, GPUOS_I32>(r, begin, end, s_red);
-    else red_generic<POL, RIMPL, true>(r, begin, end);
+  const uint32_t path = h.path(), dt = h.dtype_in0();
+  if (h.rflags() & RF_INT) {
+    if (path == PATH_RED_CONTIG) red_contig<POL, RIMPL, GPUOS_I32>(r, begin, end, s_red, tid);
+    else red_generic<POL, RIMPL, true>(r, begin, end, tid);
     return;
   }
   if (path == PATH_RED_CONTIG) {
-    if (dt == GPUOS_F32) red_contig<POL, RIMPL, GPUOS_F32>(r, begin, end, s_red);
-    else if (dt == GPUOS_F16) red_contig<POL, RIMPL, GPUOS_F16>(r, begin, end, s_red);
-    else red_contig<POL, RIMPL, GPUOS_BF16>(r, begin, end, s_red);
+    if (dt == GPUOS_F32) red_contig<POL, RIMPL, GPUOS_F32>(r, begin, end, s_red, tid);
+    else if (dt == GPUOS_F16) red_contig<POL, RIMPL, GPUOS_F16>(r, begin, end, s_red, tid);
+    else red_contig<POL, RIMPL, GPUOS_BF16>(r, begin, end, s_red, tid);
   } else {
-    red_generic<POL, RIMPL, false>(r, begin, end);
+    red_generic<POL, RIMPL, false>(r, begin, end, tid);
   }
 }
 
 // A task whose operator is a program: fetch the program into LDS (17 lanes x 16 bytes), then run
 // the ordinary elementwise paths with the interpreter as their functor.
 template <int POL>
-DEV int32_t exec_program(const Record* r, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage* progs) {
+DEV int32_t exec_program(const Record* r, const RecHead& h, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage* progs, uint32_t tid) {
   const uint32_t k = impl - GPUOS_IMPL_PROGRAM_BASE;
   if (progs == nullptr || k >= GPUOS_MAX_PROGRAMS) return GPUOS_E_BADOP;
   const rsrc_t rp = make_rsrc(progs + k, (uint32_t)sizeof(ProgramImage));
-  if (threadIdx.x < sizeof(ProgramImage) / 16) ((v4i*)&g_prog)[threadIdx.x] = Mem<POL_COHERENT>::ld16(rp, threadIdx.x * 16u);
+  if (tid < sizeof(ProgramImage) / 16) ((v4i*)&g_prog)[tid] = Mem<POL_COHERENT>::ld16(rp, tid * 16u);
   __syncthreads();
   int32_t status = GPUOS_OK;
   const uint32_t n_in = uni(g_prog.n_inputs), n_instr = uni(g_prog.n_instr);
   if (uni(g_prog.ready) != kProgramReady || n_instr < 1 || n_instr > GPUOS_PROGRAM_MAX_INSTR || n_in != uni(r->n_inputs))
     status = GPUOS_E_INVAL;                            // never defined (or not what the task was packed for)
-  else if (n_in == 1) run_elementwise<POL, kImplProg1>(r, chunk, s_red);
-  else if (n_in == 2) run_elementwise<POL, kImplProg2>(r, chunk, s_red);
-  else run_elementwise<POL, kImplProg3>(r, chunk, s_red);
+  else if (n_in == 1) run_elementwise<POL, kImplProg1>(r, h, chunk, s_red, tid);
+  else if (n_in == 2) run_elementwise<POL, kImplProg2>(r, h, chunk, s_red, tid);
+  else run_elementwise<POL, kImplProg3>(r, h, chunk, s_red, tid);
   __syncthreads();                                     // the next chunk may bring another program
   return status;
 }
 
 // returns the task status contribution of this chunk (0 or an error)
 template <int POL>
-DEV int32_t exec_chunk(const Record* r, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage* progs) {
-  if (uni(r->path) == PATH_NOP) return impl == GPUOS_IMPL_FAIL ? GPUOS_E_BADOP : GPUOS_OK;
-  if (impl >= GPUOS_IMPL_PROGRAM_BASE) return exec_program<POL>(r, impl, chunk, s_red, progs);
+DEV int32_t exec_chunk(const Record* r, const RecHead& h, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage* progs, uint32_t tid) {
+  if (h.path() == PATH_NOP) return impl == GPUOS_IMPL_FAIL ? GPUOS_E_BADOP : GPUOS_OK;
+  if (impl >= GPUOS_IMPL_PROGRAM_BASE) return exec_program<POL>(r, h, impl, chunk, s_red, progs, tid);
   // (beside the switch, not a case in every implementation's paths: see ByArity)
-  if (impl >= GPUOS_IMPL_SOFTMAX_LAST && impl <= GPUOS_IMPL_LAYERNORM_LAST && rowop_is_other(r)) {
-    const uint32_t per = uni(r->chunk), rows = uni(r->numel), begin = chunk * per;
-    rowop_other<POL>(r, impl, begin, (rows - begin < per) ? rows : begin + per, s_red);
+  if (impl >= GPUOS_IMPL_SOFTMAX_LAST && impl <= GPUOS_IMPL_LAYERNORM_LAST && rowop_is_other(h)) {
+    const uint32_t per = h.chunk(), rows = h.numel(), begin = chunk * per;
+    rowop_other<POL>(r, impl, begin, (rows - begin < per) ? rows : begin + per, s_red, tid);
     return GPUOS_OK;
   }
-  const uint32_t k = uni(r->path) == PATH_ROWS ? rows_variant(r, impl) : (uint32_t)kRowsCount;
+  const uint32_t k = h.path() == PATH_ROWS ? rows_variant(r, impl) : (uint32_t)kRowsCount;
   if (k < (uint32_t)kRowsCount) {
-    const uint32_t per = uni(r->chunk), numel = uni(r->numel), begin = chunk * per;
-    pick<0, kRowsCount, RowsExec<POL>>(k, r, begin, (numel - begin < per) ? numel : begin + per);
+    const uint32_t per = h.chunk(), numel = h.numel(), begin = chunk * per;
+    pick<0, kRowsCount, RowsExec<POL>>(k, r, begin, (numel - begin < per) ? numel : begin + per, tid);
     return GPUOS_OK;
   }
   switch (impl) {
-    case GPUOS_IMPL_ADD: run_elementwise<POL, GPUOS_IMPL_ADD>(r, chunk, s_red); break;
-    case GPUOS_IMPL_SUB: run_elementwise<POL, GPUOS_IMPL_SUB>(r, chunk, s_red); break;
-    case GPUOS_IMPL_MUL: run_elementwise<POL, GPUOS_IMPL_MUL>(r, chunk, s_red); break;
-    case GPUOS_IMPL_DIV: run_elementwise<POL, GPUOS_IMPL_DIV>(r, chunk, s_red); break;
-    case GPUOS_IMPL_RELU: run_elementwise<POL, GPUOS_IMPL_RELU>(r, chunk, s_red); break;
-    case GPUOS_IMPL_EXP: run_elementwise<POL, GPUOS_IMPL_EXP>(r, chunk, s_red); break;
-    case GPUOS_IMPL_GELU_ERF: run_elementwise<POL, GPUOS_IMPL_GELU_ERF>(r, chunk, s_red); break;
-    case GPUOS_IMPL_GELU_TANH: run_elementwise<POL, GPUOS_IMPL_GELU_TANH>(r, chunk, s_red); break;
-    case GPUOS_IMPL_SCALE: run_elementwise<POL, GPUOS_IMPL_SCALE>(r, chunk, s_red); break;
-    case GPUOS_IMPL_FMA: run_elementwise<POL, GPUOS_IMPL_FMA>(r, chunk, s_red); break;
-    case GPUOS_IMPL_SUB_EXP: run_elementwise<POL, GPUOS_IMPL_SUB_EXP>(r, chunk, s_red); break;
-    case GPUOS_IMPL_COPY: run_elementwise<POL, GPUOS_IMPL_COPY>(r, chunk, s_red); break;
-    case GPUOS_IMPL_SUM_LAST: run_reduction<POL, GPUOS_IMPL_SUM_LAST>(r, chunk, s_red); break;
-    case GPUOS_IMPL_MAX_LAST: run_reduction<POL, GPUOS_IMPL_MAX_LAST>(r, chunk, s_red); break;
-    case GPUOS_IMPL_MIN_LAST: run_reduction<POL, GPUOS_IMPL_MIN_LAST>(r, chunk, s_red); break;
-    case GPUOS_IMPL_SOFTMAX_LAST: run_rowop<POL, GPUOS_IMPL_SOFTMAX_LAST>(r, chunk, s_red); break;
-    case GPUOS_IMPL_MASKED_SOFTMAX_LAST: run_rowop<POL, GPUOS_IMPL_MASKED_SOFTMAX_LAST>(r, chunk, s_red); break;
-    case GPUOS_IMPL_LAYERNORM_LAST: run_rowop<POL, GPUOS_IMPL_LAYERNORM_LAST>(r, chunk, s_red); break;
+    case GPUOS_IMPL_ADD: run_elementwise<POL, GPUOS_IMPL_ADD>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_SUB: run_elementwise<POL, GPUOS_IMPL_SUB>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_MUL: run_elementwise<POL, GPUOS_IMPL_MUL>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_DIV: run_elementwise<POL, GPUOS_IMPL_DIV>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_RELU: run_elementwise<POL, GPUOS_IMPL_RELU>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_EXP: run_elementwise<POL, GPUOS_IMPL_EXP>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_GELU_ERF: run_elementwise<POL, GPUOS_IMPL_GELU_ERF>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_GELU_TANH: run_elementwise<POL, GPUOS_IMPL_GELU_TANH>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_SCALE: run_elementwise<POL, GPUOS_IMPL_SCALE>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_FMA: run_elementwise<POL, GPUOS_IMPL_FMA>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_SUB_EXP: run_elementwise<POL, GPUOS_IMPL_SUB_EXP>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_COPY: run_elementwise<POL, GPUOS_IMPL_COPY>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_SUM_LAST: run_reduction<POL, GPUOS_IMPL_SUM_LAST>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_MAX_LAST: run_reduction<POL, GPUOS_IMPL_MAX_LAST>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_MIN_LAST: run_reduction<POL, GPUOS_IMPL_MIN_LAST>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_SOFTMAX_LAST: run_rowop<POL, GPUOS_IMPL_SOFTMAX_LAST>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_MASKED_SOFTMAX_LAST: run_rowop<POL, GPUOS_IMPL_MASKED_SOFTMAX_LAST>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_LAYERNORM_LAST: run_rowop<POL, GPUOS_IMPL_LAYERNORM_LAST>(r, h, chunk, s_red, tid); break;
     case GPUOS_IMPL_FAIL: return GPUOS_E_BADOP;       // kill-switch stub: fail fast, write nothing
     default: return GPUOS_E_BADOP;
   }
@@ -2615,8 +2644,8 @@ DEV uint32_t record_piece_sum(const v4i& q, uint32_t part) {
 }
 
 struct BuiltinExec {                // what the library's own workers execute a chunk with
-  static DEV int32_t run(const Record* r, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage* progs) {
-    return exec_chunk<POL_COHERENT>(r, impl, chunk, s_red, progs);
+  static DEV int32_t run(const Record* r, const RecHead& h, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage* progs, uint32_t tid) {
+    return exec_chunk<POL_COHERENT>(r, h, impl, chunk, s_red, progs, tid);
   }
 };
 
@@ -2638,30 +2667,36 @@ constexpr uint64_t kStopGraceTicks = 10000000ull;   // 100 ms (100 MHz clock): h
 constexpr uint32_t kStash = 8;
 constexpr uint32_t kStashFull = (1u << kStash) - 1u;
 enum : uint32_t { kActRun = 0, kActFetch = 1, kActExit = 2 };
+constexpr uint32_t kHaveClaim = 1u << kStash, kDraining = 2u << kStash;
 
 struct WorkShared {
   Record rec[kStash];              // descriptors held
   uint64_t unit[kStash];           // their work-unit entries
   uint64_t entry[kStash];          // the operator-table slot each one claimed
   uint64_t since[kStash];          // when each began to wait (device clock)
-  uint32_t action, slot;           // the first wavefront's decision: run the unit in descriptor slot `slot`, fetch
-                                   // the newly claimed unit's descriptor into it, or leave
-  int32_t dep_status;              // 0, or the status a task whose dependency wait ran out completes with
+  // The first wavefront's decision, read by all: what to do (kAct*: run the unit in descriptor slot `slot`,
+  // fetch the newly claimed unit's descriptor into it, or leave), the slot (<< 8) and whether units
+  // were held meanwhile (<< 16); the status of a task whose dependency wait ran out, or 0; the unit.
+  alignas(16) uint32_t dec[4];
+  // The first wavefront's state from one unit to the next: descriptor slots whose units wait (a bit each),
+  // kHaveClaim (a unit number is claimed and its entry has not arrived yet), kDraining (the stop flag
+  // was seen: claim nothing more, finish what is held, leave); polls since the claim; the claimed number.
+  // Here and not in registers, most of which the call of an executor does not preserve, and in one
+  // vector each: a unit costs one read and one write of either.
+  alignas(16) uint32_t state[4];
+  // where a task's completion goes (the kernel's arguments, which a call does not leave in registers)
+  SlotState* st;
+  uint64_t* hcomp;
+  uint64_t* done_count;
+  uint64_t cap_shift;
   uint32_t rec_sum;                // weighted check sum of the record as fetched
-  // The first wavefront's state from one unit to the next, and the workgroup's counters (ST_WORK_UNITS
-  // on): here and not in registers, most of which the call of an executor does not preserve.  (The
-  // compiler spilled them to scratch memory and to lanes round the executors' call sites, a quarter
-  // of a microsecond per unit, more or less with every change of the executors.)
-  uint32_t waiting;                // bit k: descriptor slot k holds a unit that waits for a dependency
-  uint32_t have_claim;             // a unit number is claimed and its entry has not arrived yet
-  uint32_t draining;               // the stop flag was seen: claim nothing more, finish what is held, leave
-  uint32_t polls, yield_every;
-  uint64_t g;                      // the claimed unit number
-  uint64_t n_units;
-  uint32_t held_any;
+  uint64_t n_units;                // (ST_WORK_UNITS, and the counters after it)
   uint64_t ticks[ST_WORK_TICKS_TOTAL - ST_WORK_TICKS_WAIT];
   alignas(16) float red[kScratchFloats];   // (16-byte LDS vectors are written into it)
 };
+
+// A pointer known to address device or host memory, read from LDS: accessed as such, not with flat instructions.
+template <class T> DEV T* global_ptr(T* p) { return (T*)(__attribute__((address_space(1))) T*)p; }
 
 DEV uint64_t uni64(uint64_t v) {
   return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)v);
@@ -2673,19 +2708,18 @@ DEV uint64_t lane64(uint64_t v, uint32_t lane) {     // `lane` the same in every
 
 // First wavefront: fetch the descriptor that work unit `unit` names (16 lanes x 16 bytes) and the
 // operator-table slot it claimed into descriptor slot f, with the record's weighted check sum.
-DEV void fetch_descriptor(const WorkerArgs& a, WorkShared* s, rsrc_t rd, uint64_t unit, uint32_t f) {
-  const uint32_t tid = threadIdx.x;
+DEV void fetch_descriptor(const WorkerArgs& a, WorkShared* s, rsrc_t rd, uint64_t unit, uint32_t f, uint32_t lane) {
   const uint32_t slot = (uint32_t)((unit >> 20) & 0xffffu);
   const uint32_t op = (uint32_t)((unit >> 36) & 0xffu), sel = (uint32_t)((unit >> 44) & 1u);
   const bool op_valid = ((unit >> 45) & 1u) != 0;
   v4i q = {0, 0, 0, 0};
   uint64_t ent = 0;
-  if (tid < 16) q = Mem<POL_COHERENT>::ld16(rd, slot * (uint32_t)sizeof(Record) + tid * 16u);
-  if (tid == 16 && op_valid) ent = __hip_atomic_load(&a.dtable[op].slot[sel], __ATOMIC_RELAXED, SC_SYSTEM);
-  const uint32_t x = record_piece_sum(q, tid & 15u);
-  if (tid < 16) ((v4i*)&s->rec[f])[tid] = q;
-  if (tid == 16) s->entry[f] = ent;
-  if (tid == 0) s->rec_sum = x;
+  if (lane < 16) q = Mem<POL_COHERENT>::ld16(rd, slot * (uint32_t)sizeof(Record) + lane * 16u);
+  if (lane == 16 && op_valid) ent = __hip_atomic_load(&a.dtable[op].slot[sel], __ATOMIC_RELAXED, SC_SYSTEM);
+  const uint32_t x = record_piece_sum(q, lane & 15u);
+  if (lane < 16) ((v4i*)&s->rec[f])[lane] = q;
+  if (lane == 16) s->entry[f] = ent;
+  if (lane == 0) s->rec_sum = x;
 }
 
 // RING 0: the library's own workers, on the main unit ring, executing through EXEC = the built-in
@@ -2695,14 +2729,17 @@ DEV void fetch_descriptor(const WorkerArgs& a, WorkShared* s, rsrc_t rd, uint64_
 // host asks for a later one.
 template <int RING, class EXEC>
 DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
-  const uint32_t tid = threadIdx.x;
+  // (this thread's place as the wavefront's index, a scalar, and the lane; see thread_index)
+  const uint32_t wave = uni(threadIdx.x >> 6), lane = lane_id();
+  const bool leader = wave == 0 && lane == 0;
   uint64_t* const claim_ctr = RING == 0 ? &a.d->claim : &a.d->claim_j;
   const uint64_t* const unit_ring = RING == 0 ? a.units : a.units_j;
   const rsrc_t rd = make_rsrc(a.dring, (a.cap_mask + 1u) * (uint32_t)sizeof(Record));
-  auto count = [&](uint32_t which, uint64_t add) { if (tid == 0) s->ticks[which - ST_WORK_TICKS_WAIT] += add; };
-  if (tid == 0) {
-    s->waiting = s->have_claim = s->draining = s->polls = s->yield_every = s->n_units = 0;
-    s->g = 0;
+  auto count = [&](uint32_t which, uint64_t add) { if (leader) s->ticks[which - ST_WORK_TICKS_WAIT] += add; };
+  if (leader) {
+    s->state[0] = s->state[1] = s->state[2] = s->state[3] = 0;
+    s->n_units = 0;
+    s->st = a.st; s->hcomp = a.hcomp; s->done_count = &a.d->done_count; s->cap_shift = a.cap_shift;
     for (uint32_t k = 0; k < ST_WORK_TICKS_TOTAL - ST_WORK_TICKS_WAIT; ++k) s->ticks[k] = 0;
   }
   lds_wave_sync();                                    // (only the first wavefront reads them)
@@ -2713,17 +2750,18 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
     // ---- decide what to do next (first wavefront): one round of loads per poll ----
     // Lane 32 polls the claimed entry itself (its stamp is the ready flag: every waiting workgroup
     // polls a different address); lane k < kStash looks at the done words that descriptor slot k waits for.
-    if (tid < 64) {
+    if (wave == 0) {
       uint32_t action = kActExit, f = 0;
       int32_t dep_status = 0;
       uint64_t u_new = 0;
-      uint32_t waiting = uni(s->waiting), polls = uni(s->polls), yield_every = uni(s->yield_every);
-      bool have_claim = uni(s->have_claim) != 0, draining = uni(s->draining) != 0;
-      uint64_t g = uni64(s->g);
+      const v4i st = *(const v4i*)s->state;
+      uint32_t waiting = uni((uint32_t)st[0]) & kStashFull, polls = uni((uint32_t)st[1]), yield_every = 0;
+      bool have_claim = (uni((uint32_t)st[0]) & kHaveClaim) != 0, draining = (uni((uint32_t)st[0]) & kDraining) != 0;
+      uint64_t g = ((uint64_t)uni((uint32_t)st[3]) << 32) | uni((uint32_t)st[2]);
       const bool held_any = waiting != 0;
       if (!have_claim && !draining && waiting != kStashFull) {
         uint64_t gg = 0;
-        if (tid == 0) gg = __hip_atomic_fetch_add(claim_ctr, 1ull, __ATOMIC_RELAXED, SC_AGENT);
+        if (leader) gg = __hip_atomic_fetch_add(claim_ctr, 1ull, __ATOMIC_RELAXED, SC_AGENT);
         g = uni64(gg);
         have_claim = true;
         polls = 0;
@@ -2734,11 +2772,11 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
       // wait ends when resident workgroups finish work they hold.  It is bounded all the same (the
       // context's wait limit; a short grace once the stop flag is up): a task that runs into the
       // bound completes with GPUOS_E_TIMEOUT without executing, and the kernel always leaves.
-      const bool mine = tid < kStash && ((waiting >> tid) & 1u);
+      const bool mine = lane < kStash && ((waiting >> lane) & 1u);
       uint64_t need[3] = {0ull, 0ull, 0ull};
       const uint64_t* done_word[3] = {nullptr, nullptr, nullptr};
       if (mine) {
-        const Record* r = &s->rec[tid];
+        const Record* r = &s->rec[lane];
         const uint64_t ticket = r->ticket;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -2762,7 +2800,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
         Poll p;
         if (waiting == 0) {
           p.u = 0;
-          if (tid == 32 && have_claim) p.u = __hip_atomic_load(up, __ATOMIC_RELAXED, SC_SYSTEM);
+          if (lane == 32 && have_claim) p.u = __hip_atomic_load(up, __ATOMIC_RELAXED, SC_SYSTEM);
           p.seen[0] = p.seen[1] = p.seen[2] = ~0ull;
         } else {
           p.u = __hip_atomic_load(up, __ATOMIC_RELAXED, SC_SYSTEM);
@@ -2778,7 +2816,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
         if (mine && !ready && (polls & 31u) == 31u) {
           uint64_t limit = a.dep_wait_ticks;
           if (limit > kStopGraceTicks && __hip_atomic_load(&a.d->stop_dev, __ATOMIC_RELAXED, SC_SYSTEM)) limit = kStopGraceTicks;
-          if (wall_clock64() - s->since[tid] > limit) { gave_up = GPUOS_E_TIMEOUT; ready = true; }
+          if (wall_clock64() - s->since[lane] > limit) { gave_up = GPUOS_E_TIMEOUT; ready = true; }
         }
         order_loads();
         const uint64_t m_ready = __ballot(ready);
@@ -2787,6 +2825,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
           f = (uint32_t)__builtin_ctzll(m_ready);             // one makes progress)
           dep_status = __builtin_amdgcn_readlane(gave_up, (int)f);
           waiting &= ~(1u << f);
+          u_new = s->unit[f];
           action = kActRun;
           break;
         }
@@ -2794,7 +2833,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
           f = (uint32_t)__builtin_ctz(~waiting);              // a free descriptor slot (claims are made only while one exists)
           have_claim = false;
           action = kActFetch;
-          fetch_descriptor(a, s, rd, u_new, f);  // requested at once: the other wavefronts need not hear of the unit first
+          fetch_descriptor(a, s, rd, u_new, f, lane);  // requested at once: the other wavefronts need not hear of the unit first
           break;
         }
         ++polls;
@@ -2812,13 +2851,13 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
                 f = (uint32_t)__builtin_ctz(~waiting);
                 have_claim = false;
                 action = kActFetch;
-                fetch_descriptor(a, s, rd, u_new, f);
+                fetch_descriptor(a, s, rd, u_new, f, lane);
                 break;
               }
               // The number claimed will never be served.  The second ring stays in use across
               // generations of run-time kernels while the dispatcher runs on: give the number back
               // (nothing is being published to that ring at this time, so the count ends exact).
-              if (RING == 1 && tid == 0) __hip_atomic_fetch_add(claim_ctr, ~0ull, __ATOMIC_RELAXED, SC_AGENT);
+              if (RING == 1 && leader) __hip_atomic_fetch_add(claim_ctr, ~0ull, __ATOMIC_RELAXED, SC_AGENT);
               have_claim = false;
             }
             draining = true;
@@ -2832,21 +2871,18 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
         else if (polls < 64 || waiting != 0) __builtin_amdgcn_s_sleep(1);
         else __builtin_amdgcn_s_sleep(8);
       }
-      if (tid == 0) {
-        s->waiting = waiting; s->polls = polls; s->yield_every = yield_every;
-        s->have_claim = have_claim ? 1u : 0u; s->draining = draining ? 1u : 0u;
-        s->g = g;
-        s->held_any = held_any ? 1u : 0u;
-        s->action = action;
-        s->slot = f;
-        s->dep_status = dep_status;
-        if (action == kActFetch) s->unit[f] = u_new;
+      if (leader) {
+        const v4i next = {(int)(waiting | (have_claim ? kHaveClaim : 0u) | (draining ? kDraining : 0u)), (int)polls, (int)(uint32_t)g, (int)(uint32_t)(g >> 32)};
+        const v4i dec = {(int)(action | (f << 8) | (held_any ? 1u << 16 : 0u)), dep_status, (int)(uint32_t)u_new, (int)(uint32_t)(u_new >> 32)};
+        *(v4i*)s->state = next;
+        *(v4i*)s->dec = dec;
       }
     }
     __syncthreads();
-    const uint32_t action = uni(s->action), f = uni(s->slot);
+    const v4i dec = *(const v4i*)s->dec;
+    const uint32_t action = uni((uint32_t)dec[0]) & 0xffu, f = (uni((uint32_t)dec[0]) >> 8) & 0xffu;
     if (action == kActExit) {
-      if (tid == 0) {
+      if (leader) {
         uint64_t* st = a.d->stat;
         __hip_atomic_fetch_add(&st[ST_WORK_UNITS], s->n_units, __ATOMIC_RELAXED, SC_AGENT);
         for (uint32_t k = ST_WORK_TICKS_WAIT; k < ST_WORK_TICKS_TOTAL; ++k)
@@ -2856,13 +2892,28 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
       return;
     }
     const uint64_t c1 = clock_if(timing || tracing);
-    if (timing) count(s->held_any ? ST_WORK_TICKS_DEP : ST_WORK_TICKS_WAIT, c1 - c0);
+    if (timing) count(uni((uint32_t)dec[0]) >> 16 ? ST_WORK_TICKS_DEP : ST_WORK_TICKS_WAIT, c1 - c0);
     // the unit is the same for the whole workgroup: keep its fields in scalar registers
-    const uint32_t unit_lo = uni((uint32_t)s->unit[f]), unit_hi = uni((uint32_t)(s->unit[f] >> 32));
+    const uint32_t unit_lo = uni((uint32_t)dec[2]), unit_hi = uni((uint32_t)dec[3]);
     const uint64_t unit = ((uint64_t)unit_hi << 32) | unit_lo;
     const uint32_t chunk = (uint32_t)(unit & 0x3ffu), lap10 = (uint32_t)((unit >> 10) & 0x3ffu);
     const uint32_t slot = (uint32_t)((unit >> 20) & 0xffffu);
     const Record* r = &s->rec[f];
+    // What the rest of this unit's handling asks of the record, read in one go (field by field, where each
+    // is wanted, was eight LDS latencies in a row before the executor is reached).
+    struct Head : RecHead { v4i impl, links; uint64_t entry; uint32_t sum; } head;
+    auto read_head = [&]() {
+      const v4i* h = (const v4i*)r;
+      head.op = h[0]; head.impl = h[1]; head.dims = h[2]; head.links = h[3];
+      head.entry = s->entry[f];
+      head.sum = s->rec_sum;
+      asm volatile("" : "+v"(head.op), "+v"(head.impl), "+v"(head.dims), "+v"(head.links), "+v"(head.entry), "+v"(head.sum));
+    };
+    static_assert(__builtin_offsetof(Record, impl) == 16 && __builtin_offsetof(Record, version) == 20 && __builtin_offsetof(Record, status) == 24 &&
+                  __builtin_offsetof(Record, nchunks) == 28 && __builtin_offsetof(Record, dep) == 48 && __builtin_offsetof(Record, ticket) == 56, "the words that are read as vectors");
+    read_head();
+    const auto word = [](const v4i& q, int k) { return uni((uint32_t)q[k]); };
+    const auto pair = [](const v4i& q, int k) { return ((uint64_t)uni((uint32_t)q[k + 1]) << 32) | uni((uint32_t)q[k]); };
     if (action == kActFetch) {
       // ---- fetch the descriptor (16 lanes x 16 bytes) and the claimed table slot ----
       // The dispatcher does not wait for its mirror stores before it publishes a unit: the record is
@@ -2873,12 +2924,13 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
       // (the first wavefront has fetched it once already, when it saw the unit)
       bool valid = false;
       for (uint32_t attempt = 0;; ++attempt) {
-        valid = mirror_record_valid(s->rec_sum, r->ticket, slot, lap10, a.cap_mask, a.cap_shift);
+        valid = mirror_record_valid(uni(head.sum), pair(head.links, 2), slot, lap10, a.cap_mask, a.cap_shift);
         if (valid || attempt >= kMirrorRetries) break;
         __syncthreads();                                  // everyone has looked at this attempt's copy
         __builtin_amdgcn_s_sleep(2);
-        if (tid < 64) fetch_descriptor(a, s, rd, unit, f);
+        if (wave == 0) fetch_descriptor(a, s, rd, unit, f, thread_index(0));
         __syncthreads();
+        read_head();
       }
       const uint64_t c2 = clock_if(timing);
       if (timing) count(ST_WORK_TICKS_FETCH, c2 - c1);
@@ -2888,47 +2940,57 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
         __syncthreads();
         continue;
       }
-      if ((r->dep[0] | r->dep[1] | r->dep[2]) != 0 && !(r->rflags & RF_DEPS_RESOLVED)) {
+      if ((pair(head.links, 0) & 0xffffffffffffull) != 0 && !(head.rflags() & RF_DEPS_RESOLVED)) {
         // It names earlier tasks: it joins the units held, and the first wavefront looks at its done
         // words with the next poll (and runs it at once if they are all there).
-        if (tid == 0) {
-          s->waiting |= 1u << f;
+        if (leader) {
+          s->unit[f] = unit;
+          s->state[0] |= 1u << f;
           s->since[f] = wall_clock64();
         }
-        if (tid < 64) lds_wave_sync();
+        if (wave == 0) lds_wave_sync();
         continue;
       }
     }
-    int32_t status = (int32_t)uni((uint32_t)r->status);
-    const uint32_t impl = uni(r->impl);
-    if (status == GPUOS_OK && uni((uint32_t)(s->entry[f] >> 32)) != uni(r->version)) status = GPUOS_E_VERSION;
-    if (status == GPUOS_OK) status = (int32_t)uni((uint32_t)s->dep_status);
+    int32_t status = (int32_t)word(head.impl, 2);
+    const uint32_t impl = word(head.impl, 0), nchunks = word(head.impl, 3);
+    if (status == GPUOS_OK && uni((uint32_t)(head.entry >> 32)) != word(head.impl, 1)) status = GPUOS_E_VERSION;
+    if (status == GPUOS_OK) status = (int32_t)word(dec, 1);
     const uint64_t c3 = clock_if(timing);
     // a task's start in the trace is the moment a workgroup took its descriptor (a unit that waited: when it began to)
     const uint64_t c_start = (tracing && action == kActRun) ? s->since[f] : c1;
-    if (tracing && tid == 0 && chunk == 0 && r->nchunks > 1)
+    if (tracing && leader && chunk == 0 && nchunks > 1)
       __hip_atomic_store(&a.st[slot].t_first, c_start, __ATOMIC_RELAXED, SC_SYSTEM);   // in memory before this chunk is counted
     // ---- execute ----
-    if (status == GPUOS_OK) status = EXEC::run(r, impl, chunk, s->red, a.progs);
-    if (RING == 1 && tid == 0) __hip_atomic_fetch_add(&a.d->jit_units, 1ull, __ATOMIC_RELAXED, SC_AGENT);
+    if (status == GPUOS_OK) status = EXEC::run(r, head, impl, chunk, s->red, a.progs, thread_index(wave));
+    if (RING == 1 && leader) __hip_atomic_fetch_add(&a.d->jit_units, 1ull, __ATOMIC_RELAXED, SC_AGENT);
+    // What completing needs, read while the stores are still on their way: through an address made here,
+    // as the first use of a register that a call preserves waits for everything the callee left in flight.
+    uint32_t here = 0;
+    asm volatile("" : "+v"(here));
+    const Record* const rh = (const Record*)((const char*)r + here);
+    const WorkShared* const sh = (const WorkShared*)((const char*)s + here);
+    const v4i impl_w = ((const v4i*)rh)[1];
+    const uint64_t ticket = rh->ticket, cap_shift = sh->cap_shift;
+    SlotState* const st = global_ptr(sh->st);
+    uint64_t *const comp = global_ptr(sh->hcomp), *const done_count = global_ptr(sh->done_count);
     drain_stores();                   // this wave's (write-through) stores have reached memory
     __syncthreads();                  // ... and so have the other three waves'
     const uint64_t c4 = clock_if(timing || tracing);
     // ---- complete ----
-    if (tid == 0) {
-      const uint32_t nchunks = r->nchunks;
-      const uint64_t target = done_target(r->ticket, a.cap_shift);
+    if (leader) {
+      const uint32_t nchunks = (uint32_t)impl_w[3], version = (uint32_t)impl_w[1];
+      const uint64_t target = done_target(ticket, (uint32_t)cap_shift);
       bool last = true;
       if (nchunks > 1) {
         const uint64_t share = chunk + 1 == nchunks ? kDoneTask - (nchunks - 1) : 1ull;
-        last = __hip_atomic_fetch_add(&a.st[slot].done_seq, share, __ATOMIC_RELAXED, SC_AGENT) + share == target;
+        last = __hip_atomic_fetch_add(&st[slot].done_seq, share, __ATOMIC_RELAXED, SC_AGENT) + share == target;
       }
       if (last) {
-        const uint64_t ticket = r->ticket;
         if (tracing) {
           // the tracepoint lands before the completion word that lets the host read it
           const uint64_t origin = __hip_atomic_load(&a.h->clock_origin, __ATOMIC_RELAXED, SC_SYSTEM);
-          const uint64_t t_start = nchunks > 1 ? __hip_atomic_load(&a.st[slot].t_first, __ATOMIC_RELAXED, SC_SYSTEM) : c_start;
+          const uint64_t t_start = nchunks > 1 ? __hip_atomic_load(&st[slot].t_first, __ATOMIC_RELAXED, SC_SYSTEM) : c_start;
           TraceRec* tr = &a.trace[ticket & a.trace_mask];
           const uint64_t tdq = ((uint64_t)r->t_dequeue[1] << 32) | r->t_dequeue[0];
           __hip_atomic_store(&tr->t_dequeue, tdq - origin, __ATOMIC_RELAXED, SC_SYSTEM);
@@ -2938,21 +3000,21 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
           // count arrives late (seen once in a few thousand multi-chunk tasks).
           const uint64_t t_done = nchunks > 1 ? wall_clock64() : c4;
           __hip_atomic_store(&tr->t_done, t_done - origin, __ATOMIC_RELAXED, SC_SYSTEM);
-          const uint64_t w4 = (uint64_t)r->version | ((uint64_t)r->op_id << 32) | ((uint64_t)(uint8_t)(int8_t)status << 48);
+          const uint64_t w4 = (uint64_t)version | ((uint64_t)r->op_id << 32) | ((uint64_t)(uint8_t)(int8_t)status << 48);
           __hip_atomic_store((uint64_t*)&tr->op_version, w4, __ATOMIC_RELAXED, SC_SYSTEM);
           const uint64_t w5 = (uint64_t)nchunks | ((uint64_t)blockIdx.x << 32);
           __hip_atomic_store((uint64_t*)&tr->nchunks, w5, __ATOMIC_RELAXED, SC_SYSTEM);
           __hip_atomic_store(&tr->ticket, ticket, __ATOMIC_RELAXED, SC_SYSTEM);
           drain_stores();
         }
-        if (nchunks <= 1) __hip_atomic_store(&a.st[slot].done_seq, target, __ATOMIC_RELAXED, SC_SYSTEM);
-        __hip_atomic_store(&a.hcomp[slot], pack_completion(ticket, status, r->version), __ATOMIC_RELAXED, SC_SYSTEM);
-        __hip_atomic_fetch_add(&a.d->done_count, 1ull, __ATOMIC_RELAXED, SC_AGENT);
+        if (nchunks <= 1) __hip_atomic_store(&st[slot].done_seq, target, __ATOMIC_RELAXED, SC_SYSTEM);
+        __hip_atomic_store(&comp[slot], pack_completion(ticket, status, version), __ATOMIC_RELAXED, SC_SYSTEM);
+        __hip_atomic_fetch_add(done_count, 1ull, __ATOMIC_RELAXED, SC_AGENT);
       }
     }
     __syncthreads();                  // the descriptor in LDS may be overwritten after this
     const uint64_t c5 = clock_if(timing);
-    if (tid == 0) s->n_units += 1;
+    if (leader) s->n_units += 1;
     if (timing) { count(ST_WORK_TICKS_EXEC, c4 - c3); count(ST_WORK_TICKS_COMPLETE, c5 - c4); }
   }
 }

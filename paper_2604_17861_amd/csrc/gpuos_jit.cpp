@@ -152,12 +152,12 @@ std::string jit_source(const ProgramImage* imgs, uint32_t n) {
     s += "    (void)r1; (void)r2; (void)r3; (void)r4; (void)r5; (void)r6; (void)r7;\n    return r0;\n  }\n};\n";
   }
   s += "struct NativeExec {\n"
-       "  static DEV int32_t run(const Record* r, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage*) {\n"
-       "    if (uni(r->path) == PATH_NOP) return GPUOS_OK;\n"
+       "  static DEV int32_t run(const Record* r, const RecHead& h, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage*, uint32_t tid) {\n"
+       "    if (h.path() == PATH_NOP) return GPUOS_OK;\n"
        "    switch (impl - GPUOS_IMPL_PROGRAM_BASE) {\n";
   for (uint32_t k = 0; k < n; ++k) {
     std::snprintf(buf, sizeof(buf), "      case %u: if (uni(r->n_inputs) != %uu) return GPUOS_E_INVAL; "
-                  "run_elementwise<POL_COHERENT, kNativeOp + %u>(r, chunk, s_red); return GPUOS_OK;\n", k, imgs[k].n_inputs, k);
+                  "run_elementwise<POL_COHERENT, kNativeOp + %u>(r, h, chunk, s_red, tid); return GPUOS_OK;\n", k, imgs[k].n_inputs, k);
     s += buf;
   }
   s += "      default: return GPUOS_E_BADOP;\n    }\n  }\n};\n}  // namespace gpuos\n";

@@ -735,7 +735,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
   __shared__ alignas(16) float s_red[kScratchFloats];
   if (threadIdx.x == 0) s_rec = rec;
   __syncthreads();
-  exec_chunk<POL_PLAIN>(&s_rec, s_rec.impl, blockIdx.x, s_red, nullptr);   // built-in implementations only
+  exec_chunk<POL_PLAIN>(&s_rec, RecHead::of(&s_rec), s_rec.impl, blockIdx.x, s_red, nullptr, threadIdx.x);   // built-in implementations only
 }
 
 // The workgroups of a stopped worker left holding work-unit numbers beyond the last published one
