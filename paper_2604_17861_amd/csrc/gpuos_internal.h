@@ -50,6 +50,7 @@ constexpr uint32_t kMaxChunksPerTask = 1024;   // unit ring holds capacity * thi
 constexpr uint32_t kChunkElems = 16384;        // minimum elements per chunk
 constexpr uint32_t kMostChunkElems = 1u << 24; // ... and the most a context may ask for: a chunk of any path is addressed through one buffer resource
 constexpr uint32_t kNoLoad = 0x7ffffff0u;      // a buffer offset past every resource: a load there returns 0 and a store does nothing
+constexpr uint32_t kSmallTaskChunks = 4;       // a dependent task of at most this many chunks is published at once and waits in its workgroups
 constexpr uint32_t kDispatchBatch = 64;        // records mirrored per dispatcher pass
 constexpr uint32_t kThreads = 256;             // threads per workgroup of the worker
 

@@ -55,7 +55,6 @@ namespace gpuos {
 // ---------------------------------------------------------------------------
 constexpr uint32_t kPendMax = 128;         // tasks held back at a time
 constexpr uint64_t kLookaheadUnits = 8192; // work units kept published ahead of the claim counter
-constexpr uint32_t kSmallTaskChunks = 4;
 constexpr uint32_t kPrefetch = 4;          // records read together with every doorbell poll (4 x 16 lanes)
 constexpr uint32_t kStageRetries = 4096;   // re-reads of a record that fails its check word (~ms) before it is failed
 

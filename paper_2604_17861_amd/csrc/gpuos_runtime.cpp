@@ -591,9 +591,16 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   // size.  (Chunks of twice the elementwise traffic whatever the task's size: a 0.2 MB reduction
   // in a bandwidth-bound stream was two chunks of 7 rounds each and took 110 us.  Forty streaming
   // operations of 0.1-220 MB, half of them reductions: 152 us a pass before, 130 now.)
-  const uint64_t row_bytes = (uint64_t)n * dtype_size(ops[0].dtype);
-  const uint64_t most = (uint64_t)chunk_elems * 24, spread = row_bytes * (uint64_t)rows / 64;
+  // But a link of a chain of at most four regular chunks is cut into (up to) four, like an elementwise
+  // one: up to those a dependent task is published at once and waits in its workgroups, beyond them
+  // the dispatcher holds it back until what it waits for is done.
+  const uint64_t row_bytes = (uint64_t)n * dtype_size(ops[0].dtype), total = row_bytes * (uint64_t)rows;
+  const uint64_t most = (uint64_t)chunk_elems * 24, spread = total / 64;
   uint64_t rpc = (spread < 16384 ? 16384 : (spread < most ? spread : most)) / row_bytes;
+  if (chained && total <= kSmallTaskChunks * most) {
+    const uint64_t quarter = ((uint64_t)rows + kSmallTaskChunks - 1) / kSmallTaskChunks;
+    if (rpc < quarter) rpc = quarter;
+  }
   if (rpc < 1) rpc = 1;
   if (rpc >= 16) rpc = (rpc + 15) / 16 * 16;          // whole passes of the row-per-wave kernels
   const uint64_t min_rpc = ((uint64_t)rows + kMaxChunksPerTask - 1) / kMaxChunksPerTask;

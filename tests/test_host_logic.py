@@ -198,6 +198,32 @@ def test_small_tasks_are_cut_into_more_chunks_than_their_size_alone_would_give()
         assert (path, c, p) == ("TILE2D", chunks, per) and (c - 1) * p < tiles <= c * p, ((r, cc), path, c, p)
 
 
+def test_small_links_of_a_chain_stay_within_four_chunks():
+    """A dependent task of more than four chunks is held back by the dispatcher until what it waits for
+    is done; links of at most four regular chunks (192 KiB of traffic each) are published at once.  The
+    reductions of an attention softmax over 16 heads, as links and alone."""
+    from helpers import Builder
+    def plan(shape, dep, np_dt=np.float16, name="MAX_LAST"):
+        b = Builder()
+        b.add(name, b.pool(np.zeros(shape[:-1], np.float32)), [b.pool(np.zeros(shape, np_dt))], dep=(dep, 0, 0))
+        s = b.stream()
+        return R.task_plan(HostPools(s).tasks, 0, s.impl_for()[0])
+    for B, sq, want in ((1, 64, 4), (2, 64, 4), (4, 64, 4), (6, 64, 4), (1, 128, 4), (1, 150, 4), (1, 16, 1), (1, 40, 4)):
+        rows, nbytes = B * 16 * sq, B * 16 * sq * sq * 2
+        assert nbytes <= 4 * 8192 * 24
+        path, chunks, per, _ = plan((B, 16, sq, sq), 1)
+        assert path == "RED_CONTIG" and chunks <= want and (chunks - 1) * per < rows <= chunks * per, (B, sq, chunks, per)
+        assert chunks >= 2 or nbytes < 32768
+        alone = plan((B, 16, sq, sq), 0)[1]
+        assert alone >= chunks and (alone > 4 or nbytes <= 4 * 16384), (B, sq, alone)
+        assert plan((B, 16, sq, sq), 9)[1] == alone               # what lies further back than eight tickets is no chain
+    # beyond four regular chunks it is held anyway, and spread
+    assert plan((8, 16, 256, 256), 1)[1] > 4 and plan((4, 16, 128, 128), 1)[1] == 64
+    # rows too long or too few for four pieces
+    assert plan((3, 60000), 1)[1] == 3 and plan((1, 300000), 1)[1] == 1
+    assert plan((5, 4096), 1, np.float32)[1] == 3
+
+
 def test_task_plan_for_row_operations():
     """Rows of whole aligned vectors, one dtype, contiguous -> the fused executors, with further inputs
     laid out like x, repeated every `period` rows, or one row; rows of any other length from a vector
