@@ -547,8 +547,10 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
       const uint32_t row = (uint32_t)size[nd - 1];
       const uint64_t vectors = (uint64_t)((uint32_t)numel / row) * ((row + rec.vwidth - 1u) / rec.vwidth);
       rec.numel = (uint32_t)vectors;
+      // (what is at most four chunks of elements stays so where partly filled vectors make it more: see above)
+      const uint64_t most = div_up((uint64_t)numel, per) <= kSmallTaskChunks ? kSmallTaskChunks : kMaxChunksPerTask;
       per /= rec.vwidth;
-      const uint64_t min_per = (vectors + kMaxChunksPerTask - 1) / kMaxChunksPerTask;
+      const uint64_t min_per = (vectors + most - 1) / most;
       if (per < min_per) per = min_per;
       rec.chunk = (uint32_t)per;
       rec.nchunks = (uint32_t)div_up(vectors, per);

@@ -162,6 +162,25 @@ def test_no_task_is_more_than_1024_chunks(layout, code):
             assert path == want, what
 
 
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.I32])
+def test_small_rows_tasks_stay_within_four_chunks(code):
+    """A slice is cut into chunks of vectors, the last vector of a row partly filled: as a dependent task it
+    is at most as many chunks as its elements make where those are at most four, the number up to
+    which the dispatcher publishes it at once."""
+    at = [(k + 1) << 36 for k in range(4)]
+    V = 4 if code in (S.F32, S.I32) else 8
+    for C in (V, V + 1, 2 * V - 1, 2 * V + 1, 65, 100, 1001):
+        for numel in (2000, 9000, 16384, 20000, 32768, 60000, 300000):
+            R_ = numel // C
+            dense = [(at[k], [C, 1], code) for k in range(2)]
+            path, want, per, _ = plan_of("ADD", [R_, C], dense, (at[3], [C, 1], code), dep=(1, 0, 0))
+            assert path == "CONTIG"
+            path, chunks, per, _ = plan_of("ADD", [R_, C], [(at[0], [C + 3, 1], code), dense[1]], (at[3], [C + 1, 1], code), dep=(1, 0, 0))
+            vectors = R_ * -(-C // V)
+            assert path == "ROWS" and (chunks - 1) * per < vectors <= chunks * per
+            assert (chunks <= 4) if want <= 4 else (chunks > 4), (C, numel, want, chunks)
+
+
 @pytest.mark.parametrize("op", ["SOFTMAX_LAST", "MASKED_SOFTMAX_LAST", "LAYERNORM_LAST"])
 def test_rows_up_to_the_last_addressable_byte(op):
     """The executors of contiguous rows address a row by byte offsets below 0x7ffffff0, the offset that is
