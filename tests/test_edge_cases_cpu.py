@@ -171,7 +171,7 @@ def test_small_rows_tasks_stay_within_four_chunks(code):
     V = 4 if code in (S.F32, S.I32) else 8
     for C in (V, V + 1, 2 * V - 1, 2 * V + 1, 65, 100, 1001):
         for numel in (2000, 9000, 16384, 20000, 32768, 60000, 300000):
-            R_ = numel // C
+            R_ = max(numel // C, 2)
             dense = [(at[k], [C, 1], code) for k in range(2)]
             path, want, per, _ = plan_of("ADD", [R_, C], dense, (at[3], [C, 1], code), dep=(1, 0, 0))
             assert path == "CONTIG"
