@@ -31,16 +31,22 @@ def test_an_operator_swapped_under_tasks_packed_as_rows():
     from paper_2604_17861_amd import runtime as R
     rng = np.random.default_rng(3)
     P = S.program
-    for op, new in (("COPY", "RELU"), ("SCALE", (P(("NEG", 0, 0)), 1)), ("SUB", (P(("SUB", 4, 1, 0), ("MOV", 0, 4)), 2))):
-        print("swap under", op, flush=True)
+    sub = (P(("SUB", 4, 1, 0), ("MOV", 0, 4)), 2)
+    # (the last three: one scalar per row under another operator of the class and under a program, int32)
+    for op, new, kind in (("COPY", "RELU", "plain"), ("SCALE", (P(("NEG", 0, 0)), 1), "plain"), ("SUB", sub, "plain"),
+                          ("SUB", "DIV", "scalar"), ("MUL", sub, "scalar"), ("ADD", "SUB", "int32")):
+        print("swap under", op, kind, flush=True)
         b = Builder()
         prog = not isinstance(new, str)
         impl = b.define_program(200, *new) if prog else S.IMPL[new]
         for R_, C_ in ((5, 37), (90, 1001)):
-            x = b.pool(E.values(rng, (R_, C_ + 5), S.F32))[:, 2:C_ + 2]
-            y = b.pool(E.values(rng, (R_, C_), S.F32))
-            o = b.pool(np.zeros((R_, C_ + 1), np.float16 if op == "COPY" else np.float32))[:, 1:]
-            b.add(op, o, [x, y] if op == "SUB" else [x], alpha=2.0)
+            code = S.I32 if kind == "int32" else S.F32
+            x = b.pool(E.values(rng, (R_, C_ + 5), code))[:, 2:C_ + 2]
+            y = b.pool(E.values(rng, (R_, C_), code))
+            if kind != "plain":
+                y = np.broadcast_to(b.pool(E.values(rng, (R_, 1), code)), (R_, C_))
+            o = b.pool(np.zeros((R_, C_ + 1), np.float16 if op == "COPY" else np.int32 if kind == "int32" else np.float32))[:, 1:]
+            b.add(op, o, [x, y] if op in ("SUB", "MUL", "ADD") else [x], alpha=2.0)
         s = b.stream("swap_under_rows")
         dp = DevicePools(s)
         with R.Runtime(0, idle_exit_ms=20000, wait_timeout_ms=20000) as rt:
@@ -96,3 +102,38 @@ def test_gelu_rounds_the_64_bit_value(code):
         total += g.size
     print("differ", differ, "of", total, flush=True)
     assert differ <= (4 if code == S.F32 else 0)
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_row_operations_in_place(code):
+    """Rows written over the rows they are made of: the last vector of a ragged row re-reads elements
+    that another lane may have written by then, and must not use them.  The results are those of the
+    same tasks with an output of their own (which the test above compares with the oracle)."""
+    import numpy as np
+    from gpu_helpers import DevicePools, run_stream
+    from helpers import Builder
+    from paper_2604_17861_amd import runtime as R
+    V = 4 if code == S.F32 else 8
+    got = []
+    for in_place in (False, True):
+        rng = np.random.default_rng(750 + code)
+        b, outs = Builder(), []
+        for rows, n in ((70, V + 1), (300, 3 * V - 1), (131, 32 * V + 1), (65, 64 * V + 1), (17, 128 * V + 1), (9, 256 * V + 1), (9, 257 * V),
+                        (5, 512 * V + 3), (3, 1024 * V + 1), (3, 2048 * V + 1), (2, 4096 * V + V + 1), (2, 5632 * V + 1), (64, 64 * V)):
+            for name in ("SOFTMAX_LAST", "MASKED_SOFTMAX_LAST", "LAYERNORM_LAST"):
+                x = b.pool(E.values(rng, rows * n + 1, code, 3.0))[n % 2:][:rows * n].reshape(rows, n)
+                more = [np.broadcast_to(b.pool(E.values(rng, n, code)), (rows, n)) for _ in range({"S": 0, "M": 1, "L": 2}[name[0]])]
+                o = x if in_place else b.pool(np.zeros(rows * n + 1, x.dtype))[n % 2:][:rows * n].reshape(rows, n)
+                b.add(name, o, [x] + more, alpha=0.25)
+                outs.append(b._locate(o) + (rows * n * x.itemsize,))
+        s = b.stream("rows_in_place" if in_place else "rows_apart")
+        print("case", s.name, code, len(s), flush=True)
+        dp = DevicePools(s)
+        with R.Runtime(0, idle_exit_ms=20000, wait_timeout_ms=20000) as rt:
+            rt.register_table(s.table)
+            t0 = run_stream(s, rt, dp)
+            assert np.all(rt.completions(t0, len(s))["status"] == 0)
+        imgs = dp.download()
+        got.append([np.ascontiguousarray(imgs[k]).view(np.uint8).reshape(-1)[off: off + nb] for k, off, nb in outs])
+    for i, (a, c) in enumerate(zip(*got)):
+        assert np.array_equal(a, c), i

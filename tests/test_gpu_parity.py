@@ -190,8 +190,9 @@ def test_held_producer_with_more_small_dependants_than_workgroups():
 def test_dependency_wait_is_bounded():
     """cfg.dep_wait_us: a workgroup that holds a small task whose dependency is still running gives
     up after the bound; the task completes with GPUOS_E_TIMEOUT and writes nothing, everything else
-    runs, and the worker stays alive.  With a bound of one microsecond behind a 16M-element task
-    the wait usually runs out (either outcome is legal: the bound is a safety net, not a schedule)."""
+    runs, and the worker stays alive.  The task waited for is an interpreted program of 32 instructions
+    over 16M elements (milliseconds, in 1,024 chunks for fewer workgroups), the bound one microsecond,
+    looked at every 32 polls (tens of microseconds): the wait runs out."""
     from gpu_helpers import DevicePools, run_stream
     rng = np.random.default_rng(5)
     b = C.Builder()
@@ -200,26 +201,24 @@ def test_dependency_wait_is_bounded():
     y = b.pool(np.zeros(n, np.float32))
     z = b.pool(np.full(1024, 7.0, np.float32))
     w = b.pool(np.zeros(1024, np.float32))
-    b.add("GELU_ERF", y, [x])                                  # long: 1,024 chunks evaluated in fp64
+    P = S.program
+    b.define_program(200, P(*([("EXP", 4, 0)] * 31 + [("MOV", 0, 4)])), 1)
+    b.add("EXP", y, [x], op_id=200)                            # long
     b.add("COPY", z, [y[:1024]], dep=(1, 0, 0))                # small and dependent: its workgroup waits
     b.add("RELU", w, [x[:1024]])                               # independent
     s = b.stream("bounded_wait")
     dp = DevicePools(s)
-    with R.Runtime(0, idle_exit_ms=20000, wait_timeout_ms=20000, dep_wait_us=1) as rt:
-        rt.register_table(s.table)
+    with R.Runtime(0, idle_exit_ms=20000, wait_timeout_ms=20000, dep_wait_us=1, jit_mode=2) as rt:
+        rt.register_table(s.table, s.programs)
         t0 = run_stream(s, rt, dp, wait=False)
         rc = rt.wait(check=False)
         comps = rt.completions(t0, 3)
         assert rt.worker_alive()
     print("bounded wait: statuses", comps["status"], flush=True)
     assert comps["status"][0] == 0 and comps["status"][2] == 0
-    assert comps["status"][1] in (0, R.E_TIMEOUT) and rc == comps["status"][1]
+    assert comps["status"][1] == R.E_TIMEOUT and rc == R.E_TIMEOUT
     imgs = dp.download()
-    zz, yy = imgs[2].view(np.float32), imgs[1].view(np.float32)
-    if comps["status"][1] == R.E_TIMEOUT:
-        assert np.all(zz == 7.0)                               # it wrote nothing
-    else:
-        assert np.array_equal(zz, yy[:1024])
+    assert np.all(imgs[2].view(np.float32) == 7.0)             # it wrote nothing
     assert np.array_equal(imgs[3].view(np.float32), np.maximum(imgs[0].view(np.float32)[:1024], 0))
 
 
