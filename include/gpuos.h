@@ -284,7 +284,9 @@ typedef struct gpuos_config {
                                        1024, 2^24 at most).  Tasks of up to 2^20 elements and links of a chain
                                        take half of it; a task of at most four such chunks is cut
                                        into up to four; gathered and transposed inputs are spread
-                                       over up to 32 resp. 64 workgroups (gpuos_task_plan tells) */
+                                       over up to 32 resp. 64 workgroups, reductions that are no
+                                       such link of a chain over up to 64 in pieces of 16 KiB at
+                                       least (gpuos_task_plan tells) */
   uint32_t push_ring;               /* where the ring, the doorbell and the table source
                                        live: 0 = fine-grained host memory that the device
                                        polls over PCIe; 1 = device memory that the host

@@ -1355,10 +1355,11 @@ template <int RIMPL, class T> DEV T wave_reduce(T acc, uint32_t width) {
 // and the last vector of the run may hold bytes outside the tensor, in the same aligned 16 bytes as
 // one of its elements and so in the same page; they are masked like another row's.)  I32 rows take
 // the same way: with one wavefront per row and one word per lane and load, whatever the row length,
-// 24 integer operations of 0.1-50 MB took 529 us, a 13,946 x 22 maximum among them 505; now 95.
+// 24 integer operations of 0.1-50 MB took 529 us, a 13,946 x 22 maximum among them 505; 95 with this,
+// 62 with rows on 16-byte accesses besides (ew_rows).
 // Three shapes of work:
 //   short rows  (span <= 64 vectors): P lanes per row, 64 / P rows per wavefront pass,
-//               four passes in flight;
+//               eight passes in flight;
 //   medium rows: one wavefront per row, RA rows at a time, UN loads per row in flight;
 //   long rows   (>= 1024 vectors): the four wavefronts take a quarter of each row, partial
 //               results meet in LDS once per chunk (one barrier per chunk, not per row).
@@ -1542,8 +1543,9 @@ PATHFN void red_rows_quarter(RedArgs a) {
   __syncthreads();
   const uint32_t nrows = row_end - row_begin;
   if (tid < nrows) {
-    const A* p = (const A*)(s_part + tid * 4);
-    const A t = red_combine<RIMPL>(red_combine<RIMPL>(p[0], p[1]), red_combine<RIMPL>(p[2], p[3]));
+    const float* p = s_part + tid * 4;
+    auto part = [&](int k) { return __builtin_bit_cast(A, p[k]); };
+    const A t = red_combine<RIMPL>(red_combine<RIMPL>(part(0), part(1)), red_combine<RIMPL>(part(2), part(3)));
     red_store<POL>(po, row_begin + tid, odt, t);
   }
   __syncthreads();

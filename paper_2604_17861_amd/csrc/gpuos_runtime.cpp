@@ -185,7 +185,7 @@ bool all_dense(int nd, const int64_t* size, const Operand* ops, int nops) {
   return true;
 }
 
-// a / b rounded up, both below 2^32: a 32-bit division (a 64-bit one costs 10 ns, and a task needs several)
+// a / b rounded up; by a 32-bit division where both are below 2^31 (a 64-bit one costs 10 ns, and a task needs several)
 inline uint64_t div_up(uint64_t a, uint64_t b) { return a < (1ull << 31) && b < (1ull << 31) ? ((uint32_t)a + (uint32_t)b - 1u) / (uint32_t)b : (a + b - 1) / b; }
 
 // Merge adjacent dims that every operand walks as one: outer stride == inner
