@@ -592,7 +592,10 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   // one or two rounds of its workgroup (16 KiB), up to 64 of them, before chunks grow to the regular
   // size.  (Chunks of twice the elementwise traffic whatever the task's size: a 0.2 MB reduction
   // in a bandwidth-bound stream was two chunks of 7 rounds each and took 110 us.  Forty streaming
-  // operations of 0.1-220 MB, half of them reductions: 152 us a pass before, 130 now.)
+  // operations of 0.1-220 MB, half of them reductions: 152 us a pass before, 130 now.  64 and not
+  // fewer: in 32, 16 and 8 pieces those take 140, 141 and 151 us, 24 integer operations 77, 103 and 104
+  // instead of 61.  What it costs is throughput where the queue is never empty: a stream of 20,000
+  // such operations takes 53.9 ms instead of 52.9, 53.2 in 32 pieces.)
   // But a link of a chain of at most four regular chunks is cut into (up to) four, like an elementwise
   // one: up to those a dependent task is published at once and waits in its workgroups, beyond them
   // the dispatcher holds it back until what it waits for is done.
