@@ -62,6 +62,7 @@ template <int POL> struct Mem {
   }
   static DEV void stb4(rsrc_t r, uint32_t off, uint32_t w) { __builtin_amdgcn_raw_buffer_store_b32(w, r, (int)off, 0, AUX); }
   static DEV void stb2(rsrc_t r, uint32_t off, uint32_t h) { __builtin_amdgcn_raw_buffer_store_b16((uint16_t)h, r, (int)off, 0, AUX); }
+  static DEV uint32_t ldb2(rsrc_t r, uint32_t off) { return (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, AUX); }
   static DEV uint32_t ldb4(rsrc_t r, uint32_t off) { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX); }
   static DEV uint32_t ld4(const void* p, uint32_t i) {
     if (POL == POL_COHERENT) return __hip_atomic_load((const uint32_t*)p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -2704,6 +2705,9 @@ struct WorkShared {
   uint64_t* hcomp;
   uint64_t* done_count;
   uint64_t cap_shift;
+  const Record* dring;             // (a run's other descriptors)
+  const OpSlots* dtable;
+  uint32_t cap_mask;
   uint32_t rec_sum;                // weighted check sum of the record as fetched
   uint64_t n_units;                // (ST_WORK_UNITS, and the counters after it)
   uint64_t ticks[ST_WORK_TICKS_TOTAL - ST_WORK_TICKS_WAIT];
@@ -2737,6 +2741,158 @@ DEV void fetch_descriptor(const WorkerArgs& a, WorkShared* s, rsrc_t rd, uint64_
   if (lane == 0) s->rec_sum = x;
 }
 
+// ---------------------------------------------------------------------------
+// runs: a chain of elementwise tasks over buffers of one size, each reading what the one before it wrote.
+// Its units stand for all of its tasks: the workgroup that has run a chunk of one runs the same chunk
+// of the next, and what it wrote is still in its registers.  What a link cost when every task had units
+// of its own was five memory latencies in a row (done word, poll, operands, stores, their acknowledgement),
+// 5.5 us; here it costs its arithmetic and the issue of its stores, which nothing waits for before the run ends.
+// The host vouches (links()) that any two operands of the run begin at the same address or do not
+// overlap, so a lane meets only its own elements.
+// ---------------------------------------------------------------------------
+template <int POL, int DT>
+DEV void run_links(const Record* recs, uint32_t n_links, uint32_t skip, uint32_t begin, uint32_t end, uint32_t tid) {
+  using E = Elem<DT>;
+  using M = Mem<POL>;
+  constexpr uint32_t V = E::V, U = 4;
+  const uint32_t nvec = (end - begin) / V, tail = (end - begin) % V, bytes = (end - begin) * E::ES;
+  const uint64_t boff = (uint64_t)begin * E::ES;
+  auto ld1 = [](rsrc_t r, uint32_t off) { return E::ES == 4 ? M::ldb4(r, off) : M::ldb2(r, off); };
+  for (uint32_t v0 = 0;; v0 += U * kThreads) {
+    const bool last = v0 + U * kThreads >= nvec;
+    uint32_t off[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) off[u] = v0 + tid + u * kThreads < nvec ? (v0 + tid + u * kThreads) * 16u : kNoLoad;
+    const uint32_t off1 = last && tid < tail ? (nvec * V + tid) * E::ES : kNoLoad;      // an element of the ragged end (vector U holds it)
+    // what the registers hold: the buffer that `cur` and `oth` were read from or written to
+    v4i cur[U + 1], oth[U + 1];
+    uint64_t cur_p = 0, oth_p = 0;
+    auto load = [&](v4i (&q)[U + 1], uint64_t p) {
+      const rsrc_t rs = make_rsrc((const char*)(__UINTPTR_TYPE__)p + boff, bytes);
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) q[u] = M::ld16(rs, off[u]);
+      q[U] = v4i{(int)ld1(rs, off1), 0, 0, 0};
+    };
+    for (uint32_t k = 0; k < n_links; ++k) {
+      const Record* r = recs + k;
+      const uint64_t p0 = (uint64_t)(__UINTPTR_TYPE__)uni_ptr(r->ptr[0]), p1 = (uint64_t)(__UINTPTR_TYPE__)uni_ptr(r->ptr[1]);
+      const uint64_t po = (uint64_t)(__UINTPTR_TYPE__)uni_ptr(r->ptr[3]);
+      const uint32_t impl = uni(r->impl);
+      const float alpha = __builtin_bit_cast(float, uni(__builtin_bit_cast(uint32_t, r->alpha)));
+      const bool two = uni(r->n_inputs) == 2u;
+      if ((skip >> k) & 1u) continue;                    // (completes with an error, writes nothing)
+      const bool b_cur = two && p1 == cur_p;
+      bool a_cur = p0 == cur_p;
+      if (!a_cur && p0 != oth_p) {
+        if (b_cur) { load(oth, p0); oth_p = p0; }
+        else { load(cur, p0); cur_p = p0; a_cur = true; }
+      }
+      bool b_oth = false;
+      if (two && p1 != cur_p) {
+        if (p1 == oth_p) b_oth = true;
+        else if (a_cur) { load(oth, p1); oth_p = p1; b_oth = true; }
+        else { load(cur, p1); cur_p = p1; }
+      }
+      v4i qa[U + 1], qb[U + 1];
+#pragma unroll
+      for (uint32_t u = 0; u <= U; ++u) { qa[u] = a_cur ? cur[u] : oth[u]; qb[u] = b_oth ? oth[u] : cur[u]; }
+      const rsrc_t ro = make_rsrc((const char*)(__UINTPTR_TYPE__)po + boff, bytes);
+      auto sink = [&](int u, const v4i& q) {
+        if (u < (int)U) M::st16(ro, off[u], q);
+        else if (E::ES == 4) M::stb4(ro, off1, (uint32_t)q[0]);
+        else M::stb2(ro, off1, (uint32_t)q[0]);
+        cur[u] = q;
+      };
+      typedef VecArg<DT, U + 1> Arg;
+      if (two) ByArity<2>::template vectors<DT, U + 1>(impl, Arg{qa}, Arg{qb}, Arg{qa}, alpha, sink);
+      else ByArity<1>::template vectors<DT, U + 1>(impl, Arg{qa}, Arg{qa}, Arg{qa}, alpha, sink);
+      cur_p = po;
+      if (oth_p == po) oth_p = 0;
+    }
+    if (last) break;
+  }
+}
+
+// One unit of a run, from the head's descriptor (slot f) to the completion of its tasks.
+PATHFN void exec_run(WorkShared* s_v, uint32_t f_v, uint32_t chunk_v, int32_t status_v, uint32_t tid) {
+  WorkShared* s = lds_arg(s_v);
+  const uint32_t f = uni(f_v), chunk = uni(chunk_v), lane = tid & 63u;
+  const Record* head = &s->rec[f];
+  const uint32_t n = uni(head->run), cap_mask = uni(s->cap_mask), cap_shift = uni((uint32_t)s->cap_shift);
+  const uint64_t ticket = uni64(head->ticket);
+  // the descriptors, through the mirror like the head's: each proves itself (see mirror_record_valid)
+  Record* const recs = (Record*)s->red;
+  uint32_t* const ok = (uint32_t*)s->red + kRunMax * sizeof(Record) / 4;       // per task: seen whole; then the status it completes with
+  static_assert((kRunMax * sizeof(Record) + kRunMax * 4) <= kScratchFloats * 4 && kRunMax <= 64, "a run's descriptors fit the scratch");
+  const rsrc_t rd = make_rsrc(uni_ptr((uint64_t)(__UINTPTR_TYPE__)s->dring), (cap_mask + 1u) * (uint32_t)sizeof(Record));
+  const OpSlots* const table = (const OpSlots*)uni_ptr((uint64_t)(__UINTPTR_TYPE__)s->dtable);
+  bool whole = true;
+  for (uint32_t attempt = 0;; ++attempt) {
+    constexpr uint32_t kPieces = kRunMax * 16u / kThreads;
+    v4i q[kPieces];
+#pragma unroll
+    for (uint32_t j = 0; j < kPieces; ++j) {
+      const uint32_t k = (tid + j * kThreads) >> 4, slot = (uint32_t)((ticket + k) & cap_mask);
+      q[j] = Mem<POL_COHERENT>::ld16(rd, k < n ? slot * (uint32_t)sizeof(Record) + (tid & 15u) * 16u : kNoLoad);
+    }
+    uint64_t ent[kPieces];
+#pragma unroll
+    for (uint32_t j = 0; j < kPieces; ++j) {
+      // the table slot it claimed, from the lane that holds the words that name it
+      const uint32_t k = (tid + j * kThreads) >> 4, op = (uint32_t)q[j][0] & 0xffu, sel = ((uint32_t)q[j][3] >> 8) & 1u;
+      ent[j] = 0;
+      if ((tid & 15u) == 0 && k < n) ent[j] = __hip_atomic_load(&table[op].slot[sel], __ATOMIC_RELAXED, SC_SYSTEM);
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kPieces; ++j) {
+      const uint32_t k = (tid + j * kThreads) >> 4;
+      ((v4i*)recs)[tid + j * kThreads] = q[j];
+      const uint32_t x = record_piece_sum(q[j], tid & 15u);
+      // its ticket and version, in lanes 3 and 1 of the sixteen
+      const uint32_t t_lo = (uint32_t)__shfl((int)q[j][2], (int)((lane & 48u) + 3u)), t_hi = (uint32_t)__shfl((int)q[j][3], (int)((lane & 48u) + 3u));
+      const uint32_t version = (uint32_t)__shfl((int)q[j][1], (int)((lane & 48u) + 1u));
+      const uint64_t t = ticket + k;
+      const bool valid = x == record_check_seed(t) && t_lo == (uint32_t)t && t_hi == (uint32_t)(t >> 32);
+      if ((tid & 15u) == 0 && k < n) ok[k] = !valid ? 1u : ((uint32_t)(ent[j] >> 32) != version ? (uint32_t)GPUOS_E_VERSION : 0u);
+    }
+    __syncthreads();
+    whole = __ballot(lane < n && ok[lane] == 1u) == 0;
+    if (whole || attempt >= kMirrorRetries) break;
+    __syncthreads();                                     // everyone has looked at this attempt's copies
+    __builtin_amdgcn_s_sleep(2);
+  }
+  if (!whole) { __syncthreads(); return; }               // (dropped, as a lone descriptor that is never seen whole)
+  if (tid == 0 && status_v != GPUOS_OK) ok[0] = (uint32_t)status_v;
+  __syncthreads();
+  const uint32_t skip = (uint32_t)__ballot(lane < n && ok[lane] != 0);
+  const uint32_t per = uni(head->chunk), numel = uni(head->numel), begin = chunk * per, end = numel - begin < per ? numel : begin + per;
+  const uint32_t dt = uni(head->dtype[3]);
+  if (dt == GPUOS_F32) run_links<POL_COHERENT, GPUOS_F32>(recs, n, skip, begin, end, tid);
+  else if (dt == GPUOS_F16) run_links<POL_COHERENT, GPUOS_F16>(recs, n, skip, begin, end, tid);
+  else run_links<POL_COHERENT, GPUOS_BF16>(recs, n, skip, begin, end, tid);
+  drain_stores();
+  __syncthreads();                                       // every wave's stores of every task have reached memory
+  if (tid < 64) {
+    SlotState* const st = global_ptr(s->st);
+    uint64_t* const comp = global_ptr(s->hcomp);
+    const bool mine = lane < n;
+    const Record* r = recs + (mine ? lane : 0u);
+    const uint32_t nchunks = uni(head->nchunks);
+    const uint64_t t = ticket + lane, target = done_target(t, cap_shift);
+    const uint32_t slot = (uint32_t)(t & cap_mask);
+    bool last = mine;
+    if (mine && nchunks > 1) {
+      const uint64_t share = chunk + 1 == nchunks ? kDoneTask - (nchunks - 1) : 1ull;
+      last = __hip_atomic_fetch_add(&st[slot].done_seq, share, __ATOMIC_RELAXED, SC_AGENT) + share == target;
+    }
+    if (mine && nchunks <= 1) __hip_atomic_store(&st[slot].done_seq, target, __ATOMIC_RELAXED, SC_SYSTEM);
+    if (last) __hip_atomic_store(&comp[slot], pack_completion(t, (int32_t)ok[lane], r->version), __ATOMIC_RELAXED, SC_SYSTEM);
+    const uint64_t m = __ballot(last);
+    if (lane == 0 && m != 0) __hip_atomic_fetch_add(global_ptr(s->done_count), (uint64_t)__popcll(m), __ATOMIC_RELAXED, SC_AGENT);
+  }
+  __syncthreads();                                       // the descriptors and the scratch may be overwritten after this
+}
+
 // RING 0: the library's own workers, on the main unit ring, executing through EXEC = the built-in
 // chunk executor.  RING 1: the workers of a kernel compiled at run time, on the second unit ring
 // (the dispatcher routes the tasks of natively compiled operator programs there), executing through
@@ -2755,6 +2911,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
     s->state[0] = s->state[1] = s->state[2] = s->state[3] = 0;
     s->n_units = 0;
     s->st = a.st; s->hcomp = a.hcomp; s->done_count = &a.d->done_count; s->cap_shift = a.cap_shift;
+    s->dring = a.dring; s->dtable = a.dtable; s->cap_mask = a.cap_mask;
     for (uint32_t k = 0; k < ST_WORK_TICKS_TOTAL - ST_WORK_TICKS_WAIT; ++k) s->ticks[k] = 0;
   }
   lds_wave_sync();                                    // (only the first wavefront reads them)
@@ -2955,7 +3112,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
         __syncthreads();
         continue;
       }
-      if ((pair(head.links, 0) & 0xffffffffffffull) != 0 && !(head.rflags() & RF_DEPS_RESOLVED)) {
+      if ((pair(head.links, 0) & 0xffffffffffffull) != 0 &&    /* (dep[3]; the halfword behind them is `run`) */ !(head.rflags() & RF_DEPS_RESOLVED)) {
         // It names earlier tasks: it joins the units held, and the first wavefront looks at its done
         // words with the next poll (and runs it at once if they are all there).
         if (leader) {
@@ -2972,6 +3129,12 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
     if (status == GPUOS_OK && uni((uint32_t)(head.entry >> 32)) != word(head.impl, 1)) status = GPUOS_E_VERSION;
     if (status == GPUOS_OK) status = (int32_t)word(dec, 1);
     const uint64_t c3 = clock_if(timing);
+    if (RING == 0 && (uint32_t)head.links[1] >> 17 != 0) {      // a run of two or more tasks
+      exec_run(s, f, chunk, status, thread_index(wave));
+      if (leader) s->n_units += 1;
+      if (timing) { const uint64_t c4 = clock_if(timing); count(ST_WORK_TICKS_EXEC, c4 - c3); }
+      continue;
+    }
     // a task's start in the trace is the moment a workgroup took its descriptor (a unit that waited: when it began to)
     const uint64_t c_start = (tracing && action == kActRun) ? s->since[f] : c1;
     if (tracing && leader && chunk == 0 && nchunks > 1)

@@ -40,7 +40,8 @@ enum RecFlag : uint8_t {
   RF_FENCE = 1,          // dispatcher: publish only after every earlier ticket is done
   RF_VEC = 2,            // 16-byte vector access is safe (alignment and extents checked)
   RF_INT = 4,            // all tensors are I32
-  RF_DEPS_RESOLVED = 8   // set by the dispatcher: published only after the dependencies completed
+  RF_DEPS_RESOLVED = 8,  // set by the dispatcher: published only after the dependencies completed
+  RF_LINK = 16           // may be run by the workgroup that has just run the same chunk of the ticket right before (see LinkRun)
 };
 
 enum OperandKind : uint8_t { K_FULL = 0, K_ROWVEC = 1, K_ROWSCALAR = 2, K_TRANSPOSED = 3,
@@ -53,6 +54,7 @@ constexpr uint32_t kNoLoad = 0x7ffffff0u;      // a buffer offset past every res
 constexpr uint32_t kSmallTaskChunks = 4;       // a dependent task of at most this many chunks is published at once and waits in its workgroups
 constexpr uint32_t kDispatchBatch = 64;        // records mirrored per dispatcher pass
 constexpr uint32_t kThreads = 256;             // threads per workgroup of the worker
+constexpr uint32_t kRunMax = 32;               // tasks of a run (a head and the links behind it) that one workgroup takes together
 
 // The ring record ("compact descriptor", paper Section 4.1).  Written by the
 // host into the host ring; the dispatcher copies it into the device mirror and
@@ -77,7 +79,8 @@ struct alignas(16) Record {
   uint32_t red_n;            // reduction / row length
   float    alpha;
   uint16_t dep[3];
-  uint16_t pad1;
+  uint16_t run;              // tasks, this one and those right behind it, whose chunks are run together: its units stand for
+                             // all of theirs (0 or 1: it is alone; 0 in those behind it)  (dispatcher)
   uint64_t ticket;
   uint64_t ptr[4];           // in0, in1, in2, out (device addresses)
   uint32_t size[6];          // coalesced iteration shape (reductions: outer dims)
@@ -128,6 +131,15 @@ struct OpSlots {             // one logical operator: two slots + the version wo
   uint32_t version;          // 0 = unregistered
   uint32_t pad;
 };
+
+// The implementations that take part in runs: elementwise, one or two inputs, a few instructions.  (GELU, FMA
+// and operator programs keep executors of their own.)
+constexpr uint32_t kLinkUnary = (1u << GPUOS_IMPL_RELU) | (1u << GPUOS_IMPL_EXP) | (1u << GPUOS_IMPL_SCALE) | (1u << GPUOS_IMPL_COPY);
+constexpr uint32_t kLinkBinary = (1u << GPUOS_IMPL_ADD) | (1u << GPUOS_IMPL_SUB) | (1u << GPUOS_IMPL_MUL) | (1u << GPUOS_IMPL_DIV) |
+                                 (1u << GPUOS_IMPL_SUB_EXP);
+GPUOS_HD inline bool impl_links(uint32_t impl, uint32_t n_inputs) {
+  return impl < 32u && n_inputs <= 2u && (((n_inputs == 1u ? kLinkUnary : kLinkBinary) >> impl) & 1u) != 0;
+}
 
 // Control words.  HostCtl is written by the device and read by the host: it always lives in
 // fine-grained host memory.  DoorbellCtl is written by the host and polled by the dispatcher: it

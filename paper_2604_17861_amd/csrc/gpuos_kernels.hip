@@ -68,7 +68,7 @@ struct PendEntry {
   uint64_t ticket;
   PubEntry pub;
   uint16_t dep[3];
-  uint16_t pad;
+  uint16_t run;                            // tickets it stands for: this one and the links that run with it (>= 1)
 };
 
 // A staged record with a pitch of 68 words instead of 64: when the 64 lanes of a wavefront read the
@@ -150,7 +150,7 @@ DEV bool deps_complete(const WorkerArgs& a, uint64_t ticket, const uint16_t* dep
 DEV bool names_pending(const DispShared* s, uint64_t ticket, const uint16_t* dep) {
   const uint32_t np = s->npend;
   if (np == 0) return false;
-  const uint64_t first = s->pend[0].ticket, last = s->pend[np - 1].ticket;
+  const uint64_t first = s->pend[0].ticket, last = s->pend[np - 1].ticket + s->pend[np - 1].run - 1u;
   bool hit = false;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -158,12 +158,12 @@ DEV bool names_pending(const DispShared* s, uint64_t ticket, const uint16_t* dep
     if (back == 0 || back > ticket) continue;
     const uint64_t d = ticket - back;
     if (d < first || d > last) continue;
-    uint32_t lo = 0, hi = np;
+    uint32_t lo = 0, hi = np;                      // entries [0, lo) begin at or before d
     while (lo < hi) {
       const uint32_t mid = (lo + hi) >> 1;
-      if (s->pend[mid].ticket < d) lo = mid + 1; else hi = mid;
+      if (s->pend[mid].ticket <= d) lo = mid + 1; else hi = mid;
     }
-    hit = hit || (lo < np && s->pend[lo].ticket == d);
+    hit = hit || (lo > 0 && d - s->pend[lo - 1].ticket < s->pend[lo - 1].run);
   }
   return hit;
 }
@@ -559,8 +559,18 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
           rc.t_dequeue[0] = (uint32_t)tk0; rc.t_dequeue[1] = (uint32_t)(tk0 >> 32);
           if (op < GPUOS_MAX_OPS) atomicAdd(&s->opcnt[op], 1u);
         }
+        // A link goes with the record before it: no units of its own, and nothing to wait for but that one (a
+        // held head holds it, see below).  Only inside one pass, so that its mirror record is on its way
+        // before the units that stand for it are.  Not under tracing, whose records tell of
+        // one task at a time.
+        const uint64_t m_can = __ballot(status == GPUOS_OK && impl_links((uint32_t)e, rc.n_inputs));
+        const uint64_t m_mark = __ballot(!tracing && (rc.rflags & RF_LINK) != 0);
+        const uint64_t m_link = m_can & m_mark & (m_can << 1);
+        const bool link = (m_link >> tid) & 1u;
+        const uint64_t behind = tid < 63u ? ~(m_link >> (tid + 1u)) : ~0ull;
+        rc.run = (uint16_t)(link ? 0u : (uint32_t)__builtin_ctzll(behind) + 1u);
         uint32_t defer = 0;
-        if ((rc.dep[0] | rc.dep[1] | rc.dep[2]) != 0) {
+        if (!link && (rc.dep[0] | rc.dep[1] | rc.dep[2]) != 0) {
           if (rc.nchunks > kSmallTaskChunks) {
             // a large dependent task: its workers never wait; it is published once its
             // dependencies are complete (now, or later from the pending list)
@@ -608,11 +618,12 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
           if (m2 == m_def) break;
           m_def = m2;
         }
-        const uint64_t m_pub = __ballot(mine && !held);
+        const bool unit = mine && s->rec[tid].run != 0;            // (a link has no units)
+        const uint64_t m_pub = __ballot(unit && !held), m_pend = __ballot(unit && held);
         const uint64_t below = (1ull << tid) - 1ull;
         bool second = false;                                       // published now, on the second ring
         if (held) s->rec[tid].rflags |= RF_DEPS_RESOLVED;          // published only after its dependencies completed
-        if (mine) {
+        if (unit) {
           const Record& rc = s->rec[tid];
           PubEntry pe;
           pe.slot = (uint32_t)((mirrored + tid) & a.cap_mask);
@@ -624,18 +635,19 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
           pe.route = (rc.status == GPUOS_OK && rc.impl >= GPUOS_IMPL_PROGRAM_BASE && prog < GPUOS_MAX_PROGRAMS && s->native[prog] != 0) ? 1u : 0u;
           second = pe.route != 0 && !held;
           if (held) {
-            PendEntry& pd = s->pend[npend0 + (uint32_t)__popcll(m_def & below)];
+            PendEntry& pd = s->pend[npend0 + (uint32_t)__popcll(m_pend & below)];
             pd.ticket = mirrored + tid;
             pd.pub = pe;
             pd.dep[0] = rc.dep[0]; pd.dep[1] = rc.dep[1]; pd.dep[2] = rc.dep[2];
+            pd.run = rc.run;
           } else {
             s->pub[(uint32_t)__popcll(m_pub & below)] = pe;
           }
         }
         const uint64_t m_second = __ballot(second);
         if (tid == 0) {
-          st_deferred += (uint32_t)__popcll(m_def);
-          s->npend = npend0 + (uint32_t)__popcll(m_def);
+          st_deferred += (uint32_t)__popcll(m_pend);
+          s->npend = npend0 + (uint32_t)__popcll(m_pend);
           s->npub = (uint32_t)__popcll(m_pub);
           s->npub_second = m_second != 0 ? 1u : 0u;
         }

@@ -615,6 +615,54 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   return packed(rec, r);
 }
 
+// Runs: which tasks of one submit may be run by the workgroup that has just run the same chunk of the
+// task right before (RF_LINK; the dispatcher decides, links inside one of its passes go with the record
+// before them).  A link names the task right before it and nothing else, reads what that one
+// writes, and both are elementwise over contiguous aligned buffers of one size and dtype.  A chunk of it
+// then runs while other chunks of the tasks before it have not: so any two buffers of a run begin at the
+// same address (an element depends on itself only) or do not overlap.  Its chunks are the head's.
+struct LinkRun {
+  uint32_t len = 0;                              // tasks in the run that is being built (0: none)
+  uint32_t n = 0;
+  uint64_t base[6];                              // its buffers, each `bytes` long
+  uint64_t bytes = 0;
+  // the record's buffers join the run's; false if one overlaps another in part, or there are too many
+  bool take(const Record& r) {
+    for (int k = 0; k < 4; ++k) {
+      if (k < 3 && k >= r.n_inputs) continue;
+      bool known = false;
+      for (uint32_t j = 0; j < n; ++j) {
+        if (base[j] == r.ptr[k]) { known = true; break; }
+        if (r.ptr[k] - base[j] + bytes - 1u < 2u * bytes - 1u) return false;      // less than `bytes` apart, either way
+      }
+      if (known) continue;
+      if (n == sizeof(base) / sizeof(base[0])) return false;
+      base[n++] = r.ptr[k];
+    }
+    return true;
+  }
+  static bool can(const Record& r) { return r.path == PATH_CONTIG && (r.rflags & (RF_VEC | RF_INT)) == RF_VEC && impl_links(r.impl, r.n_inputs); }
+  // prev -> r, in this order in one submit
+  bool links(const Record& prev, Record& r) {
+    const uint32_t d01 = r.dep[0] | r.dep[1] | r.dep[2];
+    const bool ok = d01 == 1u && can(r) && !(r.rflags & RF_FENCE) && r.numel == prev.numel && r.dtype[3] == prev.dtype[3] &&
+                    (r.ptr[0] == prev.ptr[3] || (r.n_inputs == 2 && r.ptr[1] == prev.ptr[3]));
+    if (!ok || len == kRunMax) { len = 0; return false; }
+    if (len == 0) {                                // prev heads it
+      n = 0;
+      bytes = (uint64_t)prev.numel * dtype_size(prev.dtype[3]);
+      if (!can(prev) || !take(prev)) return false;
+      len = 1;
+    }
+    if (!take(r)) { len = 0; return false; }
+    ++len;
+    r.rflags |= RF_LINK;
+    r.chunk = prev.chunk;
+    r.nchunks = prev.nchunks;
+    return true;
+  }
+};
+
 struct OpInfo {
   uint32_t impl = 0;
   uint32_t version = 0;            // 0 = unregistered
@@ -1565,6 +1613,7 @@ int submit_impl(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, uint64_t* out
   } catch (const std::bad_alloc&) {                             // no exception may cross the C boundary
     return GPUOS_E_NOMEM;
   }
+  LinkRun run;
   for (uint32_t i = 0; i < n; ++i) {
     const gpuos_task& t = tasks[i];
     uint32_t impl = GPUOS_IMPL_NONE;
@@ -1582,6 +1631,7 @@ int submit_impl(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, uint64_t* out
     if (rc != GPUOS_OK) return rc;
     for (int k = 0; k < 3; ++k)
       if (t.dep[k] >= c->cap) return GPUOS_E_INVAL;
+    if (i != 0) run.links(staged[i - 1], staged[i]);
     // The part of the check word that does not depend on the ticket: the weighted sum of the
     // other 63 words, with the record's ticket field zero (the ticket enters through the seed only).
     staged[i].ticket = 0;

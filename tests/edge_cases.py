@@ -141,3 +141,77 @@ def gelu_values(code):
         b.add(name, b.pool(np.zeros_like(v)), [x])
         b.add(name, b.pool(np.zeros((7, y.shape[1] + 1), v.dtype))[:, 1:], [y])
     return b.stream("gelu_values_%d" % code)
+
+
+def chains(code, seed):
+    """Chains of dependent elementwise tasks over flat buffers of one length (each names the task right
+    before it), at lengths round the vector, the chunk and the block of a run, with what ends a run or keeps
+    a task out of one: operands that overlap another one in part, other lengths, an operator of another
+    kind, a further dependency, a task outside that names a task in the middle.  Exactly rounded
+    operations: the buffers at the end are those of sequential execution, byte for byte."""
+    rng = np.random.default_rng(1000 * code + seed)
+    b = Builder()
+    es = 4 if code == S.F32 else 2
+    V = 16 // es
+    lengths = [1, V - 1, V, 255 * V + 1, 1024, 4096, 4096 + V + 3, 6144, 12288 + 5, 16384, 50001]
+    for n in lengths:
+        pad = (n + 64) // 64 * 64
+        live = b.pool(to_dtype(rng.integers(-3, 4, 6 * pad).astype(np.float32), code))
+        const = b.pool(to_dtype(rng.integers(-1, 2, 2 * pad).astype(np.float32), code))
+        side = b.pool(to_dtype(np.zeros(4 * pad, np.float32), code))
+        at = lambda k: live[k * pad: k * pad + n]
+        cur, n_side = 0, 0
+        for t in range(70):
+            dep = (1, 0, 0) if t else (0, 0, 0)
+            x, o = at(cur), int(rng.integers(4))
+            kind, other = rng.random(), int(rng.integers(4))
+            if kind < 0.13 and o in (cur, other):            # (a task's own operands are the same elements or none in common)
+                kind = 1.0
+            out = at(o)
+            if kind < 0.06:                                  # written one vector further on: overlaps what the run has touched
+                out = live[o * pad + V: o * pad + V + n]
+                nxt = None
+            elif kind < 0.10 and n > 2 * V:                  # a shorter task in the chain
+                x, out, nxt = x[: n - V], out[: n - V], o
+            elif kind < 0.13:                                # misaligned by an element
+                out = live[o * pad + 1: o * pad + 1 + n]
+                nxt = None
+            else:
+                nxt = o
+            op = str(rng.choice(["ADD", "SUB", "RELU", "SCALE", "COPY", "MUL", "ADD", "FMA"]))
+            c = const[pad * int(rng.integers(2)):][: x.size]
+            if op in ("ADD", "SUB", "MUL"):
+                if op == "ADD" and rng.random() < 0.2:
+                    c = at(other)[: x.size]                  # a second live buffer (or the same one)
+                ins = [x, c] if rng.random() < 0.7 else [c, x]
+            elif op == "FMA":
+                ins = [x, const[:x.size], c]
+            else:
+                ins = [x]
+            if t > 5 and rng.random() < 0.08:
+                dep = (1, int(rng.integers(2, 6)), 0)
+            b.add(op, out, ins, alpha=0.5 if op == "SCALE" else 0.0, dep=dep)
+            if t > 3 and n_side < 4 and rng.random() < 0.05 and nxt is not None:
+                # a reader outside the chain, of a task in the middle of a run
+                b.add("COPY", side[n_side * pad: n_side * pad + n], [at(nxt)], dep=(1, 0, 0))
+                n_side += 1
+            cur = nxt if nxt is not None else o
+    return b.stream("chains_%d_%d" % (code, seed), batch=128)
+
+
+def long_chains(code, n, links=150):
+    """One chain after the other as a program issues them: x op c into two buffers in turn."""
+    rng = np.random.default_rng(n)
+    b = Builder()
+    pad = (n + 64) // 64 * 64
+    for _ in range(4):
+        x = b.pool(to_dtype(rng.uniform(-1, 1, n).astype(np.float32), code))
+        c = b.pool(to_dtype(rng.uniform(-1, 1, n).astype(np.float32), code))
+        t = b.pool(to_dtype(np.zeros(2 * pad, np.float32), code))
+        cur = x
+        for k in range(links):
+            op = ("ADD", "MUL", "RELU", "SCALE", "SUB", "DIV", "COPY")[k % 7]
+            out = t[(k & 1) * pad:][:n]
+            b.add(op, out, [cur, c] if op in ("ADD", "MUL", "SUB", "DIV") else [cur], alpha=0.99, dep=(1, 0, 0) if k else (0, 0, 0))
+            cur = out
+    return b.stream("long_chains_%d_%d" % (code, n), batch=128)
