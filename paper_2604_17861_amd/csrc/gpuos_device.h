@@ -459,7 +459,7 @@ template <int DT, int K> struct MixArg {
 
 // K vectors of an elementwise operation: floats through fp32, I32 word by word, COPY as it is (bits).
 // Each result goes to sink(u, vector) as soon as it is there.
-template <int IMPL, int DT, int K, class A, class S> DEV void ew_vectors(const A& a, const A& b, const A& c, float alpha, S sink) {
+template <int IMPL, int DT, int K, class A, class B, class C, class S> DEV void ew_vectors(const A& a, const B& b, const C& c, float alpha, S sink) {
   using E = Elem<DT>;
   constexpr int V = E::V;
 #pragma unroll
@@ -492,13 +492,13 @@ template <int IMPL, int DT, int K, class A, class S> DEV void ew_vectors(const A
 // becomes a chain that is walked case by case, and each further path put 0.25 us on every unit.)
 template <int IMPL> struct FixedOp {
   static constexpr int N = Op<IMPL>::N;
-  template <int DT, int K, class A, class S> static DEV void vectors(uint32_t, const A& a, const A& b, const A& c, float alpha, S sink) {
+  template <int DT, int K, class A, class B, class C, class S> static DEV void vectors(uint32_t, const A& a, const B& b, const C& c, float alpha, S sink) {
     ew_vectors<IMPL, DT, K>(a, b, c, alpha, sink);
   }
 };
 template <int ARITY> struct ByArity {
   static constexpr int N = ARITY;
-  template <int DT, int K, class A, class S> static DEV void vectors(uint32_t impl, const A& a, const A& b, const A& c, float alpha, S sink) {
+  template <int DT, int K, class A, class B, class C, class S> static DEV void vectors(uint32_t impl, const A& a, const B& b, const C& c, float alpha, S sink) {
     if constexpr (DT == GPUOS_I32) {
       if constexpr (N == 1) ew_vectors<GPUOS_IMPL_COPY, DT, K>(a, b, c, alpha, sink);
       else if (impl == GPUOS_IMPL_ADD) ew_vectors<GPUOS_IMPL_ADD, DT, K>(a, b, c, alpha, sink);
@@ -2576,6 +2576,20 @@ DEV void run_reduction(const Record* r, const RecHead& h, uint32_t chunk, float*
   }
 }
 
+// The interpreter's executors, behind one call: in the worker loop itself they were 66 of its 292 call sites,
+// each of which costs every unit (see rowop_other).  Calls, not jumps: an executor that is jumped to has to
+// keep its caller's registers, one that is only called leaves that to its caller, which has few.
+template <int POL>
+__attribute__((disable_tail_calls)) PATHFN void run_program_chunk(const Record* r_v, uint32_t n_in_v, uint32_t chunk_v, float* s_v, uint32_t tid) {
+  const Record* r = lds_arg(r_v);
+  float* s = lds_arg(s_v);
+  const RecHead h = RecHead::of(r);
+  const uint32_t n_in = uni(n_in_v), chunk = uni(chunk_v);
+  if (n_in == 1) run_elementwise<POL, kImplProg1>(r, h, chunk, s, tid);
+  else if (n_in == 2) run_elementwise<POL, kImplProg2>(r, h, chunk, s, tid);
+  else run_elementwise<POL, kImplProg3>(r, h, chunk, s, tid);
+}
+
 // A task whose operator is a program: fetch the program into LDS (17 lanes x 16 bytes), then run
 // the ordinary elementwise paths with the interpreter as their functor.
 template <int POL>
@@ -2589,9 +2603,7 @@ DEV int32_t exec_program(const Record* r, const RecHead& h, uint32_t impl, uint3
   const uint32_t n_in = uni(g_prog.n_inputs), n_instr = uni(g_prog.n_instr);
   if (uni(g_prog.ready) != kProgramReady || n_instr < 1 || n_instr > GPUOS_PROGRAM_MAX_INSTR || n_in != uni(r->n_inputs))
     status = GPUOS_E_INVAL;                            // never defined (or not what the task was packed for)
-  else if (n_in == 1) run_elementwise<POL, kImplProg1>(r, h, chunk, s_red, tid);
-  else if (n_in == 2) run_elementwise<POL, kImplProg2>(r, h, chunk, s_red, tid);
-  else run_elementwise<POL, kImplProg3>(r, h, chunk, s_red, tid);
+  else run_program_chunk<POL>(r, n_in, chunk, s_red, tid);
   __syncthreads();                                     // the next chunk may bring another program
   return status;
 }
@@ -2742,74 +2754,211 @@ DEV void fetch_descriptor(const WorkerArgs& a, WorkShared* s, rsrc_t rd, uint64_
 }
 
 // ---------------------------------------------------------------------------
-// runs: a chain of elementwise tasks over buffers of one size, each reading what the one before it wrote.
-// Its units stand for all of its tasks: the workgroup that has run a chunk of one runs the same chunk
-// of the next, and what it wrote is still in its registers.  What a link cost when every task had units
-// of its own was five memory latencies in a row (done word, poll, operands, stores, their acknowledgement),
-// 5.5 us; here it costs its arithmetic and the issue of its stores, which nothing waits for before the run ends.
-// The host vouches (links()) that any two operands of the run begin at the same address or do not
-// overlap, so a lane meets only its own elements.
+// runs: a chain of tasks over buffers of one shape, each reading what the one before it wrote.  Its units
+// stand for all of its tasks: the workgroup that has run a chunk of one runs the same chunk of the
+// next, and what it wrote is still in its registers.  What a link costs when every task has units of
+// its own is five memory latencies in a row (done word, poll, operands, stores, their acknowledgement),
+// 5.5 us; in a run it costs its arithmetic and the issue of its stores, which nothing waits for before the
+// run ends, and the bytes it would have read again.
+// The host vouches (LinkRun) that any two operands of the run begin at the same address or do not
+// overlap, so a lane meets only its own elements, and a row's lanes only their own row.
 // ---------------------------------------------------------------------------
-template <int POL, int DT>
-DEV void run_links(const Record* recs, uint32_t n_links, uint32_t skip, uint32_t begin, uint32_t end, uint32_t tid) {
+template <int DT, int K> struct EitherArg {              // vectors of one of two sets of registers
+  const v4i (&p)[K], (&q)[K];
+  bool second;
+  DEV v4i raw(int u) const { return second ? q[u] : p[u]; }
+  DEV float get(int u, int k) const { return Elem<DT>::get(raw(u), k); }
+};
+template <int K> struct RowArg {                         // one scalar per vector (of its row)
+  const float (&w)[K];
+  DEV v4i raw(int) const { return v4i{0, 0, 0, 0}; }
+  DEV float get(int u, int) const { return w[u]; }
+};
+template <int RIMPL, int DT, int K> DEV void link_reduce(const EitherArg<DT, K>& q, bool act, uint32_t width, float (&out)[K]) {
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    float acc = red_identity<RIMPL, float>();
+    bool nan = false;
+    if (act) acc = red_vector<RIMPL, DT>(q.raw(u), 0, 0, 0, false, acc, nan);
+    out[u] = wave_reduce<RIMPL>(red_finish<RIMPL>(acc, nan), width);
+  }
+}
+
+// The chunk of every task of a run, block by block: U vectors a lane, all tasks of the run on one block before
+// the next.  ROWS false: elements [begin, end) of flat buffers, a lane per vector, the ragged end an
+// element per lane (kept as vector U).  ROWS true: rows [begin, end) of n elements, whole vectors, P lanes a row as in
+// rowop_fused; then reductions take part and leave their results in registers as one scalar per row.
+template <int POL, int DT, bool ROWS>
+PATHFN void run_links(const Record* recs_v, uint32_t n_links_v, uint64_t skip_v, uint32_t begin_v, uint32_t end_v, uint32_t n_v, uint32_t tid) {
+  const Record* recs = lds_arg(recs_v);
+  const uint64_t skip = uni64(skip_v);
+  const uint32_t n_links = uni(n_links_v), begin = uni(begin_v), end = uni(end_v), n = uni(n_v);
   using E = Elem<DT>;
   using M = Mem<POL>;
-  constexpr uint32_t V = E::V, U = 4;
-  const uint32_t nvec = (end - begin) / V, tail = (end - begin) % V, bytes = (end - begin) * E::ES;
-  const uint64_t boff = (uint64_t)begin * E::ES;
+  constexpr uint32_t V = E::V, U = 4, K = ROWS ? U : U + 1;
+  const uint32_t len = ROWS ? n : 1u;                    // elements per counted unit
+  const uint32_t bytes = (end - begin) * len * E::ES, nvec = bytes / 16u, tail = ROWS ? 0u : (end - begin) % V;
+  const uint64_t boff = (uint64_t)begin * len * E::ES;
+  const uint32_t lane = tid & 63u, wave = tid >> 6;
+  uint32_t P = 1;
+  if (ROWS) while (P < n / V) P <<= 1;
+  const uint32_t rpw = 64u / P, sub = lane / P, j = lane & (P - 1u);
+  const bool col = !ROWS || j < n / V;                   // (a row's lanes past its last vector)
   auto ld1 = [](rsrc_t r, uint32_t off) { return E::ES == 4 ? M::ldb4(r, off) : M::ldb2(r, off); };
-  for (uint32_t v0 = 0;; v0 += U * kThreads) {
-    const bool last = v0 + U * kThreads >= nvec;
-    uint32_t off[U];
+  // What a task asks for, in lane k for task k: a read of a lane costs a link less than reads of LDS, whose latency
+  // nothing hides.  (Not for rows, whose links are longer, and short of registers.)
+  uint32_t h_ptr[3][2] = {}, h_what = 0, h_alpha = 0, h_C = 0;
+  if (!ROWS && lane < n_links) {
+    const Record* r = recs + lane;
+    const v4i p01 = ((const v4i*)r->ptr)[0], p23 = ((const v4i*)r->ptr)[1];
+    h_ptr[0][0] = (uint32_t)p01[0]; h_ptr[0][1] = (uint32_t)p01[1]; h_ptr[1][0] = (uint32_t)p01[2]; h_ptr[1][1] = (uint32_t)p01[3];
+    h_ptr[2][0] = (uint32_t)p23[2]; h_ptr[2][1] = (uint32_t)p23[3];
+    const uint32_t path = r->path, kinds = path == PATH_ROW2D ? (uint32_t)r->okind[0] | ((uint32_t)r->okind[1] << 4) : 0u;
+    static_assert(K_FULL == 0, "operands of the other paths are whole");
+    h_what = r->impl | (path << 8) | ((uint32_t)r->n_inputs << 12) | (kinds << 16) | ((uint32_t)r->dtype[1] << 24) | ((uint32_t)r->dtype[3] << 28);
+    h_alpha = __builtin_bit_cast(uint32_t, r->alpha);
+    h_C = r->size[1];
+  }
+  auto at_lane = [](uint32_t v, uint32_t k) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k); };
+  auto ptr_of = [&](uint32_t k, int i) {                 // input 0 or 1, or (2) the output
+    if (ROWS) return (uint64_t)(__UINTPTR_TYPE__)uni_ptr(recs[k].ptr[i == 2 ? 3 : i]);
+    return ((uint64_t)at_lane(h_ptr[i][1], k) << 32) | at_lane(h_ptr[i][0], k);
+  };
+  auto what_of = [&](uint32_t k) {
+    if (!ROWS) return at_lane(h_what, k);
+    const RecHead h = RecHead::of(recs + k);             // (bytes 0-15: inputs 4, dtypes 6 and 8, kinds 10 and 11)
+    const uint32_t path = h.path(), w1 = uni((uint32_t)h.op[1]), w2 = uni((uint32_t)h.op[2]);
+    const uint32_t kinds = path == PATH_ROW2D ? ((w2 >> 16) & 15u) | (((w2 >> 24) & 15u) << 4) : 0u;
+    return uni(recs[k].impl) | (path << 8) | ((w1 & 15u) << 12) | (kinds << 16) | (((w1 >> 16) & 15u) << 24) | ((w2 & 15u) << 28);
+  };
+  static_assert(__builtin_offsetof(Record, n_inputs) == 4 && __builtin_offsetof(Record, okind) == 10, "the words of what_of");
+  auto C_of = [&](uint32_t k) { return ROWS ? uni(recs[k].size[1]) : at_lane(h_C, k); };
+  auto alpha_of = [&](uint32_t k) { return __builtin_bit_cast(float, ROWS ? uni(__builtin_bit_cast(uint32_t, recs[k].alpha)) : at_lane(h_alpha, k)); };
+  // The first tasks' operands from outside the run (a mask, the other operand of an update): one of them is
+  // requested with the head's first operand.  (A load behind the first stores is waited for behind them.)
+  const uint64_t head_p = ptr_of(0, 0);
+  const uint32_t head_kind = (what_of(0) >> 16) & 15u, head_C = C_of(0);
+  uint64_t ext_p = 0;
+  uint32_t ext_kind = 0, ext_C = 0;
+#pragma unroll 1
+  for (uint32_t k = 0; k < n_links && k < 3u && ext_p == 0; ++k) {
+    const uint32_t what = what_of(k);
+    auto outside = [&](uint64_t p, uint32_t kind) {
+      if (ext_p != 0 || kind == K_ROWSCALAR || p == head_p || (k > 0 && p == ptr_of(0, 2)) || (k > 1 && p == ptr_of(1, 2))) return;
+      ext_p = p; ext_kind = kind; ext_C = C_of(k);
+    };
+    if (k > 0) outside(ptr_of(k, 0), (what >> 16) & 15u);
+    if (((what >> 12) & 15u) == 2u) outside(ptr_of(k, 1), (what >> 20) & 15u);
+  }
+  for (uint32_t b0 = ROWS ? begin : 0u;;) {
+    const bool last = ROWS ? b0 + 4u * rpw * U >= end : b0 + U * kThreads >= nvec;
+    uint32_t off[U], row[U];
 #pragma unroll
-    for (uint32_t u = 0; u < U; ++u) off[u] = v0 + tid + u * kThreads < nvec ? (v0 + tid + u * kThreads) * 16u : kNoLoad;
-    const uint32_t off1 = last && tid < tail ? (nvec * V + tid) * E::ES : kNoLoad;      // an element of the ragged end (vector U holds it)
-    // what the registers hold: the buffer that `cur` and `oth` were read from or written to
-    v4i cur[U + 1], oth[U + 1];
-    uint64_t cur_p = 0, oth_p = 0;
-    auto load = [&](v4i (&q)[U + 1], uint64_t p) {
+    for (uint32_t u = 0; u < U; ++u) {
+      if (ROWS) {
+        row[u] = b0 + (u * 4u + wave) * rpw + sub;
+        off[u] = col && row[u] < end ? ((row[u] - begin) * (n / V) + j) * 16u : kNoLoad;
+      } else {
+        off[u] = b0 + tid + u * kThreads < nvec ? (b0 + tid + u * kThreads) * 16u : kNoLoad;
+      }
+    }
+    const uint32_t off1 = !ROWS && last && tid < tail ? (nvec * V + tid) * E::ES : kNoLoad;
+    // what the registers hold: the buffer that `cur`, `oth` and `sc` were read from or written to
+    v4i cur[K], oth[K];
+    float sc[U];
+    uint64_t cur_p = 0, oth_p = 0, sc_p = 0;
+    auto load = [&](v4i (&q)[K], uint64_t p, uint32_t kind, uint32_t C) {
+      if (kind == K_ROWVEC) {                            // C elements over and over
+        const rsrc_t rs = make_rsrc((const void*)(__UINTPTR_TYPE__)p, C * E::ES);
+        const uint32_t cv = C / V, first = (uint32_t)(boff / 16u);         // (a task has less than 2^31 elements)
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) q[u] = M::ld16(rs, off[u] != kNoLoad ? (first + off[u] / 16u) % cv * 16u : kNoLoad);
+        if constexpr (!ROWS) q[U] = v4i{0, 0, 0, 0};     // (whole vectors: no ragged end)
+        return;
+      }
       const rsrc_t rs = make_rsrc((const char*)(__UINTPTR_TYPE__)p + boff, bytes);
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) q[u] = M::ld16(rs, off[u]);
-      q[U] = v4i{(int)ld1(rs, off1), 0, 0, 0};
+      if constexpr (!ROWS) q[U] = v4i{(int)ld1(rs, off1), 0, 0, 0};
     };
+    // Loaded vectors are waited for where they are loaded.  Left to the compiler, which does not see on which way
+    // round the loop it came to a use, every link waited for the stores of the one before.
+    auto arrive = [&](v4i (&q)[K]) {
+#pragma unroll
+      for (uint32_t u = 0; u < K; ++u) asm volatile("" : "+v"(q[u]));
+    };
+    load(cur, head_p, head_kind, head_C);
+    cur_p = head_p;
+    if (ext_p != 0) { load(oth, ext_p, ext_kind, ext_C); oth_p = ext_p; arrive(oth); }
+    arrive(cur);
     for (uint32_t k = 0; k < n_links; ++k) {
-      const Record* r = recs + k;
-      const uint64_t p0 = (uint64_t)(__UINTPTR_TYPE__)uni_ptr(r->ptr[0]), p1 = (uint64_t)(__UINTPTR_TYPE__)uni_ptr(r->ptr[1]);
-      const uint64_t po = (uint64_t)(__UINTPTR_TYPE__)uni_ptr(r->ptr[3]);
-      const uint32_t impl = uni(r->impl);
-      const float alpha = __builtin_bit_cast(float, uni(__builtin_bit_cast(uint32_t, r->alpha)));
-      const bool two = uni(r->n_inputs) == 2u;
+      const uint64_t p0 = ptr_of(k, 0), p1 = ptr_of(k, 1), po = ptr_of(k, 2);
+      const uint32_t what = what_of(k), impl = what & 0xffu, path = (what >> 8) & 15u, C = C_of(k);
+      const float alpha = alpha_of(k);
+      const bool two = ((what >> 12) & 15u) == 2u;
+      const uint32_t kind0 = (what >> 16) & 15u, kind1 = (what >> 20) & 15u;
+      const bool scalar = ROWS && two && kind1 == K_ROWSCALAR, pair = two && !scalar;
       if ((skip >> k) & 1u) continue;                    // (completes with an error, writes nothing)
-      const bool b_cur = two && p1 == cur_p;
+      const bool b_cur = pair && p1 == cur_p;
       bool a_cur = p0 == cur_p;
       if (!a_cur && p0 != oth_p) {
-        if (b_cur) { load(oth, p0); oth_p = p0; }
-        else { load(cur, p0); cur_p = p0; a_cur = true; }
+        if (b_cur) { load(oth, p0, kind0, C); oth_p = p0; arrive(oth); }
+        else { load(cur, p0, kind0, C); cur_p = p0; a_cur = true; arrive(cur); }
       }
       bool b_oth = false;
-      if (two && p1 != cur_p) {
+      if (pair && p1 != cur_p) {
         if (p1 == oth_p) b_oth = true;
-        else if (a_cur) { load(oth, p1); oth_p = p1; b_oth = true; }
-        else { load(cur, p1); cur_p = p1; }
+        else if (a_cur) { load(oth, p1, kind1, C); oth_p = p1; b_oth = true; arrive(oth); }
+        else { load(cur, p1, kind1, C); cur_p = p1; arrive(cur); }
       }
-      v4i qa[U + 1], qb[U + 1];
+      typedef EitherArg<DT, K> Arg;
+      const Arg qa = {cur, oth, !a_cur}, qb = {cur, oth, b_oth};
+      if constexpr (ROWS) {
+        if (path == PATH_RED_CONTIG) {
+          if (impl == GPUOS_IMPL_SUM_LAST) link_reduce<GPUOS_IMPL_SUM_LAST, DT>(qa, col, P, sc);
+          else if (impl == GPUOS_IMPL_MAX_LAST) link_reduce<GPUOS_IMPL_MAX_LAST, DT>(qa, col, P, sc);
+          else link_reduce<GPUOS_IMPL_MIN_LAST, DT>(qa, col, P, sc);
+          const uint32_t odt = what >> 28;
 #pragma unroll
-      for (uint32_t u = 0; u <= U; ++u) { qa[u] = a_cur ? cur[u] : oth[u]; qb[u] = b_oth ? oth[u] : cur[u]; }
+          for (uint32_t u = 0; u < U; ++u) {
+            const bool mine = j == 0 && row[u] < end;
+            const uint32_t at = row[u] - begin;
+            if (odt == GPUOS_F32) {
+              M::stb4(make_rsrc((const char*)(__UINTPTR_TYPE__)po + (uint64_t)begin * 4u, (end - begin) * 4u), mine ? at * 4u : kNoLoad, __builtin_bit_cast(uint32_t, sc[u]));
+            } else {
+              const uint32_t h = odt == GPUOS_F16 ? f2h(sc[u]) : f2b(sc[u]);
+              M::stb2(make_rsrc((const char*)(__UINTPTR_TYPE__)po + (uint64_t)begin * 2u, (end - begin) * 2u), mine ? at * 2u : kNoLoad, h);
+              sc[u] = odt == GPUOS_F16 ? h2f(h) : b2f(h);
+            }
+          }
+          sc_p = po;
+          continue;
+        }
+        if (scalar && p1 != sc_p) {                      // a scalar per row from memory
+          const uint32_t sdt = (what >> 24) & 15u;
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) sc[u] = row[u] < end ? load_rt<POL>((const void*)(__UINTPTR_TYPE__)p1, row[u], sdt) : 0.0f;
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) asm volatile("" : "+v"(sc[u]));
+          sc_p = p1;
+        }
+      }
       const rsrc_t ro = make_rsrc((const char*)(__UINTPTR_TYPE__)po + boff, bytes);
       auto sink = [&](int u, const v4i& q) {
-        if (u < (int)U) M::st16(ro, off[u], q);
+        if (u < (int)U) M::st16(ro, off[u < (int)U ? u : 0], q);
         else if (E::ES == 4) M::stb4(ro, off1, (uint32_t)q[0]);
         else M::stb2(ro, off1, (uint32_t)q[0]);
         cur[u] = q;
+        __builtin_amdgcn_sched_barrier(0);               // (a vector at a time: interleaved they need registers that callers keep)
       };
-      typedef VecArg<DT, U + 1> Arg;
-      if (two) ByArity<2>::template vectors<DT, U + 1>(impl, Arg{qa}, Arg{qb}, Arg{qa}, alpha, sink);
-      else ByArity<1>::template vectors<DT, U + 1>(impl, Arg{qa}, Arg{qa}, Arg{qa}, alpha, sink);
+      if (!two) ByArity<1>::template vectors<DT, K>(impl, qa, qa, qa, alpha, sink);
+      else if (pair) ByArity<2>::template vectors<DT, K>(impl, qa, qb, qa, alpha, sink);
+      else if constexpr (ROWS) ByArity<2>::template vectors<DT, K>(impl, qa, RowArg<K>{sc}, qa, alpha, sink);
       cur_p = po;
       if (oth_p == po) oth_p = 0;
     }
     if (last) break;
+    b0 += ROWS ? 4u * rpw * U : U * kThreads;
   }
 }
 
@@ -2864,12 +3013,30 @@ PATHFN void exec_run(WorkShared* s_v, uint32_t f_v, uint32_t chunk_v, int32_t st
   if (!whole) { __syncthreads(); return; }               // (dropped, as a lone descriptor that is never seen whole)
   if (tid == 0 && status_v != GPUOS_OK) ok[0] = (uint32_t)status_v;
   __syncthreads();
-  const uint32_t skip = (uint32_t)__ballot(lane < n && ok[lane] != 0);
-  const uint32_t per = uni(head->chunk), numel = uni(head->numel), begin = chunk * per, end = numel - begin < per ? numel : begin + per;
-  const uint32_t dt = uni(head->dtype[3]);
-  if (dt == GPUOS_F32) run_links<POL_COHERENT, GPUOS_F32>(recs, n, skip, begin, end, tid);
-  else if (dt == GPUOS_F16) run_links<POL_COHERENT, GPUOS_F16>(recs, n, skip, begin, end, tid);
-  else run_links<POL_COHERENT, GPUOS_BF16>(recs, n, skip, begin, end, tid);
+  const uint64_t skip = __ballot(lane < n && ok[lane] != 0);
+  // rows, if one of the tasks reduces rows or has a scalar per row: their length, and the head's chunk in rows
+  uint32_t row_n = 0;
+  if (lane < n) {
+    const Record* r = recs + lane;
+    if (r->path == PATH_RED_CONTIG) row_n = r->red_n;
+    else if (r->path == PATH_ROW2D && r->okind[1] == K_ROWSCALAR) row_n = r->size[1];
+  }
+  const uint64_t m_rows = __ballot(row_n != 0);
+  const uint32_t len = m_rows != 0 ? (uint32_t)__builtin_amdgcn_readlane((int)row_n, (int)__builtin_ctzll(m_rows)) : 0u;
+  const bool counts_rows = uni(head->path) == PATH_RED_CONTIG;
+  uint32_t per = uni(head->chunk), numel = uni(head->numel);
+  if (len != 0 && !counts_rows) { per /= len; numel /= len; }
+  const uint32_t begin = chunk * per, end = numel - begin < per ? numel : begin + per;
+  const uint32_t dt = uni(head->dtype[0]);
+  if (len == 0) {
+    if (dt == GPUOS_F32) run_links<POL_COHERENT, GPUOS_F32, false>(recs, n, skip, begin, end, 0, tid);
+    else if (dt == GPUOS_F16) run_links<POL_COHERENT, GPUOS_F16, false>(recs, n, skip, begin, end, 0, tid);
+    else run_links<POL_COHERENT, GPUOS_BF16, false>(recs, n, skip, begin, end, 0, tid);
+  } else {
+    if (dt == GPUOS_F32) run_links<POL_COHERENT, GPUOS_F32, true>(recs, n, skip, begin, end, len, tid);
+    else if (dt == GPUOS_F16) run_links<POL_COHERENT, GPUOS_F16, true>(recs, n, skip, begin, end, len, tid);
+    else run_links<POL_COHERENT, GPUOS_BF16, true>(recs, n, skip, begin, end, len, tid);
+  }
   drain_stores();
   __syncthreads();                                       // every wave's stores of every task have reached memory
   if (tid < 64) {

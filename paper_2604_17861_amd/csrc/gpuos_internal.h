@@ -54,7 +54,7 @@ constexpr uint32_t kNoLoad = 0x7ffffff0u;      // a buffer offset past every res
 constexpr uint32_t kSmallTaskChunks = 4;       // a dependent task of at most this many chunks is published at once and waits in its workgroups
 constexpr uint32_t kDispatchBatch = 64;        // records mirrored per dispatcher pass
 constexpr uint32_t kThreads = 256;             // threads per workgroup of the worker
-constexpr uint32_t kRunMax = 32;               // tasks of a run (a head and the links behind it) that one workgroup takes together
+constexpr uint32_t kRunMax = 64;               // tasks of a run (a head and the links behind it) that one workgroup takes together
 
 // The ring record ("compact descriptor", paper Section 4.1).  Written by the
 // host into the host ring; the dispatcher copies it into the device mirror and
@@ -132,13 +132,15 @@ struct OpSlots {             // one logical operator: two slots + the version wo
   uint32_t pad;
 };
 
-// The implementations that take part in runs: elementwise, one or two inputs, a few instructions.  (GELU, FMA
-// and operator programs keep executors of their own.)
+// The implementations that take part in runs: elementwise ones of one or two inputs and a few instructions, and
+// reductions.  (GELU, FMA, row operations and operator programs keep executors of their own.)
 constexpr uint32_t kLinkUnary = (1u << GPUOS_IMPL_RELU) | (1u << GPUOS_IMPL_EXP) | (1u << GPUOS_IMPL_SCALE) | (1u << GPUOS_IMPL_COPY);
 constexpr uint32_t kLinkBinary = (1u << GPUOS_IMPL_ADD) | (1u << GPUOS_IMPL_SUB) | (1u << GPUOS_IMPL_MUL) | (1u << GPUOS_IMPL_DIV) |
                                  (1u << GPUOS_IMPL_SUB_EXP);
-GPUOS_HD inline bool impl_links(uint32_t impl, uint32_t n_inputs) {
-  return impl < 32u && n_inputs <= 2u && (((n_inputs == 1u ? kLinkUnary : kLinkBinary) >> impl) & 1u) != 0;
+constexpr uint32_t kLinkReduce = (1u << GPUOS_IMPL_SUM_LAST) | (1u << GPUOS_IMPL_MAX_LAST) | (1u << GPUOS_IMPL_MIN_LAST);
+GPUOS_HD inline bool impl_links(uint32_t impl, uint32_t n_inputs, uint32_t path) {
+  const uint32_t set = path == PATH_RED_CONTIG ? kLinkReduce : (n_inputs == 1u ? kLinkUnary : (n_inputs == 2u ? kLinkBinary : 0u));
+  return impl < 32u && ((set >> impl) & 1u) != 0;
 }
 
 // Control words.  HostCtl is written by the device and read by the host: it always lives in

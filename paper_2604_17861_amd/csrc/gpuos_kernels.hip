@@ -563,7 +563,7 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
         // held head holds it, see below).  Only inside one pass, so that its mirror record is on its way
         // before the units that stand for it are.  Not under tracing, whose records tell of
         // one task at a time.
-        const uint64_t m_can = __ballot(status == GPUOS_OK && impl_links((uint32_t)e, rc.n_inputs));
+        const uint64_t m_can = __ballot(status == GPUOS_OK && impl_links((uint32_t)e, rc.n_inputs, rc.path));
         const uint64_t m_mark = __ballot(!tracing && (rc.rflags & RF_LINK) != 0);
         const uint64_t m_link = m_can & m_mark & (m_can << 1);
         const bool link = (m_link >> tid) & 1u;

@@ -215,3 +215,50 @@ def long_chains(code, n, links=150):
             b.add(op, out, [cur, c] if op in ("ADD", "MUL", "SUB", "DIV") else [cur], alpha=0.99, dep=(1, 0, 0) if k else (0, 0, 0))
             cur = out
     return b.stream("long_chains_%d_%d" % (code, n), batch=128)
+
+
+def row_chains(code, seed):
+    """Chains over rows (scale, mask, maximum, difference, sum, quotient and variations), at row lengths of one vector
+    to 65 and a ragged one, masks repeated over leading dims, results of reductions used at once, again
+    later, overwritten, stored in 16 bits, or scalars that lay in memory before.  Values are small integers until the
+    last step, so that sums are exact in any order."""
+    rng = np.random.default_rng(2000 * code + seed)
+    b = Builder()
+    V = 4 if code == S.F32 else 8
+    for n, B, R in ((V, 3, 5), (2 * V, 2, 64), (3 * V, 1, 130), (8 * V, 5, 33), (13 * V, 2, 40), (32 * V, 4, 32), (33 * V, 1, 9), (64 * V, 2, 17),
+                    (65 * V, 2, 9), (5 * V + 1, 2, 11), (8 * V, 8, 1024)):
+        size = (B, R, n)
+        pool = lambda hi: b.pool(to_dtype(rng.integers(-hi, hi + 1, size).astype(np.float32), code))
+        x, t1, t2, e, y = pool(8), pool(1), pool(1), pool(1), pool(1)
+        mask = np.broadcast_to(b.pool(to_dtype(rng.integers(-4, 1, (R, n)).astype(np.float32), code)), size)
+        vec = np.broadcast_to(b.pool(to_dtype(rng.integers(1, 5, (n,)).astype(np.float32), code)), size)
+        rc = int(rng.choice([S.F32, code]))
+        scal = lambda c: b.pool(to_dtype(rng.integers(-2, 3, (B, R)).astype(np.float32), c))
+        m, l, k = scal(rc), scal(S.F32), scal(S.F32)
+        rows = lambda s: np.broadcast_to(s[..., None], size)
+        D = dict(dep=(1, 0, 0))
+        b.add("SCALE", t1, [x], alpha=2.0)
+        b.add("ADD", t2, [t1, mask] if rng.random() < 0.5 else [mask, t1], **D)
+        b.add("MAX_LAST", m, [t2], **D)
+        b.add("SUB", e, [t2, rows(m)], **D)
+        b.add("RELU", t1, [e], **D)
+        what = seed % 6
+        if what == 1:                                        # a row vector in place of the mask, in place
+            b.add("ADD", e, [e, vec], **D)
+        elif what == 2:                                      # a scalar per row that no task of the chain wrote
+            b.add("MUL", e, [e, rows(k)], **D)
+        elif what == 3:                                      # the maximum again, behind another reduction
+            b.add("MIN_LAST", l, [e], **D)
+            b.add("ADD", e, [e, rows(l)], **D)
+            b.add("SUB", e, [e, rows(m)], **D)
+        elif what == 4:                                      # written over by the next reduction
+            b.add("MIN_LAST", m, [t1], **D)
+            b.add("SUB", e, [t2, rows(m)], **D)
+        elif what == 5 and n % V == 0:                       # another row length ends it
+            half = e.reshape(B, R * n // V, V)
+            b.add("MAX_LAST", b.pool(to_dtype(np.zeros((B, R * n // V), np.float32), S.F32)), [half], **D)
+            b.add("ADD", e, [e, t2], **D)
+        b.add("SUM_LAST", l, [e], **D)
+        b.add("SUB" if seed % 2 else "MUL", y, [e, rows(l)], **D)
+        b.add("DIV", y, [y, vec], **D)
+    return b.stream("row_chains_%d_%d" % (code, seed), batch=[128, 7, 12][seed % 3])

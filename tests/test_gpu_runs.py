@@ -38,6 +38,15 @@ def test_chains_with_what_ends_a_run(code, capacity):
         _run(s, capacity)
 
 
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_chains_over_rows(code):
+    for seed in range(6):
+        s = E.row_chains(code, seed)
+        print("row chains", code, seed, len(s), flush=True)
+        stats = _run(s)
+        assert stats["disp_records"] == len(s)
+
+
 @pytest.mark.parametrize("code,n", [(S.F32, 1000), (S.F32, 16384), (S.F16, 4097), (S.BF16, 40000)])
 def test_long_chains_are_run_together(code, n):
     s = E.long_chains(code, n)
