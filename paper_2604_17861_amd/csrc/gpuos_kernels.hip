@@ -85,16 +85,15 @@ struct DispShared {
   PubEntry pub[kDispatchBatch];            // tasks whose units are published in this pass (<= 64)
   uint32_t ubeg[kDispatchBatch + 1];       // exclusive prefix of their nchunks
   PendEntry pend[kPendMax];
-  uint32_t defer[kDispatchBatch];          // per record of the batch: held back
-  uint32_t bad[kDispatchBatch], ok[kDispatchBatch];   // staging: record still fails its check / passed on this read
-  uint32_t nbad;
+  uint32_t ok[kDispatchBatch];             // staging: record passed its check on this read
   uint32_t pre[kPrefetch];                 // prefetched with the poll and valid
   uint32_t preok[kDispatchBatch];          // requested while the previous batch was written out: arrived whole
   uint32_t opcnt[GPUOS_MAX_OPS];           // tracing: tasks dispatched per operator since the last flush
   uint32_t ready[kPendMax];                // per pending entry: dependencies complete
   uint32_t native[GPUOS_MAX_PROGRAMS];     // per operator program: 1 = its tasks go to the second ring (native code is being served there)
   uint64_t tail, epoch_word;
-  uint32_t n, npend, npub, npub_second;
+  uint32_t npend, npub, npub_second;
+  uint64_t claimed;                        // last value read from the claim counter
   uint64_t lane_tickets, lane_units;       // what the first wavefront's short cut for lone tasks has dispatched / published
   uint32_t lane_counted;                   // ... and whether it counted an operator (tracing)
 };
@@ -168,28 +167,27 @@ DEV bool names_pending(const DispShared* s, uint64_t ticket, const uint16_t* dep
   return hit;
 }
 
-// Write the work units of s->pub[0 .. npub) and make them claimable.  Called by the whole
-// workgroup; returns the number of units published.
-// Ring `route` only: entries of the other ring count as zero units (they keep their place in the
-// list, so both rings see their tasks in list order).
-DEV uint32_t dispatcher_publish(const WorkerArgs& a, DispShared* s, uint32_t npub, uint64_t units_w, uint32_t route = 0) {
+// First wavefront: the units of s->pub[0 .. npub) that go to ring `route`, numbered: entries of the other ring
+// count as zero units (they keep their place in the list, so both rings see their tasks in list order).
+DEV void dispatcher_number_units(DispShared* s, uint32_t npub, uint32_t route) {
+  const uint32_t tid = threadIdx.x;
+  // inclusive scan over the wavefront with DPP: shifts by 1, 2, 4, 8 inside each row of 16 lanes
+  // (lanes the shift runs out of the row for add 0), then lane 15 of a row to the whole next row
+  // (rows 1 and 3), then lane 31 to rows 2 and 3.  Six shuffles through the LDS crossbar before.
+  int v = (int)((tid < npub && s->pub[tid].route == route) ? s->pub[tid].nchunks : 0u);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  s->ubeg[tid + 1] = (uint32_t)v;                // (entries past npub hold the total: the search below counts them out)
+  if (tid == 0) s->ubeg[0] = 0;
+}
+// Write those units and make them claimable (by the whole workgroup); returns how many there are.
+DEV uint32_t dispatcher_store_units(const WorkerArgs& a, DispShared* s, uint32_t npub, uint64_t units_w, uint32_t route) {
   const uint32_t tid = threadIdx.x;
   uint64_t* const ring = route == 0 ? a.units : a.units_j;
-  if (tid < 64) {                                  // wave 0: inclusive scan of nchunks
-    // inclusive scan over the wavefront with DPP: shifts by 1, 2, 4, 8 inside each row of 16 lanes
-    // (lanes the shift runs out of the row for add 0), then lane 15 of a row to the whole next row
-    // (rows 1 and 3), then lane 31 to rows 2 and 3.  Six shuffles through the LDS crossbar before.
-    int v = (int)((tid < npub && s->pub[tid].route == route) ? s->pub[tid].nchunks : 0u);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
-    s->ubeg[tid + 1] = (uint32_t)v;                // (entries past npub hold the total: the search below counts them out)
-    if (tid == 0) s->ubeg[0] = 0;
-  }
-  __syncthreads();
   const uint32_t total = s->ubeg[npub];
   // (no wait for the mirror stores of this pass: a worker checks the record it fetches, see mirror_record_valid)
   for (uint32_t u = tid; u < total; u += kThreads) {
@@ -210,6 +208,13 @@ DEV uint32_t dispatcher_publish(const WorkerArgs& a, DispShared* s, uint32_t npu
                                  unit_stamp(g, a.unit_shift)),
                        __ATOMIC_RELAXED, SC_SYSTEM);
   }
+  return total;
+}
+// Both, between barriers.
+DEV uint32_t dispatcher_publish(const WorkerArgs& a, DispShared* s, uint32_t npub, uint64_t units_w, uint32_t route = 0) {
+  if (threadIdx.x < 64) dispatcher_number_units(s, npub, route);
+  __syncthreads();
+  const uint32_t total = dispatcher_store_units(a, s, npub, units_w, route);
   __syncthreads();                                 // s->pub / s->ubeg may be rewritten after this
   return total;
 }
@@ -262,6 +267,120 @@ DEV void dispatcher_service_pending(const WorkerArgs& a, DispShared* s, UnitCurs
   dispatcher_publish_all(a, s, npub, uc, any_second);   // its barriers also cover the new pending count
 }
 
+// First wavefront: plan a batch of n <= 64 staged records, beginning with ticket `mirrored` (m_bad: records that
+// never passed their check).  Resolves the operator table ("claim time": slot, version, impl, status) and the
+// dependencies in the records themselves, splits the batch into tasks that are published now (s->pub) and tasks
+// that are held back (s->pend), and numbers the units of the main ring (s->ubeg).
+DEV void dispatcher_plan(const WorkerArgs& a, DispShared* s, uint32_t n, uint64_t mirrored, uint64_t m_bad, bool tracing, uint64_t tk0, uint64_t& st_deferred) {
+  const uint32_t tid = threadIdx.x;
+  uint32_t defer = 0;
+  if (tid < n) {
+    Record& rc = s->rec[tid];
+    const uint32_t op = rc.op_id;
+    const uint64_t ticket = mirrored + tid;
+    int32_t status = GPUOS_OK;
+    uint64_t e = 0;
+    if ((m_bad >> tid) & 1u) {                                         // never passed its check: do not trust any field
+      status = GPUOS_E_INVAL;
+      rc.path = PATH_NOP; rc.nchunks = 1; rc.dep[0] = rc.dep[1] = rc.dep[2] = 0; rc.rflags = 0;
+    } else if (op >= GPUOS_MAX_OPS) status = GPUOS_E_BADOP;   // bounds check on the op id
+    else {
+      e = s->entry[op];
+      if (e == 0) status = GPUOS_E_BADOP;                      // never registered
+    }
+    rc.impl = (uint32_t)e;
+    rc.version = (uint32_t)(e >> 32);
+    rc.sel = (uint8_t)((e >> 32) & 1u);
+    rc.status = status;
+    if (status != GPUOS_OK || rc.nchunks == 0) rc.nchunks = 1; // one unit reports the task
+    rc.ticket = ticket;
+    if (tracing) {
+      rc.t_dequeue[0] = (uint32_t)tk0; rc.t_dequeue[1] = (uint32_t)(tk0 >> 32);
+      if (op < GPUOS_MAX_OPS) atomicAdd(&s->opcnt[op], 1u);
+    }
+    // A link goes with the record before it: no units of its own, and nothing to wait for but that one (a
+    // held head holds it, see below).  Only inside one pass, so that its mirror record is on its way
+    // before the units that stand for it are.  Not under tracing, whose records tell of
+    // one task at a time.
+    const uint64_t m_can = __ballot(status == GPUOS_OK && impl_links((uint32_t)e, rc.n_inputs, rc.path));
+    const uint64_t m_mark = __ballot(!tracing && (rc.rflags & RF_LINK) != 0);
+    const uint64_t m_link = m_can & m_mark & (m_can << 1);
+    const bool link = (m_link >> tid) & 1u;
+    const uint64_t behind = tid < 63u ? ~(m_link >> (tid + 1u)) : ~0ull;
+    rc.run = (uint16_t)(link ? 0u : (uint32_t)__builtin_ctzll(behind) + 1u);
+    if (!link && (rc.dep[0] | rc.dep[1] | rc.dep[2]) != 0) {
+      if (rc.nchunks > kSmallTaskChunks) {
+        // a large dependent task: its workers never wait; it is published once its
+        // dependencies are complete (now, or later from the pending list)
+        rc.rflags |= RF_DEPS_RESOLVED;
+        defer = deps_complete(a, ticket, rc.dep) ? 0u : 1u;
+      } else {
+        // a small one is published at once and its workers wait, unless it names a task that is
+        // itself held back: then it joins the pending list behind that task (tasks held in this
+        // very pass are found below, in the split)
+        defer = names_pending(s, ticket, rc.dep) ? 1u : 0u;
+      }
+    }
+  }
+  lds_wave_sync();
+  const uint32_t npend0 = s->npend;
+  const bool mine = tid < n;
+  bool held = mine && defer != 0;
+  // A task that names a task held in this pass is held too (a large one already is: such a
+  // dependency cannot be complete).  Dependencies point backwards, so a few rounds of
+  // "held if one of my in-pass dependencies is held" reach the fixed point.
+  uint64_t dep_mask = 0;                                     // records of this pass the task names
+  if (mine && !held) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint32_t back = s->rec[tid].dep[k];
+      if (back != 0 && back <= tid) dep_mask |= 1ull << (tid - back);
+    }
+  }
+  uint64_t m_def = __ballot(held);
+  while (true) {
+    held = held || (dep_mask & m_def) != 0;
+    const uint64_t m2 = __ballot(held);
+    if (m2 == m_def) break;
+    m_def = m2;
+  }
+  const bool unit = mine && s->rec[tid].run != 0;            // (a link has no units)
+  const uint64_t m_pub = __ballot(unit && !held), m_pend = __ballot(unit && held);
+  const uint64_t below = (1ull << tid) - 1ull;
+  bool second = false;                                       // published now, on the second ring
+  if (held) s->rec[tid].rflags |= RF_DEPS_RESOLVED;          // published only after its dependencies completed
+  if (unit) {
+    const Record& rc = s->rec[tid];
+    PubEntry pe;
+    pe.slot = (uint32_t)((mirrored + tid) & a.cap_mask);
+    pe.nchunks = rc.nchunks;
+    pe.opinfo = (rc.op_id & 0xffu) | ((uint32_t)rc.sel << 8) | ((rc.status == GPUOS_OK ? 1u : 0u) << 9) |
+                ((uint32_t)(((mirrored + tid) >> a.cap_shift) & 0x3ffu) << 16);
+    // tasks of a program that a run-time kernel holds as native code go to that kernel's ring
+    const uint32_t prog = rc.impl - GPUOS_IMPL_PROGRAM_BASE;
+    pe.route = (rc.status == GPUOS_OK && rc.impl >= GPUOS_IMPL_PROGRAM_BASE && prog < GPUOS_MAX_PROGRAMS && s->native[prog] != 0) ? 1u : 0u;
+    second = pe.route != 0 && !held;
+    if (held) {
+      PendEntry& pd = s->pend[npend0 + (uint32_t)__popcll(m_pend & below)];
+      pd.ticket = mirrored + tid;
+      pd.pub = pe;
+      pd.dep[0] = rc.dep[0]; pd.dep[1] = rc.dep[1]; pd.dep[2] = rc.dep[2];
+      pd.run = rc.run;
+    } else {
+      s->pub[(uint32_t)__popcll(m_pub & below)] = pe;
+    }
+  }
+  const uint64_t m_second = __ballot(second);
+  if (tid == 0) {
+    st_deferred += (uint32_t)__popcll(m_pend);
+    s->npend = npend0 + (uint32_t)__popcll(m_pend);
+    s->npub = (uint32_t)__popcll(m_pub);
+    s->npub_second = m_second != 0 ? 1u : 0u;
+  }
+  lds_wave_sync();
+  dispatcher_number_units(s, s->npub, 0);
+}
+
 DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
   const uint32_t tid = threadIdx.x;
   // A context whose worker was stopped and started again continues its ticket and work-unit
@@ -272,7 +391,7 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
   uc.w[0] = __hip_atomic_load(&a.d->tail_units, __ATOMIC_RELAXED, SC_SYSTEM);
   uc.w[1] = __hip_atomic_load(&a.d->tail_units_j, __ATOMIC_RELAXED, SC_SYSTEM);
   for (uint32_t op = tid; op < GPUOS_MAX_OPS; op += kThreads) { s->entry[op] = 0; s->opcnt[op] = 0; }
-  if (tid == 0) { s->npend = 0; s->lane_counted = 0; }
+  if (tid == 0) { s->npend = 0; s->lane_counted = 0; s->claimed = uc.w[0]; }
   __syncthreads();
   uint64_t idle_since = wall_clock64();
   if (tid == 0) {
@@ -289,7 +408,6 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
   bool stopping = false;
   uint64_t st_batches = 0, st_records = 0, st_units = 0, st_stage = 0, st_resolve = 0, st_write = 0, st_busy = 0;
   uint64_t st_deferred = 0;
-  uint64_t claimed = uc.w[0];              // last value read from the claim counter (thread 0)
   constexpr uint32_t kStagePieces = kDispatchBatch * 16u / kThreads;      // 16-byte pieces of a batch per thread
   static_assert(kStagePieces * kThreads == kDispatchBatch * 16u, "a batch is staged in whole rounds of the workgroup");
   uint64_t pre_base = ~0ull;               // first ticket of the records requested ahead (they wait in s->rec)
@@ -333,9 +451,7 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
           // lookahead window) takes the ordinary way.
           order_loads();
           const uint32_t x0 = record_piece_sum(q, part);
-          const uint32_t claimed_lo = __builtin_amdgcn_readfirstlane((uint32_t)claimed);
-          const uint32_t claimed_hi = __builtin_amdgcn_readfirstlane((uint32_t)(claimed >> 32));
-          const uint64_t claimed0 = ((uint64_t)claimed_hi << 32) | claimed_lo;       // thread 0 keeps the count
+          const uint64_t claimed0 = uni64(s->claimed);
           bool lone = __builtin_amdgcn_readfirstlane((uint32_t)(x0 == record_check_seed(mirrored))) != 0 &&
                       !(uc.w[0] > claimed0 && uc.w[0] - claimed0 >= kLookaheadUnits);
           if (lone) {
@@ -441,54 +557,52 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
     dispatcher_service_pending(a, s, uc);
 
     // ---- mirror new records, batch by batch ----
+    // A pass has three barriers: every wavefront finds out by itself what the batch is (the same few LDS words) and
+    // requests its share of the next one; the first plans the batch, alone and without a barrier; then all
+    // write it out.  (As a dozen short steps with a barrier behind each a pass of config2 took 4.2-4.7 us.)
     bool first_batch = true;                       // the prefetched records belong to the first batch after a poll
     while (mirrored < tail) {
       // Dequeue only a bounded distance ahead of execution: the dependency state seen at dequeue
       // time is then close to what the workers will see, and the pending list stays short.
-      if (tid == 0) {
-        // the claim counter only grows: re-read it only when the cached value says "too far ahead"
-        if (uc.w[0] > claimed && uc.w[0] - claimed >= kLookaheadUnits)
-          claimed = __hip_atomic_load(&a.d->claim, __ATOMIC_RELAXED, SC_SYSTEM);
-        const uint32_t room = kPendMax - s->npend;
-        uint32_t take = (uint32_t)((tail - mirrored) < kDispatchBatch ? (tail - mirrored) : kDispatchBatch);
-        if (take > room) take = room;
-        if (uc.w[0] > claimed && uc.w[0] - claimed >= kLookaheadUnits) take = 0;
-        s->n = take;
+      // The claim counter only grows: it is read again only when the value at hand says "too far ahead".
+      if (uc.w[0] > s->claimed && uc.w[0] - s->claimed >= kLookaheadUnits) {
+        __syncthreads();
+        if (tid == 0) s->claimed = __hip_atomic_load(&a.d->claim, __ATOMIC_RELAXED, SC_SYSTEM);
+        __syncthreads();
       }
-      __syncthreads();
-      uint32_t n = s->n;                           // (written again only behind the barriers of staging, or of the next poll)
-      if (n == 0) {                                                // throttled: let the workers catch up
+      const bool throttled = uc.w[0] > s->claimed && uc.w[0] - s->claimed >= kLookaheadUnits;
+      const uint32_t room = kPendMax - s->npend, lane = tid & 63u;
+      uint32_t n = (uint32_t)((tail - mirrored) < kDispatchBatch ? (tail - mirrored) : kDispatchBatch);
+      if (n > room) n = room;
+      if (throttled || n == 0) {                                   // let the workers catch up
+        __syncthreads();                                           // everyone has read the pending count
         dispatcher_service_pending(a, s, uc);
         if (s->npend == 0) __builtin_amdgcn_s_sleep(8);
+        __syncthreads();
         break;                                                     // back to the poll loop (stop, table, heartbeat)
       }
       const uint64_t tk0 = clock_if(timing || tracing);
-      // stage: 16 pieces of 16 bytes per record.  System-scope loads: an ordinary load of host
-      // memory may hit a line the CU's vector cache kept from the previous lap of the ring.
-      // Every record carries a check word (a weighted sum of its 64 words must equal a seed made
-      // from its ticket): a record that has not landed completely yet, or is left over from the previous lap,
-      // fails the check and is read again; one that never passes is completed with an error
-      // instead of being executed.
       // Records requested ahead (with the poll, or while the previous batch was written out) already
-      // lie in s->rec and were checked as they arrived: a batch made of such records only is staged
-      // by one ballot and one barrier.  Everything else is read here, and read again until it checks.
-      static_assert(kDispatchBatch == 64, "one wavefront looks at the whole batch");
-      if (tid < kDispatchBatch) {
-        const bool ahead = (pre_base == mirrored && tid < pre_n && s->preok[tid] != 0) || (first_batch && tid < kPrefetch && s->pre[tid] != 0);
-        const bool bad = tid < n && !ahead;
-        s->bad[tid] = bad ? 1u : 0u;
-        const uint64_t m = __ballot(bad);
-        if (tid == 0) s->nbad = (uint32_t)__popcll(m);
-      }
+      // lie in s->rec and were checked as they arrived.
+      static_assert(kDispatchBatch == 64, "a wavefront looks at the whole batch");
+      const bool ahead = (pre_base == mirrored && lane < pre_n && s->preok[lane] != 0) || (first_batch && lane < kPrefetch && s->pre[lane] != 0);
       first_batch = false;
-      __syncthreads();
-      for (uint32_t attempt = 0; s->nbad != 0 && attempt < kStageRetries; ++attempt) {
+      uint64_t m_bad = __ballot(lane < n && !ahead);               // the same in every wavefront
+      if (m_bad != 0) {
+        // stage: 16 pieces of 16 bytes per record.  System-scope loads: an ordinary load of host
+        // memory may hit a line the CU's vector cache kept from the previous lap of the ring.
+        // Every record carries a check word (a weighted sum of its 64 words must equal a seed made
+        // from its ticket): a record that has not landed completely yet, or is left over from the previous lap,
+        // fails the check and is read again; one that never passes is completed with an error
+        // instead of being executed.
+        for (uint32_t attempt = 0; m_bad != 0 && attempt < kStageRetries; ++attempt) {
+          if (attempt != 0) __builtin_amdgcn_s_sleep(16);
+          __syncthreads();                                         // everyone has read the last attempt's verdicts
 #pragma unroll
-        for (uint32_t j = 0; j < kStagePieces; ++j) {
-          const uint32_t p = tid + j * kThreads;
-          if (p < n * 16u) {
+          for (uint32_t j = 0; j < kStagePieces; ++j) {
+            const uint32_t p = tid + j * kThreads;
             const uint32_t rix = p >> 4, part = p & 15u;
-            if (s->bad[rix]) {                                     // uniform over the 16 lanes of a record
+            if ((m_bad >> rix) & 1u) {                             // uniform over the 16 lanes of a record
               const uint32_t slot = (uint32_t)((mirrored + rix) & a.cap_mask);
               const v4i q = Mem<POL_COHERENT>::ld16(rh, slot * (uint32_t)sizeof(Record) + part * 16u);
               ((v4i*)&s->rec[rix])[part] = q;
@@ -496,30 +610,19 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
               if (part == 0) s->ok[rix] = (x == record_check_seed(mirrored + rix)) ? 1u : 0u;
             }
           }
+          __syncthreads();
+          m_bad &= ~__ballot(((m_bad >> lane) & 1u) && s->ok[lane]);
         }
-        __syncthreads();
-        if (tid < 64) {
-          const bool still_bad = tid < n && s->bad[tid] && !s->ok[tid];
-          if (tid < n && s->bad[tid] && s->ok[tid]) s->bad[tid] = 0;
-          const uint64_t m = __ballot(still_bad);
-          if (tid == 0) s->nbad = (uint32_t)__popcll(m);
-        }
-        __syncthreads();
-        if (s->nbad == 0) break;
-        __builtin_amdgcn_s_sleep(16);
       }
       const uint64_t tk1 = clock_if(timing);
       // a FENCE task starts a batch of its own: cut the batch in front of the first one after slot 0
-      if (tid < 64) {
-        const bool f = tid >= 1 && tid < n && (s->rec[tid].rflags & RF_FENCE);
-        const uint64_t m = __ballot(f);
-        if (tid == 0) s->n = m ? (uint32_t)__builtin_ctzll(m) : n;
+      {
+        const uint64_t m = __ballot(lane >= 1 && lane < n && !((m_bad >> lane) & 1u) && (s->rec[lane].rflags & RF_FENCE));
+        if (m) n = (uint32_t)__builtin_ctzll(m);
       }
-      __syncthreads();
-      n = s->n;
+      const bool fence = !(m_bad & 1u) && (uni(s->rec[0].rflags) & RF_FENCE) != 0;
       // Request the next batch now, if the doorbell value already covers it: the loads travel while
-      // this batch is resolved, written to the mirror and published (2.5 us; behind the mirror and
-      // publish steps alone the copy at the end of the pass still waited for them).  A piece that turns
+      // this batch is planned and written out.  A piece that turns
       // out incomplete fails its record's check word when it arrives and is read again at staging time.
       pre_base = mirrored + n;
       pre_n = tail > pre_base ? (uint32_t)((tail - pre_base) < kDispatchBatch ? (tail - pre_base) : kDispatchBatch) : 0u;
@@ -534,61 +637,10 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
         const uint32_t slot = (uint32_t)((pre_base + (p >> 4)) & a.cap_mask);
         pre_q[j] = Mem<POL_COHERENT>::ld16(rh, p < pre_n * 16u ? slot * (uint32_t)sizeof(Record) + (p & 15u) * 16u : kNoLoad);
       }
-      // resolve the operator table ("claim time": slot, version, impl, status) and the dependencies
-      if (tid < n) {
-        Record& rc = s->rec[tid];
-        const uint32_t op = rc.op_id;
-        const uint64_t ticket = mirrored + tid;
-        int32_t status = GPUOS_OK;
-        uint64_t e = 0;
-        if (s->bad[tid]) {                                         // never passed its check: do not trust any field
-          status = GPUOS_E_INVAL;
-          rc.path = PATH_NOP; rc.nchunks = 1; rc.dep[0] = rc.dep[1] = rc.dep[2] = 0; rc.rflags = 0;
-        } else if (op >= GPUOS_MAX_OPS) status = GPUOS_E_BADOP;   // bounds check on the op id
-        else {
-          e = s->entry[op];
-          if (e == 0) status = GPUOS_E_BADOP;                      // never registered
-        }
-        rc.impl = (uint32_t)e;
-        rc.version = (uint32_t)(e >> 32);
-        rc.sel = (uint8_t)((e >> 32) & 1u);
-        rc.status = status;
-        if (status != GPUOS_OK || rc.nchunks == 0) rc.nchunks = 1; // one unit reports the task
-        rc.ticket = ticket;
-        if (tracing) {
-          rc.t_dequeue[0] = (uint32_t)tk0; rc.t_dequeue[1] = (uint32_t)(tk0 >> 32);
-          if (op < GPUOS_MAX_OPS) atomicAdd(&s->opcnt[op], 1u);
-        }
-        // A link goes with the record before it: no units of its own, and nothing to wait for but that one (a
-        // held head holds it, see below).  Only inside one pass, so that its mirror record is on its way
-        // before the units that stand for it are.  Not under tracing, whose records tell of
-        // one task at a time.
-        const uint64_t m_can = __ballot(status == GPUOS_OK && impl_links((uint32_t)e, rc.n_inputs, rc.path));
-        const uint64_t m_mark = __ballot(!tracing && (rc.rflags & RF_LINK) != 0);
-        const uint64_t m_link = m_can & m_mark & (m_can << 1);
-        const bool link = (m_link >> tid) & 1u;
-        const uint64_t behind = tid < 63u ? ~(m_link >> (tid + 1u)) : ~0ull;
-        rc.run = (uint16_t)(link ? 0u : (uint32_t)__builtin_ctzll(behind) + 1u);
-        uint32_t defer = 0;
-        if (!link && (rc.dep[0] | rc.dep[1] | rc.dep[2]) != 0) {
-          if (rc.nchunks > kSmallTaskChunks) {
-            // a large dependent task: its workers never wait; it is published once its
-            // dependencies are complete (now, or later from the pending list)
-            rc.rflags |= RF_DEPS_RESOLVED;
-            defer = deps_complete(a, ticket, rc.dep) ? 0u : 1u;
-          } else {
-            // a small one is published at once and its workers wait, unless it names a task that is
-            // itself held back: then it joins the pending list behind that task (tasks held in this
-            // very pass are found below, in the split)
-            defer = names_pending(s, ticket, rc.dep) ? 1u : 0u;
-          }
-        }
-        s->defer[tid] = defer;
-      }
-      __syncthreads();
       // a leading FENCE: everything earlier must be published and complete first
-      if (s->rec[0].rflags & RF_FENCE) {
-        while (s->npend != 0) dispatcher_service_pending(a, s, uc);
+      if (fence) {
+        __syncthreads();
+        while (s->npend != 0) { dispatcher_service_pending(a, s, uc); __syncthreads(); }
         if (tid == 0) {
           while (__hip_atomic_load(&a.d->done_count, __ATOMIC_RELAXED, SC_SYSTEM) < mirrored)
             __builtin_amdgcn_s_sleep(4);
@@ -596,90 +648,47 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
         }
         __syncthreads();
       }
-      if (tid < 64) {                                              // wave 0 holds all n <= 64 records: split by ballot
-        const uint32_t npend0 = s->npend;
-        const bool mine = tid < n;
-        bool held = mine && s->defer[tid] != 0;
-        // A task that names a task held in this pass is held too (a large one already is: such a
-        // dependency cannot be complete).  Dependencies point backwards, so a few rounds of
-        // "held if one of my in-pass dependencies is held" reach the fixed point.
-        uint64_t dep_mask = 0;                                     // records of this pass the task names
-        if (mine && !held) {
-#pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            const uint32_t back = s->rec[tid].dep[k];
-            if (back != 0 && back <= tid) dep_mask |= 1ull << (tid - back);
-          }
-        }
-        uint64_t m_def = __ballot(held);
-        while (true) {
-          held = held || (dep_mask & m_def) != 0;
-          const uint64_t m2 = __ballot(held);
-          if (m2 == m_def) break;
-          m_def = m2;
-        }
-        const bool unit = mine && s->rec[tid].run != 0;            // (a link has no units)
-        const uint64_t m_pub = __ballot(unit && !held), m_pend = __ballot(unit && held);
-        const uint64_t below = (1ull << tid) - 1ull;
-        bool second = false;                                       // published now, on the second ring
-        if (held) s->rec[tid].rflags |= RF_DEPS_RESOLVED;          // published only after its dependencies completed
-        if (unit) {
-          const Record& rc = s->rec[tid];
-          PubEntry pe;
-          pe.slot = (uint32_t)((mirrored + tid) & a.cap_mask);
-          pe.nchunks = rc.nchunks;
-          pe.opinfo = (rc.op_id & 0xffu) | ((uint32_t)rc.sel << 8) | ((rc.status == GPUOS_OK ? 1u : 0u) << 9) |
-                      ((uint32_t)(((mirrored + tid) >> a.cap_shift) & 0x3ffu) << 16);
-          // tasks of a program that a run-time kernel holds as native code go to that kernel's ring
-          const uint32_t prog = rc.impl - GPUOS_IMPL_PROGRAM_BASE;
-          pe.route = (rc.status == GPUOS_OK && rc.impl >= GPUOS_IMPL_PROGRAM_BASE && prog < GPUOS_MAX_PROGRAMS && s->native[prog] != 0) ? 1u : 0u;
-          second = pe.route != 0 && !held;
-          if (held) {
-            PendEntry& pd = s->pend[npend0 + (uint32_t)__popcll(m_pend & below)];
-            pd.ticket = mirrored + tid;
-            pd.pub = pe;
-            pd.dep[0] = rc.dep[0]; pd.dep[1] = rc.dep[1]; pd.dep[2] = rc.dep[2];
-            pd.run = rc.run;
-          } else {
-            s->pub[(uint32_t)__popcll(m_pub & below)] = pe;
-          }
-        }
-        const uint64_t m_second = __ballot(second);
-        if (tid == 0) {
-          st_deferred += (uint32_t)__popcll(m_pend);
-          s->npend = npend0 + (uint32_t)__popcll(m_pend);
-          s->npub = (uint32_t)__popcll(m_pub);
-          s->npub_second = m_second != 0 ? 1u : 0u;
-        }
-      }
+      __syncthreads();                                             // everyone has read what the plan is about to change
+      if (tid < 64) dispatcher_plan(a, s, n, mirrored, m_bad, tracing, tk0, st_deferred);
       __syncthreads();
       const uint64_t tk2 = clock_if(timing);
-      // write the records into the device mirror (write-through stores), held-back ones included
-      // each record leaves with a check word of its own over what it now holds (resolved fields, ticket)
-      for (uint32_t p = tid; p < n * 16u; p += kThreads) {
-        const uint32_t rix = p >> 4, part = p & 15u;
-        const uint32_t slot = (uint32_t)((mirrored + rix) & a.cap_mask);
-        v4i q = ((const v4i*)&s->rec[rix])[part];
-        if (part == 15u) q[3] = 0;
-        const uint32_t x = record_piece_sum(q, part);              // the 16 lanes of a record share a row
-        if (part == 15u) q[3] = (int)(record_check_seed(mirrored + rix) - x);
-        Mem<POL_COHERENT>::st16(rd, slot * (uint32_t)sizeof(Record) + part * 16u, q);
+      // Write the records into the device mirror (write-through stores), held-back ones included; each leaves
+      // with a check word of its own over what it now holds (resolved fields, ticket).  A thread takes its pieces out
+      // of the staging, puts the next batch's in their place (checked as they arrive: the next pass
+      // finds the verdict in s->preok), and only then stores: a wait for those loads behind the stores
+      // would be one for the stores too.
+      v4i out_q[kStagePieces];
+#pragma unroll
+      for (uint32_t j = 0; j < kStagePieces; ++j) {
+        const uint32_t p = tid + j * kThreads, rix = p >> 4, part = p & 15u;
+        out_q[j] = ((const v4i*)&s->rec[rix])[part];
+        if (part == 15u) out_q[j][3] = 0;
+        const uint32_t x = record_piece_sum(out_q[j], part);       // the 16 lanes of a record share a row
+        if (part == 15u) out_q[j][3] = (int)(record_check_seed(mirrored + rix) - x);
       }
-      const uint64_t before = uc.w[0] + uc.w[1];
-      dispatcher_publish_all(a, s, s->npub, uc, s->npub_second != 0);       // (no wait for the stores above: see mirror_record_valid)
-      const uint32_t total = (uint32_t)(uc.w[0] + uc.w[1] - before);
-      // nothing reads this batch's staging any more (the mirror has it, held-back tasks were copied
-      // to the pending list): it takes the records requested ahead
-      // (and each is checked as it arrives: the next pass finds the verdict in s->preok)
 #pragma unroll
       for (uint32_t j = 0; j < kStagePieces; ++j) {
         const uint32_t p = tid + j * kThreads;
-        if (p < pre_n * 16u) {                                       // uniform over the 16 lanes of a record
+        if (p < pre_n * 16u) {                                     // uniform over the 16 lanes of a record
           ((v4i*)&s->rec[p >> 4])[p & 15u] = pre_q[j];
           const uint32_t x = record_piece_sum(pre_q[j], p & 15u);
           if ((p & 15u) == 0) s->preok[p >> 4] = (x == record_check_seed(pre_base + (p >> 4))) ? 1u : 0u;
         }
       }
+#pragma unroll
+      for (uint32_t j = 0; j < kStagePieces; ++j) {
+        const uint32_t p = tid + j * kThreads;
+        const uint32_t slot = (uint32_t)((mirrored + (p >> 4)) & a.cap_mask);
+        Mem<POL_COHERENT>::st16(rd, p < n * 16u ? slot * (uint32_t)sizeof(Record) + (p & 15u) * 16u : kNoLoad, out_q[j]);
+      }
+      const uint64_t before = uc.w[0] + uc.w[1];
+      uc.w[0] += dispatcher_store_units(a, s, s->npub, uc.w[0], 0);        // (no wait for the stores above: see mirror_record_valid)
+      if (s->npub_second != 0) {
+        __syncthreads();
+        uc.w[1] += dispatcher_publish(a, s, s->npub, uc.w[1], 1);
+      }
+      const uint32_t total = (uint32_t)(uc.w[0] + uc.w[1] - before);
+      __syncthreads();
       mirrored += n;
       if (tid == 0) __hip_atomic_store(&a.h->dispatched, mirrored, __ATOMIC_RELAXED, SC_SYSTEM);
       if (timing || a.idle_exit_ticks != 0) idle_since = wall_clock64();
