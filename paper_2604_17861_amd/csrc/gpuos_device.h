@@ -395,8 +395,76 @@ template <> struct OpOut<GPUOS_IMPL_SUB_EXP, GPUOS_BF16> { static constexpr int 
 // o[k] = f(x[k], y[k], z[k], alpha) for the K elements a lane holds: element by element for the
 // built-in implementations (the compiler unrolls it back into straight code), instruction by
 // instruction for a program.
+// GELU of a vector of 16-bit elements: evaluated in fp32 with a bound on its relative error, and in fp64, as above,
+// where the two ends of that bound do not round to the same 16-bit value (Ziv's rounding test).  The result
+// is that of fp64 on every input.  Bound by arithmetic (half of it gone, a large tensor is bound by memory):
+// what decides is instructions an element, 30 against 60.
+//   ERF   the formula of Op<GELU_ERF> with k = 3 and degree 8 (2^-25.1); a * a is exact for a 16-bit a, so the
+//         exponent is carried in two words.  Off by at most 2^-21.7 over all inputs, plus the last bits of the
+//         hardware's reciprocal and exponential.
+//   TANH  x / (1 + 2^z), off by at most 2^-22.5 max(|z|, 1).
+// (Near zero, at infinity and for NaN both ends round alike.  bf16 reaches down to where fp32 has no more normal
+// numbers: there, below -12 and -9, fp64 decides always.)
+template <int IMPL> DEV float gelu_fp32(float x, float& eps) {
+  if (IMPL == GPUOS_IMPL_GELU_ERF) {
+    const float a = __builtin_fabsf(x), c = __builtin_fminf(a, 12.0f), s = c * c;
+    const float d = __builtin_amdgcn_rcpf(c + 3.0f), t = __builtin_fmaf(-6.0f, d, 1.0f);
+    float p = -0.00028271329938434064f;
+    p = __builtin_fmaf(p, t, -0.0009280924568884075f);
+    p = __builtin_fmaf(p, t, 0.0010787147330120206f);
+    p = __builtin_fmaf(p, t, 0.0069399685598909855f);
+    p = __builtin_fmaf(p, t, -0.01047808863222599f);
+    p = __builtin_fmaf(p, t, -0.04725917801260948f);
+    p = __builtin_fmaf(p, t, 0.23001901805400848f);
+    p = __builtin_fmaf(p, t, -0.5093321204185486f);
+    p = __builtin_fmaf(p, t, 0.7290836572647095f);
+    constexpr float KH = (float)-kHalfLog2e, KL = (float)(-kHalfLog2e - (double)KH);
+    const float z = s * KH, e = __builtin_fmaf(s, KL, __builtin_fmaf(s, KH, -z));        // the exponent is z + e
+    float q = p * d * __builtin_amdgcn_exp2f(z);
+    q = __builtin_fmaf(q, e * 0.6931472f, q);
+    eps = 0x1p-21f;
+    return __builtin_copysignf(__builtin_fmaf(-c, q, 0.5f * (x + a)), x);
+  }
+  const float s = x * x, z = x * __builtin_fmaf((float)kTanhZ3, s, (float)kTanhZ1);
+  eps = __builtin_fmaf(__builtin_fabsf(z), 0x1p-22f, 0x1.8p-22f);
+  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z));
+}
+template <int IMPL, int DT> DEV void gelu_16bit(const float (&x)[8], float (&o)[8]) {
+  using E = Elem<DT>;
+  v4i lo = {0, 0, 0, 0}, hi = {0, 0, 0, 0};
+  float least = x[0];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    float eps;
+    o[k] = gelu_fp32<IMPL>(x[k], eps);
+    E::put(lo, k, __builtin_fmaf(-eps, o[k], o[k]));
+    E::put(hi, k, __builtin_fmaf(eps, o[k], o[k]));
+    least = __builtin_fminf(least, x[k]);
+  }
+  const v4i diff = lo ^ hi;
+  const float limit = DT == GPUOS_F16 ? -__builtin_inff() : (IMPL == GPUOS_IMPL_GELU_ERF ? -12.0f : -9.0f);
+  if (__ballot((diff[0] | diff[1] | diff[2] | diff[3]) != 0 || least < limit) == 0) return;
+  // (one element of the eight after the other: few vectors have more than one in doubt, and the code is there once)
+#pragma unroll 1
+  for (int k = 0; k < 8; ++k) {
+    float xk = x[0];
+    int dk = diff[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) { xk = j == k ? x[j] : xk; dk = j == k ? diff[j >> 1] : dk; }
+    const bool doubt = ((uint32_t)dk & (k & 1 ? 0xffff0000u : 0xffffu)) != 0 || xk < limit;
+    if (__ballot(doubt) == 0) continue;
+    const float y = Op<IMPL>::f(xk, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o[j] = doubt && j == k ? y : o[j];
+  }
+}
+
 template <int IMPL, int K, int DT = GPUOS_F32>
 DEV void apply_vec(const float (&x)[K], const float (&y)[K], const float (&z)[K], float alpha, float (&o)[K]) {
+  if constexpr ((IMPL == GPUOS_IMPL_GELU_ERF || IMPL == GPUOS_IMPL_GELU_TANH) && DT != GPUOS_F32 && K == 8) {
+    gelu_16bit<IMPL, DT>(x, o);
+    return;
+  }
   if (IMPL == kImplProg1 || IMPL == kImplProg2 || IMPL == kImplProg3) {
     run_program_vec<K>(x, y, z, alpha, o);
   } else {

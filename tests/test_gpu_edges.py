@@ -137,3 +137,42 @@ def test_row_operations_in_place(code):
         got.append([np.ascontiguousarray(imgs[k]).view(np.uint8).reshape(-1)[off: off + nb] for k, off, nb in outs])
     for i, (a, c) in enumerate(zip(*got)):
         assert np.array_equal(a, c), i
+
+
+@pytest.mark.parametrize("code", [S.F16, S.BF16])
+def test_gelu_of_16bit_inputs_is_the_rounded_fp64_value(code):
+    """Every 16-bit pattern, in three orders, through both GELUs: the 16-bit output is the fp32 output (evaluated
+    in fp64) rounded once more, bit for bit."""
+    import numpy as np
+    from gpu_helpers import DevicePools, run_stream
+    from helpers import Builder, bf16_bits_to_f32
+    from parity_cases import to_dtype
+    from paper_2604_17861_amd import runtime as R
+    b, pairs = Builder(), []
+    for seed in range(3):
+        bits = np.random.default_rng(seed).permutation(65536).astype(np.uint16)
+        X = b.pool(bits.view(np.float16).copy() if code == S.F16 else bits)
+        for name in ("GELU_ERF", "GELU_TANH"):
+            o16, o32 = b.pool(np.zeros(65536, X.dtype)), b.pool(np.zeros(65536, np.float32))
+            b.add(name, o16, [X])
+            b.add(name, o32, [X])
+            pairs.append((len(b.bases) - 2, len(b.bases) - 1))
+    s = b.stream("gelu_16bit_%d" % code)
+    dp = DevicePools(s)
+    with R.Runtime(idle_exit_ms=20000, wait_timeout_ms=20000) as rt:
+        rt.register_table(s.table)
+        run_stream(s, rt, dp)
+    got = dp.download()
+    for k16, k32 in pairs:
+        y16, y32 = got[k16].view(np.uint16), got[k32].view(np.float32)
+        if code == S.F16:
+            with np.errstate(over="ignore"):
+                want = y32.astype(np.float16).view(np.uint16)
+        else:
+            w = y32.view(np.uint32).astype(np.uint64)
+            want = ((w + 0x7FFF + ((w >> 16) & 1)) >> 16).astype(np.uint16)
+        nan = np.isnan(y32)
+        is_nan = np.isnan(y16.view(np.float16)) if code == S.F16 else np.isnan(bf16_bits_to_f32(y16))
+        assert np.array_equal(nan, is_nan)
+        bad = np.nonzero((y16 != want) & ~nan)[0]
+        assert len(bad) == 0, (code, k16, len(bad), y32[bad[:5]], y16[bad[:5]], want[bad[:5]])
