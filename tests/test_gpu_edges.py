@@ -176,3 +176,33 @@ def test_gelu_of_16bit_inputs_is_the_rounded_fp64_value(code):
         assert np.array_equal(nan, is_nan)
         bad = np.nonzero((y16 != want) & ~nan)[0]
         assert len(bad) == 0, (code, k16, len(bad), y32[bad[:5]], y16[bad[:5]], want[bad[:5]])
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_long_softmax_rows_at_every_alignment(code):
+    """Rows too long for the workgroup's registers, cut at memory's 16-byte blocks where input and output lie alike in
+    them and from the row's first element on where they do not; nothing outside the output is written."""
+    import numpy as np
+    from gpu_helpers import DevicePools, compare_with_oracle, run_stream
+    from helpers import Builder
+    from paper_2604_17861_amd import runtime as R
+    rng = np.random.default_rng(40 + code)
+    V, rows, pad = (4 if code == S.F32 else 8), 3, 16
+    b, outs = Builder(), []
+    for n in (16385, 16384 + V - 1, 20001, 32003):
+        for xo, oo in ((0, 0), (1, 1), (V - 1, V - 1), (2, 0), (0, 1)):
+            x = b.pool(E.values(rng, rows * n + 2 * pad, code))
+            o = b.pool(np.zeros_like(x))
+            b.add("SOFTMAX_LAST", o[pad + oo: pad + oo + rows * n].reshape(rows, n), [x[pad + xo: pad + xo + rows * n].reshape(rows, n)])
+            outs.append((len(b.bases) - 1, pad + oo, rows * n))
+    s = b.stream("long_softmax_%d" % code)
+    dp = DevicePools(s)
+    with R.Runtime(idle_exit_ms=20000, wait_timeout_ms=20000) as rt:
+        rt.register_table(s.table)
+        t0 = run_stream(s, rt, dp)
+        comps = rt.completions(t0, len(s))
+    got = dp.download()
+    print(compare_with_oracle(s, got, versions=comps["op_version"]), flush=True)
+    for k, first, count in outs:
+        words = got[k].view(np.uint32 if code == S.F32 else np.uint16)
+        assert not words[:first].any() and not words[first + count:].any()
