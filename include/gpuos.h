@@ -286,7 +286,11 @@ typedef struct gpuos_config {
                                        into up to four; gathered and transposed inputs are spread
                                        over up to 32 resp. 64 workgroups, reductions that are no
                                        such link of a chain over up to 64 in pieces of 16 KiB at
-                                       least (gpuos_task_plan tells) */
+                                       least (gpuos_task_plan tells of a task by itself; tasks of
+                                       one submit that each name the one before and read what it
+                                       writes, over tensors of one size, may be run together
+                                       by the workgroups of the first, all cut alike; not under
+                                       tracing) */
   uint32_t push_ring;               /* where the ring, the doorbell and the table source
                                        live: 0 = fine-grained host memory that the device
                                        polls over PCIe; 1 = device memory that the host

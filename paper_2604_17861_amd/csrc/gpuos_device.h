@@ -2736,7 +2736,7 @@ DEV int32_t exec_program(const Record* r, const RecHead& h, uint32_t impl, uint3
 template <int POL>
 DEV int32_t exec_chunk(const Record* r, const RecHead& h, uint32_t impl, uint32_t chunk, float* s_red, const ProgramImage* progs, uint32_t tid) {
   if (h.path() == PATH_NOP) return impl == GPUOS_IMPL_FAIL ? GPUOS_E_BADOP : GPUOS_OK;
-  if (impl >= GPUOS_IMPL_PROGRAM_BASE) return exec_program<POL>(r, h, impl, chunk, s_red, progs, tid);
+  if (__builtin_expect(impl >= GPUOS_IMPL_PROGRAM_BASE, 0)) return exec_program<POL>(r, h, impl, chunk, s_red, progs, tid);
   // (beside the switch, not a case in every implementation's paths: see ByArity)
   if (impl >= GPUOS_IMPL_SOFTMAX_LAST && impl <= GPUOS_IMPL_LAYERNORM_LAST && rowop_is_other(h)) {
     const uint32_t per = h.chunk(), rows = h.numel(), begin = chunk * per;
@@ -3420,7 +3420,7 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
     if (status == GPUOS_OK && uni((uint32_t)(head.entry >> 32)) != word(head.impl, 1)) status = GPUOS_E_VERSION;
     if (status == GPUOS_OK) status = (int32_t)word(dec, 1);
     const uint64_t c3 = clock_if(timing);
-    if (RING == 0 && (uint32_t)head.links[1] >> 17 != 0) {      // a run of two or more tasks
+    if (RING == 0 && __builtin_expect((uni((uint32_t)head.links[1]) >> 17) != 0, 0)) {      // a run of two or more tasks (off the way of the rest)
       exec_run(s, f, chunk, status, thread_index(wave));
       if (leader) s->n_units += 1;
       if (timing) { const uint64_t c4 = clock_if(timing); count(ST_WORK_TICKS_EXEC, c4 - c3); }

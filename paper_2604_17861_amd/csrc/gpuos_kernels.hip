@@ -446,7 +446,7 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
           // ---- short cut for a lone task ----
           // One new record, whole (its check word holds), no table change, nothing held back: this
           // wavefront resolves, mirrors and publishes it by itself and polls on.  The other three
-          // stay at the barrier below; the dozen barriers of a batch pass are not on a lone task's
+          // stay at the barrier below; the barriers of a batch pass are not on a lone task's
           // way.  Anything special (a dependency, a fence, many chunks, the second ring, a full
           // lookahead window) takes the ordinary way.
           order_loads();
@@ -559,7 +559,8 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
     // ---- mirror new records, batch by batch ----
     // A pass has three barriers: every wavefront finds out by itself what the batch is (the same few LDS words) and
     // requests its share of the next one; the first plans the batch, alone and without a barrier; then all
-    // write it out.  (As a dozen short steps with a barrier behind each a pass of config2 took 4.2-4.7 us.)
+    // write it out.  (As a dozen short steps with a barrier behind each a pass of 64 mixed
+    // tasks took 4.7 us, 3.7 so.)
     bool first_batch = true;                       // the prefetched records belong to the first batch after a poll
     while (mirrored < tail) {
       // Dequeue only a bounded distance ahead of execution: the dependency state seen at dequeue
@@ -653,33 +654,30 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
       __syncthreads();
       const uint64_t tk2 = clock_if(timing);
       // Write the records into the device mirror (write-through stores), held-back ones included; each leaves
-      // with a check word of its own over what it now holds (resolved fields, ticket).  A thread takes its pieces out
-      // of the staging, puts the next batch's in their place (checked as they arrive: the next pass
-      // finds the verdict in s->preok), and only then stores: a wait for those loads behind the stores
-      // would be one for the stores too.
-      v4i out_q[kStagePieces];
+      // with a check word of its own over what it now holds (resolved fields, ticket).  Then a thread puts the next batch's
+      // pieces where it took its own out (checked as they arrive: the next pass finds the verdict in s->preok), and only then
+      // the units are stored: the wait for those loads leaves the mirror stores in flight, and the records
+      // have a head start (a worker that sees its unit first fetches its record twice).
 #pragma unroll
       for (uint32_t j = 0; j < kStagePieces; ++j) {
         const uint32_t p = tid + j * kThreads, rix = p >> 4, part = p & 15u;
-        out_q[j] = ((const v4i*)&s->rec[rix])[part];
-        if (part == 15u) out_q[j][3] = 0;
-        const uint32_t x = record_piece_sum(out_q[j], part);       // the 16 lanes of a record share a row
-        if (part == 15u) out_q[j][3] = (int)(record_check_seed(mirrored + rix) - x);
+        v4i q = ((const v4i*)&s->rec[rix])[part];
+        if (part == 15u) q[3] = 0;
+        const uint32_t x = record_piece_sum(q, part);              // the 16 lanes of a record share a row
+        if (part == 15u) q[3] = (int)(record_check_seed(mirrored + rix) - x);
+        const uint32_t slot = (uint32_t)((mirrored + rix) & a.cap_mask);
+        Mem<POL_COHERENT>::st16(rd, p < n * 16u ? slot * (uint32_t)sizeof(Record) + part * 16u : kNoLoad, q);
       }
+      if (pre_n != 0) {
 #pragma unroll
-      for (uint32_t j = 0; j < kStagePieces; ++j) {
-        const uint32_t p = tid + j * kThreads;
-        if (p < pre_n * 16u) {                                     // uniform over the 16 lanes of a record
-          ((v4i*)&s->rec[p >> 4])[p & 15u] = pre_q[j];
-          const uint32_t x = record_piece_sum(pre_q[j], p & 15u);
-          if ((p & 15u) == 0) s->preok[p >> 4] = (x == record_check_seed(pre_base + (p >> 4))) ? 1u : 0u;
+        for (uint32_t j = 0; j < kStagePieces; ++j) {
+          const uint32_t p = tid + j * kThreads;
+          if (p < pre_n * 16u) {                                   // uniform over the 16 lanes of a record
+            ((v4i*)&s->rec[p >> 4])[p & 15u] = pre_q[j];
+            const uint32_t x = record_piece_sum(pre_q[j], p & 15u);
+            if ((p & 15u) == 0) s->preok[p >> 4] = (x == record_check_seed(pre_base + (p >> 4))) ? 1u : 0u;
+          }
         }
-      }
-#pragma unroll
-      for (uint32_t j = 0; j < kStagePieces; ++j) {
-        const uint32_t p = tid + j * kThreads;
-        const uint32_t slot = (uint32_t)((mirrored + (p >> 4)) & a.cap_mask);
-        Mem<POL_COHERENT>::st16(rd, p < n * 16u ? slot * (uint32_t)sizeof(Record) + (p & 15u) * 16u : kNoLoad, out_q[j]);
       }
       const uint64_t before = uc.w[0] + uc.w[1];
       uc.w[0] += dispatcher_store_units(a, s, s->npub, uc.w[0], 0);        // (no wait for the stores above: see mirror_record_valid)
