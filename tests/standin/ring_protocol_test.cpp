@@ -18,6 +18,7 @@ extern "C" uint64_t standin_errors();
 extern "C" void standin_leave_before(uint64_t ticket);
 extern "C" void standin_stall_ms(uint32_t ms);
 extern "C" uint64_t standin_records();
+extern "C" uint64_t standin_links();
 extern "C" uint64_t standin_alloc_calls();
 extern "C" void standin_scratch_dirty();
 extern "C" uint64_t standin_scratch_nonzero(uint64_t n);
@@ -118,8 +119,62 @@ static void chunks_stay_addressable() {
   std::printf("chunks within 32-bit offsets: ok\n");
 }
 
+// Which tasks of a submit the host marks as links of a run: whoever reads what the task right before it wrote, over
+// buffers that are the same or apart, and nobody else.
+static void runs_are_marked() {
+  gpuos_ctx* c = make(256);
+  CHECK(gpuos_register_op(c, 11, GPUOS_IMPL_MAX_LAST, nullptr) == GPUOS_OK);
+  const uint32_t n = 1000;
+  auto ptr = [](int k) { return (void*)(uintptr_t)(0x1000000 + 0x100000 * k); };
+  auto link = [&](int in, int other, int out, uint16_t dep = 1) {
+    gpuos_task t = add_task(7, n, dep);
+    t.in[0].ptr = ptr(in); t.in[1].ptr = ptr(other); t.out.ptr = ptr(out);
+    return t;
+  };
+  auto links_of = [&](std::vector<gpuos_task> v) {
+    const uint64_t before = standin_links();
+    v[0].dep[0] = 0;
+    CHECK(gpuos_submit_flush(c, v.data(), (uint32_t)v.size(), nullptr) == GPUOS_OK);
+    CHECK(gpuos_wait(c, GPUOS_ALL, 0) == GPUOS_OK);
+    return standin_links() - before;
+  };
+  std::vector<gpuos_task> v = {link(0, 1, 2), link(2, 1, 3), link(3, 1, 2), link(2, 1, 2)};   // two buffers in turn, then in place
+  CHECK(links_of(v) == 3);
+  auto with = [&](int k, auto change) { std::vector<gpuos_task> w = v; change(w[k]); return links_of(w); };
+  CHECK(with(1, [&](gpuos_task& t) { t.dep[0] = 0; }) == 2);                                  // names nothing
+  CHECK(with(2, [&](gpuos_task& t) { t.dep[1] = 2; }) == 2);                                  // names another one too (and heads the next run)
+  CHECK(with(1, [&](gpuos_task& t) { t.flags = GPUOS_FLAG_FENCE; }) == 2);
+  CHECK(with(1, [&](gpuos_task& t) { t.size[0] = n - 4; }) == 1);                             // another length: neither before nor behind it
+  CHECK(with(3, [&](gpuos_task& t) { t.in[0].ptr = ptr(1); }) == 2);                          // does not read what the one before wrote
+  CHECK(with(1, [&](gpuos_task& t) { t.in[1].ptr = (char*)ptr(1) + 16; }) == 1);              // overlaps a buffer of the run in part
+  CHECK(with(2, [&](gpuos_task& t) { t.out.ptr = (char*)ptr(1) - 16; }) == 1);
+  CHECK(with(1, [&](gpuos_task& t) { t.in[0].ptr = (char*)t.in[0].ptr + 4; }) == 1);          // not aligned to a vector
+  CHECK(with(1, [&](gpuos_task& t) { for (auto* q : {&t.in[0], &t.in[1], &t.out}) q->dtype = GPUOS_F16; }) == 1);
+  std::vector<gpuos_task> big = v;                                                            // more chunks than a waiting task may have
+  for (auto& t : big) t.size[0] = 200000;
+  CHECK(links_of(big) == 0);
+  std::vector<gpuos_task> many(150, link(2, 1, 2));
+  CHECK(links_of(many) == 150 - 3);                                                           // runs of at most 64: three heads
+  // a reduction over rows and what reads its scalars: 250 rows of 4, and rows of 5 that are no whole vectors
+  auto rows = [&](int64_t r, int64_t len) {
+    gpuos_task m = add_task(11, 1, 1), d = add_task(7, 1, 1);
+    m.n_inputs = 1; m.ndim = 2; m.size[0] = r; m.size[1] = len;
+    m.in[0].ptr = ptr(2); m.in[0].stride[0] = len; m.in[0].stride[1] = 1; m.out.ptr = ptr(5);
+    d.ndim = 2; d.size[0] = r; d.size[1] = len;
+    d.in[0].ptr = ptr(2); d.in[0].stride[0] = len; d.in[0].stride[1] = 1;
+    d.in[1].ptr = ptr(5); d.in[1].stride[0] = 1; d.in[1].stride[1] = 0;
+    d.out.ptr = ptr(3); d.out.stride[0] = len; d.out.stride[1] = 1;
+    return std::vector<gpuos_task>{link(0, 1, 2), m, d};
+  };
+  CHECK(links_of(rows(250, 4)) == 2);
+  CHECK(links_of(rows(200, 5)) == 0);
+  CHECK(gpuos_shutdown(c) == GPUOS_OK);
+  std::printf("ok: links of runs are marked, and nothing else\n");
+}
+
 int main() {
   check_word_rejects_mixtures();
+  runs_are_marked();
   chunks_stay_addressable();
   // 1. many producers, tiny rings: every ticket exactly once, consecutive inside a call, in-order log
   for (uint32_t cap : {2u, 8u, 64u}) {
