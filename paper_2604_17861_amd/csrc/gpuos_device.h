@@ -2265,9 +2265,9 @@ DEV void softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, flo
   // that holds a tensor's first or last element may hold bytes outside it, in the same page.)  Cut from a row's
   // first element on, each store is written in two parts: 2 x 1,024 rows of 32,003 fp32 wrote 1.7 times and
   // read 2.2 times their bytes, 204 us; 181 so.
-  const uint32_t skew = (uint32_t)(__UINTPTR_TYPE__)po & 15u;
-  const bool blocks = RAGGED && !MASK && ((uint32_t)(__UINTPTR_TYPE__)px & 15u) == skew;
-  const uint32_t front = blocks ? skew : 0u, window = blocks ? (skew + chunk_bytes + 15u) & ~15u : chunk_bytes;
+  const BlockCut bc = RAGGED && !MASK ? block_cut((__UINTPTR_TYPE__)px, (__UINTPTR_TYPE__)po, chunk_bytes) : BlockCut{false, 0u, chunk_bytes};
+  const bool blocks = bc.blocks;
+  const uint32_t front = bc.front, window = bc.window;
   const rsrc_t rx = make_rsrc(px - front, window);
   const rsrc_t ro = make_rsrc(po - front, window);
   rsrc_t rm = rx;

@@ -56,6 +56,16 @@ constexpr uint32_t kDispatchBatch = 64;        // records mirrored per dispatche
 constexpr uint32_t kThreads = 256;             // threads per workgroup of the worker
 constexpr uint32_t kRunMax = 64;               // tasks of a run (a head and the links behind it) that one workgroup takes together
 
+// Long ragged rows are cut where memory's 16-byte blocks begin if input and output lie alike in them: the chunk is
+// addressed from the block on that holds its first byte (`front` bytes before it) to the end of the one that holds its last.
+// (Not where that end would lie past kNoLoad, a row of 2 GiB: the stores that are to do nothing would land in its last block.)
+struct BlockCut { bool blocks; uint32_t front, window; };
+GPUOS_HD inline BlockCut block_cut(uint64_t x, uint64_t out, uint32_t bytes) {
+  const uint32_t skew = (uint32_t)out & 15u;
+  if (((uint32_t)x & 15u) != skew || skew + bytes > kNoLoad) return BlockCut{false, 0u, bytes};
+  return BlockCut{true, skew, (skew + bytes + 15u) & ~15u};
+}
+
 // The ring record ("compact descriptor", paper Section 4.1).  Written by the
 // host into the host ring; the dispatcher copies it into the device mirror and
 // fills impl / version / sel / status from the operator table.

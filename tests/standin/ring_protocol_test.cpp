@@ -119,6 +119,23 @@ static void chunks_stay_addressable() {
   std::printf("chunks within 32-bit offsets: ok\n");
 }
 
+// Rows cut at memory's 16-byte blocks: the resource covers the whole chunk, and no store that is to do nothing (kNoLoad) falls
+// inside it, up to the longest rows that the ragged executors take.
+static void block_cuts_stay_below_the_offset_that_does_nothing() {
+  for (uint32_t es : {2u, 4u})
+    for (uint32_t skew = 0; skew < 16; skew += es)
+      for (uint32_t bytes : {65540u, 128012u, gpuos::kNoLoad - 32, gpuos::kNoLoad - 16 - es, gpuos::kNoLoad - 16, gpuos::kNoLoad - 12, gpuos::kNoLoad - 8,
+                             gpuos::kNoLoad - es, gpuos::kNoLoad}) {
+        const uint64_t x = 0x7f0000000000ull + skew, o = 0x7e0000000000ull + skew;
+        const gpuos::BlockCut c = gpuos::block_cut(x, o, bytes);
+        CHECK(c.window <= gpuos::kNoLoad && c.window >= c.front + bytes);
+        CHECK(c.blocks ? c.front == skew && c.window % 16 == 0 : c.front == 0 && c.window == bytes);
+        CHECK(c.blocks == (skew + bytes <= gpuos::kNoLoad));
+        CHECK(!gpuos::block_cut(x, o + es, bytes).blocks);
+      }
+  std::printf("ok: rows cut at blocks stay below the offset that does nothing\n");
+}
+
 // Which tasks of a submit the host marks as links of a run: whoever reads what the task right before it wrote, over
 // buffers that are the same or apart, and nobody else.
 static void runs_are_marked() {
@@ -174,6 +191,7 @@ static void runs_are_marked() {
 
 int main() {
   check_word_rejects_mixtures();
+  block_cuts_stay_below_the_offset_that_does_nothing();
   runs_are_marked();
   chunks_stay_addressable();
   // 1. many producers, tiny rings: every ticket exactly once, consecutive inside a call, in-order log
