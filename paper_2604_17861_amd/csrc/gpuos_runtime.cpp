@@ -616,12 +616,12 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
 // and both work on contiguous aligned tensors of as many elements and one dtype: elementwise, with a mask
 // repeated over leading dims, with one scalar per row, or reducing rows (of whole vectors, up to 64; one row length in a run).
 // A chunk of it then runs while other chunks of the tasks before it have not, so an element may depend on
-// nothing but itself and its row: any two buffers of a run are the same one, seen alike, or do not overlap.
+// nothing but itself and its row: any two buffers of a run are the same one, of one dtype and seen alike, or do not overlap.
 // What it gives: links of 1K-16K elements 5.5 us each on their own, 0.4 in a run; and in a long chain
 // each intermediate is written but not read again.
 struct LinkRun {
   enum : uint8_t { kWhole, kRepeated, kPerRow };   // how a buffer is seen: element by element, [C] over and over, a scalar per row
-  struct Buffer { uint64_t base, bytes; uint8_t seen; bool written; };
+  struct Buffer { uint64_t base, bytes; uint8_t dtype, seen; bool written; };
   Buffer buf[10];
   uint32_t n = 0;                                  // buffers
   uint32_t len = 0;                                // tasks in the run that is being built (0: none)
@@ -639,10 +639,10 @@ struct LinkRun {
     if (r.okind[0] == K_FULL && r.okind[1] == K_ROWSCALAR) return r.size[0] == 1 || r.stride[1][0] == 1;
     return (r.okind[0] == K_FULL && r.okind[1] == K_ROWVEC) || (r.okind[0] == K_ROWVEC && r.okind[1] == K_FULL);
   }
-  bool take(uint64_t base, uint64_t bytes, uint8_t seen, bool write) {
+  bool take(uint64_t base, uint64_t bytes, uint8_t dt, uint8_t seen, bool write) {
     for (uint32_t j = 0; j < n; ++j) {
       Buffer& b = buf[j];
-      if (b.base == base && b.bytes == bytes && b.seen == seen) {
+      if (b.base == base && b.bytes == bytes && b.dtype == dt && b.seen == seen) {
         // (scalars of a row that were written and are no longer in registers would be read by other lanes than wrote them)
         if (seen == kPerRow && !write && b.written && base != last_reduced) return false;
         b.written = b.written || write;
@@ -651,7 +651,7 @@ struct LinkRun {
       if (base < b.base + b.bytes && b.base < base + bytes) return false;
     }
     if (n == sizeof(buf) / sizeof(buf[0])) return false;
-    buf[n++] = Buffer{base, bytes, seen, write};
+    buf[n++] = Buffer{base, bytes, dt, seen, write};
     return true;
   }
   // the record's buffers and shape join the run's
@@ -662,20 +662,20 @@ struct LinkRun {
       const uint32_t kind = r.path == PATH_ROW2D ? r.okind[k] : (uint32_t)K_FULL;
       if (kind == K_ROWSCALAR) {
         row_r = r.size[1];
-        if (!take(r.ptr[k], (uint64_t)r.size[0] * dtype_size(r.dtype[k]), kPerRow, false)) return false;
+        if (!take(r.ptr[k], (uint64_t)r.size[0] * dtype_size(r.dtype[k]), r.dtype[k], kPerRow, false)) return false;
       } else if (kind == K_ROWVEC) {
         if (repeat != 0 && repeat != r.size[1]) return false;
         repeat = r.size[1];
-        if (!take(r.ptr[k], repeat * es, kRepeated, false)) return false;
-      } else if (!take(r.ptr[k], whole, kWhole, false)) {
+        if (!take(r.ptr[k], repeat * es, r.dtype[k], kRepeated, false)) return false;
+      } else if (!take(r.ptr[k], whole, r.dtype[k], kWhole, false)) {
         return false;
       }
     }
     if (r.path == PATH_RED_CONTIG) {
       row_r = r.red_n;
-      if (!take(r.ptr[3], (uint64_t)r.numel * dtype_size(r.dtype[3]), kPerRow, true)) return false;
+      if (!take(r.ptr[3], (uint64_t)r.numel * dtype_size(r.dtype[3]), r.dtype[3], kPerRow, true)) return false;
       last_reduced = r.ptr[3];
-    } else if (!take(r.ptr[3], whole, kWhole, true)) {
+    } else if (!take(r.ptr[3], whole, r.dtype[3], kWhole, true)) {
       return false;
     }
     if (row_r != 0) {

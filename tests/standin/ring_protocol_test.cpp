@@ -184,6 +184,12 @@ static void runs_are_marked() {
     return std::vector<gpuos_task>{link(0, 1, 2), m, d};
   };
   CHECK(links_of(rows(250, 4)) == 2);
+  for (uint32_t dt : {GPUOS_F16, GPUOS_BF16}) {                                               // the scalars read as what they were written as, or not
+    std::vector<gpuos_task> h = rows(250, 4);
+    h[1].out.dtype = GPUOS_F16;
+    h[2].in[1].dtype = (uint8_t)dt;
+    CHECK(links_of(h) == (dt == GPUOS_F16 ? 2 : 1));
+  }
   CHECK(links_of(rows(200, 5)) == 0);
   CHECK(gpuos_shutdown(c) == GPUOS_OK);
   std::printf("ok: links of runs are marked, and nothing else\n");
