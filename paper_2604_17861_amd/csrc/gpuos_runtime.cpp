@@ -627,7 +627,7 @@ struct LinkRun {
   uint32_t len = 0;                                // tasks in the run that is being built (0: none)
   uint64_t elems = 0;
   uint32_t dtype = 0, row = 0, repeat = 0;         // row length, elements of a repeated operand (0: not known, none)
-  uint64_t last_reduced = 0;                       // what the last reduction wrote: its scalars are in registers
+  uint64_t scalars = 0;                            // the per-row buffer whose scalars are in registers: the last one written or read (run_links' sc_p)
 
   static uint64_t elements(const Record& r) { return r.path == PATH_RED_CONTIG ? (uint64_t)r.numel * r.red_n : r.numel; }
   static uint32_t dtype_of(const Record& r) { return r.path == PATH_RED_CONTIG ? r.dtype[0] : r.dtype[3]; }
@@ -643,8 +643,9 @@ struct LinkRun {
     for (uint32_t j = 0; j < n; ++j) {
       Buffer& b = buf[j];
       if (b.base == base && b.bytes == bytes && b.dtype == dt && b.seen == seen) {
-        // (scalars of a row that were written and are no longer in registers would be read by other lanes than wrote them)
-        if (seen == kPerRow && !write && b.written && base != last_reduced) return false;
+        // Scalars of a row that were written and are no longer in registers would be read by other lanes than wrote
+        // them.  (Nor are they written again: should that task then not run, its operator replaced, the one behind it would read the first's.)
+        if (seen == kPerRow && b.written && base != scalars) return false;
         b.written = b.written || write;
         return true;
       }
@@ -663,6 +664,7 @@ struct LinkRun {
       if (kind == K_ROWSCALAR) {
         row_r = r.size[1];
         if (!take(r.ptr[k], (uint64_t)r.size[0] * dtype_size(r.dtype[k]), r.dtype[k], kPerRow, false)) return false;
+        scalars = r.ptr[k];
       } else if (kind == K_ROWVEC) {
         if (repeat != 0 && repeat != r.size[1]) return false;
         repeat = r.size[1];
@@ -674,7 +676,7 @@ struct LinkRun {
     if (r.path == PATH_RED_CONTIG) {
       row_r = r.red_n;
       if (!take(r.ptr[3], (uint64_t)r.numel * dtype_size(r.dtype[3]), r.dtype[3], kPerRow, true)) return false;
-      last_reduced = r.ptr[3];
+      scalars = r.ptr[3];
     } else if (!take(r.ptr[3], whole, r.dtype[3], kWhole, true)) {
       return false;
     }
@@ -692,7 +694,7 @@ struct LinkRun {
                     elements(r) == elements(prev) && dtype_of(r) == dtype_of(prev);
     if (!ok) return false;
     if (len == 0) {
-      n = 0; row = repeat = 0; last_reduced = 0;
+      n = 0; row = repeat = 0; scalars = 0;
       elems = elements(prev);
       dtype = dtype_of(prev);
       if (!form(prev) || !take(prev)) return false;

@@ -262,3 +262,27 @@ def row_chains(code, seed):
         b.add("SUB" if seed % 2 else "MUL", y, [e, rows(l)], **D)
         b.add("DIV", y, [y, vec], **D)
     return b.stream("row_chains_%d_%d" % (code, seed), batch=[128, 7, 12][seed % 3])
+
+
+def scalar_chains(code):
+    """Chains over rows whose scalars are not in registers any more when a task asks for them: other scalars of
+    the rows were read in between, or they are read as another 16-bit format than they were written in."""
+    rng = np.random.default_rng(3000 + code)
+    b = Builder()
+    V = 4 if code == S.F32 else 8
+    for n, rows in ((V, 7), (8 * V, 200), (16 * V, 3000), (64 * V, 33)):
+        pool = lambda hi, size: b.pool(to_dtype(rng.integers(-hi, hi + 1, size).astype(np.float32), code))
+        per_row = lambda s: np.broadcast_to(s[:, None], (rows, n))
+        D = dict(dep=(1, 0, 0))
+        for m_code in (S.F32, S.F16):
+            x, t, y, z = pool(8, (rows, n)), pool(1, (rows, n)), pool(1, (rows, n)), pool(1, (rows, n))
+            m, k = (b.pool(to_dtype(rng.integers(1, 3, rows).astype(np.float32), m_code)) for _ in range(2))
+            b.add("SCALE", t, [x], alpha=2.0)
+            b.add("MAX_LAST", m, [t], **D)
+            b.add("SUB", y, [t, per_row(m)], **D)
+            b.add("MUL", y, [y, per_row(k)], **D)
+            b.add("SUB", y, [y, per_row(m)], **D)
+            b.add("MUL", y, [y, per_row(k)], **D)
+            b.add("MIN_LAST", m, [y], **D)
+            b.add("SUB", z, [y, per_row(m.view(np.uint16) if m_code == S.F16 else m)], **D)
+    return b.stream("scalar_chains_%d" % code, batch=8)

@@ -191,6 +191,21 @@ static void runs_are_marked() {
     CHECK(links_of(h) == (dt == GPUOS_F16 ? 2 : 1));
   }
   CHECK(links_of(rows(200, 5)) == 0);
+  // scalars that a task of the run wrote are not in registers any more behind other scalars of the rows: who reads or writes them
+  // then begins a run of its own (add m, add k, add m again; the same with a reduction into m at the end)
+  {
+    std::vector<gpuos_task> h = rows(250, 4);
+    gpuos_task by_m = h[2], by_k = h[2];
+    by_m.in[0].ptr = by_m.out.ptr = by_k.in[0].ptr = by_k.out.ptr = ptr(3);
+    by_k.in[1].ptr = ptr(6);
+    gpuos_task again = h[1];
+    again.in[0].ptr = ptr(3);
+    CHECK(links_of({h[0], h[1], h[2], by_m, by_k, by_k}) == 5);
+    CHECK(links_of({h[0], h[1], h[2], by_k, by_m}) == 3);
+    CHECK(links_of({h[0], h[1], h[2], by_k, by_m, by_k}) == 4);
+    CHECK(links_of({h[0], h[1], h[2], by_k, again}) == 3);
+    CHECK(links_of({h[0], h[1], h[2], again, by_m}) == 4);
+  }
   CHECK(gpuos_shutdown(c) == GPUOS_OK);
   std::printf("ok: links of runs are marked, and nothing else\n");
 }

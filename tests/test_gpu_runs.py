@@ -47,6 +47,13 @@ def test_chains_over_rows(code):
         assert stats["disp_records"] == len(s)
 
 
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_scalars_that_left_the_registers(code):
+    s = E.scalar_chains(code)
+    print("scalar chains", code, len(s), flush=True)
+    _run(s)
+
+
 @pytest.mark.parametrize("code,n", [(S.F32, 1000), (S.F32, 16384), (S.F16, 4097), (S.BF16, 40000)])
 def test_long_chains_are_run_together(code, n):
     s = E.long_chains(code, n)
