@@ -655,10 +655,10 @@ struct LinkRun {
     buf[n++] = Buffer{base, bytes, dt, seen, write};
     return true;
   }
-  // the record's buffers and shape join the run's
+  // the record's buffers and shape join the run's (refused: the run is complete, and its shape is as it was)
   bool take(const Record& r) {
     const uint64_t es = dtype_size(dtype), whole = elems * es;
-    uint32_t row_r = 0;
+    uint32_t row_r = 0, repeat_r = repeat;
     for (int k = 0; k < r.n_inputs; ++k) {
       const uint32_t kind = r.path == PATH_ROW2D ? r.okind[k] : (uint32_t)K_FULL;
       if (kind == K_ROWSCALAR) {
@@ -666,9 +666,9 @@ struct LinkRun {
         if (!take(r.ptr[k], (uint64_t)r.size[0] * dtype_size(r.dtype[k]), r.dtype[k], kPerRow, false)) return false;
         scalars = r.ptr[k];
       } else if (kind == K_ROWVEC) {
-        if (repeat != 0 && repeat != r.size[1]) return false;
-        repeat = r.size[1];
-        if (!take(r.ptr[k], repeat * es, r.dtype[k], kRepeated, false)) return false;
+        if (repeat_r != 0 && repeat_r != r.size[1]) return false;
+        repeat_r = r.size[1];
+        if (!take(r.ptr[k], repeat_r * es, r.dtype[k], kRepeated, false)) return false;
       } else if (!take(r.ptr[k], whole, r.dtype[k], kWhole, false)) {
         return false;
       }
@@ -683,9 +683,13 @@ struct LinkRun {
     if (row_r != 0) {
       const uint32_t V = 16u / (uint32_t)es;
       if ((row != 0 && row != row_r) || row_r % V != 0 || row_r / V > 64u) return false;
-      row = row_r;
+    } else {
+      row_r = row;
     }
-    return row == 0 || repeat % row == 0;
+    if (row_r != 0 && repeat_r % row_r != 0) return false;
+    row = row_r;
+    repeat = repeat_r;
+    return true;
   }
   // may r go with prev, the task before it in one submit?  (prev's run goes on, or prev heads one)
   bool links(const Record& prev, const Record& r) {

@@ -191,6 +191,21 @@ static void runs_are_marked() {
     CHECK(links_of(h) == (dt == GPUOS_F16 ? 2 : 1));
   }
   CHECK(links_of(rows(200, 5)) == 0);
+  // a task that is refused changes nothing: three large adds, the last one's bias 24 wide, stay by themselves whether a reduction
+  // over rows of 16, which does not go with that bias, follows or not; nor does a refused one's bias keep another out
+  {
+    std::vector<gpuos_task> h = {link(0, 1, 2), link(2, 1, 3), link(3, 4, 2)};
+    for (auto& t : h) t.size[0] = 240000;
+    gpuos_task& bias = h[2];
+    bias.ndim = 2; bias.size[0] = 10000; bias.size[1] = 24;
+    for (auto* q : {&bias.in[0], &bias.in[1], &bias.out}) { q->stride[0] = q == &bias.in[1] ? 0 : 24; q->stride[1] = 1; }
+    for (int k = 0; k < 3; ++k) for (auto* q : {&h[k].in[0], &h[k].in[1], &h[k].out}) q->ptr = (void*)((uintptr_t)q->ptr * 16);
+    CHECK(links_of(h) == 0);
+    gpuos_task max16 = rows(15000, 16)[1];
+    max16.in[0].ptr = h[2].out.ptr;
+    h.push_back(max16);
+    CHECK(links_of(h) == 0);
+  }
   // scalars that a task of the run wrote are not in registers any more behind other scalars of the rows: who reads or writes them
   // then begins a run of its own (add m, add k, add m again; the same with a reduction into m at the end)
   {
