@@ -392,57 +392,49 @@ template <> struct OpOut<GPUOS_IMPL_EXP, GPUOS_BF16> { static constexpr int N = 
 template <> struct OpOut<GPUOS_IMPL_SUB_EXP, GPUOS_F16> { static constexpr int N = 2; static DEV float f(float x, float y, float, float) { const float d = x - y; return exp_for_16bit<GPUOS_F16>(d); } };
 template <> struct OpOut<GPUOS_IMPL_SUB_EXP, GPUOS_BF16> { static constexpr int N = 2; static DEV float f(float x, float y, float, float) { const float d = x - y; return exp_for_16bit<GPUOS_BF16>(d); } };
 
-// o[k] = f(x[k], y[k], z[k], alpha) for the K elements a lane holds: element by element for the
-// built-in implementations (the compiler unrolls it back into straight code), instruction by
-// instruction for a program.
-// GELU of a vector of 16-bit elements: evaluated in fp32 with a bound on its relative error, and in fp64, as above,
-// where the two ends of that bound do not round to the same 16-bit value (Ziv's rounding test).  The result
-// is that of fp64 on every input.  Bound by arithmetic (half of it gone, a large tensor is bound by memory):
-// what decides is instructions an element, 30 against 60.
-//   ERF   the formula of Op<GELU_ERF> with k = 3 and degree 8 (2^-25.1); a * a is exact for a 16-bit a, so the
-//         exponent is carried in two words.  Off by at most 2^-21.7 over all inputs, plus the last bits of the
-//         hardware's reciprocal and exponential.
-//   TANH  x / (1 + 2^z), off by at most 2^-22.5 max(|z|, 1).
-// (Near zero, at infinity and for NaN both ends round alike.  bf16 reaches down to where fp32 has no more normal
-// numbers: there, below -12 and -9, fp64 decides always.)
-template <int IMPL> DEV float gelu_fp32(float x, float& eps) {
-  if (IMPL == GPUOS_IMPL_GELU_ERF) {
-    const float a = __builtin_fabsf(x), c = __builtin_fminf(a, 12.0f), s = c * c;
-    const float d = __builtin_amdgcn_rcpf(c + 3.0f), t = __builtin_fmaf(-6.0f, d, 1.0f);
-    float p = -0.00028271329938434064f;
-    p = __builtin_fmaf(p, t, -0.0009280924568884075f);
-    p = __builtin_fmaf(p, t, 0.0010787147330120206f);
-    p = __builtin_fmaf(p, t, 0.0069399685598909855f);
-    p = __builtin_fmaf(p, t, -0.01047808863222599f);
-    p = __builtin_fmaf(p, t, -0.04725917801260948f);
-    p = __builtin_fmaf(p, t, 0.23001901805400848f);
-    p = __builtin_fmaf(p, t, -0.5093321204185486f);
-    p = __builtin_fmaf(p, t, 0.7290836572647095f);
-    constexpr float KH = (float)-kHalfLog2e, KL = (float)(-kHalfLog2e - (double)KH);
-    const float z = s * KH, e = __builtin_fmaf(s, KL, __builtin_fmaf(s, KH, -z));        // the exponent is z + e
-    float q = p * d * __builtin_amdgcn_exp2f(z);
-    q = __builtin_fmaf(q, e * 0.6931472f, q);
-    eps = 0x1p-21f;
-    return __builtin_copysignf(__builtin_fmaf(-c, q, 0.5f * (x + a)), x);
-  }
-  const float s = x * x, z = x * __builtin_fmaf((float)kTanhZ3, s, (float)kTanhZ1);
-  eps = __builtin_fmaf(__builtin_fabsf(z), 0x1p-22f, 0x1.8p-22f);
-  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z));
+// GELU_ERF of a vector of bf16 elements: evaluated in fp32 with a bound on its relative error, and in fp64, as above,
+// where the two ends of that bound do not round to the same bf16 value (Ziv's rounding test).  Bound by arithmetic (half
+// of it gone, a large tensor is bound by memory): what decides is instructions an element, 30 against 60.
+// The formula of Op<GELU_ERF> with k = 3 and degree 8 (2^-25.1); a * a is exact for a 16-bit a, so the
+// exponent is carried in two words.  2^-21 is no sum of worst cases (2^-21.7 for the formula in fp32, and the last
+// bits of the hardware's reciprocal and exponential on top would pass it): there are 65,536 inputs, and the tests compare
+// every one with fp64, bit for bit.  (Near zero, at infinity and for NaN both ends round alike.  bf16 reaches down
+// to where fp32 has no more normal numbers: there, below -12, fp64 decides always.)
+// It is for batches of several vectors a lane.  A wavefront falls back for one vector in 16, and waits for a chain of
+// 60 dependent instructions then, which other vectors in flight hide and a lone one does not.  Not for f16 and not for GELU_TANH, which are in doubt 8 and 2 times as often (three
+// more bits of a result; a bound that grows with the exponent): four tasks of 164K elements, fp64 against this, f16 ERF 26.1
+// and 27.7 us, f16 TANH 21.1 and 27.4, bf16 TANH 20.8 and 25.0; two of 8.4M, 54.4 and 52.1, 40.3 and 51.2, 40.0 and 45.3.
+DEV float gelu_erf_fp32(float x) {
+  const float a = __builtin_fabsf(x), c = __builtin_fminf(a, 12.0f), s = c * c;
+  const float d = __builtin_amdgcn_rcpf(c + 3.0f), t = __builtin_fmaf(-6.0f, d, 1.0f);
+  float p = -0.00028271329938434064f;
+  p = __builtin_fmaf(p, t, -0.0009280924568884075f);
+  p = __builtin_fmaf(p, t, 0.0010787147330120206f);
+  p = __builtin_fmaf(p, t, 0.0069399685598909855f);
+  p = __builtin_fmaf(p, t, -0.01047808863222599f);
+  p = __builtin_fmaf(p, t, -0.04725917801260948f);
+  p = __builtin_fmaf(p, t, 0.23001901805400848f);
+  p = __builtin_fmaf(p, t, -0.5093321204185486f);
+  p = __builtin_fmaf(p, t, 0.7290836572647095f);
+  constexpr float KH = (float)-kHalfLog2e, KL = (float)(-kHalfLog2e - (double)KH);
+  const float z = s * KH, e = __builtin_fmaf(s, KL, __builtin_fmaf(s, KH, -z));        // the exponent is z + e
+  float q = p * d * __builtin_amdgcn_exp2f(z);
+  q = __builtin_fmaf(q, e * 0.6931472f, q);
+  return __builtin_copysignf(__builtin_fmaf(-c, q, 0.5f * (x + a)), x);
 }
-template <int IMPL, int DT> DEV void gelu_16bit(const float (&x)[8], float (&o)[8]) {
-  using E = Elem<DT>;
+DEV void gelu_erf_bf16(const float (&x)[8], float (&o)[8]) {
+  using E = Elem<GPUOS_BF16>;
+  constexpr float eps = 0x1p-21f, limit = -12.0f;
   v4i lo = {0, 0, 0, 0}, hi = {0, 0, 0, 0};
   float least = x[0];
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    float eps;
-    o[k] = gelu_fp32<IMPL>(x[k], eps);
+    o[k] = gelu_erf_fp32(x[k]);
     E::put(lo, k, __builtin_fmaf(-eps, o[k], o[k]));
     E::put(hi, k, __builtin_fmaf(eps, o[k], o[k]));
     least = __builtin_fminf(least, x[k]);
   }
   const v4i diff = lo ^ hi;
-  const float limit = DT == GPUOS_F16 ? -__builtin_inff() : (IMPL == GPUOS_IMPL_GELU_ERF ? -12.0f : -9.0f);
   if (__ballot((diff[0] | diff[1] | diff[2] | diff[3]) != 0 || least < limit) == 0) return;
   // (one element of the eight after the other: few vectors have more than one in doubt, and the code is there once)
 #pragma unroll 1
@@ -453,16 +445,19 @@ template <int IMPL, int DT> DEV void gelu_16bit(const float (&x)[8], float (&o)[
     for (int j = 1; j < 8; ++j) { xk = j == k ? x[j] : xk; dk = j == k ? diff[j >> 1] : dk; }
     const bool doubt = ((uint32_t)dk & (k & 1 ? 0xffff0000u : 0xffffu)) != 0 || xk < limit;
     if (__ballot(doubt) == 0) continue;
-    const float y = Op<IMPL>::f(xk, 0.f, 0.f, 0.f);
+    const float y = Op<GPUOS_IMPL_GELU_ERF>::f(xk, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[j] = doubt && j == k ? y : o[j];
   }
 }
 
-template <int IMPL, int K, int DT = GPUOS_F32>
+// o[k] = f(x[k], y[k], z[k], alpha) for the K elements a lane holds (one of BATCH vectors in flight): element by element for
+// the built-in implementations (the compiler unrolls it back into straight code), instruction by
+// instruction for a program.
+template <int IMPL, int K, int DT = GPUOS_F32, int BATCH = 1>
 DEV void apply_vec(const float (&x)[K], const float (&y)[K], const float (&z)[K], float alpha, float (&o)[K]) {
-  if constexpr ((IMPL == GPUOS_IMPL_GELU_ERF || IMPL == GPUOS_IMPL_GELU_TANH) && DT != GPUOS_F32 && K == 8) {
-    gelu_16bit<IMPL, DT>(x, o);
+  if constexpr (IMPL == GPUOS_IMPL_GELU_ERF && DT == GPUOS_BF16 && K == 8 && BATCH > 1) {
+    gelu_erf_bf16(x, o);
     return;
   }
   if (IMPL == kImplProg1 || IMPL == kImplProg2 || IMPL == kImplProg3) {
@@ -544,7 +539,7 @@ template <int IMPL, int DT, int K, class A, class B, class C, class S> DEV void 
       for (int k = 0; k < V; ++k) {
         xa[k] = a.get(u, k); xb[k] = N > 1 ? b.get(u, k) : 0.f; xc[k] = N > 2 ? c.get(u, k) : 0.f;
       }
-      apply_vec<IMPL, V, DT>(xa, xb, xc, alpha, xo);
+      apply_vec<IMPL, V, DT, K>(xa, xb, xc, alpha, xo);
 #pragma unroll
       for (int k = 0; k < V; ++k) E::put(q, k, xo[k]);
     }
@@ -593,14 +588,14 @@ template <int ARITY> struct ByArity {
 // PATH_CONTIG: out[i] = f(a[i], b[i], c[i]), all operands the same dtype.
 // 16 bytes per lane per access, four accesses in flight per operand.
 // ---------------------------------------------------------------------------
-template <int POL, int IMPL, int DT>
-PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
+template <int POL, int IMPL, int DT, int U>
+DEV void ew_contig_rounds(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   uint32_t begin = uni(begin_v);
   const uint32_t end = uni(end_v);
   using E = Elem<DT>;
   using M = Mem<POL>;
-  constexpr int V = E::V, N = Op<IMPL>::N, U = 4;
+  constexpr int V = E::V, N = Op<IMPL>::N;
   const char* pa = uni_ptr(r->ptr[0]);
   const char* pb = N > 1 ? uni_ptr(r->ptr[1]) : pa;
   const char* pc = N > 2 ? uni_ptr(r->ptr[2]) : pa;
@@ -614,7 +609,7 @@ PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint3
     const rsrc_t ra = make_rsrc(pa + boff, bytes), rb = make_rsrc(pb + boff, bytes), rc = make_rsrc(pc + boff, bytes);
     const rsrc_t ro = make_rsrc(po + boff, bytes);
     uint32_t v = tid;
-    for (; v + (U - 1) * kThreads < nvec; v += U * kThreads) {
+    for (; U > 1 && v + (U - 1) * kThreads < nvec; v += U * kThreads) {
       v4i qa[U], qb[U], qc[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -641,6 +636,19 @@ PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint3
     else
       E::template store1<POL>(po, i, OpOut<IMPL, DT>::f(E::template load1<POL>(pa, i), N > 1 ? E::template load1<POL>(pb, i) : 0.f,
                                                  N > 2 ? E::template load1<POL>(pc, i) : 0.f, alpha));
+  }
+}
+template <int POL, int IMPL, int DT>
+PATHFN void ew_contig_batches(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) { ew_contig_rounds<POL, IMPL, DT, 4>(r_v, begin_v, end_v, tid); }
+template <int POL, int IMPL, int DT>
+PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
+  if constexpr (IMPL == GPUOS_IMPL_GELU_ERF && DT == GPUOS_BF16) {
+    // (Batches need registers that callers keep, 128 bytes a lane to save and restore: with them in one function
+    // four tasks of 2,048 elements took 13.0 us, 12.4 so; of 8.4M, 38.8 and 39.5.)
+    if (uni(end_v) - uni(begin_v) >= 4u * kThreads * Elem<DT>::V) ew_contig_batches<POL, IMPL, DT>(r_v, begin_v, end_v, tid);
+    else ew_contig_rounds<POL, IMPL, DT, 1>(r_v, begin_v, end_v, tid);
+  } else {
+    ew_contig_rounds<POL, IMPL, DT, 4>(r_v, begin_v, end_v, tid);
   }
 }
 

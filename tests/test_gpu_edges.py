@@ -178,6 +178,36 @@ def test_gelu_of_16bit_inputs_is_the_rounded_fp64_value(code):
         assert len(bad) == 0, (code, k16, len(bad), y32[bad[:5]], y16[bad[:5]], want[bad[:5]])
 
 
+@pytest.mark.parametrize("n", [2048, 8191, 8192, 8193, 12288, 12289, 33000, 65536])
+def test_gelu_of_bf16_inputs_round_a_batch(n):
+    """Round the batch of 8,192 elements from which on a chunk is evaluated in fp32 first: the result is the fp32
+    output (evaluated in fp64) rounded once more, bit for bit, aligned and one element off."""
+    import numpy as np
+    from gpu_helpers import DevicePools, run_stream
+    from helpers import Builder
+    from paper_2604_17861_amd import runtime as R
+    b, pairs = Builder(), []
+    bits = np.random.default_rng(n).permutation(65536).astype(np.uint16)
+    bits = np.append(bits[(bits & 0x7fff) <= 0x7f80], bits[:1024])[:n]            # (no NaN, whose bits are free)
+    bits[(bits & 0x7fff) > 0x7f80] = 0
+    for off in (0, 1):
+        X = b.pool(np.append(np.zeros(off, np.uint16), bits))[off:]
+        o16, o32 = b.pool(np.zeros(bits.size + off, np.uint16))[off:], b.pool(np.zeros(bits.size, np.float32))
+        b.add("GELU_ERF", o16, [X])
+        b.add("GELU_ERF", o32, [X])
+        pairs.append((len(b.bases) - 2, len(b.bases) - 1, off))
+    s = b.stream("gelu_bf16_batch_%d" % n)
+    dp = DevicePools(s)
+    with R.Runtime(idle_exit_ms=20000, wait_timeout_ms=20000) as rt:
+        rt.register_table(s.table)
+        run_stream(s, rt, dp)
+    got = dp.download()
+    for k16, k32, off in pairs:
+        w = got[k32].view(np.uint32).astype(np.uint64)
+        want = ((w + 0x7FFF + ((w >> 16) & 1)) >> 16).astype(np.uint16)
+        assert np.array_equal(got[k16].view(np.uint16)[off:], want)
+
+
 @pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
 def test_long_softmax_rows_at_every_alignment(code):
     """Rows too long for the workgroup's registers, cut at memory's 16-byte blocks where input and output lie alike in
