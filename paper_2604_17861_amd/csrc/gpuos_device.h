@@ -2708,20 +2708,6 @@ DEV void run_reduction(const Record* r, const RecHead& h, uint32_t chunk, float*
   }
 }
 
-// The interpreter's executors, behind one call: in the worker loop itself they were 66 of its 292 call sites,
-// each of which costs every unit (see rowop_other).  Calls, not jumps: an executor that is jumped to has to
-// keep its caller's registers, one that is only called leaves that to its caller, which has few.
-template <int POL>
-__attribute__((disable_tail_calls)) PATHFN void run_program_chunk(const Record* r_v, uint32_t n_in_v, uint32_t chunk_v, float* s_v, uint32_t tid) {
-  const Record* r = lds_arg(r_v);
-  float* s = lds_arg(s_v);
-  const RecHead h = RecHead::of(r);
-  const uint32_t n_in = uni(n_in_v), chunk = uni(chunk_v);
-  if (n_in == 1) run_elementwise<POL, kImplProg1>(r, h, chunk, s, tid);
-  else if (n_in == 2) run_elementwise<POL, kImplProg2>(r, h, chunk, s, tid);
-  else run_elementwise<POL, kImplProg3>(r, h, chunk, s, tid);
-}
-
 // A task whose operator is a program: fetch the program into LDS (17 lanes x 16 bytes), then run
 // the ordinary elementwise paths with the interpreter as their functor.
 template <int POL>
@@ -2735,7 +2721,9 @@ DEV int32_t exec_program(const Record* r, const RecHead& h, uint32_t impl, uint3
   const uint32_t n_in = uni(g_prog.n_inputs), n_instr = uni(g_prog.n_instr);
   if (uni(g_prog.ready) != kProgramReady || n_instr < 1 || n_instr > GPUOS_PROGRAM_MAX_INSTR || n_in != uni(r->n_inputs))
     status = GPUOS_E_INVAL;                            // never defined (or not what the task was packed for)
-  else run_program_chunk<POL>(r, n_in, chunk, s_red, tid);
+  else if (n_in == 1) run_elementwise<POL, kImplProg1>(r, h, chunk, s_red, tid);
+  else if (n_in == 2) run_elementwise<POL, kImplProg2>(r, h, chunk, s_red, tid);
+  else run_elementwise<POL, kImplProg3>(r, h, chunk, s_red, tid);
   __syncthreads();                                     // the next chunk may bring another program
   return status;
 }
