@@ -588,8 +588,8 @@ template <int ARITY> struct ByArity {
 // PATH_CONTIG: out[i] = f(a[i], b[i], c[i]), all operands the same dtype.
 // 16 bytes per lane per access, four accesses in flight per operand.
 // ---------------------------------------------------------------------------
-template <int POL, int IMPL, int DT, int U>
-DEV void ew_contig_rounds(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
+template <int POL, int IMPL, int DT, int U = 4>
+PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
   const Record* r = lds_arg(r_v);
   uint32_t begin = uni(begin_v);
   const uint32_t end = uni(end_v);
@@ -638,20 +638,6 @@ DEV void ew_contig_rounds(const Record* r_v, uint32_t begin_v, uint32_t end_v, u
                                                  N > 2 ? E::template load1<POL>(pc, i) : 0.f, alpha));
   }
 }
-template <int POL, int IMPL, int DT>
-PATHFN void ew_contig_batches(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) { ew_contig_rounds<POL, IMPL, DT, 4>(r_v, begin_v, end_v, tid); }
-template <int POL, int IMPL, int DT>
-PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
-  if constexpr (IMPL == GPUOS_IMPL_GELU_ERF && DT == GPUOS_BF16) {
-    // (Batches need registers that callers keep, 128 bytes a lane to save and restore: with them in one function
-    // four tasks of 2,048 elements took 13.0 us, 12.4 so; of 8.4M, 38.8 and 39.5.)
-    if (uni(end_v) - uni(begin_v) >= 4u * kThreads * Elem<DT>::V) ew_contig_batches<POL, IMPL, DT>(r_v, begin_v, end_v, tid);
-    else ew_contig_rounds<POL, IMPL, DT, 1>(r_v, begin_v, end_v, tid);
-  } else {
-    ew_contig_rounds<POL, IMPL, DT, 4>(r_v, begin_v, end_v, tid);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // PATH_ROW2D: contiguous [R, C] output of dtype DT, C a multiple of the vector
 // width; each input is a full [R, C] tensor (dtype DT), a row vector [C]
@@ -2650,7 +2636,12 @@ DEV void run_elementwise(const Record* r, const RecHead& h, uint32_t chunk, floa
   if (path == PATH_CONTIG) {
     if (dt == GPUOS_F32) ew_contig<POL, IMPL, GPUOS_F32>(r, begin, end, tid);
     else if (dt == GPUOS_F16) ew_contig<POL, IMPL, GPUOS_F16>(r, begin, end, tid);
-    else ew_contig<POL, IMPL, GPUOS_BF16>(r, begin, end, tid);
+    else if constexpr (IMPL == GPUOS_IMPL_GELU_ERF) {
+      // (Batches in fp32 need registers that callers keep, 128 bytes a lane to save and restore: with both in one
+      // function four tasks of 2,048 elements took 13.0 us, 12.1 so.)
+      if (end - begin >= 4u * kThreads * 8u) ew_contig<POL, IMPL, GPUOS_BF16>(r, begin, end, tid);
+      else ew_contig<POL, IMPL, GPUOS_BF16, 1>(r, begin, end, tid);
+    } else ew_contig<POL, IMPL, GPUOS_BF16>(r, begin, end, tid);
   } else if (path == PATH_ROW2D && Op<IMPL>::N >= 2) {
     constexpr int I2 = Op<IMPL>::N >= 2 ? IMPL : GPUOS_IMPL_ADD;
     const uint32_t k0 = uni(r->okind[0]), k1 = uni(r->okind[1]);
