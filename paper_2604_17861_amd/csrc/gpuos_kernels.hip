@@ -167,20 +167,23 @@ DEV bool names_pending(const DispShared* s, uint64_t ticket, const uint16_t* dep
   return hit;
 }
 
-// First wavefront: the units of s->pub[0 .. npub) that go to ring `route`, numbered: entries of the other ring
-// count as zero units (they keep their place in the list, so both rings see their tasks in list order).
-DEV void dispatcher_number_units(DispShared* s, uint32_t npub, uint32_t route) {
-  const uint32_t tid = threadIdx.x;
-  // inclusive scan over the wavefront with DPP: shifts by 1, 2, 4, 8 inside each row of 16 lanes
-  // (lanes the shift runs out of the row for add 0), then lane 15 of a row to the whole next row
-  // (rows 1 and 3), then lane 31 to rows 2 and 3.  Six shuffles through the LDS crossbar before.
-  int v = (int)((tid < npub && s->pub[tid].route == route) ? s->pub[tid].nchunks : 0u);
+// Inclusive sum over the wavefront with DPP: shifts by 1, 2, 4, 8 inside each row of 16 lanes
+// (lanes the shift runs out of the row for add 0), then lane 15 of a row to the whole next row
+// (rows 1 and 3), then lane 31 to rows 2 and 3.  Six shuffles through the LDS crossbar before.
+DEV int wave_prefix_sum(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);
   v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
   v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
   v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
   v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
   v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+// First wavefront: the units of s->pub[0 .. npub) that go to ring `route`, numbered: entries of the other ring
+// count as zero units (they keep their place in the list, so both rings see their tasks in list order).
+DEV void dispatcher_number_units(DispShared* s, uint32_t npub, uint32_t route) {
+  const uint32_t tid = threadIdx.x;
+  const int v = wave_prefix_sum((int)((tid < npub && s->pub[tid].route == route) ? s->pub[tid].nchunks : 0u));
   s->ubeg[tid + 1] = (uint32_t)v;                // (entries past npub hold the total: the search below counts them out)
   if (tid == 0) s->ubeg[0] = 0;
 }
@@ -271,114 +274,121 @@ DEV void dispatcher_service_pending(const WorkerArgs& a, DispShared* s, UnitCurs
 // never passed their check).  Resolves the operator table ("claim time": slot, version, impl, status) and the
 // dependencies in the records themselves, splits the batch into tasks that are published now (s->pub) and tasks
 // that are held back (s->pend), and numbers the units of the main ring (s->ubeg).
+// A lane reads what it asks of its record in one go, keeps it in registers and writes it back at the end: this is a
+// chain of LDS latencies that every pass waits for, a pass of two records as long as one of 64.  (Field by field from
+// LDS it took 1.35 us of a pass's 2.5.)
 DEV void dispatcher_plan(const WorkerArgs& a, DispShared* s, uint32_t n, uint64_t mirrored, uint64_t m_bad, bool tracing, uint64_t tk0, uint64_t& st_deferred) {
   const uint32_t tid = threadIdx.x;
-  uint32_t defer = 0;
-  if (tid < n) {
-    Record& rc = s->rec[tid];
-    const uint32_t op = rc.op_id;
-    const uint64_t ticket = mirrored + tid;
-    int32_t status = GPUOS_OK;
-    uint64_t e = 0;
-    if ((m_bad >> tid) & 1u) {                                         // never passed its check: do not trust any field
-      status = GPUOS_E_INVAL;
-      rc.path = PATH_NOP; rc.nchunks = 1; rc.dep[0] = rc.dep[1] = rc.dep[2] = 0; rc.rflags = 0;
-    } else if (op >= GPUOS_MAX_OPS) status = GPUOS_E_BADOP;   // bounds check on the op id
-    else {
-      e = s->entry[op];
-      if (e == 0) status = GPUOS_E_BADOP;                      // never registered
-    }
-    rc.impl = (uint32_t)e;
-    rc.version = (uint32_t)(e >> 32);
-    rc.sel = (uint8_t)((e >> 32) & 1u);
-    rc.status = status;
-    if (status != GPUOS_OK || rc.nchunks == 0) rc.nchunks = 1; // one unit reports the task
-    rc.ticket = ticket;
-    if (tracing) {
-      rc.t_dequeue[0] = (uint32_t)tk0; rc.t_dequeue[1] = (uint32_t)(tk0 >> 32);
-      if (op < GPUOS_MAX_OPS) atomicAdd(&s->opcnt[op], 1u);
-    }
-    // A link goes with the record before it: no units of its own, and nothing to wait for but that one (a
-    // held head holds it, see below).  Only inside one pass, so that its mirror record is on its way
-    // before the units that stand for it are.  Not under tracing, whose records tell of
-    // one task at a time.
-    const uint64_t m_can = __ballot(status == GPUOS_OK && impl_links((uint32_t)e, rc.n_inputs, rc.path));
-    const uint64_t m_mark = __ballot(!tracing && (rc.rflags & RF_LINK) != 0);
-    const uint64_t m_link = m_can & m_mark & (m_can << 1);
-    const bool link = (m_link >> tid) & 1u;
-    const uint64_t behind = tid < 63u ? ~(m_link >> (tid + 1u)) : ~0ull;
-    rc.run = (uint16_t)(link ? 0u : (uint32_t)__builtin_ctzll(behind) + 1u);
-    if (!link && (rc.dep[0] | rc.dep[1] | rc.dep[2]) != 0) {
-      if (rc.nchunks > kSmallTaskChunks) {
-        // a large dependent task: its workers never wait; it is published once its
-        // dependencies are complete (now, or later from the pending list)
-        rc.rflags |= RF_DEPS_RESOLVED;
-        defer = deps_complete(a, ticket, rc.dep) ? 0u : 1u;
-      } else {
-        // a small one is published at once and its workers wait, unless it names a task that is
-        // itself held back: then it joins the pending list behind that task (tasks held in this
-        // very pass are found below, in the split)
-        defer = names_pending(s, ticket, rc.dep) ? 1u : 0u;
-      }
+  const bool mine = tid < n, bad = (m_bad >> tid) & 1u;
+  static_assert(offsetof(Record, path) == 2 && offsetof(Record, n_inputs) == 4 && offsetof(Record, rflags) == 9 && offsetof(Record, sel) == 13 &&
+                offsetof(Record, impl) == 16 && offsetof(Record, version) == 20 && offsetof(Record, status) == 24 && offsetof(Record, nchunks) == 28 &&
+                offsetof(Record, dep) == 48 && offsetof(Record, run) == 54 && offsetof(Record, ticket) == 56, "the words that are read and written as vectors");
+  v4i* const words = (v4i*)&s->rec[tid];
+  v4i w0 = words[0], w1 = words[1], w3 = words[3];
+  const uint32_t npend0 = s->npend;
+  if (bad) { w0[0] &= (int)0xff00ffff; w0[2] &= (int)0xffff00ff; w1[3] = 1; w3[0] = 0; w3[1] = 0; }       // (path, rflags, dep): do not trust any field
+  static_assert(PATH_NOP == 0, "the path of a record that is not trusted");
+  const uint32_t op = (uint32_t)w0[0] & 0xffffu, path = ((uint32_t)w0[0] >> 16) & 0xffu, n_inputs = (uint32_t)w0[1] & 0xffu;
+  uint32_t rflags = ((uint32_t)w0[2] >> 8) & 0xffu, nchunks = (uint32_t)w1[3];
+  const uint16_t dep[3] = {(uint16_t)((uint32_t)w3[0] & 0xffffu), (uint16_t)((uint32_t)w3[0] >> 16), (uint16_t)((uint32_t)w3[1] & 0xffffu)};
+  const bool deps = (dep[0] | dep[1] | dep[2]) != 0;
+  const uint64_t ticket = mirrored + tid;
+  const uint64_t e = !bad && op < GPUOS_MAX_OPS ? s->entry[op] : 0ull;          // bounds check on the op id; 0: never registered
+  const int32_t status = bad ? GPUOS_E_INVAL : (e == 0 ? GPUOS_E_BADOP : GPUOS_OK);
+  const uint32_t impl = (uint32_t)e, sel = (uint32_t)(e >> 32) & 1u;
+  if (status != GPUOS_OK || nchunks == 0) nchunks = 1;         // one unit reports the task
+  if (tracing && mine) {
+    s->rec[tid].t_dequeue[0] = (uint32_t)tk0; s->rec[tid].t_dequeue[1] = (uint32_t)(tk0 >> 32);
+    if (op < GPUOS_MAX_OPS) atomicAdd(&s->opcnt[op], 1u);
+  }
+  // A link goes with the record before it: no units of its own, and nothing to wait for but that one (a
+  // held head holds it, see below).  Only inside one pass, so that its mirror record is on its way
+  // before the units that stand for it are.  Not under tracing, whose records tell of
+  // one task at a time.
+  const uint64_t m_can = __ballot(mine && status == GPUOS_OK && impl_links(impl, n_inputs, path));
+  const uint64_t m_mark = __ballot(!tracing && (rflags & RF_LINK) != 0);
+  const uint64_t m_link = m_can & m_mark & (m_can << 1);
+  const bool link = (m_link >> tid) & 1u;
+  const uint64_t behind = tid < 63u ? ~(m_link >> (tid + 1u)) : ~0ull;
+  const uint32_t run = link ? 0u : (uint32_t)__builtin_ctzll(behind) + 1u;
+  bool held = false;
+  if (mine && !link && deps) {
+    if (nchunks > kSmallTaskChunks) {
+      // a large dependent task: its workers never wait; it is published once its
+      // dependencies are complete (now, or later from the pending list)
+      rflags |= RF_DEPS_RESOLVED;
+      held = !deps_complete(a, ticket, dep);
+    } else {
+      // a small one is published at once and its workers wait, unless it names a task that is
+      // itself held back: then it joins the pending list behind that task (tasks held in this
+      // very pass are found below, in the split)
+      held = names_pending(s, ticket, dep);
     }
   }
-  lds_wave_sync();
-  const uint32_t npend0 = s->npend;
-  const bool mine = tid < n;
-  bool held = mine && defer != 0;
   // A task that names a task held in this pass is held too (a large one already is: such a
   // dependency cannot be complete).  Dependencies point backwards, so a few rounds of
   // "held if one of my in-pass dependencies is held" reach the fixed point.
-  uint64_t dep_mask = 0;                                     // records of this pass the task names
-  if (mine && !held) {
+  uint64_t m_def = __ballot(held);
+  if (m_def != 0) {
+    uint64_t dep_mask = 0;                                     // records of this pass the task names
+    if (mine && !held) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const uint32_t back = s->rec[tid].dep[k];
-      if (back != 0 && back <= tid) dep_mask |= 1ull << (tid - back);
+      for (int k = 0; k < 3; ++k) {
+        const uint32_t back = dep[k];
+        if (back != 0 && back <= tid) dep_mask |= 1ull << (tid - back);
+      }
+    }
+    while (true) {
+      held = held || (dep_mask & m_def) != 0;
+      const uint64_t m2 = __ballot(held);
+      if (m2 == m_def) break;
+      m_def = m2;
     }
   }
-  uint64_t m_def = __ballot(held);
-  while (true) {
-    held = held || (dep_mask & m_def) != 0;
-    const uint64_t m2 = __ballot(held);
-    if (m2 == m_def) break;
-    m_def = m2;
-  }
-  const bool unit = mine && s->rec[tid].run != 0;            // (a link has no units)
+  const bool unit = mine && run != 0;                        // (a link has no units)
   const uint64_t m_pub = __ballot(unit && !held), m_pend = __ballot(unit && held);
   const uint64_t below = (1ull << tid) - 1ull;
-  bool second = false;                                       // published now, on the second ring
-  if (held) s->rec[tid].rflags |= RF_DEPS_RESOLVED;          // published only after its dependencies completed
+  const uint32_t pub_before = (uint32_t)__popcll(m_pub & below);
+  if (held) rflags |= RF_DEPS_RESOLVED;                      // published only after its dependencies completed
+  // tasks of a program that a run-time kernel holds as native code go to that kernel's ring
+  const uint32_t prog = impl - GPUOS_IMPL_PROGRAM_BASE;
+  PubEntry pe;
+  pe.slot = (uint32_t)(ticket & a.cap_mask);
+  pe.nchunks = nchunks;
+  pe.opinfo = (op & 0xffu) | (sel << 8) | ((status == GPUOS_OK ? 1u : 0u) << 9) | ((uint32_t)((ticket >> a.cap_shift) & 0x3ffu) << 16);
+  pe.route = (status == GPUOS_OK && impl >= GPUOS_IMPL_PROGRAM_BASE && prog < GPUOS_MAX_PROGRAMS && s->native[prog] != 0) ? 1u : 0u;
   if (unit) {
-    const Record& rc = s->rec[tid];
-    PubEntry pe;
-    pe.slot = (uint32_t)((mirrored + tid) & a.cap_mask);
-    pe.nchunks = rc.nchunks;
-    pe.opinfo = (rc.op_id & 0xffu) | ((uint32_t)rc.sel << 8) | ((rc.status == GPUOS_OK ? 1u : 0u) << 9) |
-                ((uint32_t)(((mirrored + tid) >> a.cap_shift) & 0x3ffu) << 16);
-    // tasks of a program that a run-time kernel holds as native code go to that kernel's ring
-    const uint32_t prog = rc.impl - GPUOS_IMPL_PROGRAM_BASE;
-    pe.route = (rc.status == GPUOS_OK && rc.impl >= GPUOS_IMPL_PROGRAM_BASE && prog < GPUOS_MAX_PROGRAMS && s->native[prog] != 0) ? 1u : 0u;
-    second = pe.route != 0 && !held;
     if (held) {
       PendEntry& pd = s->pend[npend0 + (uint32_t)__popcll(m_pend & below)];
-      pd.ticket = mirrored + tid;
+      pd.ticket = ticket;
       pd.pub = pe;
-      pd.dep[0] = rc.dep[0]; pd.dep[1] = rc.dep[1]; pd.dep[2] = rc.dep[2];
-      pd.run = rc.run;
+      pd.dep[0] = dep[0]; pd.dep[1] = dep[1]; pd.dep[2] = dep[2];
+      pd.run = (uint16_t)run;
     } else {
-      s->pub[(uint32_t)__popcll(m_pub & below)] = pe;
+      s->pub[pub_before] = pe;
     }
   }
-  const uint64_t m_second = __ballot(second);
+  if (mine) {
+    w0[2] = (int)(((uint32_t)w0[2] & 0xffff00ffu) | (rflags << 8));
+    w0[3] = (int)(((uint32_t)w0[3] & 0xffff00ffu) | (sel << 8));
+    w1[0] = (int)impl; w1[1] = (int)(uint32_t)(e >> 32); w1[2] = status; w1[3] = (int)nchunks;
+    w3[1] = (int)(((uint32_t)w3[1] & 0xffffu) | (run << 16));
+    w3[2] = (int)(uint32_t)ticket; w3[3] = (int)(uint32_t)(ticket >> 32);
+    words[0] = w0; words[1] = w1; words[3] = w3;
+  }
+  // the units of the main ring, numbered as dispatcher_number_units does (entries past npub hold the total)
+  const bool pub = (m_pub >> tid) & 1u;
+  const int sum = wave_prefix_sum(pub && pe.route == 0 ? (int)nchunks : 0), total = __builtin_amdgcn_readlane(sum, 63);
+  const uint32_t npub = (uint32_t)__popcll(m_pub);
+  s->ubeg[1u + (pub ? pub_before : npub + tid - pub_before)] = (uint32_t)(pub ? sum : total);
+  const uint64_t m_second = __ballot(pub && pe.route != 0);  // published now, on the second ring
   if (tid == 0) {
+    s->ubeg[0] = 0;
     st_deferred += (uint32_t)__popcll(m_pend);
     s->npend = npend0 + (uint32_t)__popcll(m_pend);
-    s->npub = (uint32_t)__popcll(m_pub);
+    s->npub = npub;
     s->npub_second = m_second != 0 ? 1u : 0u;
   }
-  lds_wave_sync();
-  dispatcher_number_units(s, s->npub, 0);
 }
 
 DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
@@ -560,7 +570,7 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
     // A pass has three barriers: every wavefront finds out by itself what the batch is (the same few LDS words) and
     // requests its share of the next one; the first plans the batch, alone and without a barrier; then all
     // write it out.  (As a dozen short steps with a barrier behind each a pass of 64 mixed
-    // tasks took 4.7 us, 3.7 so.)
+    // tasks took 4.3 us, 3.3 so.)
     bool first_batch = true;                       // the prefetched records belong to the first batch after a poll
     while (mirrored < tail) {
       // Dequeue only a bounded distance ahead of execution: the dependency state seen at dequeue
@@ -660,6 +670,7 @@ DEV void run_dispatcher(const WorkerArgs& a, DispShared* s) {
       // have a head start (a worker that sees its unit first fetches its record twice).
 #pragma unroll
       for (uint32_t j = 0; j < kStagePieces; ++j) {
+        if (j * (kThreads / 16u) >= uni(n)) break;                 // (16 records a round: most passes of a few tasks have one)
         const uint32_t p = tid + j * kThreads, rix = p >> 4, part = p & 15u;
         v4i q = ((const v4i*)&s->rec[rix])[part];
         if (part == 15u) q[3] = 0;
