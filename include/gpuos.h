@@ -289,8 +289,9 @@ typedef struct gpuos_config {
                                        least (gpuos_task_plan tells of a task by itself; tasks of
                                        one submit that each name the one before and read what it
                                        writes, over tensors of one size, may be run together
-                                       by the workgroups of the first, all cut alike; not under
-                                       tracing) */
+                                       by the workgroups of the first, all cut alike: up to 64
+                                       tasks and 2^30 elements, which then complete together at
+                                       the end of the last; not under tracing) */
   uint32_t push_ring;               /* where the ring, the doorbell and the table source
                                        live: 0 = fine-grained host memory that the device
                                        polls over PCIe; 1 = device memory that the host
@@ -316,7 +317,10 @@ typedef struct gpuos_config {
   uint32_t dep_wait_us;             /* bound, in microseconds, on the time a worker workgroup waits
                                        for a dependency of the task it holds (what it waits for was
                                        published before its own unit, so the wait ends by itself; the
-                                       bound is a safety net).  A task that runs into it completes
+                                       bound is a safety net).  A dependency that is run together with
+                                       others (see chunk_elems) is complete when all of them are: a bound
+                                       covers 64 tasks or 2^30 elements of a chain, not one task.
+                                       A task that runs into it completes
                                        with GPUOS_E_TIMEOUT and writes nothing; its dependants run.
                                        0 => wait_timeout_ms                                    */
   uint32_t jit_mode;                /* operators defined as programs (gpuos_define_program): 0 => they
@@ -437,7 +441,8 @@ int gpuos_submit_flush(gpuos_ctx* ctx, const gpuos_task* tasks, uint32_t n, uint
  * (GPUOS_ALL: everything submitted).  timeout_ns == 0 uses wait_timeout_ms.
  * Returns the ticket's device status (for GPUOS_ALL: the first non-OK status
  * among tickets completed since the previous GPUOS_ALL wait), or
- * GPUOS_E_TIMEOUT / GPUOS_E_DEAD. */
+ * GPUOS_E_TIMEOUT / GPUOS_E_DEAD.  Tasks of one submit that are run together (see
+ * gpuos_config.chunk_elems) complete together: a wait for the first of them is a wait for the last. */
 int gpuos_wait(gpuos_ctx* ctx, uint64_t ticket, uint64_t timeout_ns);
 
 /* Copy the completion records of tickets [first_ticket, first_ticket + n) to
@@ -463,7 +468,9 @@ int gpuos_shutdown(gpuos_ctx* ctx);
  * dispatcher polls; then summed over all worker workgroups: work units executed
  * and 10 ns ticks spent waiting for work, fetching descriptors, waiting for
  * dependencies, executing, completing, and alive in total; out[15]: tasks the
- * dispatcher held back until their dependencies had completed. */
+ * dispatcher held back until their dependencies had completed.  Tasks that are run together (see
+ * gpuos_config.chunk_elems) have the first one's units, count as one that is held back, and their
+ * units' executing time contains the fetching of the other descriptors and the completing. */
 int gpuos_worker_stats(gpuos_ctx* ctx, uint64_t out[16]);
 
 /* Milliseconds the worker kernel ran, from HIP events on its stream (valid

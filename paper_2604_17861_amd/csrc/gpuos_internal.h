@@ -55,6 +55,7 @@ constexpr uint32_t kSmallTaskChunks = 4;       // a dependent task of at most th
 constexpr uint32_t kDispatchBatch = 64;        // records mirrored per dispatcher pass
 constexpr uint32_t kThreads = 256;             // threads per workgroup of the worker
 constexpr uint32_t kRunMax = 64;               // tasks of a run (a head and the links behind it) that one workgroup takes together
+constexpr uint64_t kRunElements = 1ull << 30;   // ... and elements of all of them: 0.7 ms at the rate of large chains, by which a wait for a run's first task is longer than by itself
 
 // Long ragged rows are cut where memory's 16-byte blocks begin if input and output lie alike in them: the chunk is
 // addressed from the block on that holds its first byte (`front` bytes before it) to the end of the one that holds its last.

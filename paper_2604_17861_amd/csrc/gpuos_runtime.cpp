@@ -617,6 +617,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
 // repeated over leading dims, with one scalar per row, or reducing rows (of whole vectors, up to 64; one row length in a run).
 // A chunk of it then runs while other chunks of the tasks before it have not, so an element may depend on
 // nothing but itself and its row: any two buffers of a run are the same one, of one dtype and seen alike, or do not overlap.
+// Its tasks complete together, at its end: a run is bounded in tasks and in elements.
 // What it gives: links of 1K-16K elements 5.5 us each on their own, 0.4 in a run; and in a long chain
 // each intermediate is written but not read again.
 struct LinkRun {
@@ -693,7 +694,7 @@ struct LinkRun {
   }
   // may r go with prev, the task before it in one submit?  (prev's run goes on, or prev heads one)
   bool links(const Record& prev, const Record& r) {
-    const bool ok = (r.dep[0] | r.dep[1] | r.dep[2]) == 1u && len < kRunMax && !(r.rflags & RF_FENCE) &&
+    const bool ok = (r.dep[0] | r.dep[1] | r.dep[2]) == 1u && len < kRunMax && (len ? len + 1u : 2u) * elements(r) <= kRunElements && !(r.rflags & RF_FENCE) &&
                     (r.ptr[0] == prev.ptr[3] || (r.n_inputs == 2 && r.ptr[1] == prev.ptr[3])) && form(r) &&
                     elements(r) == elements(prev) && dtype_of(r) == dtype_of(prev);
     if (!ok) return false;

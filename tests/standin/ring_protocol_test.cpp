@@ -221,6 +221,13 @@ static void runs_are_marked() {
     CHECK(links_of({h[0], h[1], h[2], by_k, again}) == 3);
     CHECK(links_of({h[0], h[1], h[2], again, by_m}) == 4);
   }
+  // a run's tasks complete at its end: together they are at most 2^30 elements
+  for (int64_t r : {1ll << 22, 1ll << 23}) {
+    std::vector<gpuos_task> h = rows(r, 64);
+    h[0].size[0] = r * 64;
+    for (auto& t : h) for (auto* q : {&t.in[0], &t.in[1], &t.out}) q->ptr = (void*)((uintptr_t)q->ptr << 16);
+    CHECK(links_of(h) == (r == 1 << 22 ? 2 : 1));
+  }
   CHECK(gpuos_shutdown(c) == GPUOS_OK);
   std::printf("ok: links of runs are marked, and nothing else\n");
 }
