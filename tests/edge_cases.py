@@ -217,7 +217,7 @@ def long_chains(code, n, links=150):
     return b.stream("long_chains_%d_%d" % (code, n), batch=128)
 
 
-def row_chains(code, seed):
+def row_chains(code, seed, shapes=None):
     """Chains over rows (scale, mask, maximum, difference, sum, quotient and variations), at row lengths of one vector
     to 65 and a ragged one, masks repeated over leading dims, results of reductions used at once, again
     later, overwritten, stored in 16 bits, or scalars that lay in memory before.  Values are small integers until the
@@ -225,8 +225,8 @@ def row_chains(code, seed):
     rng = np.random.default_rng(2000 * code + seed)
     b = Builder()
     V = 4 if code == S.F32 else 8
-    for n, B, R in ((V, 3, 5), (2 * V, 2, 64), (3 * V, 1, 130), (8 * V, 5, 33), (13 * V, 2, 40), (32 * V, 4, 32), (33 * V, 1, 9), (64 * V, 2, 17),
-                    (65 * V, 2, 9), (5 * V + 1, 2, 11), (8 * V, 8, 1024)):
+    for n, B, R in shapes or ((V, 3, 5), (2 * V, 2, 64), (3 * V, 1, 130), (8 * V, 5, 33), (13 * V, 2, 40), (32 * V, 4, 32), (33 * V, 1, 9), (64 * V, 2, 17),
+                              (65 * V, 2, 9), (5 * V + 1, 2, 11), (8 * V, 8, 1024)):
         size = (B, R, n)
         pool = lambda hi: b.pool(to_dtype(rng.integers(-hi, hi + 1, size).astype(np.float32), code))
         x, t1, t2, e, y = pool(8), pool(1), pool(1), pool(1), pool(1)
