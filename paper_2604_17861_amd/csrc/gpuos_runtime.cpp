@@ -717,7 +717,13 @@ struct LinkRun {
       Record* const first = end - len;
       uint32_t rows_per = 0, nchunks = first->nchunks, chunk = first->chunk;
       if (row != 0) {
-        // in blocks, what a workgroup holds at a time: four vectors a lane; smaller where a task has few of them
+        // In blocks, what a workgroup holds at a time (four vectors a lane).  Up to 384 blocks, half the workgroups that a GPU
+        // holds, a chunk is one: the most workgroups.  Beyond, two and from 768 on four, so that a chain stays at about 200
+        // chunks: each costs its unit, the descriptors of all tasks and a wait for its last stores, and other chains fill the
+        // GPU.  (Thousands of chains in flight, 24 at a time: 855 K tasks/s so, 745 with both bounds twice as high, 650 in single
+        // blocks.  24 chains and 12 of 1,024 blocks: 162 us, 170, 179; 318, 341, 393.  What it costs is a large
+        // chain by itself: 66.7 us over 1,024 blocks, 47.6 and 55.0.)  Below 16 blocks they are quartered, which measures as whole
+        // ones do: 21.8 and 21.4 us over 4 blocks.
         const uint64_t rows = elems / row;
         uint32_t P = 1;
         while (P < row / (16u / dtype_size(dtype))) P <<= 1;
