@@ -401,9 +401,10 @@ template <> struct OpOut<GPUOS_IMPL_SUB_EXP, GPUOS_BF16> { static constexpr int 
 // every one with fp64, bit for bit.  (Near zero, at infinity and for NaN both ends round alike.  bf16 reaches down
 // to where fp32 has no more normal numbers: there, below -12, fp64 decides always.)
 // It is for batches of several vectors a lane.  A wavefront falls back for one vector in 16, and waits for a chain of
-// 60 dependent instructions then, which other vectors in flight hide and a lone one does not.  Not for f16 and not for GELU_TANH, which are in doubt 8 and 2 times as often (three
-// more bits of a result; a bound that grows with the exponent): four tasks of 164K elements, fp64 against this, f16 ERF 26.1
-// and 27.7 us, f16 TANH 21.1 and 27.4, bf16 TANH 20.8 and 25.0; two of 8.4M, 54.4 and 52.1, 40.3 and 51.2, 40.0 and 45.3.
+// 60 dependent instructions then, which other vectors in flight hide and a lone one does not.  Not for f16 and not for
+// GELU_TANH, which are in doubt 8 and 2 times as often (three more bits of a result; a bound that grows with the exponent):
+// four tasks of 164K elements, fp64 against this, f16 ERF 26.1 and 27.7 us, f16 TANH 21.1 and 27.4, bf16 TANH 20.8 and 25.0;
+// two of 8.4M, 54.4 and 52.1, 40.3 and 51.2, 40.0 and 45.3.  (bf16 ERF: 26.3 and 22.2; 54.9 and 38.8.)
 DEV float gelu_erf_fp32(float x) {
   const float a = __builtin_fabsf(x), c = __builtin_fminf(a, 12.0f), s = c * c;
   const float d = __builtin_amdgcn_rcpf(c + 3.0f), t = __builtin_fmaf(-6.0f, d, 1.0f);
@@ -3089,8 +3090,8 @@ __attribute__((not_tail_called)) PATHFN void run_links(const Record* recs_v, uin
 // One unit of a run, from the head's descriptor (slot f) to the completion of its tasks.
 // Neither this nor run_links keeps a register for its caller (both are called, never jumped to, and the compiler sees
 // every call): a chunk of 8K elements, 82 KB of a chain's memory traffic, saved and restored another 66 KB of them.
-// The worker, which would have to keep its own registers instead, calls it where it holds none (see run_worker).  Chains of six over fp16
-// rows, 24 in flight: 675 K tasks/s with the registers saved, 785 without, 855 with the call there.
+// The worker, which would have to keep its own registers instead, calls it where it holds none (see run_worker).
+// Chains of six over fp16 rows, 24 in flight: 675 K tasks/s with the registers saved, 785 without, 855 with the call there.
 __attribute__((not_tail_called, disable_tail_calls)) PATHFN void exec_run(WorkShared* s_v, uint32_t f_v, uint32_t chunk_v, int32_t status_v, uint32_t tid) {
   WorkShared* s = lds_arg(s_v);
   const uint32_t f = uni(f_v), chunk = uni(chunk_v), lane = tid & 63u;
@@ -3501,8 +3502,9 @@ DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
   const uint64_t w_start = clock_if(timing);
   RunUnit run = {0, 0, 0, 0};
   while (serve_units<RING, EXEC>(a, s, gen, wave, w_start, run)) {
-    // A run, outside the loop over other units: its call keeps no register (see exec_run).  Within that loop the worker kept
-    // its own for it in scratch memory, over other calls too: masked softmax 45.9 us instead of 38.1, 24 integer operations 66.0 instead of 60.7.
+    // A run, outside the loop over other units: its call keeps no register (see exec_run).  Within that loop the worker
+    // kept its own for it in scratch memory, over other calls too: masked softmax took 45.9 us instead of 38.1, 24 integer
+    // operations 66.0 instead of 60.7.
     if constexpr (RING == 0) {
       exec_run(s, run.f, run.chunk, run.status, thread_index(wave));
       if (thread_index(wave) == 0) {

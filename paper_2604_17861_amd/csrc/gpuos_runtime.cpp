@@ -694,7 +694,8 @@ struct LinkRun {
   }
   // may r go with prev, the task before it in one submit?  (prev's run goes on, or prev heads one)
   bool links(const Record& prev, const Record& r) {
-    const bool ok = (r.dep[0] | r.dep[1] | r.dep[2]) == 1u && len < kRunMax && (len ? len + 1u : 2u) * elements(r) <= kRunElements && !(r.rflags & RF_FENCE) &&
+    const bool ok = (r.dep[0] | r.dep[1] | r.dep[2]) == 1u && len < kRunMax && !(r.rflags & RF_FENCE) &&
+                    (len ? len + 1u : 2u) * elements(r) <= kRunElements &&
                     (r.ptr[0] == prev.ptr[3] || (r.n_inputs == 2 && r.ptr[1] == prev.ptr[3])) && form(r) &&
                     elements(r) == elements(prev) && dtype_of(r) == dtype_of(prev);
     if (!ok) return false;
