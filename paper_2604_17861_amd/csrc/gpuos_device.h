@@ -1374,10 +1374,8 @@ template <> DEV int32_t red_identity<GPUOS_IMPL_MAX_LAST, int32_t>() { return (i
 template <> DEV int32_t red_identity<GPUOS_IMPL_MIN_LAST, int32_t>() { return 0x7fffffff; }
 template <int RIMPL> DEV float red_combine(float a, float b) {
   if (RIMPL == GPUOS_IMPL_SUM_LAST) return a + b;
-  if (a != a) return a;                               // max / min propagate NaN
-  if (b != b) return b;
-  if (RIMPL == GPUOS_IMPL_MAX_LAST) return a > b ? a : b;
-  return a < b ? a : b;
+  if (RIMPL == GPUOS_IMPL_MAX_LAST) return __builtin_elementwise_maximum(a, b);      // (IEEE maximum and minimum: NaN goes through)
+  return __builtin_elementwise_minimum(a, b);
 }
 template <int RIMPL> DEV int32_t red_combine(int32_t a, int32_t b) {
   if (RIMPL == GPUOS_IMPL_SUM_LAST) return (int32_t)((uint32_t)a + (uint32_t)b);
@@ -1385,30 +1383,39 @@ template <int RIMPL> DEV int32_t red_combine(int32_t a, int32_t b) {
   return a < b ? a : b;
 }
 
-// The partner of a lane in step OFF of an all-reduce butterfly over aligned groups of 2 * OFF
-// lanes.  Steps 1 and 2 swap inside a quad and steps 4 and 8 mirror a half row / a row of 16 lanes
-// (lane i with i ^ 7, i ^ 15): DPP operand modifiers, no trip through the LDS crossbar that a
-// shuffle takes.  The masks 1, 2, 7, 15, 16, 32 are independent, so the steps still reach every
-// lane of the group.  Steps 16 and 32 cross rows and stay shuffles.  All lanes must be active.
-template <int OFF> DEV int butterfly_partner(int v) {
-  if (OFF == 1) return __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xf, 0xf, false);      // quad_perm [1,0,3,2]
-  if (OFF == 2) return __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xf, 0xf, false);      // quad_perm [2,3,0,1]
-  if (OFF == 4) return __builtin_amdgcn_update_dpp(v, v, 0x141, 0xf, 0xf, false);     // row_half_mirror
-  if (OFF == 8) return __builtin_amdgcn_update_dpp(v, v, 0x140, 0xf, 0xf, false);     // row_mirror
-  return __shfl_xor(v, OFF, 64);
+// Step OFF of an all-reduce butterfly over aligned groups of 2 * OFF lanes: a lane's own value and its
+// partner's, in either order.  Steps 1 and 2 swap inside a quad and steps 4 and 8 mirror a half row / a row of
+// 16 lanes (lane i with i ^ 7, i ^ 15), DPP operand modifiers; steps 16 and 32 swap rows and halves between two
+// copies.  None takes a trip through the LDS crossbar as a shuffle does.  The masks 1, 2, 7, 15, 16, 32 are
+// independent, so the steps reach every lane of the group.  All lanes must be active.
+template <int OFF> DEV void butterfly_pair(int v, int& a, int& b) {
+  a = v;
+  if (OFF == 1) b = __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xf, 0xf, false);      // quad_perm [1,0,3,2]
+  else if (OFF == 2) b = __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xf, 0xf, false); // quad_perm [2,3,0,1]
+  else if (OFF == 4) b = __builtin_amdgcn_update_dpp(v, v, 0x141, 0xf, 0xf, false);     // row_half_mirror
+  else if (OFF == 8) b = __builtin_amdgcn_update_dpp(v, v, 0x140, 0xf, 0xf, false);     // row_mirror
+  else {
+    auto two = OFF == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = (int)two[0];
+    b = (int)two[1];
+  }
 }
-template <int OFF> DEV float butterfly_partner(float v) {
-  return __builtin_bit_cast(float, butterfly_partner<OFF>(__builtin_bit_cast(int, v)));
+template <int OFF> DEV void butterfly_pair(float v, float& a, float& b) {
+  int x, y;
+  butterfly_pair<OFF>(__builtin_bit_cast(int, v), x, y);
+  a = __builtin_bit_cast(float, x);
+  b = __builtin_bit_cast(float, y);
 }
 
 // all-reduce over the `width` lanes (power of two <= 64, aligned) a lane belongs to
 template <int RIMPL, class T> DEV T wave_reduce(T acc, uint32_t width) {
-  if (width > 32) acc = red_combine<RIMPL>(acc, butterfly_partner<32>(acc));
-  if (width > 16) acc = red_combine<RIMPL>(acc, butterfly_partner<16>(acc));
-  if (width > 8) acc = red_combine<RIMPL>(acc, butterfly_partner<8>(acc));
-  if (width > 4) acc = red_combine<RIMPL>(acc, butterfly_partner<4>(acc));
-  if (width > 2) acc = red_combine<RIMPL>(acc, butterfly_partner<2>(acc));
-  if (width > 1) acc = red_combine<RIMPL>(acc, butterfly_partner<1>(acc));
+  T a, b;
+  if (width > 32) { butterfly_pair<32>(acc, a, b); acc = red_combine<RIMPL>(a, b); }
+  if (width > 16) { butterfly_pair<16>(acc, a, b); acc = red_combine<RIMPL>(a, b); }
+  if (width > 8) { butterfly_pair<8>(acc, a, b); acc = red_combine<RIMPL>(a, b); }
+  if (width > 4) { butterfly_pair<4>(acc, a, b); acc = red_combine<RIMPL>(a, b); }
+  if (width > 2) { butterfly_pair<2>(acc, a, b); acc = red_combine<RIMPL>(a, b); }
+  if (width > 1) { butterfly_pair<1>(acc, a, b); acc = red_combine<RIMPL>(a, b); }
   return acc;
 }
 
@@ -1421,38 +1428,28 @@ template <int RIMPL, class T> DEV T wave_reduce(T acc, uint32_t width) {
 // the same way: with one wavefront per row and one word per lane and load, whatever the row length,
 // 24 integer operations of 0.1-50 MB took 529 us, a 13,946 x 22 maximum among them 505; 95 with this,
 // 62 with rows on 16-byte accesses besides (ew_rows).
-// Three shapes of work:
-//   short rows  (span <= 64 vectors): P lanes per row, 64 / P rows per wavefront pass,
-//               eight passes in flight;
-//   medium rows: one wavefront per row, RA rows at a time, UN loads per row in flight;
+// Four shapes of work:
+//   whole short rows (<= 64 vectors, each a whole number of them): P lanes per row, 64 / P rows per
+//               wavefront pass, eight passes at a time;
+//   other short rows (<= 128): through LDS, by the piece of as many rows as fit;
+//   medium rows: a wavefront reads its rows as one run, in groups of 64 vectors;
 //   long rows   (>= 1024 vectors): the four wavefronts take a quarter of each row, partial
 //               results meet in LDS once per chunk (one barrier per chunk, not per row).
-// Per-element accumulation.  SUM adds.  MAX / MIN must propagate NaN: the running value ignores
-// NaN (one compare + select) and `nan` remembers whether one was seen (one unordered compare,
-// or-ed into a wavefront-uniform mask register); red_finish folds the two before the lanes are combined.
-template <int RIMPL> DEV int32_t red_step(int32_t acc, int32_t x, bool&) { return red_combine<RIMPL>(acc, x); }
-template <int RIMPL> DEV int32_t red_finish(int32_t acc, bool) { return acc; }
-template <int RIMPL> DEV float red_step(float acc, float x, bool& nan) {
-  if (RIMPL == GPUOS_IMPL_SUM_LAST) return acc + x;
-  nan = nan || (x != x);
-  if (RIMPL == GPUOS_IMPL_MAX_LAST) return x > acc ? x : acc;
-  return x < acc ? x : acc;
-}
-template <int RIMPL> DEV float red_finish(float acc, bool nan) {
-  if (RIMPL == GPUOS_IMPL_SUM_LAST) return acc;
-  return nan ? __builtin_nanf("") : acc;
-}
-
-// Two elements per step for max / min: one three-operand max (min) and ONE unordered compare of
-// the two new elements with each other, which is true exactly when either is a NaN.  The hardware
-// max / min skip quiet NaNs, which is fine: the flag decides the result (red_finish).  Three
-// operations per element (compare, compare, select) become one; the 16-bit reductions were
-// bound by them.
-template <int RIMPL> DEV float red_step2(float acc, float x0, float x1, bool& nan) {
-  nan = nan || __builtin_isunordered(x0, x1);
+// 134 MB of fp32 rows of 24, 75, 136, 256, 486, 1,060 and 2,634 took 67, 135, 121, 71, 92, 69 and 57 us (P lanes per row
+// or one wavefront per row from memory, all requested before any was looked at and again nothing in flight while it was), 47, 49, 59,
+// 46, 54, 49 and 53 so; 16-bit rows as much.
+// Per-element accumulation.  SUM adds; MAX / MIN are IEEE maximum and minimum, one instruction of three operands for two
+// elements, through which a NaN goes (red_finish gives it one form).  (With the hardware's older maximum, which skips NaNs, a
+// flag beside it took a compare a pair, and combining lanes four operations a step: rows of 136 fp32 121 us for
+// 134 MB, of which this and steps without shuffles took off 30.)
+template <int RIMPL> DEV int32_t red_step(int32_t acc, int32_t x) { return red_combine<RIMPL>(acc, x); }
+template <int RIMPL> DEV float red_step(float acc, float x) { return red_combine<RIMPL>(acc, x); }
+template <int RIMPL> DEV int32_t red_finish(int32_t acc) { return acc; }
+template <int RIMPL> DEV float red_finish(float acc) { return RIMPL != GPUOS_IMPL_SUM_LAST && acc != acc ? __builtin_nanf("") : acc; }
+template <int RIMPL> DEV float red_step2(float acc, float x0, float x1) {
   float r;
-  if (RIMPL == GPUOS_IMPL_MAX_LAST) asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(acc), "v"(x0), "v"(x1));
-  else asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(acc), "v"(x0), "v"(x1));
+  if (RIMPL == GPUOS_IMPL_MAX_LAST) asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(acc), "v"(x0), "v"(x1));
+  else asm("v_minimum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(acc), "v"(x0), "v"(x1));
   return r;
 }
 
@@ -1460,21 +1457,21 @@ template <int DT> DEV typename RedAcc<DT>::T red_get(const v4i& q, int k) { retu
 template <> DEV int32_t red_get<GPUOS_I32>(const v4i& q, int k) { return q[k]; }
 
 template <int RIMPL, int DT>
-DEV typename RedAcc<DT>::T red_vector(const v4i& q, uint32_t f0, uint32_t lo, uint32_t hi, bool edge, typename RedAcc<DT>::T acc, bool& nan) {
+DEV typename RedAcc<DT>::T red_vector(const v4i& q, uint32_t f0, uint32_t lo, uint32_t hi, bool edge, typename RedAcc<DT>::T acc) {
   // q holds elements f0 .. f0+V-1 of the flat run; the row is [lo, hi)
   using E = Elem<DT>;
   if (!edge) {
     if constexpr (RIMPL == GPUOS_IMPL_SUM_LAST || DT == GPUOS_I32) {
 #pragma unroll
-      for (int k = 0; k < E::V; ++k) acc = red_step<RIMPL>(acc, red_get<DT>(q, k), nan);
+      for (int k = 0; k < E::V; ++k) acc = red_step<RIMPL>(acc, red_get<DT>(q, k));
     } else {
 #pragma unroll
-      for (int k = 0; k < E::V; k += 2) acc = red_step2<RIMPL>(acc, E::get(q, k), E::get(q, k + 1), nan);
+      for (int k = 0; k < E::V; k += 2) acc = red_step2<RIMPL>(acc, E::get(q, k), E::get(q, k + 1));
     }
   } else {
 #pragma unroll
     for (int k = 0; k < E::V; ++k)
-      if (f0 + k >= lo && f0 + k < hi) acc = red_step<RIMPL>(acc, red_get<DT>(q, k), nan);
+      if (f0 + k >= lo && f0 + k < hi) acc = red_step<RIMPL>(acc, red_get<DT>(q, k));
   }
   return acc;
 }
@@ -1507,64 +1504,116 @@ DEV RedRun red_run(const RedArgs& a) {
   return run;
 }
 
-template <int POL, int RIMPL, int DT, int RA, int UN>
-PATHFN void red_rows_wave(RedArgs a) {
+// Row `i` of the chunk's results, where `act`: no branch round the store, and none under a condition of its own.  (The
+// compiler counts what is in flight per path: where a store may or may not have been issued, the next wait for
+// loads waits for it too.)
+template <int POL> DEV void red_put(rsrc_t ro, uint32_t i, uint32_t odt, float v, bool act) {
+  if (odt == GPUOS_F32) Mem<POL>::stb4(ro, act ? i * 4u : kNoLoad, __builtin_bit_cast(uint32_t, v));
+  else Mem<POL>::stb2(ro, act ? i * 2u : kNoLoad, odt == GPUOS_F16 ? f2h(v) : f2b(v));
+}
+template <int POL> DEV void red_put(rsrc_t ro, uint32_t i, uint32_t, int32_t v, bool act) { Mem<POL>::stb4(ro, act ? i * 4u : kNoLoad, (uint32_t)v); }
+DEV rsrc_t red_out(const RedArgs& a, uint32_t row_begin, uint32_t row_end, uint32_t odt) {
+  const uint32_t os = odt == GPUOS_F16 || odt == GPUOS_BF16 ? 2u : 4u;
+  return make_rsrc(uni_ptr((uint64_t)a.po) + (uint64_t)row_begin * os, (row_end - row_begin) * os);
+}
+// K elements join a lane's accumulator; sums in pairs (a shorter chain, and a smaller error).
+template <int RIMPL, int K> DEV int32_t red_join(int32_t acc, const int32_t (&x)[K]) {
+#pragma unroll
+  for (int k = 0; k < K; ++k) acc = red_combine<RIMPL>(acc, x[k]);
+  return acc;
+}
+template <int RIMPL, int K> DEV float red_join(float acc, const float (&x)[K]) {
+  if constexpr (RIMPL == GPUOS_IMPL_SUM_LAST) {
+    float t[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) t[k] = x[k];
+#pragma unroll
+    for (int w = K / 2; w > 0; w /= 2)
+#pragma unroll
+      for (int k = 0; k < w; ++k) t[k] += t[k + w];
+    return acc + t[0];
+  } else {
+#pragma unroll
+    for (int k = 0; k < K; k += 2) acc = red_step2<RIMPL>(acc, x[k], x[k + 1]);
+    return acc;
+  }
+}
+
+// Rows of 65 to 1,023 vectors, whatever their alignment.  A wavefront takes a share of the chunk's rows, which is one
+// dense run of memory, and reads it in groups of 64 vectors, four of them while it works on the four before; a row ends where
+// it ends, within a group, and that group is looked at once for either row.  Bound by memory latency: what counts is
+// that four to eight loads a lane are always in flight.  (Row by row, four rows' or one row's eight loads at a time and then
+// all of their arithmetic with nothing in flight: 134 MB of fp32 rows of 1,060 69 us, of 2,634 57 us.)
+template <int POL, int RIMPL, int DT>
+PATHFN void red_rows_stream(RedArgs a) {
   const RedRun run = red_run(a);
-  const uint32_t tid = a.tid;
-  char* po = (char*)uni_ptr((uint64_t)a.po);
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end);
   using E = Elem<DT>;
   using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
-  constexpr uint32_t V = E::V;
-  const uint32_t lane = tid & 63u, wave = tid >> 6;
+  constexpr uint32_t V = E::V, U = 4;
+  const uint32_t lane = a.tid & 63u, wave = uni(a.tid >> 6);
   const uint32_t n = run.n;
-  // wave w takes rows row_begin + w, + 4, + 8, ... ; RA of them at a time
-  for (uint32_t row0 = row_begin + wave; row0 < row_end; row0 += 4 * RA) {
-    A acc[RA];
-    bool nan[RA];
-    uint32_t lo[RA], hi[RA], j0[RA], j1[RA];
-    uint32_t span = 0;
+  const rsrc_t ro = red_out(a, row_begin, row_end, odt);
+  const uint32_t per = (row_end - row_begin + 3u) / 4u, w0 = row_begin + wave * per, w1 = row_end - w0 < per ? row_end : w0 + per;
+  if (wave * per >= row_end - row_begin) return;
+  uint32_t row = w0, lo = w0 * n + run.skew, hi = lo + n;    // the row being read: elements [lo, hi) of the run
+  const uint32_t j_last = (w1 * n + run.skew - 1u) / V;
+  A acc = red_identity<RIMPL, A>(), res = 0;                 // (lane L of `res`: the L-th result since the last store)
+  uint32_t kept = 0;
+  auto fetch = [&](v4i (&q)[U], uint32_t j) {
 #pragma unroll
-    for (int i = 0; i < RA; ++i) {
-      acc[i] = red_identity<RIMPL, A>();
-      nan[i] = false;
-      const uint32_t row = row0 + 4 * i;
-      lo[i] = row * n + run.skew;
-      hi[i] = lo[i] + n;
-      j0[i] = lo[i] / V;
-      j1[i] = (hi[i] - 1) / V;
-      if (row >= row_end) { hi[i] = lo[i]; j1[i] = j0[i]; }
-      const uint32_t sp = j1[i] - j0[i] + 1;
-      span = sp > span ? sp : span;
-    }
-    for (uint32_t v = lane; v < span; v += 64 * UN) {
-      v4i q[RA][UN];
+    for (uint32_t u = 0; u < U; ++u) q[u] = M::ld16(run.rin, j + u * 64u + lane <= j_last ? (j + u * 64u + lane) * 16u : kNoLoad);
+  };
+  auto take = [&](const v4i (&q)[U], uint32_t j) {           // true: the last row is complete
 #pragma unroll
-      for (int i = 0; i < RA; ++i)
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t g0 = (j + u * 64u) * V, g1 = g0 + 64u * V;
+      while (true) {
+        if (lo <= g0 && hi >= g1) {
+          A x[V];
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {   // vectors past the row are not fetched
-          const uint32_t j = j0[i] + v + u * 64;
-          q[i][u] = M::ld16(run.rin, (j <= j1[i] && hi[i] > lo[i]) ? j * 16u : kNoLoad);
+          for (uint32_t k = 0; k < V; ++k) x[k] = red_get<DT>(q[u], (int)k);
+          acc = red_join<RIMPL>(acc, x);
+        } else {
+          A x[V];
+          const uint32_t d = g0 + lane * V - lo;             // (unsigned: elements before the row are past its end)
+#pragma unroll
+          for (uint32_t k = 0; k < V; ++k) x[k] = d + k < n ? red_get<DT>(q[u], (int)k) : red_identity<RIMPL, A>();
+          acc = red_join<RIMPL>(acc, x);
         }
-#pragma unroll
-      for (int i = 0; i < RA; ++i)
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-          const uint32_t j = j0[i] + v + u * 64;
-          if (j <= j1[i] && hi[i] > lo[i])
-            acc[i] = red_vector<RIMPL, DT>(q[i][u], j * V, lo[i], hi[i], j == j0[i] || j == j1[i], acc[i], nan[i]);
-        }
+        if (hi > g1) break;                                  // the row goes on
+        const A t = wave_reduce<RIMPL>(red_finish<RIMPL>(acc), 64);
+        if (lane == kept) res = t;
+        ++kept;
+        ++row;
+        if (kept == 64u || row == w1) { red_put<POL>(ro, row - row_begin - kept + lane, odt, res, lane < kept); kept = 0; }
+        if (row == w1) return true;
+        acc = red_identity<RIMPL, A>();
+        lo = hi;
+        hi += n;
+        if (lo >= g1) break;
+      }
     }
-#pragma unroll
-    for (int i = 0; i < RA; ++i) {
-      const A t = wave_reduce<RIMPL>(red_finish<RIMPL>(acc[i], nan[i]), 64);
-      if (lane == 0 && row0 + 4 * i < row_end) red_store<POL>(po, row0 + 4 * i, odt, t);
-    }
+    return false;
+  };
+  v4i qa[U], qb[U];
+  uint32_t j = lo / V;
+  fetch(qa, j);
+  while (true) {
+    fetch(qb, j + 64u * U);
+    if (take(qa, j)) break;
+    fetch(qa, j + 128u * U);
+    if (take(qb, j + 64u * U)) break;
+    j += 128u * U;
   }
 }
 
 constexpr uint32_t kRedPartialRows = 64;   // rows of partial results the LDS scratch holds
+constexpr uint32_t kRedPieceVectors = 448; // ... and vectors of a wavefront's own rows
+// Rows of up to this many vectors go by way of the LDS.  (Beyond, a group of 64 vectors holds few rows' ends and
+// the wavefront reads them as they come: rows of 130 to 450 vectors take the same time either way, and longer ones no LDS holds.)
+constexpr uint32_t kRedLdsSpan = 128;
 
 template <int POL, int RIMPL, int DT>
 PATHFN void red_rows_quarter(RedArgs a) {
@@ -1587,7 +1636,6 @@ PATHFN void red_rows_quarter(RedArgs a) {
     const uint32_t q_begin = j0 + wave * sq;
     const uint32_t q_end = (q_begin + sq <= j1 + 1) ? q_begin + sq : j1 + 1;
     A a0 = red_identity<RIMPL, A>(), a1 = a0;
-    bool nan = false;
     for (uint32_t v = q_begin + lane; v < q_end; v += 64 * UN) {
       v4i q[UN];
 #pragma unroll
@@ -1596,12 +1644,12 @@ PATHFN void red_rows_quarter(RedArgs a) {
       for (int u = 0; u < UN; ++u) {
         const uint32_t j = v + u * 64;
         if (j < q_end) {
-          if ((u & 1) == 0) a0 = red_vector<RIMPL, DT>(q[u], j * V, lo, hi, j == j0 || j == j1, a0, nan);
-          else a1 = red_vector<RIMPL, DT>(q[u], j * V, lo, hi, j == j0 || j == j1, a1, nan);
+          if ((u & 1) == 0) a0 = red_vector<RIMPL, DT>(q[u], j * V, lo, hi, j == j0 || j == j1, a0);
+          else a1 = red_vector<RIMPL, DT>(q[u], j * V, lo, hi, j == j0 || j == j1, a1);
         }
       }
     }
-    const A t = wave_reduce<RIMPL>(red_finish<RIMPL>(red_combine<RIMPL>(a0, a1), nan), 64);
+    const A t = wave_reduce<RIMPL>(red_finish<RIMPL>(red_combine<RIMPL>(a0, a1)), 64);
     if (lane == 0) s_part[(row - row_begin) * 4 + wave] = __builtin_bit_cast(float, t);
   }
   __syncthreads();
@@ -1615,56 +1663,76 @@ PATHFN void red_rows_quarter(RedArgs a) {
   __syncthreads();
 }
 
+// Rows of up to 448 vectors that are not whole aligned vectors.  A wavefront takes a share of the chunk's rows and reads it
+// densely, as many whole rows at a time as 448 vectors hold, puts them into its part of the LDS and
+// requests the next; from there rows have no edges: P lanes a row, element by element.  Bound by memory latency: seven
+// loads a lane are in flight throughout.  (P lanes a row straight from memory, masked element by element at either end, 64 lanes
+// for the 35 vectors of a row of 136 fp32: 134 MB of those took 121 us.)
 template <int POL, int RIMPL, int DT>
-PATHFN void red_rows_short(RedArgs a) {
+PATHFN void red_rows_lds(RedArgs a) {
   const RedRun run = red_run(a);
-  const uint32_t tid = a.tid;
-  char* po = (char*)uni_ptr((uint64_t)a.po);
-  const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end), max_span = uni(a.max_span);
+  const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end);
   using E = Elem<DT>;
   using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
-  constexpr uint32_t V = E::V;
-  constexpr int UP = 8;
-  const uint32_t lane = tid & 63u, wave = tid >> 6;
+  constexpr uint32_t V = E::V, K = 8;
+  const uint32_t lane = a.tid & 63u, wave = uni(a.tid >> 6);
+  char* const mem = (char*)lds_arg(a.s_part) + wave * kRedPieceVectors * 16u;
+  static_assert(kRedPieceVectors * 16 * 4 <= kScratchFloats * 4 && kRedPieceVectors % 64 == 0, "a piece per wavefront");
+  constexpr uint32_t NV = kRedPieceVectors / 64u;
   const uint32_t n = run.n;
-  uint32_t P = 1;                                     // lanes per row: power of two >= the widest span
-  while (P < max_span) P <<= 1;
-  const uint32_t rpw = 64u / P, sub = lane / P, j = lane & (P - 1u);
-  const bool gather = UP * rpw <= 64u;                // the pass's rows fit one lane each
-  // one wavefront pass covers the UP * rpw consecutive rows base .. base + UP * rpw - 1
-  for (uint32_t base = row_begin + wave * rpw * UP; base < row_end; base += 4 * rpw * UP) {
-    v4i q[UP];
-    uint32_t lo[UP], hi[UP], j0[UP], j1[UP];
+  const rsrc_t ro = red_out(a, row_begin, row_end, odt);
+  const uint32_t per = (row_end - row_begin + 3u) / 4u, w0 = row_begin + wave * per, w1 = row_end - w0 < per ? row_end : w0 + per;
+  if (wave * per >= row_end - row_begin) return;
+  // rows a piece: the most that fit with a partly covered vector at either end, evened out over the pieces
+  const uint32_t most = ((kRedPieceVectors - 1u) * V + 1u) / n, pieces = (per + most - 1u) / most, R = (per + pieces - 1u) / pieces;
+  uint32_t P = 64;
+  while (P > 1u && 64u / P < R) P >>= 1;
+  const uint32_t rps = 64u / P, sub = lane / P, first = lane & (P - 1u), whole = n / (P * K);    // whole: rounds of K elements that every lane has
+  v4i q[NV];
+  auto fetch = [&](uint32_t row) {
+    const uint32_t end = w1 - row < R ? w1 : row + R;
+    const uint32_t j0 = (row * n + run.skew) / V, j1 = (end * n + run.skew - 1u) / V;
 #pragma unroll
-    for (int u = 0; u < UP; ++u) {
-      const uint32_t row = base + u * rpw + sub;
-      lo[u] = row * n + run.skew;
-      hi[u] = lo[u] + n;
-      j0[u] = lo[u] / V;
-      j1[u] = (hi[u] - 1) / V;
-      q[u] = M::ld16(run.rin, (row < row_end && j0[u] + j <= j1[u]) ? (j0[u] + j) * 16u : kNoLoad);
-    }
-    A mine = 0;                                // lane L ends up with the result of row base + L
+    for (uint32_t u = 0; u < NV; ++u) q[u] = M::ld16(run.rin, row < w1 && j0 + u * 64u + lane <= j1 ? (j0 + u * 64u + lane) * 16u : kNoLoad);
+  };
+  auto get = [&](uint32_t i) {
+    if constexpr (DT == GPUOS_I32) return ((const int32_t*)mem)[i];
+    else if constexpr (DT == GPUOS_F32) return ((const float*)mem)[i];
+    else if constexpr (DT == GPUOS_F16) return h2f(((const uint16_t*)mem)[i]);
+    else return b2f(((const uint16_t*)mem)[i]);
+  };
+  fetch(w0);
+  for (uint32_t row = w0; row < w1; row += R) {
 #pragma unroll
-    for (int u = 0; u < UP; ++u) {
-      const uint32_t row = base + u * rpw + sub;
-      const uint32_t jj = j0[u] + j;
+    for (uint32_t u = 0; u < NV; ++u) ((v4i*)mem)[u * 64u + lane] = q[u];
+    lds_wave_sync();
+    fetch(row + R);
+    const uint32_t rows = w1 - row < R ? w1 - row : R, lead = (row * n + run.skew) & (V - 1u);
+    for (uint32_t rb = 0; rb < rows; rb += rps) {
+      const uint32_t mr = rb + sub, at = lead + (mr < rows ? mr : rows - 1u) * n;
       A acc = red_identity<RIMPL, A>();
-      bool nan = false;
-      if (row < row_end && jj <= j1[u])
-        acc = red_vector<RIMPL, DT>(q[u], jj * V, lo[u], hi[u], jj == j0[u] || jj == j1[u], acc, nan);
-      acc = wave_reduce<RIMPL>(red_finish<RIMPL>(acc, nan), P);
-      // every lane of sub-group s now holds the result of row base + u * rpw + s
-      if (gather) {
-        const A got = __shfl(acc, (int)((lane & (rpw - 1u)) * P), 64);
-        if (lane / rpw == (uint32_t)u) mine = got;
-      } else if (row < row_end && j == 0) {
-        red_store<POL>(po, row, odt, acc);            // rows of one or two vectors: the owners are adjacent lanes already
+      uint32_t e = first;
+      A x[K];
+      for (uint32_t b = 0; b < whole; ++b) {
+#pragma unroll
+        for (uint32_t k = 0; k < K; ++k) x[k] = get(at + e + k * P);
+        e += K * P;
+        acc = red_join<RIMPL>(acc, x);
       }
+      if (whole * K * P < n) {                               // the last elements: of a maximum, some are taken twice
+#pragma unroll
+        for (uint32_t k = 0; k < K; ++k) {
+          const uint32_t i = e + k * P;
+          x[k] = get(at + (i < n ? i : n - 1u));
+          if (RIMPL == GPUOS_IMPL_SUM_LAST) x[k] = i < n ? x[k] : (A)0;
+        }
+        acc = red_join<RIMPL>(acc, x);
+      }
+      const A t = wave_reduce<RIMPL>(red_finish<RIMPL>(acc), P);
+      red_put<POL>(ro, row - row_begin + mr, odt, t, first == 0 && mr < rows);
     }
-    // UP * rpw consecutive rows, one lane each: a coalesced store instead of one 4-byte store per row
-    if (gather && lane < UP * rpw && base + lane < row_end) red_store<POL>(po, base + lane, odt, mine);
+    lds_wave_sync();
   }
 }
 
@@ -1675,40 +1743,55 @@ template <int POL, int RIMPL, int DT>
 PATHFN void red_rows_short_aligned(RedArgs a) {
   const RedRun run = red_run(a);
   const uint32_t tid = a.tid;
-  char* po = (char*)uni_ptr((uint64_t)a.po);
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end), vpr = uni(a.max_span);
+  using E = Elem<DT>;
   using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
-  constexpr int UP = 8;
-  const uint32_t lane = tid & 63u, wave = tid >> 6;
+  constexpr uint32_t UP = 8;
+  const uint32_t lane = tid & 63u, wave = uni(tid >> 6);
   uint32_t P = 1;                                     // lanes per row: power of two >= vectors per row
   while (P < vpr) P <<= 1;
   const uint32_t rpw = 64u / P, sub = lane / P, j = lane & (P - 1u);
   const bool gather = UP * rpw <= 64u;                // the pass's rows fit one lane each
   const bool mine = j < vpr;
-  for (uint32_t base = row_begin + wave * rpw * UP; base < row_end; base += 4 * rpw * UP) {
-    v4i q[UP];
+  const rsrc_t ro = red_out(a, row_begin, row_end, odt);
+  // (four vectors a lane are requested while the four before are worked on)
+  constexpr uint32_t H = UP / 2;
+  v4i qa[H], qb[H];
+  auto fetch = [&](v4i (&q)[H], uint32_t base) {
 #pragma unroll
-    for (int u = 0; u < UP; ++u) {
+    for (uint32_t u = 0; u < H; ++u) {
       const uint32_t row = base + u * rpw + sub;
-      q[u] = M::ld16(run.rin, (row < row_end && mine) ? ((row - row_begin) * vpr + j) * 16u : kNoLoad);
+      q[u] = M::ld16(run.rin, row < row_end && mine ? ((row - row_begin) * vpr + j) * 16u : kNoLoad);
     }
-    A res = 0;                                 // lane L ends up with the result of row base + L
+  };
+  A res = 0;                                   // lane L ends up with the result of row base + L
+  auto take = [&](const v4i (&q)[H], uint32_t base, uint32_t u0) {
 #pragma unroll
-    for (int u = 0; u < UP; ++u) {
-      const uint32_t row = base + u * rpw + sub;
-      A acc = red_identity<RIMPL, A>();
-      bool nan = false;
-      if (row < row_end && mine) acc = red_vector<RIMPL, DT>(q[u], 0, 0, 0, false, acc, nan);
-      acc = wave_reduce<RIMPL>(red_finish<RIMPL>(acc, nan), P);
+    for (uint32_t u = 0; u < H; ++u) {
+      const uint32_t row = base + (u0 + u) * rpw + sub;
+      A x[E::V], acc = red_identity<RIMPL, A>();
+#pragma unroll
+      for (int k = 0; k < E::V; ++k) x[k] = red_get<DT>(q[u], k);
+      acc = red_join<RIMPL>(acc, x);
+      acc = mine ? red_finish<RIMPL>(acc) : red_identity<RIMPL, A>();
+      acc = wave_reduce<RIMPL>(acc, P);
       if (gather) {
         const A got = __shfl(acc, (int)((lane & (rpw - 1u)) * P), 64);
-        if (lane / rpw == (uint32_t)u) res = got;
-      } else if (row < row_end && j == 0) {
-        red_store<POL>(po, row, odt, acc);
+        if (lane / rpw == u0 + u) res = got;
+      } else {
+        red_put<POL>(ro, row - row_begin, odt, acc, row < row_end && j == 0);
       }
     }
-    if (gather && lane < UP * rpw && base + lane < row_end) red_store<POL>(po, base + lane, odt, res);
+  };
+  uint32_t base = row_begin + wave * rpw * UP;
+  fetch(qa, base);
+  for (; base < row_end; base += 4 * rpw * UP) {
+    fetch(qb, base + H * rpw);
+    take(qa, base, 0);
+    fetch(qa, base + 4 * rpw * UP);
+    take(qb, base, H);
+    if (gather) red_put<POL>(ro, base + lane - row_begin, odt, res, lane < UP * rpw && base + lane < row_end);
   }
 }
 
@@ -1731,10 +1814,9 @@ DEV void red_contig(const Record* r, uint32_t row_begin, uint32_t row_end, float
   const bool whole = n % V == 0 && a.lead == 0;       // every row is whole vectors
   a.max_span = whole ? n / V : (n + V - 2) / V + 1;
   if (a.max_span <= 64u && whole) red_rows_short_aligned<POL, RIMPL, DT>(a);
-  else if (a.max_span <= 64u) red_rows_short<POL, RIMPL, DT>(a);
+  else if (a.max_span <= kRedLdsSpan) red_rows_lds<POL, RIMPL, DT>(a);
   else if (a.max_span >= 1024u && row_end - row_begin <= kRedPartialRows) red_rows_quarter<POL, RIMPL, DT>(a);
-  else if (a.max_span < 256u) red_rows_wave<POL, RIMPL, DT, 4, 2>(a);
-  else red_rows_wave<POL, RIMPL, DT, 2, 4>(a);
+  else red_rows_stream<POL, RIMPL, DT>(a);
 }
 
 // PATH_RED_GENERIC: one wave per output row; outer index decomposed over the
@@ -1792,22 +1874,15 @@ PATHFN void red_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v, uin
 // Arithmetic is fp32.  Lanes outside a row feed the identity (-inf to the softmax, 0 to the
 // sums).  The softmax maximum ignores NaN; a NaN still poisons its row through the sum.
 // ---------------------------------------------------------------------------
-DEV float bfly_sum(float v, uint32_t width) {
-  if (width > 32) v += butterfly_partner<32>(v);
-  if (width > 16) v += butterfly_partner<16>(v);
-  if (width > 8) v += butterfly_partner<8>(v);
-  if (width > 4) v += butterfly_partner<4>(v);
-  if (width > 2) v += butterfly_partner<2>(v);
-  if (width > 1) v += butterfly_partner<1>(v);
-  return v;
-}
-DEV float bfly_max(float v, uint32_t width) {
-  if (width > 32) v = __builtin_fmaxf(v, butterfly_partner<32>(v));
-  if (width > 16) v = __builtin_fmaxf(v, butterfly_partner<16>(v));
-  if (width > 8) v = __builtin_fmaxf(v, butterfly_partner<8>(v));
-  if (width > 4) v = __builtin_fmaxf(v, butterfly_partner<4>(v));
-  if (width > 2) v = __builtin_fmaxf(v, butterfly_partner<2>(v));
-  if (width > 1) v = __builtin_fmaxf(v, butterfly_partner<1>(v));
+DEV float bfly_sum(float v, uint32_t width) { return wave_reduce<GPUOS_IMPL_SUM_LAST>(v, width); }
+DEV float bfly_max(float v, uint32_t width) {          // (NaN is left out, the sum of exponentials brings it back)
+  float a, b;
+  if (width > 32) { butterfly_pair<32>(v, a, b); v = __builtin_fmaxf(a, b); }
+  if (width > 16) { butterfly_pair<16>(v, a, b); v = __builtin_fmaxf(a, b); }
+  if (width > 8) { butterfly_pair<8>(v, a, b); v = __builtin_fmaxf(a, b); }
+  if (width > 4) { butterfly_pair<4>(v, a, b); v = __builtin_fmaxf(a, b); }
+  if (width > 2) { butterfly_pair<2>(v, a, b); v = __builtin_fmaxf(a, b); }
+  if (width > 1) { butterfly_pair<1>(v, a, b); v = __builtin_fmaxf(a, b); }
   return v;
 }
 
@@ -2526,15 +2601,21 @@ PATHFN void rowop_other(const Record* r_v, uint32_t impl_v, uint32_t begin_v, ui
 // What the choice of an executor asks of a record, in registers: the worker reads it with the rest of the
 // record's head, in one go (field by field it was two more LDS latencies in a row on every unit).
 struct RecHead {
-  v4i op, dims;                                        // bytes 0-15 and 32-47 of the record
-  static DEV RecHead of(const Record* r) { const v4i* h = (const v4i*)r; return {h[0], h[2]}; }
-  DEV uint32_t path() const { return (uni((uint32_t)op[0]) >> 16) & 0xffu; }
-  DEV uint32_t dtype_in0() const { return (uni((uint32_t)op[1]) >> 8) & 0xffu; }
-  DEV uint32_t dtype_out() const { return uni((uint32_t)op[2]) & 0xffu; }
-  DEV uint32_t rflags() const { return (uni((uint32_t)op[2]) >> 8) & 0xffu; }
-  DEV uint32_t chunk() const { return uni((uint32_t)dims[0]); }
-  DEV uint32_t numel() const { return uni((uint32_t)dims[1]); }
-  DEV uint32_t red_n() const { return uni((uint32_t)dims[2]); }
+  uint32_t op[3], dims[3];                             // words 0-2 and 8-10 of the record
+  static DEV RecHead of(const Record* r) {
+    const v4i* h = (const v4i*)r;
+    return of(h[0], h[2]);
+  }
+  static DEV RecHead of(const v4i& q0, const v4i& q2) {
+    return {{uni((uint32_t)q0[0]), uni((uint32_t)q0[1]), uni((uint32_t)q0[2])}, {uni((uint32_t)q2[0]), uni((uint32_t)q2[1]), uni((uint32_t)q2[2])}};
+  }
+  DEV uint32_t path() const { return (op[0] >> 16) & 0xffu; }
+  DEV uint32_t dtype_in0() const { return (op[1] >> 8) & 0xffu; }
+  DEV uint32_t dtype_out() const { return op[2] & 0xffu; }
+  DEV uint32_t rflags() const { return (op[2] >> 8) & 0xffu; }
+  DEV uint32_t chunk() const { return dims[0]; }
+  DEV uint32_t numel() const { return dims[1]; }
+  DEV uint32_t red_n() const { return dims[2]; }
 };
 static_assert(__builtin_offsetof(Record, path) == 2 && __builtin_offsetof(Record, dtype) == 5 && __builtin_offsetof(Record, rflags) == 9 &&
               __builtin_offsetof(Record, chunk) == 32 && __builtin_offsetof(Record, numel) == 36 && __builtin_offsetof(Record, red_n) == 40, "the words of RecHead");
@@ -2680,27 +2761,36 @@ DEV void run_elementwise(const Record* r, const RecHead& h, uint32_t chunk, floa
   }
 }
 
+// The executors of reductions, behind one call as well (it ends in jumps): they were 60 call sites of the worker's loop, which
+// with other executors in their place fetched 102 of its values from scratch memory, a lone addition 8.8 us instead of 8.2.
 template <int POL, int RIMPL>
 DEV void run_reduction(const Record* r, const RecHead& h, uint32_t chunk, float* s_red, uint32_t tid) {
   const uint32_t per = h.chunk(), rows = h.numel();
   const uint32_t begin = chunk * per;
   const uint32_t end = (rows - begin < per) ? rows : begin + per;
   const uint32_t path = h.path(), dt = h.dtype_in0();
-  if (h.rflags() & RF_INT) {
-    if (path == PATH_RED_CONTIG) red_contig<POL, RIMPL, GPUOS_I32>(r, begin, end, s_red, tid);
-    else red_generic<POL, RIMPL, true>(r, begin, end, tid);
-    return;
-  }
   if (path == PATH_RED_CONTIG) {
-    if (dt == GPUOS_F32) red_contig<POL, RIMPL, GPUOS_F32>(r, begin, end, s_red, tid);
+    if (h.rflags() & RF_INT) red_contig<POL, RIMPL, GPUOS_I32>(r, begin, end, s_red, tid);
+    else if (dt == GPUOS_F32) red_contig<POL, RIMPL, GPUOS_F32>(r, begin, end, s_red, tid);
     else if (dt == GPUOS_F16) red_contig<POL, RIMPL, GPUOS_F16>(r, begin, end, s_red, tid);
     else red_contig<POL, RIMPL, GPUOS_BF16>(r, begin, end, s_red, tid);
   } else {
-    red_generic<POL, RIMPL, false>(r, begin, end, tid);
+    if (h.rflags() & RF_INT) red_generic<POL, RIMPL, true>(r, begin, end, tid);
+    else red_generic<POL, RIMPL, false>(r, begin, end, tid);
   }
 }
+template <int POL>
+PATHFN void run_reductions(const Record* r_v, uint32_t impl_v, uint32_t chunk_v, float* s_v, uint32_t tid) {
+  const Record* r = lds_arg(r_v);
+  float* s = lds_arg(s_v);
+  const RecHead h = RecHead::of(r);
+  const uint32_t impl = uni(impl_v), chunk = uni(chunk_v);
+  if (impl == GPUOS_IMPL_SUM_LAST) run_reduction<POL, GPUOS_IMPL_SUM_LAST>(r, h, chunk, s, tid);
+  else if (impl == GPUOS_IMPL_MAX_LAST) run_reduction<POL, GPUOS_IMPL_MAX_LAST>(r, h, chunk, s, tid);
+  else run_reduction<POL, GPUOS_IMPL_MIN_LAST>(r, h, chunk, s, tid);
+}
 
-// The interpreter's executors, behind one call: in the worker's loop itself they are 44 of its 293 call sites, which cost
+// The interpreter's executors, behind one call: in the worker's loop itself they were 44 of its 293 call sites, which cost
 // other operations' registers (softmax over rows of 32,003 fp32 elements: 180.4 us with them there, 175.9 so).  It ends in
 // jumps: where it made calls it had to keep for its caller all that its callees use, 376 bytes a lane, and
 // x / (1 + e^-x) over four tensors of 2,048 fp32 elements took 35.7 us instead of 16.0.
@@ -2763,9 +2853,7 @@ DEV int32_t exec_chunk(const Record* r, const RecHead& h, uint32_t impl, uint32_
     case GPUOS_IMPL_FMA: run_elementwise<POL, GPUOS_IMPL_FMA>(r, h, chunk, s_red, tid); break;
     case GPUOS_IMPL_SUB_EXP: run_elementwise<POL, GPUOS_IMPL_SUB_EXP>(r, h, chunk, s_red, tid); break;
     case GPUOS_IMPL_COPY: run_elementwise<POL, GPUOS_IMPL_COPY>(r, h, chunk, s_red, tid); break;
-    case GPUOS_IMPL_SUM_LAST: run_reduction<POL, GPUOS_IMPL_SUM_LAST>(r, h, chunk, s_red, tid); break;
-    case GPUOS_IMPL_MAX_LAST: run_reduction<POL, GPUOS_IMPL_MAX_LAST>(r, h, chunk, s_red, tid); break;
-    case GPUOS_IMPL_MIN_LAST: run_reduction<POL, GPUOS_IMPL_MIN_LAST>(r, h, chunk, s_red, tid); break;
+    case GPUOS_IMPL_SUM_LAST: case GPUOS_IMPL_MAX_LAST: case GPUOS_IMPL_MIN_LAST: run_reductions<POL>(r, impl, chunk, s_red, tid); break;
     case GPUOS_IMPL_SOFTMAX_LAST: run_rowop<POL, GPUOS_IMPL_SOFTMAX_LAST>(r, h, chunk, s_red, tid); break;
     case GPUOS_IMPL_MASKED_SOFTMAX_LAST: run_rowop<POL, GPUOS_IMPL_MASKED_SOFTMAX_LAST>(r, h, chunk, s_red, tid); break;
     case GPUOS_IMPL_LAYERNORM_LAST: run_rowop<POL, GPUOS_IMPL_LAYERNORM_LAST>(r, h, chunk, s_red, tid); break;
@@ -2846,6 +2934,8 @@ struct WorkShared {
   const OpSlots* dtable;
   uint32_t cap_mask;
   uint32_t rec_sum;                // weighted check sum of the record as fetched
+  uint64_t begun, started;         // clocks of the unit that runs: performance counters, tracing
+  uint64_t entered;                // ... and of the worker's start
   uint64_t n_units;                // (ST_WORK_UNITS, and the counters after it)
   uint64_t ticks[ST_WORK_TICKS_TOTAL - ST_WORK_TICKS_WAIT];
   alignas(16) float red[kScratchFloats];   // (16-byte LDS vectors are written into it)
@@ -2903,9 +2993,8 @@ template <int RIMPL, int DT, int K> DEV void link_reduce(const EitherArg<DT, K>&
 #pragma unroll
   for (int u = 0; u < K; ++u) {
     float acc = red_identity<RIMPL, float>();
-    bool nan = false;
-    if (act) acc = red_vector<RIMPL, DT>(q.raw(u), 0, 0, 0, false, acc, nan);
-    out[u] = wave_reduce<RIMPL>(red_finish<RIMPL>(acc, nan), width);
+    if (act) acc = red_vector<RIMPL, DT>(q.raw(u), 0, 0, 0, false, acc);
+    out[u] = wave_reduce<RIMPL>(red_finish<RIMPL>(acc), width);
   }
 }
 
@@ -2952,7 +3041,7 @@ __attribute__((not_tail_called)) PATHFN void run_links(const Record* recs_v, uin
   auto what_of = [&](uint32_t k) {
     if (!ROWS) return at_lane(h_what, k);
     const RecHead h = RecHead::of(recs + k);             // (bytes 0-15: inputs 4, dtypes 6 and 8, kinds 10 and 11)
-    const uint32_t path = h.path(), w1 = uni((uint32_t)h.op[1]), w2 = uni((uint32_t)h.op[2]);
+    const uint32_t path = h.path(), w1 = h.op[1], w2 = h.op[2];
     const uint32_t kinds = path == PATH_ROW2D ? ((w2 >> 16) & 15u) | (((w2 >> 24) & 15u) << 4) : 0u;
     return uni(recs[k].impl) | (path << 8) | ((w1 & 15u) << 12) | (kinds << 16) | (((w1 >> 16) & 15u) << 24) | ((w2 & 15u) << 28);
   };
@@ -3195,14 +3284,14 @@ __attribute__((not_tail_called, disable_tail_calls)) PATHFN void exec_run(WorkSh
 // the EXEC that kernel brings; `gen` is the generation of that kernel: its workers leave when the
 // host asks for a later one.
 //
-// serve_units: unit after unit, until the worker leaves (false) or one is a run's (true: `run` says which).
-struct RunUnit {
-  uint32_t f, chunk;
+// next_unit: the next unit that can run (its descriptor and what it needs of it: `u`), or false: the worker leaves.
+struct Unit {
+  RecHead head;
+  uint32_t f, chunk, impl, run;                       // descriptor slot, chunk, implementation; tasks that it stands for
   int32_t status;
-  uint64_t begun;                                     // (performance counters)
 };
-template <int RING, class EXEC>
-DEV bool serve_units(const WorkerArgs& a, WorkShared* s, uint32_t gen, uint32_t wave, uint64_t w_start, RunUnit& run) {
+template <int RING>
+DEV bool next_unit(const WorkerArgs& a, WorkShared* s, uint32_t gen, uint32_t wave, Unit& out) {
   const uint32_t lane = thread_index(0);              // (anew, and all that follows from it: nothing is kept over a run)
   const bool leader = wave == 0 && lane == 0;
   uint64_t* const claim_ctr = RING == 0 ? &a.d->claim : &a.d->claim_j;
@@ -3352,7 +3441,7 @@ DEV bool serve_units(const WorkerArgs& a, WorkShared* s, uint32_t gen, uint32_t 
         __hip_atomic_fetch_add(&st[ST_WORK_UNITS], s->n_units, __ATOMIC_RELAXED, SC_AGENT);
         for (uint32_t k = ST_WORK_TICKS_WAIT; k < ST_WORK_TICKS_TOTAL; ++k)
           __hip_atomic_fetch_add(&st[k], s->ticks[k - ST_WORK_TICKS_WAIT], __ATOMIC_RELAXED, SC_AGENT);
-        __hip_atomic_fetch_add(&st[ST_WORK_TICKS_TOTAL], c0 - w_start, __ATOMIC_RELAXED, SC_AGENT);
+        __hip_atomic_fetch_add(&st[ST_WORK_TICKS_TOTAL], c0 - s->entered, __ATOMIC_RELAXED, SC_AGENT);
       }
       return false;
     }
@@ -3366,7 +3455,7 @@ DEV bool serve_units(const WorkerArgs& a, WorkShared* s, uint32_t gen, uint32_t 
     const Record* r = &s->rec[f];
     // What the rest of this unit's handling asks of the record, read in one go (field by field, where each
     // is wanted, was eight LDS latencies in a row before the executor is reached).
-    struct Head : RecHead { v4i impl, links; uint64_t entry; uint32_t sum; } head;
+    struct { v4i op, impl, dims, links; uint64_t entry; uint32_t sum; } head;
     auto read_head = [&]() {
       const v4i* h = (const v4i*)r;
       head.op = h[0]; head.impl = h[1]; head.dims = h[2]; head.links = h[3];
@@ -3405,7 +3494,7 @@ DEV bool serve_units(const WorkerArgs& a, WorkShared* s, uint32_t gen, uint32_t 
         __syncthreads();
         continue;
       }
-      if ((pair(head.links, 0) & 0xffffffffffffull) != 0 &&    /* (dep[3]; the halfword behind them is `run`) */ !(head.rflags() & RF_DEPS_RESOLVED)) {
+      if ((pair(head.links, 0) & 0xffffffffffffull) != 0 &&    /* (dep[3]; the halfword behind them is `run`) */ (((uint32_t)word(head.op, 2) >> 8) & RF_DEPS_RESOLVED) == 0) {
         // It names earlier tasks: it joins the units held, and the first wavefront looks at its done
         // words with the next poll (and runs it at once if they are all there).
         if (leader) {
@@ -3421,97 +3510,122 @@ DEV bool serve_units(const WorkerArgs& a, WorkShared* s, uint32_t gen, uint32_t 
     const uint32_t impl = word(head.impl, 0), nchunks = word(head.impl, 3);
     if (status == GPUOS_OK && uni((uint32_t)(head.entry >> 32)) != word(head.impl, 1)) status = GPUOS_E_VERSION;
     if (status == GPUOS_OK) status = (int32_t)word(dec, 1);
-    const uint64_t c3 = clock_if(timing);
-    if (RING == 0 && __builtin_expect((uni((uint32_t)head.links[1]) >> 17) != 0, 0)) {      // a run of two or more tasks
-      run.f = f; run.chunk = chunk; run.status = status; run.begun = c3;
-      return true;
-    }
-    // a task's start in the trace is the moment a workgroup took its descriptor (a unit that waited: when it began to)
-    const uint64_t c_start = (tracing && action == kActRun) ? s->since[f] : c1;
-    if (tracing && leader && chunk == 0 && nchunks > 1)
-      __hip_atomic_store(&a.st[slot].t_first, c_start, __ATOMIC_RELAXED, SC_SYSTEM);   // in memory before this chunk is counted
-    // ---- execute ----
-    if (status == GPUOS_OK) status = EXEC::run(r, head, impl, chunk, s->red, a.progs, thread_index(wave));
-    if (RING == 1 && leader) __hip_atomic_fetch_add(&a.d->jit_units, 1ull, __ATOMIC_RELAXED, SC_AGENT);
-    // What completing needs, read while the stores are still on their way: through an address made here,
-    // as the first use of a register that a call preserves waits for everything the callee left in flight.
-    uint32_t here = 0;
-    asm volatile("" : "+v"(here));
-    const Record* const rh = (const Record*)((const char*)r + here);
-    const WorkShared* const sh = (const WorkShared*)((const char*)s + here);
-    const v4i impl_w = ((const v4i*)rh)[1];
-    const uint64_t ticket = rh->ticket, cap_shift = sh->cap_shift;
-    SlotState* const st = global_ptr(sh->st);
-    uint64_t *const comp = global_ptr(sh->hcomp), *const done_count = global_ptr(sh->done_count);
-    drain_stores();                   // this wave's (write-through) stores have reached memory
-    __syncthreads();                  // ... and so have the other three waves'
-    const uint64_t c4 = clock_if(timing || tracing);
-    // ---- complete ----
-    if (leader) {
-      const uint32_t nchunks = (uint32_t)impl_w[3], version = (uint32_t)impl_w[1];
-      const uint64_t target = done_target(ticket, (uint32_t)cap_shift);
-      bool last = true;
-      if (nchunks > 1) {
-        const uint64_t share = chunk + 1 == nchunks ? kDoneTask - (nchunks - 1) : 1ull;
-        last = __hip_atomic_fetch_add(&st[slot].done_seq, share, __ATOMIC_RELAXED, SC_AGENT) + share == target;
-      }
-      if (last) {
-        if (tracing) {
-          // the tracepoint lands before the completion word that lets the host read it
-          const uint64_t origin = __hip_atomic_load(&a.h->clock_origin, __ATOMIC_RELAXED, SC_SYSTEM);
-          const uint64_t t_start = nchunks > 1 ? __hip_atomic_load(&st[slot].t_first, __ATOMIC_RELAXED, SC_SYSTEM) : c_start;
-          TraceRec* tr = &a.trace[ticket & a.trace_mask];
-          const uint64_t tdq = ((uint64_t)r->t_dequeue[1] << 32) | r->t_dequeue[0];
-          __hip_atomic_store(&tr->t_dequeue, tdq - origin, __ATOMIC_RELAXED, SC_SYSTEM);
-          __hip_atomic_store(&tr->t_start, t_start - origin, __ATOMIC_RELAXED, SC_SYSTEM);
-          // The clock is read here, once this workgroup knows it finished the task: the time taken
-          // right after its own chunk (c4) can lie before the start of chunk 0 when this workgroup's
-          // count arrives late (seen once in a few thousand multi-chunk tasks).
-          const uint64_t t_done = nchunks > 1 ? wall_clock64() : c4;
-          __hip_atomic_store(&tr->t_done, t_done - origin, __ATOMIC_RELAXED, SC_SYSTEM);
-          const uint64_t w4 = (uint64_t)version | ((uint64_t)r->op_id << 32) | ((uint64_t)(uint8_t)(int8_t)status << 48);
-          __hip_atomic_store((uint64_t*)&tr->op_version, w4, __ATOMIC_RELAXED, SC_SYSTEM);
-          const uint64_t w5 = (uint64_t)nchunks | ((uint64_t)blockIdx.x << 32);
-          __hip_atomic_store((uint64_t*)&tr->nchunks, w5, __ATOMIC_RELAXED, SC_SYSTEM);
-          __hip_atomic_store(&tr->ticket, ticket, __ATOMIC_RELAXED, SC_SYSTEM);
-          drain_stores();
-        }
-        if (nchunks <= 1) __hip_atomic_store(&st[slot].done_seq, target, __ATOMIC_RELAXED, SC_SYSTEM);
-        __hip_atomic_store(&comp[slot], pack_completion(ticket, status, version), __ATOMIC_RELAXED, SC_SYSTEM);
-        __hip_atomic_fetch_add(done_count, 1ull, __ATOMIC_RELAXED, SC_AGENT);
+    out = Unit{RecHead::of(head.op, head.dims), f, chunk, impl, word(head.links, 1) >> 16, status};
+    if (timing || tracing) {
+      // a task's start in the trace is the moment a workgroup took its descriptor (a unit that waited: when it began to)
+      const uint64_t c_start = (tracing && action == kActRun) ? s->since[f] : c1;
+      if (leader) {
+        s->begun = clock_if(timing);
+        s->started = c_start;
+        if (tracing && chunk == 0 && nchunks > 1)
+          __hip_atomic_store(&a.st[slot].t_first, c_start, __ATOMIC_RELAXED, SC_SYSTEM);   // in memory before this chunk is counted
       }
     }
-    __syncthreads();                  // the descriptor in LDS may be overwritten after this
-    const uint64_t c5 = clock_if(timing);
-    if (leader) s->n_units += 1;
-    if (timing) { count(ST_WORK_TICKS_EXEC, c4 - c3); count(ST_WORK_TICKS_COMPLETE, c5 - c4); }
+    return true;
   }
 }
+
+// A chunk that has been executed, to the completion of its task.  All it goes by lies in LDS.
+template <int RING>
+DEV void complete_unit(const WorkerArgs& a, WorkShared* s, int32_t status, uint32_t tid) {
+  const bool leader = tid == 0;
+  const bool timing = a.timing != 0, tracing = a.trace != nullptr;
+  const v4i dec = *(const v4i*)s->dec;
+  const uint32_t f = (uni((uint32_t)dec[0]) >> 8) & 0xffu, unit_lo = uni((uint32_t)dec[2]), unit_hi = uni((uint32_t)dec[3]);
+  const uint64_t unit = ((uint64_t)unit_hi << 32) | unit_lo;
+  const uint32_t chunk = (uint32_t)(unit & 0x3ffu), slot = (uint32_t)((unit >> 20) & 0xffffu);
+  const Record* r = &s->rec[f];
+  if (RING == 1 && leader) __hip_atomic_fetch_add(&a.d->jit_units, 1ull, __ATOMIC_RELAXED, SC_AGENT);
+  // (read while the stores are still on their way)
+  const v4i impl_w = ((const v4i*)r)[1];
+  const uint64_t ticket = r->ticket;
+  SlotState* const st = a.st;
+  uint64_t *const comp = a.hcomp, *const done_count = &a.d->done_count;
+  const uint32_t cap_shift = a.cap_shift;
+  drain_stores();                   // this wave's (write-through) stores have reached memory
+  __syncthreads();                  // ... and so have the other three waves'
+  const uint64_t c4 = clock_if(timing || tracing);
+  // ---- complete ----
+  if (leader) {
+    const uint32_t nchunks = (uint32_t)impl_w[3], version = (uint32_t)impl_w[1];
+    const uint64_t target = done_target(ticket, cap_shift);
+    bool last = true;
+    if (nchunks > 1) {
+      const uint64_t share = chunk + 1 == nchunks ? kDoneTask - (nchunks - 1) : 1ull;
+      last = __hip_atomic_fetch_add(&st[slot].done_seq, share, __ATOMIC_RELAXED, SC_AGENT) + share == target;
+    }
+    if (last) {
+      if (tracing) {
+        // the tracepoint lands before the completion word that lets the host read it
+        const uint64_t origin = __hip_atomic_load(&a.h->clock_origin, __ATOMIC_RELAXED, SC_SYSTEM);
+        const uint64_t t_start = nchunks > 1 ? __hip_atomic_load(&st[slot].t_first, __ATOMIC_RELAXED, SC_SYSTEM) : s->started;
+        TraceRec* tr = &a.trace[ticket & a.trace_mask];
+        const uint64_t tdq = ((uint64_t)r->t_dequeue[1] << 32) | r->t_dequeue[0];
+        __hip_atomic_store(&tr->t_dequeue, tdq - origin, __ATOMIC_RELAXED, SC_SYSTEM);
+        __hip_atomic_store(&tr->t_start, t_start - origin, __ATOMIC_RELAXED, SC_SYSTEM);
+        // The clock is read here, once this workgroup knows it finished the task: the time taken
+        // right after its own chunk (c4) can lie before the start of chunk 0 when this workgroup's
+        // count arrives late (seen once in a few thousand multi-chunk tasks).
+        const uint64_t t_done = nchunks > 1 ? wall_clock64() : c4;
+        __hip_atomic_store(&tr->t_done, t_done - origin, __ATOMIC_RELAXED, SC_SYSTEM);
+        const uint64_t w4 = (uint64_t)version | ((uint64_t)r->op_id << 32) | ((uint64_t)(uint8_t)(int8_t)status << 48);
+        __hip_atomic_store((uint64_t*)&tr->op_version, w4, __ATOMIC_RELAXED, SC_SYSTEM);
+        const uint64_t w5 = (uint64_t)nchunks | ((uint64_t)blockIdx.x << 32);
+        __hip_atomic_store((uint64_t*)&tr->nchunks, w5, __ATOMIC_RELAXED, SC_SYSTEM);
+        __hip_atomic_store(&tr->ticket, ticket, __ATOMIC_RELAXED, SC_SYSTEM);
+        drain_stores();
+      }
+      if (nchunks <= 1) __hip_atomic_store(&st[slot].done_seq, target, __ATOMIC_RELAXED, SC_SYSTEM);
+      __hip_atomic_store(&comp[slot], pack_completion(ticket, status, version), __ATOMIC_RELAXED, SC_SYSTEM);
+      __hip_atomic_fetch_add(done_count, 1ull, __ATOMIC_RELAXED, SC_AGENT);
+    }
+  }
+  __syncthreads();                  // the descriptor in LDS may be overwritten after this
+  const uint64_t c5 = clock_if(timing);
+  if (leader) {
+    s->n_units += 1;
+    if (timing) { s->ticks[ST_WORK_TICKS_EXEC - ST_WORK_TICKS_WAIT] += c4 - s->begun; s->ticks[ST_WORK_TICKS_COMPLETE - ST_WORK_TICKS_WAIT] += c5 - c4; }
+  }
+}
+
+// The kernel's arguments (its first parameter), apart from the dispatcher's: with values that both read kept over both,
+// either held the other's in registers (1,000 small additions 95.7 us instead of 85.0).
+DEV const WorkerArgs& worker_args() {
+  typedef const __attribute__((address_space(4))) WorkerArgs* args_t;
+  args_t p = (args_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const WorkerArgs*)p;
+}
+
 template <int RING, class EXEC>
-DEV void run_worker(const WorkerArgs& a, WorkShared* s, uint32_t gen = 0) {
-  const uint32_t wave = uni(threadIdx.x >> 6);        // (this thread's place as the wavefront's index, a scalar, and the lane; see thread_index)
-  if (wave == 0 && lane_id() == 0) {
+DEV void run_worker(WorkShared* s, uint32_t gen = 0) {
+  const WorkerArgs& a = worker_args();
+  const uint32_t my_wave = uni(threadIdx.x >> 6);     // (this thread's place as the wavefront's index, a scalar, and the lane; see thread_index)
+  if (my_wave == 0 && lane_id() == 0) {
     s->state[0] = s->state[1] = s->state[2] = s->state[3] = 0;
     s->n_units = 0;
     s->st = a.st; s->hcomp = a.hcomp; s->done_count = &a.d->done_count; s->cap_shift = a.cap_shift;
     s->dring = a.dring; s->dtable = a.dtable; s->cap_mask = a.cap_mask;
     for (uint32_t k = 0; k < ST_WORK_TICKS_TOTAL - ST_WORK_TICKS_WAIT; ++k) s->ticks[k] = 0;
+    s->entered = clock_if(a.timing != 0);
   }
   lds_wave_sync();                                    // (only the first wavefront reads them)
-  const bool timing = a.timing != 0;
-  const uint64_t w_start = clock_if(timing);
-  RunUnit run = {0, 0, 0, 0};
-  while (serve_units<RING, EXEC>(a, s, gen, wave, w_start, run)) {
-    // A run, outside the loop over other units: its call keeps no register (see exec_run).  Within that loop the worker
-    // kept its own for it in scratch memory, over other calls too: masked softmax took 45.9 us instead of 38.1, 24 integer
-    // operations 66.0 instead of 60.7.
-    if constexpr (RING == 0) {
-      exec_run(s, run.f, run.chunk, run.status, thread_index(wave));
+  while (true) {
+    uint32_t wave = my_wave;
+    asm volatile("" : "+s"(wave));                    // (nothing that follows from it is kept from one unit to the next)
+    Unit u;
+    if (!next_unit<RING>(a, s, gen, wave, u)) return;
+    if (RING == 0 && __builtin_expect(u.run > 1u, 0)) {                  // a run of two or more tasks
+      exec_run(s, u.f, u.chunk, u.status, thread_index(wave));
       if (thread_index(wave) == 0) {
         s->n_units += 1;
-        if (timing) s->ticks[ST_WORK_TICKS_EXEC - ST_WORK_TICKS_WAIT] += clock_if(timing) - run.begun;
+        if (a.timing != 0) s->ticks[ST_WORK_TICKS_EXEC - ST_WORK_TICKS_WAIT] += wall_clock64() - s->begun;
       }
+      continue;
     }
+    int32_t status = u.status;
+    if (status == GPUOS_OK) status = EXEC::run(&s->rec[u.f], u.head, u.impl, u.chunk, s->red, a.progs, thread_index(wave));
+    complete_unit<RING>(a, s, status, thread_index(wave));
   }
 }
 

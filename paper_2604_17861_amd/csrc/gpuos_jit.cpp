@@ -166,7 +166,7 @@ std::string jit_source(const ProgramImage* imgs, uint32_t n) {
        "  __shared__ gpuos::WorkShared sh;\n"
        "  if (blockIdx.x == 0 && threadIdx.x == 0)\n"
        "    __hip_atomic_store(&a.h->jit_alive, gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);\n"
-       "  gpuos::run_worker<1, gpuos::NativeExec>(a, &sh, gen);\n}\n";
+       "  gpuos::run_worker<1, gpuos::NativeExec>(&sh, gen);\n}\n";
   return s;
 }
 

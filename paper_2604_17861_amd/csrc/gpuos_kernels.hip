@@ -755,7 +755,7 @@ union KernelShared {
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) gpuos_worker_kernel(WorkerArgs a) {
   __shared__ KernelShared sh;
   if (blockIdx.x == 0) run_dispatcher(a, &sh.disp);
-  else run_worker<0, BuiltinExec>(a, &sh.work);
+  else run_worker<0, BuiltinExec>(&sh.work);
 }
 
 // one ordinary launch per task: block b executes chunk b

@@ -32,6 +32,28 @@ def reduction_edges(code):
     return b.stream("reduction_edges_%d" % code)
 
 
+def reduction_shares(code):
+    """Contiguous rows that wavefronts share out and read densely: row lengths at either side of each shape of
+    work (rows put into LDS by the piece, one piece a row and many; rows that end within a group of 64
+    vectors, at its end, several in one; more than 64 rows a wavefront), rows that no piece or share
+    divides, a NaN in a row's first or last element, between rows that have none."""
+    rng = np.random.default_rng(720 + code)
+    b = Builder()
+    V = 4 if code in (S.F32, S.I32) else 8
+    odt = np.int32 if code == S.I32 else np.float32
+    for rows, n, lead in ((1030, 3, 1), (411, 2 * V + 1, 0), (197, 14 * V - 1, 2), (77, 126 * V + 2, 0), (78, 127 * V - 1, 1), (79, 127 * V, 1),
+                          (45, 127 * V + 1, 0), (46, 128 * V, 0), (47, 65 * V, 0), (13, 223 * V + 1, 1), (9, 447 * V + 1, 0), (9, 448 * V, 0),
+                          (300, 64 * V, 0), (260, 63 * V, 0), (50, 34 * V, 0), (90, V, 0), (21, 1022 * V, 0), (9000, 65 * V, 0)):
+        x = b.pool(values(rng, rows * n + lead, code))[lead:].reshape(rows, n)
+        if code != S.I32:
+            nan = to_dtype(np.array([np.nan], np.float32), code)[0]
+            x[1::7, -1] = nan
+            x[3::7, 0] = nan
+        for name in ("SUM_LAST", "MAX_LAST", "MIN_LAST"):
+            b.add(name, b.pool(np.zeros(rows, odt)), [x])
+    return b.stream("reduction_shares_%d" % code)
+
+
 def rows_edges(code):
     """Rows contiguous in every operand under outer dims of any strides: slices read and written, head
     splits, per-row scalars of any dtype, repeated rows, unaligned bases; rows of exactly one vector, of

@@ -15,6 +15,12 @@ def test_reductions_at_their_edges(code):
 
 
 @pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16, S.I32])
+def test_reductions_of_shared_out_rows(code):
+    stats, _ = _run_and_check(E.reduction_shares(code))
+    print(stats, flush=True)
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16, S.I32])
 def test_rows_at_their_edges(code):
     stats, _ = _run_and_check(E.rows_edges(code))
     print(stats, flush=True)
