@@ -54,6 +54,9 @@ DEV rsrc_t make_rsrc(const void* base, uint32_t bytes) {
 template <int POL> struct Mem {
   static constexpr int AUX = POL == POL_COHERENT ? 19 : 2;     // sc0|sc1|nt  or  nt
   static DEV v4i ld16(rsrc_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX); }
+  static DEV v4i ld16(rsrc_t r, uint32_t off, uint32_t more) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)more, AUX); }      // (`more`: the same in every lane)
+  // (No store of the kind: with an offset in a scalar register the compiler lets the next instruction overwrite the stored registers,
+  // and on gfx950 a 16-byte store still reads them then: softmax of 16-bit rows wrote pieces of the next vector's arguments.)
   static DEV void st16(rsrc_t r, uint32_t off, v4i q) { __builtin_amdgcn_raw_buffer_store_b128(q, r, (int)off, 0, AUX); }
   static DEV void st8(rsrc_t r, uint32_t off, uint32_t w0, uint32_t w1) {
     typedef int v2i __attribute__((ext_vector_type(2)));
@@ -2313,170 +2316,241 @@ DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* 
 
 // Softmax rows too long for the workgroup's registers (over 16,384 elements): two passes over the row.
 // The first keeps a running maximum and a sum relative to it per lane, rescaled once per
-// batch of four vectors; the second writes.  What the first has left in registers (the last twelve
-// vectors of a lane, eight of 16-bit elements) and in LDS (its first six) is not read again, the rest
-// comes from the memory-side cache.
-template <int POL, int ROP, int DT, bool RAGGED>
-DEV void softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
+// batch of vectors; the second writes.
+// A lane's first NB batches of three vectors stay in registers (up to eighteen, 72 of the 128: with twenty some went through scratch
+// memory) and the next six in LDS; the second pass reads only what is left, of a row of 32,003 fp32 elements eight of 32.  Bound by memory: 2 x 1,024 such rows took 175 us with twelve in registers, and as many of a caller's
+// saved and restored (525 MB read, 392 MB written, of 262 each).
+// A row has more vectors a lane than stay in registers: those are whole and need no look at the row's end.
+// Ragged rows are cut where memory's 16-byte blocks begin, if x and the output lie alike in them: a block at
+// either end of a row is shared with its neighbour, every other access is a whole aligned one.  (The block
+// that holds a tensor's first or last element may hold bytes outside it, in the same page.)  Cut from a row's
+// first element on, each store is written in two parts: 2 x 1,024 rows of 32,003 fp32 wrote 1.7 times and
+// read 2.2 times their bytes, 204 us; 181 cut at blocks.
+template <int POL, int DT, int NB, bool RAGGED>
+DEV void softmax_held(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
   using E = Elem<DT>;
   using M = Mem<POL>;
-  constexpr uint32_t V = E::V;
-  constexpr bool MASK = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST;
-  constexpr uint32_t U = 4, NB = MASK ? 0 : (DT == GPUOS_F32 ? 3 : 2);       // batches kept in registers (masked rows: none)
-  constexpr uint32_t NL = MASK ? 0 : 6, NR = NB * U;                        // vectors per lane kept in LDS / in registers
+  constexpr uint32_t V = E::V, U = 3, NR = NB * U, NL = 6;
   const uint32_t n = uni(r->red_n);
-  const float alpha = r->alpha;
   const uint32_t chunk_bytes = (row_end - row_begin) * n * E::ES;
   const uint64_t chunk_off = (uint64_t)row_begin * n * E::ES;
   const char* const px = uni_ptr(r->ptr[0]) + chunk_off;
   const char* const po = uni_ptr(r->ptr[3]) + chunk_off;
-  // Ragged rows are cut where memory's 16-byte blocks begin, if x and the output lie alike in them: a block at
-  // either end of a row is shared with its neighbour, every other access is a whole aligned one.  (The block
-  // that holds a tensor's first or last element may hold bytes outside it, in the same page.)  Cut from a row's
-  // first element on, each store is written in two parts: 2 x 1,024 rows of 32,003 fp32 wrote 1.7 times and
-  // read 2.2 times their bytes, 204 us; 181 so.
-  const BlockCut bc = RAGGED && !MASK ? block_cut((__UINTPTR_TYPE__)px, (__UINTPTR_TYPE__)po, chunk_bytes) : BlockCut{false, 0u, chunk_bytes};
+  const BlockCut bc = RAGGED ? block_cut((__UINTPTR_TYPE__)px, (__UINTPTR_TYPE__)po, chunk_bytes) : BlockCut{false, 0u, chunk_bytes};
   const bool blocks = bc.blocks;
   const uint32_t front = bc.front, window = bc.window;
   const rsrc_t rx = make_rsrc(px - front, window);
   const rsrc_t ro = make_rsrc(po - front, window);
-  rsrc_t rm = rx;
-  uint32_t period = 0;
-  if (MASK) {
-    if (uni(r->okind[1]) == K_FULL) rm = make_rsrc(uni_ptr(r->ptr[1]) + chunk_off, chunk_bytes);
-    else { period = uni(r->stride[1][0]); rm = make_rsrc(uni_ptr(r->ptr[1]), period * n * E::ES); }
-  }
   WgReduce wg = {s_v, 0, tid};
-  v4i* const kept = (v4i*)(s_v + 16) + tid;            // vector i of this lane lies at kept[i * kThreads]
-  static_assert(16 + 6 * kThreads * 4 <= kScratchFloats, "six vectors per lane");
+  v4i* const kept = (v4i*)(s_v + 16) + tid;            // vector NR + i of this lane lies at kept[i * kThreads]
+  static_assert(16 + NL * kThreads * 4 <= kScratchFloats, "six vectors per lane");
+  // (A vector's index anew wherever it is asked for: kept for every vector, as the compiler would have it, the indices
+  // and what follows from them go through scratch memory.)
+  auto vector = [&](uint32_t i) {
+    uint32_t v = tid;
+    asm volatile("" : "+v"(v));
+    return v + kThreads * i;
+  };
   for (uint32_t row = row_begin; row < row_end; ++row) {
     // vector `vec` begins at element vec * V - lead of the row (or, its last where rows are not cut at blocks, at n - V)
-    // and owns the elements of the row from its own element first(vec) on
     const uint32_t start = front + (row - row_begin) * n * E::ES, lead = blocks ? (start & 15u) / E::ES : 0u;
     const uint32_t vpr = (lead + n + V - 1) / V;
-    const uint32_t x0 = start - lead * E::ES;          // the first vector's first byte
+    const uint32_t x0 = start - lead * E::ES, mine = x0 + tid * 16u;       // the first vector's first byte, this lane's first
     const uint32_t T = (vpr + kThreads - 1) / kThreads;        // vectors per lane, the last partly filled
-    const uint32_t held = T > NR ? T - NR : 0u;        // vectors [held, T) of a lane end the first pass in registers
     const uint32_t back = RAGGED && !blocks ? vpr * V - n : 0u;          // elements the last vector is shifted back by
-    auto at_of = [&](uint32_t vec) { return (vec * V - (RAGGED && vec == vpr - 1 ? back : 0u)) * (uint32_t)E::ES; };
-    auto own = [&](uint32_t vec, int e) {
-      if (!RAGGED) return true;
-      const uint32_t at = vec * V + e;                 // (counted from the first vector's first element)
-      return blocks ? at - lead < n : vec != vpr - 1 || (uint32_t)e >= back;
+    constexpr uint32_t kStep = kThreads * 16u;
+    auto at_of = [&](uint32_t vec) { return x0 + vec * 16u - (RAGGED && vec == vpr - 1 ? back * (uint32_t)E::ES : 0u); };    // (past NR)
+    auto fetch = [&](uint32_t i) {
+      const uint32_t vec = vector(i);
+      return M::ld16(rx, vec < vpr ? at_of(vec) : kNoLoad);
     };
-    const uint32_t m0 = MASK ? (period ? row % period : row - row_begin) * n * E::ES : 0u;
-    auto fetch = [&](uint32_t i, v4i& q, v4i& mq) {
-      const uint32_t vec = tid + kThreads * i, at = at_of(vec);
-      q = M::ld16(rx, vec < vpr ? x0 + at : kNoLoad);
-      if (MASK) mq = M::ld16(rm, vec < vpr ? m0 + at : kNoLoad);
-    };
-    // Elements that are not this vector's (or of a vector not below lim) become -inf, once: they then count for
-    // nothing in the maximum and the sum.
-    auto settle = [&](uint32_t i, uint32_t lim, v4i& q) {
-      if (MASK) return;
-      const uint32_t vec = tid + kThreads * i;
+    // Elements that are not the row's become -inf, once: they then count for nothing in the maximum and the sum.
+    auto settle = [&](uint32_t i, v4i& q) {
+      const uint32_t vec = vector(i);
       const bool tail = vec + 1u == vpr;
-      const int lo = (int)(!RAGGED ? 0u : (vec == 0 ? lead : (tail ? back : 0u)));
-      const int hi = i < lim && vec < vpr ? (RAGGED && blocks && tail ? (int)(lead + n - vec * V) : (int)V) : 0;
+      const int lo = tail ? (int)back : 0;
+      const int hi = vec < vpr ? (RAGGED && blocks && tail ? (int)(lead + n - vec * V) : (int)V) : 0;
 #pragma unroll
       for (int e = 0; e < (int)V; ++e) E::put(q, e, e >= lo && e < hi ? E::get(q, e) : -__builtin_inff());
     };
-    // the softmax argument of element e of vector i, -inf where it is not this vector's (or i is not below lim)
-    auto arg = [&](uint32_t i, uint32_t lim, const v4i& q, const v4i& mq, int e) {
-      const uint32_t vec = tid + kThreads * i;
-      float x = E::get(q, e);
-      if (MASK) x = alpha * x + E::get(mq, e);
-      return !MASK || (i < lim && vec < vpr && own(vec, e)) ? x : -__builtin_inff();
-    };
     float m = -__builtin_inff(), sum = 0.0f;
-    auto take = [&](uint32_t i0, uint32_t lim, const v4i (&q)[U], const v4i (&mq)[U]) {
+    auto take = [&](const v4i (&q)[U]) {
       float mb = m;
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u)
 #pragma unroll
-        for (int e = 0; e < (int)V; ++e) mb = __builtin_fmaxf(mb, arg(i0 + u, lim, q[u], mq[u], e));
+        for (int e = 0; e < (int)V; ++e) mb = __builtin_fmaxf(mb, E::get(q[u], e));
       const float ref = mb == -__builtin_inff() ? 0.0f : mb;       // (nothing but -inf so far: relative to 0, every term is 0)
       float part[U];                                   // (added in pairs: a shorter chain, and a smaller error)
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
         float t[V];
 #pragma unroll
-        for (int e = 0; e < (int)V; ++e) t[e] = __expf(arg(i0 + u, lim, q[u], mq[u], e) - ref);
+        for (int e = 0; e < (int)V; ++e) t[e] = __expf(E::get(q[u], e) - ref);
 #pragma unroll
         for (int w = (int)V / 2; w > 0; w /= 2)
 #pragma unroll
           for (int e = 0; e < w; ++e) t[e] += t[e + w];
         part[u] = t[0];
+        __builtin_amdgcn_sched_barrier(0);             // (a vector at a time: interleaved they need more registers than there are)
       }
-      sum = sum * __expf(m - ref) + ((part[0] + part[1]) + (part[2] + part[3]));
+      sum = sum * __expf(m - ref) + ((part[0] + part[1]) + part[2]);
       m = mb;
+      __builtin_amdgcn_sched_barrier(0);
     };
-    v4i keep[NB ? NB : 1][U];
-    const v4i zero = {0, 0, 0, 0};
-    for (uint32_t i0 = 0; i0 < held; i0 += U) {
-      v4i q[U], mq[U];
+    v4i keep[NB][U], q[U];
+    auto fetch_batch = [&](uint32_t i0) {
 #pragma unroll
-      for (uint32_t u = 0; u < U; ++u) { mq[u] = zero; fetch(i0 + u, q[u], mq[u]); }
+      for (uint32_t u = 0; u < U; ++u) q[u] = fetch(i0 + u);
+    };
+    auto take_batch = [&](uint32_t i0) {
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u)
-        if (i0 + u < NL) kept[(i0 + u) * kThreads] = q[u];
+        if (i0 + u < NR + NL) kept[(i0 + u - NR) * kThreads] = q[u];
 #pragma unroll
-      for (uint32_t u = 0; u < U; ++u) settle(i0 + u, held, q[u]);
-      take(i0, held, q, mq);
+      for (uint32_t u = 0; u < U; ++u) { settle(i0 + u, q[u]); __builtin_amdgcn_sched_barrier(0); }
+      take(q);
+    };
+    // The first batch of those that do not stay in registers, then all that do, are requested in one go; the second of the
+    // former while the latter are looked at.
+    fetch_batch(NR);
+#pragma unroll
+    for (uint32_t i = 0; i < NR; ++i) keep[i / U][i % U] = M::ld16(rx, mine, i * kStep);
+    take_batch(NR);
+    if (T > NR + U) fetch_batch(NR + U);
+    if (RAGGED) {                                      // (the first lane's first vector begins before the row)
+#pragma unroll
+      for (uint32_t e = 0; e < V; ++e) E::put(keep[0][0], (int)e, tid != 0 || e >= lead ? E::get(keep[0][0], (int)e) : -__builtin_inff());
     }
-    v4i none[U];
-#pragma unroll
-    for (uint32_t u = 0; u < U; ++u) none[u] = zero;
-#pragma unroll
-    for (uint32_t c = 0; c < NB; ++c)
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u) fetch(held + c * U + u, keep[c][u], none[u]);
 #pragma unroll
     for (uint32_t c = 0; c < NB; ++c) {
+      take(keep[c]);
 #pragma unroll
-      for (uint32_t u = 0; u < U; ++u) settle(held + c * U + u, T, keep[c][u]);
-      take(held + c * U, T, keep[c], none);
+      for (uint32_t u = 0; u < U; ++u) asm volatile("" : "+v"(keep[c][u]));      // (its fp32 values are not kept, they are made again)
     }
+    for (uint32_t i0 = NR + U; i0 < T; i0 += U) {
+      if (i0 != NR + U) fetch_batch(i0);
+      take_batch(i0);
+    }
+    if (T > NR + NL) fetch_batch(NR + NL);             // (what is read again: ahead of the row's stores, which later loads wait for)
     const float M_ = wg.max(m);
     const float inv = 1.0f / wg.sum(sum * __expf(m - M_));
-    auto put = [&](uint32_t i, const v4i& q, const v4i& mq) {
-      const uint32_t vec = tid + kThreads * i;
+    auto result = [&](const v4i& x) {
       v4i oq;
 #pragma unroll
-      for (int e = 0; e < (int)V; ++e) {
-        float x = E::get(q, e);
-        if (MASK) x = alpha * x + E::get(mq, e);
-        E::put(oq, e, __expf(x - M_) * inv);
-      }
-      const bool act = i < T && vec < vpr;
-      const uint32_t off = x0 + at_of(vec);
+      for (int e = 0; e < (int)V; ++e) E::put(oq, e, __expf(E::get(x, e) - M_) * inv);
+      return oq;
+    };
+    auto put = [&](uint32_t i, const v4i& x) {         // vector 0, and those past NR
+      const uint32_t vec = vector(i);
+      const v4i oq = result(x);
+      const bool act = vec < vpr;
+      const uint32_t off = i == 0 ? mine : at_of(vec);
       // (partly owned: the last vector where it is shifted or ends the row in a block, the first where the row begins in one)
       const bool part = RAGGED && ((vec == 0 && lead != 0) || (vec == vpr - 1 && (vpr * V != lead + n)));
       M::st16(ro, act && !part ? off : kNoLoad, oq);
       if (RAGGED && act && part) {
 #pragma unroll
-        for (int e = 0; e < (int)V; ++e)
-          if (own(vec, e)) {
+        for (int e = 0; e < (int)V; ++e) {
+          const uint32_t at = vec * V + e;             // (counted from the first vector's first element)
+          if (blocks ? at - lead < n : (uint32_t)e >= back) {
             if (E::ES == 4) M::stb4(ro, off + e * 4u, (uint32_t)oq[e & 3]);
             else M::stb2(ro, off + e * 2u, (uint32_t)oq[e / 2] >> ((e & 1) * 16));
           }
+        }
       }
     };
+    if (RAGGED) put(0, keep[0][0]);
+    else M::st16(ro, mine, result(keep[0][0]));
 #pragma unroll
-    for (uint32_t c = 0; c < NB; ++c)
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u) put(held + c * U + u, keep[c][u], zero);
-    for (uint32_t i = 0; i < NL && i < held; ++i) put(i, kept[i * kThreads], zero);
-    for (uint32_t i0 = NL; i0 < held; i0 += U) {
-      v4i q[U], mq[U];
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u) { mq[u] = zero; fetch(i0 + u, q[u], mq[u]); }
+    for (uint32_t i = 1; i < NR; ++i) {
+      M::st16(ro, x0 + vector(i) * 16u, result(keep[i / U][i % U]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    for (uint32_t i = NR; i < NR + NL && i < T; ++i) put(i, kept[(i - NR) * kThreads]);
+    for (uint32_t i0 = NR + NL; i0 < T; i0 += U) {
+      if (i0 != NR + NL) fetch_batch(i0);
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u)
-        if (i0 + u < held) put(i0 + u, q[u], mq[u]);
+        if (i0 + u < T) put(i0 + u, q[u]);
     }
   }
   __syncthreads();                                     // the LDS belongs to the next chunk after this
+}
+
+// Masked softmax rows too long for the workgroup's registers: two passes over row and mask, nothing kept between them.
+template <int POL, int DT, bool RAGGED>
+DEV void masked_softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
+  using E = Elem<DT>;
+  using M = Mem<POL>;
+  constexpr uint32_t V = E::V, U = 4;
+  const uint32_t n = uni(r->red_n);
+  const RowCut<V, RAGGED> cut(n);
+  const uint32_t vpr = cut.vpr;
+  const float alpha = r->alpha;
+  const uint32_t chunk_bytes = (row_end - row_begin) * n * E::ES;
+  const uint64_t chunk_off = (uint64_t)row_begin * n * E::ES;
+  const rsrc_t rx = make_rsrc(uni_ptr(r->ptr[0]) + chunk_off, chunk_bytes);
+  const rsrc_t ro = make_rsrc(uni_ptr(r->ptr[3]) + chunk_off, chunk_bytes);
+  rsrc_t rm = rx;
+  uint32_t period = 0;
+  if (uni(r->okind[1]) == K_FULL) rm = make_rsrc(uni_ptr(r->ptr[1]) + chunk_off, chunk_bytes);
+  else { period = uni(r->stride[1][0]); rm = make_rsrc(uni_ptr(r->ptr[1]), period * n * E::ES); }
+  WgReduce wg = {s_v, 0, tid};
+  for (uint32_t row = row_begin; row < row_end; ++row) {
+    const uint32_t x0 = (row - row_begin) * n * E::ES, m0 = (period ? row % period : row - row_begin) * n * E::ES;
+    v4i q[U], mq[U];
+    auto fetch_batch = [&](uint32_t v0) {
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t vec = v0 + u * kThreads, at = cut.begin(vec) * E::ES;
+        q[u] = M::ld16(rx, vec < vpr ? x0 + at : kNoLoad);
+        mq[u] = M::ld16(rm, vec < vpr ? m0 + at : kNoLoad);
+      }
+    };
+    float m = -__builtin_inff(), sum = 0.0f;
+    for (uint32_t v0 = tid; v0 < vpr + tid; v0 += U * kThreads) {          // (whole rounds: every lane, the last ones with nothing)
+      fetch_batch(v0);
+      float x[U][V], mb = m;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < (int)V; ++e) {
+          const uint32_t vec = v0 + u * kThreads;
+          const float a = alpha * E::get(q[u], e) + E::get(mq[u], e);
+          x[u][e] = vec < vpr && (!RAGGED || e >= cut.first(vec)) ? a : -__builtin_inff();
+          mb = __builtin_fmaxf(mb, x[u][e]);
+        }
+      const float ref = mb == -__builtin_inff() ? 0.0f : mb;       // (nothing but -inf so far: relative to 0, every term is 0)
+      float part[U];                                   // (added in pairs: a shorter chain, and a smaller error)
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+#pragma unroll
+        for (int e = 0; e < (int)V; ++e) x[u][e] = __expf(x[u][e] - ref);
+#pragma unroll
+        for (int w = (int)V / 2; w > 0; w /= 2)
+#pragma unroll
+          for (int e = 0; e < w; ++e) x[u][e] += x[u][e + w];
+        part[u] = x[u][0];
+      }
+      sum = sum * __expf(m - ref) + ((part[0] + part[1]) + (part[2] + part[3]));
+      m = mb;
+    }
+    const float M_ = wg.max(m);
+    const float inv = 1.0f / wg.sum(sum * __expf(m - M_));
+    for (uint32_t v0 = tid; v0 < vpr + tid; v0 += U * kThreads) {
+      fetch_batch(v0);
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t vec = v0 + u * kThreads;
+        v4i oq;
+#pragma unroll
+        for (int e = 0; e < (int)V; ++e) E::put(oq, e, __expf(alpha * E::get(q[u], e) + E::get(mq[u], e) - M_) * inv);
+        row_store<POL, DT, RAGGED>(ro, x0 + cut.begin(vec) * E::ES, oq, vec < vpr, cut.first(vec));
+      }
+    }
+  }
+  __syncthreads();                                     // the LDS slots belong to the next chunk after this
 }
 
 // Layer norm rows too long for the workgroup's registers: three passes of vector loads over the row.
@@ -2543,6 +2617,17 @@ DEV void rowop_mid(const Record* r, uint32_t begin, uint32_t end, float* s, uint
   if (vpr <= 512u) rowop_wg<POL, ROP, DT, 2, P32, RAGGED>(r, begin, end, s, tid);
   else rowop_wg<POL, ROP, DT, 4, P32, RAGGED>(r, begin, end, s, tid);
 }
+// How many batches stay in registers: the most that every row of the length has whole, while LDS and they hold the row, or four
+// and five.
+template <int POL, int DT, bool RAGGED>
+DEV void softmax_held_rows(const Record* r, uint32_t begin, uint32_t end, float* s, uint32_t tid) {      // rows of over 4,096 vectors, 2,048 of 16-bit elements
+  constexpr uint32_t kMore = (DT == GPUOS_F32 ? 21u : 15u) * kThreads;
+  constexpr int FEW = DT == GPUOS_F32 ? 5 : 2, MORE = DT == GPUOS_F32 ? 6 : 5;
+  static_assert(FEW * 3 <= (DT == GPUOS_F32 ? 16 : 8) && MORE * 3u * kThreads <= kMore, "the rows are longer than what they keep");
+  const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
+  if (vpr <= kMore) softmax_held<POL, DT, FEW, RAGGED>(r, begin, end, s, tid);
+  else softmax_held<POL, DT, MORE, RAGGED>(r, begin, end, s, tid);
+}
 template <int POL, int ROP, int DT, bool P32, bool RAGGED>
 DEV void rowop_long(const Record* r, uint32_t begin, uint32_t end, float* s, uint32_t tid) {
   const uint32_t vpr = (uni(r->red_n) + Elem<DT>::V - 1) / Elem<DT>::V;
@@ -2553,7 +2638,8 @@ DEV void rowop_long(const Record* r, uint32_t begin, uint32_t end, float* s, uin
   if constexpr (!MASK && DT == GPUOS_F32) {
     if (vpr <= 4096u) return rowop_wg<POL, ROP, DT, 16, P32, RAGGED>(r, begin, end, s, tid);
   }
-  if constexpr (RowOp<ROP>::SOFTMAX) softmax_long<POL, ROP, DT, RAGGED>(r, begin, end, s, tid);
+  if constexpr (MASK) masked_softmax_long<POL, DT, RAGGED>(r, begin, end, s, tid);
+  else if constexpr (RowOp<ROP>::SOFTMAX) { if constexpr (POL == POL_PLAIN) softmax_held_rows<POL, DT, RAGGED>(r, begin, end, s, tid); }      // (the worker: exec_away)
   else layernorm_long<POL, DT, P32, RAGGED>(r, begin, end, s, tid);
 }
 enum { kRowShort, kRowMid, kRowLong };
@@ -2624,6 +2710,11 @@ static_assert(__builtin_offsetof(Record, path) == 2 && __builtin_offsetof(Record
 DEV bool rowop_is_other(const RecHead& h) {
   const uint32_t path = h.path();
   return path == PATH_ROW_RAGGED || (path == PATH_ROW_FUSED && h.red_n() > (h.dtype_out() == GPUOS_F32 ? 4096u : 8192u));
+}
+// ... and those of them that the worker runs by exec_away: softmax rows that do not fit the registers
+DEV bool rowop_is_away(const RecHead& h, uint32_t impl) {
+  const uint32_t path = h.path();
+  return impl == GPUOS_IMPL_SOFTMAX_LAST && (path == PATH_ROW_RAGGED || path == PATH_ROW_FUSED) && h.red_n() > 16384u;
 }
 template <int POL, int ROP>
 DEV void run_rowop(const Record* r, const RecHead& h, uint32_t chunk, float* s_red, uint32_t tid) {
@@ -3278,6 +3369,28 @@ __attribute__((not_tail_called, disable_tail_calls)) PATHFN void exec_run(WorkSh
   __syncthreads();                                       // the descriptors and the scratch may be overwritten after this
 }
 
+// What the worker runs away from its choice of executors: one that would use most of the registers that a function keeps for
+// its caller, and keeps none (it is called and never jumped to, and the compiler sees every call).  Kept, they were 63 KiB written and
+// read back for a row of 125 KiB.  All it goes by lies in LDS: what is live where the choice below is
+// made goes through scratch memory, a trip to memory under load for each level of choices.
+template <int DT, bool RAGGED>
+__attribute__((not_tail_called)) PATHFN void softmax_away(WorkShared* s_v, uint32_t tid) {
+  WorkShared* s = lds_arg(s_v);
+  const v4i dec = *(const v4i*)s->dec;
+  const Record* r = &s->rec[(uni((uint32_t)dec[0]) >> 8) & 0xffu];
+  const uint32_t per = uni(r->chunk), rows = uni(r->numel), begin = (uni((uint32_t)dec[2]) & 0x3ffu) * per;
+  softmax_held_rows<POL_COHERENT, DT, RAGGED>(r, begin, rows - begin < per ? rows : begin + per, s->red, tid);
+}
+__attribute__((not_tail_called)) PATHFN void exec_away(WorkShared* s_v, uint32_t wave_v) {
+  WorkShared* s = lds_arg(s_v);
+  const uint32_t wave = uni(wave_v);
+  const Record* r = &s->rec[(uni(s->dec[0]) >> 8) & 0xffu];
+  const uint32_t k = 2u * uni(r->dtype[3]) + (uni(r->path) == PATH_ROW_RAGGED ? 1u : 0u);
+  if (k < 2u) { if (k == 0) softmax_away<GPUOS_F32, false>(s, thread_index(wave)); else softmax_away<GPUOS_F32, true>(s, thread_index(wave)); }
+  else if (k < 4u) { if (k == 2) softmax_away<GPUOS_F16, false>(s, thread_index(wave)); else softmax_away<GPUOS_F16, true>(s, thread_index(wave)); }
+  else { if (k == 4) softmax_away<GPUOS_BF16, false>(s, thread_index(wave)); else softmax_away<GPUOS_BF16, true>(s, thread_index(wave)); }
+}
+
 // RING 0: the library's own workers, on the main unit ring, executing through EXEC = the built-in
 // chunk executor.  RING 1: the workers of a kernel compiled at run time, on the second unit ring
 // (the dispatcher routes the tasks of natively compiled operator programs there), executing through
@@ -3624,7 +3737,8 @@ DEV void run_worker(WorkShared* s, uint32_t gen = 0) {
       continue;
     }
     int32_t status = u.status;
-    if (status == GPUOS_OK) status = EXEC::run(&s->rec[u.f], u.head, u.impl, u.chunk, s->red, a.progs, thread_index(wave));
+    if (RING == 0 && __builtin_expect(status == GPUOS_OK && rowop_is_away(u.head, u.impl), 0)) exec_away(s, wave);
+    else if (status == GPUOS_OK) status = EXEC::run(&s->rec[u.f], u.head, u.impl, u.chunk, s->red, a.progs, thread_index(wave));
     complete_unit<RING>(a, s, status, thread_index(wave));
   }
 }

@@ -582,27 +582,24 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   const bool rows_contig = rows == 1 || (nd == 1 && oo[0].stride[0] == n && oo[1].stride[0] == 1);
   // (a row fits one buffer resource; rows are read as aligned vectors whatever n and the base's alignment are)
   rec.path = (s_last == 1 && rows_contig && n * 4 < kMaxExtent) ? PATH_RED_CONTIG : PATH_RED_GENERIC;
-  // A reduction writes almost nothing and its rows are a chain of memory latencies (load a few rows,
-  // combine, next), which grow to 10-20 us while the GPU streams: a small task is cut into chunks of
-  // one or two rounds of its workgroup (16 KiB), up to 64 of them, before chunks grow to the regular
-  // size.  (Chunks of twice the elementwise traffic whatever the task's size: a 0.2 MB reduction
-  // in a bandwidth-bound stream was two chunks of 7 rounds each and took 110 us.  Forty streaming
-  // operations of 0.1-220 MB, half of them reductions: 152 us a pass before, 130 now.  64 and not
-  // fewer: in 32, 16 and 8 pieces those take 140, 141 and 151 us, 24 integer operations 77, 103 and 104
-  // instead of 61.  What it costs is throughput where the queue is never empty: a stream of 20,000
-  // such operations takes 53.9 ms instead of 52.9, 53.2 in 32 pieces.)
+  // A reduction writes almost nothing and its rows are a chain of memory latencies, which grow to 10-20 us while the GPU
+  // streams: a task is cut into chunks of 32 KiB, up to 128 of them, before chunks grow to the regular size.  (Chunks of twice
+  // the elementwise traffic whatever the task's size: a 0.2 MB reduction in a bandwidth-bound stream was two chunks and
+  // took 110 us.  Forty streaming operations of 0.1-220 MB, half of them reductions, in up to 64 pieces of 16 KiB at least,
+  // 64 of 32 KiB and 128 of 32 KiB: 109.5, 108.6 and 107.7 us; 24 integer operations 54.0, 53.9 and 51.1.  Smaller pieces are bound by
+  // their claims, 12 ns each one after the other whoever makes them: 143 sums of 512K bf16 elements 143 us in pieces of 16 KiB, 105 so.)
   // But a link of a chain of at most four regular chunks is cut into (up to) four, like an elementwise
   // one: up to those a dependent task is published at once and waits in its workgroups, beyond them
   // the dispatcher holds it back until what it waits for is done.
   const uint64_t row_bytes = (uint64_t)n * dtype_size(ops[0].dtype), total = row_bytes * (uint64_t)rows;
-  const uint64_t most = (uint64_t)chunk_elems * 24, spread = total / 64;
-  uint64_t rpc = (spread < 16384 ? 16384 : (spread < most ? spread : most)) / row_bytes;
+  const uint64_t most = (uint64_t)chunk_elems * 24, spread = total / 128;
+  uint64_t rpc = (spread < 32768 ? 32768 : (spread < most ? spread : most)) / row_bytes;
   if (chained && total <= kSmallTaskChunks * most) {
     const uint64_t quarter = ((uint64_t)rows + kSmallTaskChunks - 1) / kSmallTaskChunks;
     if (rpc < quarter) rpc = quarter;
   }
   if (rpc < 1) rpc = 1;
-  if (rpc >= 16) rpc = (rpc + 15) / 16 * 16;          // whole passes of the row-per-wave kernels
+  if (rpc >= 4) rpc = rpc / 4 * 4;                    // the same share of rows for each wavefront
   const uint64_t min_rpc = ((uint64_t)rows + kMaxChunksPerTask - 1) / kMaxChunksPerTask;
   if (rpc < min_rpc) rpc = min_rpc;
   rec.chunk = (uint32_t)rpc;

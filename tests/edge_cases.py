@@ -132,6 +132,28 @@ def row_operation_edges(code):
     return b.stream("row_operation_edges_%d" % code)
 
 
+def long_softmax_rows(code):
+    """Softmax rows of which a workgroup keeps a part in registers and in LDS: either side of every length at
+    which it keeps more, fits no more or reads another batch again, at every alignment of rows cut at blocks of memory (x
+    and the result at one offset) and at none; infinities at a row's ends."""
+    rng = np.random.default_rng(730 + code)
+    b = Builder()
+    V = 4 if code == S.F32 else 8
+    dt = np_dtype(code)
+    lengths = [16 * 256, 21 * 256, 22 * 256, 24 * 256, 27 * 256] if code == S.F32 else [8 * 256, 12 * 256, 14 * 256, 15 * 256, 21 * 256, 24 * 256]
+    for i, (vectors, more) in enumerate((v, m) for v in lengths for m in (-1, 0, 1, 2 * V + 3)):
+        n = vectors * V + more
+        if n <= 16384:
+            continue
+        x_at, o_at = ((0, 0), (1, 1), (V - 1, V - 1), (0, 1))[i % 4]
+        x = b.pool(values(rng, 3 * n + x_at, code, 3.0))[x_at:].reshape(3, n)
+        if code != S.BF16:
+            x[1, 0] = x[1, -1] = -np.inf
+            x[2, : n // 2] = -np.inf
+        b.add("SOFTMAX_LAST", b.pool(np.zeros(3 * n + o_at, dt))[o_at:].reshape(3, n), [x])
+    return b.stream("long_softmax_rows_%d" % code)
+
+
 def large_gathers():
     """Gathered tasks of more elements than 1,024 of the gather path's regular chunks hold: a product
     with every other column of a matrix, and a stride-2 slice of 16-bit elements.  (A chunk never run

@@ -72,6 +72,12 @@ def test_row_operations_at_their_edges(code):
     print(stats, flush=True)
 
 
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_softmax_rows_kept_in_part(code):
+    stats, _ = _run_and_check(E.long_softmax_rows(code))
+    print(stats, flush=True)
+
+
 def test_gathers_larger_than_1024_regular_chunks():
     stats, _ = _run_and_check(E.large_gathers())
     print(stats, flush=True)
