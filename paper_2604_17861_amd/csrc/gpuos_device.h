@@ -63,6 +63,10 @@ template <int POL> struct Mem {
     const v2i q = {(int)w0, (int)w1};
     __builtin_amdgcn_raw_buffer_store_b64(q, r, (int)off, 0, AUX);
   }
+  static DEV v4i ld8(rsrc_t r, uint32_t off) {
+    const auto q = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, AUX);
+    return v4i{(int)q[0], (int)q[1], 0, 0};
+  }
   static DEV void stb4(rsrc_t r, uint32_t off, uint32_t w) { __builtin_amdgcn_raw_buffer_store_b32(w, r, (int)off, 0, AUX); }
   static DEV void stb2(rsrc_t r, uint32_t off, uint32_t h) { __builtin_amdgcn_raw_buffer_store_b16((uint16_t)h, r, (int)off, 0, AUX); }
   static DEV uint32_t ldb2(rsrc_t r, uint32_t off) { return (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, AUX); }
@@ -1147,6 +1151,88 @@ PATHFN void ew_staged(const Record* r_v, uint32_t begin_v, uint32_t end_v, float
   }
 }
 
+// PATH_STAGED under RF_PAIRS: contiguous output, inputs of its dtype that are contiguous or every second element of a buffer.  Both
+// halves of each pair are read and one is dropped: no LDS, no rounds, nothing to wait for but memory.  A lane makes 8 bytes of the output
+// from 16 of such an input, so that every access of a wavefront is one run of memory, and computes two of them together.  (Gathered through LDS the rounds are latencies in a row: products of 400 x 579 fp32 with every other column took 61 us
+// for 147 MB, 1,238 x 2,359 bf16 93 us for 140 MB; 52 and 55 so.)  The tensor's last vector goes element by element: behind
+// its last element may be nothing to read.
+template <int POL, class OPER, int DT>
+PATHFN void ew_pairs(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
+  const Record* r = lds_arg(r_v);
+  const uint32_t begin = uni(begin_v), end = uni(end_v);
+  using E = Elem<DT>;
+  using M = Mem<POL>;
+  constexpr uint32_t V = E::V;
+  constexpr int N = OPER::N, U = N > 2 ? 2 : 4;
+  const uint32_t n = uni(r->size[2]), impl = uni(r->impl);
+  const float alpha = __builtin_bit_cast(float, uni(__builtin_bit_cast(uint32_t, r->alpha)));
+  uint32_t nvec = (end - begin) / V;
+  if (end == n && nvec * V == end - begin) --nvec;
+  const char* p[3];
+  rsrc_t rs[3];
+  uint32_t step[3];                                      // 1 or 2
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int kk = k < N ? k : 0;
+    step[k] = uni(r->stride[kk][2]);
+    p[k] = uni_ptr(r->ptr[kk]) + (uint64_t)begin * step[k] * E::ES;
+    rs[k] = make_rsrc(p[k], (end < n ? (end - begin) * step[k] : (end - begin - 1u) * step[k] + 1u) * E::ES);
+  }
+  char* const po = (char*)uni_ptr(r->ptr[3]) + (uint64_t)begin * E::ES;
+  const rsrc_t ro = make_rsrc(po, (end - begin) * E::ES);
+  const uint32_t units = 2u * nvec;
+  for (uint32_t v = tid; v - tid < units; v += 2 * U * kThreads) {
+    v4i q[3][U], h[3][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t a = v + 2 * u * kThreads, b = a + kThreads;
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        if (step[k] == 2u) {
+          q[k][u] = M::ld16(rs[k], a < units ? a * 16u : kNoLoad);
+          h[k][u] = M::ld16(rs[k], b < units ? b * 16u : kNoLoad);
+        } else {
+          q[k][u] = M::ld8(rs[k], a < units ? a * 8u : kNoLoad);
+          h[k][u] = M::ld8(rs[k], b < units ? b * 8u : kNoLoad);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const v4i a = q[k < N ? k : 0][u], b = h[k < N ? k : 0][u];
+        if (k >= N) { q[k][u] = a; continue; }
+        v4i c;
+        if (E::ES == 4) c = v4i{a[0], a[2], b[0], b[2]};
+        else {                                           // the low halves of two words
+          c[0] = (int)__builtin_amdgcn_perm((uint32_t)a[1], (uint32_t)a[0], 0x05040100u);
+          c[1] = (int)__builtin_amdgcn_perm((uint32_t)a[3], (uint32_t)a[2], 0x05040100u);
+          c[2] = (int)__builtin_amdgcn_perm((uint32_t)b[1], (uint32_t)b[0], 0x05040100u);
+          c[3] = (int)__builtin_amdgcn_perm((uint32_t)b[3], (uint32_t)b[2], 0x05040100u);
+        }
+#pragma unroll
+        for (int w = 0; w < 4; ++w) q[k][u][w] = step[k] == 2u ? c[w] : (w < 2 ? a[w] : b[w - 2]);
+      }
+    typedef VecArg<DT, U> Arg;
+    OPER::template vectors<DT, U>(impl, Arg{q[0]}, Arg{q[1]}, Arg{q[2]}, alpha, [&](int u, const v4i& o) {
+      const uint32_t a = v + 2 * u * kThreads, b = a + kThreads;
+      M::st8(ro, a < units ? a * 8u : kNoLoad, (uint32_t)o[0], (uint32_t)o[1]);
+      M::st8(ro, b < units ? b * 8u : kNoLoad, (uint32_t)o[2], (uint32_t)o[3]);
+    });
+  }
+  for (uint32_t i = nvec * V + tid; i < end - begin; i += kThreads) {      // one element each, in the lowest place of a vector
+    v4i q[3][1];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) q[k][0] = v4i{(int)(E::ES == 4 ? M::ld4(p[k < N ? k : 0], i * step[k]) : M::ld2(p[k < N ? k : 0], i * step[k])), 0, 0, 0};
+    typedef VecArg<DT, 1> Arg;
+    OPER::template vectors<DT, 1>(impl, Arg{q[0]}, Arg{q[1]}, Arg{q[2]}, alpha, [&](int, const v4i& o) {
+      if (E::ES == 4) M::st4(po, i, (uint32_t)o[0]);
+      else M::st2(po, i, (uint32_t)o[0]);
+    });
+  }
+}
+
 // ---------------------------------------------------------------------------
 // PATH_GENERIC: row-major index decomposition over <= 6 coalesced dims, per
 // operand strides (0 on broadcast dims), per operand dtype.
@@ -1219,7 +1305,12 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
   using EI = Elem<DTI>;
   using EO = Elem<DTO>;
   using M = Mem<POL>;
-  constexpr int V = EI::V > EO::V ? EI::V : EO::V, NI = V / EI::V, NO = V / EO::V;
+  constexpr int V = EI::V > EO::V ? EI::V : EO::V;
+  // A cast that widens gives each vector of eight elements to two lanes, four elements each, so that a wavefront's store is
+  // one run of memory.  (One lane for both halves leaves every other 16 bytes to the next store, and memory takes each
+  // for itself: 24M elements from bf16 to fp32 took 98 us, 45 so.)
+  constexpr int LN = EI::ES < EO::ES ? 2 : 1, VL = V / LN, NI = LN == 2 ? 1 : V / EI::V, NO = VL / EO::V;
+  constexpr uint32_t kStep = kThreads / LN;
   constexpr int N = OPER::N;
   constexpr int U = 4;
   const uint32_t A = uni(r->size[0]), B = uni(r->size[1]), R = uni(r->size[2]), C = uni(r->size[3]);
@@ -1251,9 +1342,10 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
   const uint32_t impl = uni(r->impl);
   // (row, vector) of this lane's first unit by division, then steps of 256 units with carries
   const bool deep = A * B > 1;
-  uint32_t v = begin + tid;
+  const uint32_t ti = tid / LN, half = LN == 2 ? (tid & 1u) * VL : 0u;
+  uint32_t v = begin + ti;
   uint32_t row = v / VR, vc = v - row * VR, b = 0, a = 0;
-  const uint32_t s_rows = kThreads / VR, s_vc = kThreads - s_rows * VR;
+  const uint32_t s_rows = kStep / VR, s_vc = kStep - s_rows * VR;
   uint32_t s_r = s_rows, s_b = 0, s_a = 0;
   if (deep) {
     const uint32_t t = row / R;
@@ -1265,15 +1357,15 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
     s_a = ts / B;
     s_b = ts - s_a * B;
   }
-  for (; v - tid < end; ) {
+  for (; v - ti < end; ) {
     v4i q[3][U][NI];
     uint32_t w[3][U], oo[U];
     bool last[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool act = v + u * kThreads < end;
+      const bool act = v + u * kStep < end;
       last[u] = tail != 0 && vc == VR - 1;
-      const uint32_t col = last[u] ? C - V : vc * V;
+      const uint32_t col = (last[u] ? C - V : vc * V) + half;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         if (k < N || k == 3) {
@@ -1285,7 +1377,7 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
             // moves nothing: no branch between the loads of a round)
             const uint32_t of = act && !(SCALARS && scalar[k]) ? o + col * EI::ES : kNoLoad;
 #pragma unroll
-            for (int i = 0; i < NI; ++i) q[k][u][i] = M::ld16(rs[k], of + i * 16u);
+            for (int i = 0; i < NI; ++i) q[k][u][i] = LN == 2 ? M::ld8(rs[k], of) : M::ld16(rs[k], of + i * 16u);
             if (SCALARS) w[k][u] = M::ldb4(rs[k], act && scalar[k] ? (lead[k] + o) & ~3u : kNoLoad) >> (((lead[k] + o) & 2u) * 8u);
           }
         }
@@ -1301,13 +1393,13 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
       }
     }
     auto sink = [&](int u, const v4i (&qo)[NO]) {
-      const bool act = v + u * kThreads < end;
+      const bool act = v + u * kStep < end;
 #pragma unroll
       for (int i = 0; i < NO; ++i) M::st16(rs[3], act && !last[u] ? oo[u] + i * 16u : kNoLoad, qo[i]);
       if (tail != 0 && act && last[u]) {
 #pragma unroll
-        for (int e = 1; e < V; ++e)
-          if ((uint32_t)e >= V - tail) {
+        for (int e = LN == 2 ? 0 : 1; e < VL; ++e)
+          if (half + (uint32_t)e >= V - tail) {
             if (EO::ES == 4) M::stb4(rs[3], oo[u] + e * 4u, (uint32_t)qo[e / EO::V][e % EO::V]);
             else M::stb2(rs[3], oo[u] + e * 2u, (uint32_t)qo[e / EO::V][(e % EO::V) / 2] >> ((e & 1) * 16));
           }
@@ -1318,7 +1410,7 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
       for (int u = 0; u < U; ++u) {
         v4i qo[NO];
 #pragma unroll
-        for (int e = 0; e < V; ++e) EO::put(qo[e / EO::V], e % EO::V, EI::get(q[0][u][e / EI::V], e % EI::V));
+        for (int e = 0; e < VL; ++e) EO::put(qo[e / EO::V], e % EO::V, EI::get(q[0][u][e / EI::V], e % EI::V));
         sink(u, qo);
       }
     } else {
@@ -1346,7 +1438,7 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
         OPER::template vectors<DTI, U>(impl, Arg{qv[0]}, Arg{qv[1]}, Arg{qv[2]}, alpha, sink1);
       }
     }
-    v += U * kThreads;
+    v += U * kStep;
   }
 }
 
@@ -2746,7 +2838,7 @@ DEV void run_rowop(const Record* r, const RecHead& h, uint32_t chunk, float* s_r
 // The executors of PATH_ROWS: by arity without (groups of three: fp32, fp16, bf16) and with per-row
 // scalars, the operators of many instructions, casts, I32.
 enum : uint32_t { kClsUnary = 0, kClsBinary = 1, kClsTernary = 2, kClsErf = 3, kClsTanh = 4, kClsNone = 15 };
-constexpr int kRowsScalar = 15, kRowsCast = 21, kRowsInt = 27, kRowsCount = 30;
+constexpr int kRowsScalar = 15, kRowsCast = 21, kRowsInt = 27, kRowsPairs = 30, kRowsCount = 31;      // (pairs: PATH_STAGED under RF_PAIRS)
 template <int CLS> struct OperOf;
 template <> struct OperOf<kClsUnary> { typedef ByArity<1> T; };
 template <> struct OperOf<kClsBinary> { typedef ByArity<2> T; };
@@ -2754,6 +2846,17 @@ template <> struct OperOf<kClsTernary> { typedef ByArity<3> T; };
 template <> struct OperOf<kClsErf> { typedef FixedOp<GPUOS_IMPL_GELU_ERF> T; };
 template <> struct OperOf<kClsTanh> { typedef FixedOp<GPUOS_IMPL_GELU_TANH> T; };
 static_assert(GPUOS_F32 == 0 && GPUOS_F16 == 1 && GPUOS_BF16 == 2, "the float dtypes count the members of a group");
+// class by implementation, a nibble each: ADD SUB MUL DIV binary, RELU EXP unary, both GELUs, SCALE unary, FMA, SUB_EXP binary, COPY unary
+DEV uint32_t op_class(uint32_t impl) { return impl < 16u ? (uint32_t)(0xfff012043001111full >> (4u * impl)) & 15u : (uint32_t)kClsNone; }
+// The executors of pairs (RF_PAIRS), behind one call that ends in jumps.
+template <int POL> struct PairsExec {
+  template <int K> static DEV void run(const Record* r, uint32_t begin, uint32_t end, uint32_t tid) { ew_pairs<POL, typename OperOf<K / 3>::T, K % 3>(r, begin, end, tid); }
+};
+template <int POL>
+PATHFN void run_pairs(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_t tid) {
+  const Record* r = lds_arg(r_v);
+  pick<0, 15, PairsExec<POL>>(op_class(uni(r->impl)) * 3u + uni(r->dtype[3]), r, uni(begin_v), uni(end_v), tid);
+}
 template <int POL> struct RowsExec {
   template <int K> static DEV void run(const Record* r, uint32_t begin, uint32_t end, uint32_t tid) {
     if constexpr (K < kRowsScalar) ew_rows<POL, typename OperOf<K / 3>::T, K % 3, K % 3, false>(r, begin, end, tid);
@@ -2763,15 +2866,15 @@ template <int POL> struct RowsExec {
       constexpr int FROM = (K - kRowsCast) / 2, TO = (K - kRowsCast) % 2 + ((K - kRowsCast) % 2 >= FROM ? 1 : 0);
       ew_rows<POL, ByArity<1>, FROM, TO, false>(r, begin, end, tid);
     }
-    else if constexpr (K < kRowsCount - 1) ew_rows<POL, ByArity<K - kRowsInt + 1>, GPUOS_I32, GPUOS_I32, false>(r, begin, end, tid);
-    else ew_rows<POL, ByArity<2>, GPUOS_I32, GPUOS_I32, true>(r, begin, end, tid);
+    else if constexpr (K < kRowsPairs - 1) ew_rows<POL, ByArity<K - kRowsInt + 1>, GPUOS_I32, GPUOS_I32, false>(r, begin, end, tid);
+    else if constexpr (K < kRowsPairs) ew_rows<POL, ByArity<2>, GPUOS_I32, GPUOS_I32, true>(r, begin, end, tid);
+    else run_pairs<POL>(r, begin, end, tid);
   }
 };
 
 // the executor of a PATH_ROWS task, kRowsCount if it has none
 DEV uint32_t rows_variant(const Record* r, uint32_t impl) {
-  // class by implementation, a nibble each: ADD SUB MUL DIV binary, RELU EXP unary, both GELUs, SCALE unary, FMA, SUB_EXP binary, COPY unary
-  const uint32_t cls = impl < 16u ? (uint32_t)(0xfff012043001111full >> (4u * impl)) & 15u : (uint32_t)kClsNone;
+  const uint32_t cls = op_class(impl);
   const uint32_t dt = uni(r->dtype[3]), dti = uni(r->vdtype);
   const bool scalars = uni((uint32_t)r->okind[0] | (uint32_t)r->okind[1] | (uint32_t)r->okind[2]) != 0;
   if (uni(r->rflags) & RF_INT) {
@@ -2925,7 +3028,7 @@ DEV int32_t exec_chunk(const Record* r, const RecHead& h, uint32_t impl, uint32_
     rowop_other<POL>(r, impl, begin, (rows - begin < per) ? rows : begin + per, s_red, tid);
     return GPUOS_OK;
   }
-  const uint32_t k = h.path() == PATH_ROWS ? rows_variant(r, impl) : (uint32_t)kRowsCount;
+  const uint32_t k = h.path() == PATH_ROWS ? rows_variant(r, impl) : ((h.rflags() & RF_PAIRS) != 0 && op_class(impl) <= kClsTanh ? (uint32_t)kRowsPairs : (uint32_t)kRowsCount);
   if (k < (uint32_t)kRowsCount) {
     const uint32_t per = h.chunk(), numel = h.numel(), begin = chunk * per;
     pick<0, kRowsCount, RowsExec<POL>>(k, r, begin, (numel - begin < per) ? numel : begin + per, tid);

@@ -41,6 +41,7 @@ enum RecFlag : uint8_t {
   RF_VEC = 2,            // 16-byte vector access is safe (alignment and extents checked)
   RF_INT = 4,            // all tensors are I32
   RF_DEPS_RESOLVED = 8,  // set by the dispatcher: published only after the dependencies completed
+  RF_PAIRS = 32,         // PATH_STAGED: one dim, every operand of one dtype, inputs contiguous or every second element
   RF_LINK = 16           // may be run by the workgroup that has just run the same chunk of the ticket right before (see LinkRun)
 };
 
