@@ -32,8 +32,7 @@ namespace gpuos {
 // half of the HBM bandwidth when a thousand workgroups do it.  Instead every
 // access to task data, descriptors and work units made by the persistent
 // kernel carries the system-scope cache policy (sc0 sc1: stores write through
-// to memory, loads do not hit stale lines), plus nt on the 16-byte streaming
-// accesses.  With that, "release" is: wait until this wave's stores are
+// to memory, loads do not hit stale lines).  With that, "release" is: wait until this wave's stores are
 // acknowledged (s_waitcnt), then publish with a relaxed atomic store; "acquire"
 // is: observe the flag with a relaxed atomic load, then read with the same
 // policy.  No L2-wide maintenance happens in the steady state.
@@ -41,7 +40,18 @@ namespace gpuos {
 // 16-byte accesses go through buffer instructions whose resource is rebased to
 // the chunk being processed: the hardware bounds-checks them (out-of-range
 // loads return 0, stores are dropped).  The ordinary one-launch-per-task kernel
-// uses POL_PLAIN (non-temporal, kernel-boundary coherence as for any kernel).
+// uses POL_PLAIN (kernel-boundary coherence as for any kernel).
+//
+// The non-temporal hint (nt) keeps a line out of the memory-side cache (256 MB): what the next operation reads
+// is then in memory, and the parts of a line that two stores write each go there by themselves.  So:
+//   * elementwise operations and reductions store without it, and load with it where a task reads 8 MB or more
+//     (RF_STREAM), so that it leaves what is there in place;
+//   * runs have it on nothing (each link's result is read by no one but may be, their inputs are the chain's);
+//   * row operations store with it and load without: the rows' readers are a matrix product away, and the inputs stay.
+// Measured against nt on every 16-byte access, three sets of buffers in turn / one set over and over: 24 chains of six
+// tasks 155.6 us, 134; masked softmax 38.4 and 32.3 / 37.9 and 32.4; layer norm 41.0 and 36.5; 24 layout changes 57.7 and 57.9 / 57.5 and 49.8
+// (rows of 363 bf16 copied into a wider matrix, 149 MB: 86 and 52); integers 51.5 and 45.6 / 51.4 and 44.3; softmax over 32,003
+// columns 139 and 134 / 139 and 117; forty streaming operations of 503 MB 110.3 and 111.6 / 110 and 95.7.
 // ---------------------------------------------------------------------------
 enum { POL_PLAIN = 0, POL_COHERENT = 1 };
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -51,24 +61,24 @@ DEV rsrc_t make_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
 }
 
-template <int POL> struct Mem {
-  static constexpr int AUX = POL == POL_COHERENT ? 19 : 2;     // sc0|sc1|nt  or  nt
+template <int POL, bool LOADS_NT = false, bool STORES_NT = false> struct Mem {
+  static constexpr int BASE = POL == POL_COHERENT ? 17 : 0, AUX = BASE | (LOADS_NT ? 2 : 0), AUXS = BASE | (STORES_NT ? 2 : 0);     // sc0|sc1, nt
   static DEV v4i ld16(rsrc_t r, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX); }
   static DEV v4i ld16(rsrc_t r, uint32_t off, uint32_t more) { return __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)more, AUX); }      // (`more`: the same in every lane)
   // (No store of the kind: with an offset in a scalar register the compiler lets the next instruction overwrite the stored registers,
   // and on gfx950 a 16-byte store still reads them then: softmax of 16-bit rows wrote pieces of the next vector's arguments.)
-  static DEV void st16(rsrc_t r, uint32_t off, v4i q) { __builtin_amdgcn_raw_buffer_store_b128(q, r, (int)off, 0, AUX); }
+  static DEV void st16(rsrc_t r, uint32_t off, v4i q) { __builtin_amdgcn_raw_buffer_store_b128(q, r, (int)off, 0, AUXS); }
   static DEV void st8(rsrc_t r, uint32_t off, uint32_t w0, uint32_t w1) {
     typedef int v2i __attribute__((ext_vector_type(2)));
     const v2i q = {(int)w0, (int)w1};
-    __builtin_amdgcn_raw_buffer_store_b64(q, r, (int)off, 0, AUX);
+    __builtin_amdgcn_raw_buffer_store_b64(q, r, (int)off, 0, AUXS);
   }
   static DEV v4i ld8(rsrc_t r, uint32_t off) {
     const auto q = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, AUX);
     return v4i{(int)q[0], (int)q[1], 0, 0};
   }
-  static DEV void stb4(rsrc_t r, uint32_t off, uint32_t w) { __builtin_amdgcn_raw_buffer_store_b32(w, r, (int)off, 0, AUX); }
-  static DEV void stb2(rsrc_t r, uint32_t off, uint32_t h) { __builtin_amdgcn_raw_buffer_store_b16((uint16_t)h, r, (int)off, 0, AUX); }
+  static DEV void stb4(rsrc_t r, uint32_t off, uint32_t w) { __builtin_amdgcn_raw_buffer_store_b32(w, r, (int)off, 0, AUXS); }
+  static DEV void stb2(rsrc_t r, uint32_t off, uint32_t h) { __builtin_amdgcn_raw_buffer_store_b16((uint16_t)h, r, (int)off, 0, AUXS); }
   static DEV uint32_t ldb2(rsrc_t r, uint32_t off) { return (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, AUX); }
   static DEV uint32_t ldb4(rsrc_t r, uint32_t off) { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX); }
   static DEV uint32_t ld4(const void* p, uint32_t i) {
@@ -617,17 +627,25 @@ PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint3
     const rsrc_t ra = make_rsrc(pa + boff, bytes), rb = make_rsrc(pb + boff, bytes), rc = make_rsrc(pc + boff, bytes);
     const rsrc_t ro = make_rsrc(po + boff, bytes);
     uint32_t v = tid;
-    for (; U > 1 && v + (U - 1) * kThreads < nvec; v += U * kThreads) {
-      v4i qa[U], qb[U], qc[U];
+    auto batches = [&](auto mem) {
+      using ML = decltype(mem);
+      for (; U > 1 && v + (U - 1) * kThreads < nvec; v += U * kThreads) {
+        v4i qa[U], qb[U], qc[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        qa[u] = M::ld16(ra, (v + u * kThreads) * 16u);
-        qb[u] = N > 1 ? M::ld16(rb, (v + u * kThreads) * 16u) : qa[u];
-        qc[u] = N > 2 ? M::ld16(rc, (v + u * kThreads) * 16u) : qa[u];
+        for (int u = 0; u < U; ++u) {
+          qa[u] = ML::ld16(ra, (v + u * kThreads) * 16u);
+          qb[u] = N > 1 ? ML::ld16(rb, (v + u * kThreads) * 16u) : qa[u];
+          qc[u] = N > 2 ? ML::ld16(rc, (v + u * kThreads) * 16u) : qa[u];
+        }
+        typedef VecArg<DT, U> Arg;
+        ew_vectors<IMPL, DT, U>(Arg{qa}, Arg{qb}, Arg{qc}, alpha, [&](int u, const v4i& q) { M::st16(ro, (v + u * kThreads) * 16u, q); });
       }
-      typedef VecArg<DT, U> Arg;
-      ew_vectors<IMPL, DT, U>(Arg{qa}, Arg{qb}, Arg{qc}, alpha, [&](int u, const v4i& q) { M::st16(ro, (v + u * kThreads) * 16u, q); });
-    }
+    };
+    // (operators of many instructions are bound by those)
+    constexpr bool SHORT = IMPL == GPUOS_IMPL_ADD || IMPL == GPUOS_IMPL_SUB || IMPL == GPUOS_IMPL_MUL || IMPL == GPUOS_IMPL_RELU ||
+                           IMPL == GPUOS_IMPL_SCALE || IMPL == GPUOS_IMPL_FMA || IMPL == GPUOS_IMPL_COPY;
+    if (SHORT && (uni(r->rflags) & RF_STREAM) != 0) batches(Mem<POL, SHORT>{});
+    else batches(M{});
     for (; v < nvec; v += kThreads) {
       v4i qa[1], qb[1], qc[1];
       qa[0] = M::ld16(ra, v * 16u);
@@ -1181,6 +1199,9 @@ PATHFN void ew_pairs(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32
   char* const po = (char*)uni_ptr(r->ptr[3]) + (uint64_t)begin * E::ES;
   const rsrc_t ro = make_rsrc(po, (end - begin) * E::ES);
   const uint32_t units = 2u * nvec;
+  const bool stream = (uni(r->rflags) & RF_STREAM) != 0;
+  auto ld16 = [&](rsrc_t q, uint32_t off) { return stream ? Mem<POL, true>::ld16(q, off) : M::ld16(q, off); };
+  auto ld8 = [&](rsrc_t q, uint32_t off) { return stream ? Mem<POL, true>::ld8(q, off) : M::ld8(q, off); };
   for (uint32_t v = tid; v - tid < units; v += 2 * U * kThreads) {
     v4i q[3][U], h[3][U];
 #pragma unroll
@@ -1189,11 +1210,11 @@ PATHFN void ew_pairs(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32
 #pragma unroll
       for (int k = 0; k < N; ++k) {
         if (step[k] == 2u) {
-          q[k][u] = M::ld16(rs[k], a < units ? a * 16u : kNoLoad);
-          h[k][u] = M::ld16(rs[k], b < units ? b * 16u : kNoLoad);
+          q[k][u] = ld16(rs[k], a < units ? a * 16u : kNoLoad);
+          h[k][u] = ld16(rs[k], b < units ? b * 16u : kNoLoad);
         } else {
-          q[k][u] = M::ld8(rs[k], a < units ? a * 8u : kNoLoad);
-          h[k][u] = M::ld8(rs[k], b < units ? b * 8u : kNoLoad);
+          q[k][u] = ld8(rs[k], a < units ? a * 8u : kNoLoad);
+          h[k][u] = ld8(rs[k], b < units ? b * 8u : kNoLoad);
         }
       }
     }
@@ -1340,6 +1361,12 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
   }
   const float alpha = __builtin_bit_cast(float, uni(__builtin_bit_cast(uint32_t, r->alpha)));
   const uint32_t impl = uni(r->impl);
+  const bool stream = (uni(r->rflags) & RF_STREAM) != 0;
+  auto load = [&](rsrc_t rs, uint32_t off) {
+    typedef Mem<POL, true> S;
+    if (LN == 2) return stream ? S::ld8(rs, off) : M::ld8(rs, off);
+    return stream ? S::ld16(rs, off) : M::ld16(rs, off);
+  };
   // (row, vector) of this lane's first unit by division, then steps of 256 units with carries
   const bool deep = A * B > 1;
   const uint32_t ti = tid / LN, half = LN == 2 ? (tid & 1u) * VL : 0u;
@@ -1377,7 +1404,7 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
             // moves nothing: no branch between the loads of a round)
             const uint32_t of = act && !(SCALARS && scalar[k]) ? o + col * EI::ES : kNoLoad;
 #pragma unroll
-            for (int i = 0; i < NI; ++i) q[k][u][i] = LN == 2 ? M::ld8(rs[k], of) : M::ld16(rs[k], of + i * 16u);
+            for (int i = 0; i < NI; ++i) q[k][u][i] = load(rs[k], of + i * 16u);
             if (SCALARS) w[k][u] = M::ldb4(rs[k], act && scalar[k] ? (lead[k] + o) & ~3u : kNoLoad) >> (((lead[k] + o) & 2u) * 8u);
           }
         }
@@ -1583,6 +1610,7 @@ struct RedArgs {       // what a row-reduction variant is called with (plain val
   uint32_t n;
   char* po;
   uint32_t odt, row_begin, row_end, max_span;
+  uint32_t stream;     // loads with nt
   uint32_t tid;
   float* s_part;       // LDS
 };
@@ -1656,9 +1684,15 @@ PATHFN void red_rows_stream(RedArgs a) {
   const uint32_t j_last = (w1 * n + run.skew - 1u) / V;
   A acc = red_identity<RIMPL, A>(), res = 0;                 // (lane L of `res`: the L-th result since the last store)
   uint32_t kept = 0;
+  const bool stream = uni(a.stream) != 0;
   auto fetch = [&](v4i (&q)[U], uint32_t j) {
+    if (stream) {
 #pragma unroll
-    for (uint32_t u = 0; u < U; ++u) q[u] = M::ld16(run.rin, j + u * 64u + lane <= j_last ? (j + u * 64u + lane) * 16u : kNoLoad);
+      for (uint32_t u = 0; u < U; ++u) q[u] = Mem<POL, true>::ld16(run.rin, j + u * 64u + lane <= j_last ? (j + u * 64u + lane) * 16u : kNoLoad);
+    } else {
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) q[u] = M::ld16(run.rin, j + u * 64u + lane <= j_last ? (j + u * 64u + lane) * 16u : kNoLoad);
+    }
   };
   auto take = [&](const v4i (&q)[U], uint32_t j) {           // true: the last row is complete
 #pragma unroll
@@ -1905,7 +1939,7 @@ DEV void red_contig(const Record* r, uint32_t row_begin, uint32_t row_end, float
   a.base = pin - a.lead * E::ES + (uint64_t)a.base_elem * E::ES;
   a.bytes = ((a.lead + row_end * n - a.base_elem) * E::ES + 15u) & ~15u;
   a.po = (char*)uni_ptr(r->ptr[3]);
-  a.odt = uni(r->dtype[3]); a.row_begin = row_begin; a.row_end = row_end; a.s_part = s_part; a.tid = tid;
+  a.stream = uni(r->rflags) & RF_STREAM; a.odt = uni(r->dtype[3]); a.row_begin = row_begin; a.row_end = row_end; a.s_part = s_part; a.tid = tid;
   const bool whole = n % V == 0 && a.lead == 0;       // every row is whole vectors
   a.max_span = whole ? n / V : (n + V - 2) / V + 1;
   if (a.max_span <= 64u && whole) red_rows_short_aligned<POL, RIMPL, DT>(a);
@@ -2021,15 +2055,16 @@ template <int V, bool RAGGED> struct RowCut {
 // (softmax of 65,536 x 24 fp32: 28.7 us with the branch, 25.6 without; layer norm of 1,024 x 2,048 bf16 19.5 and 26.5).
 template <int POL, int DT, bool RAGGED, bool STRAIGHT = false> DEV void row_store(rsrc_t ro, uint32_t off, const v4i& q, bool act, int first) {
   using E = Elem<DT>;
-  if (!RAGGED && STRAIGHT) { Mem<POL>::st16(ro, act ? off : kNoLoad, q); return; }
-  if (!RAGGED) { if (act) Mem<POL>::st16(ro, off, q); return; }
-  Mem<POL>::st16(ro, act && first == 0 ? off : kNoLoad, q);
+  using M = Mem<POL, false, true>;
+  if (!RAGGED && STRAIGHT) { M::st16(ro, act ? off : kNoLoad, q); return; }
+  if (!RAGGED) { if (act) M::st16(ro, off, q); return; }
+  M::st16(ro, act && first == 0 ? off : kNoLoad, q);
   if (act && first != 0) {
 #pragma unroll
     for (int e = 1; e < (int)E::V; ++e)
       if (e >= first) {
-        if (E::ES == 4) Mem<POL>::stb4(ro, off + e * 4u, (uint32_t)q[e & 3]);
-        else Mem<POL>::stb2(ro, off + e * 2u, (uint32_t)q[e / 2] >> ((e & 1) * 16));
+        if (E::ES == 4) M::stb4(ro, off + e * 4u, (uint32_t)q[e & 3]);
+        else M::stb2(ro, off + e * 2u, (uint32_t)q[e / 2] >> ((e & 1) * 16));
       }
   }
 }
@@ -2041,7 +2076,7 @@ template <int POL, int DT, bool RAGGED, bool STRAIGHT = false> DEV void row_stor
 template <int POL, int ROP, int DT, int KW, int UP, bool P32, bool RAGGED>
 DEV void rowop_fused(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
   using E = Elem<DT>;
-  using M = Mem<POL>;
+  using M = Mem<POL, false, true>;
   using RO = RowOp<ROP>;
   constexpr uint32_t V = E::V;
   constexpr bool MASK = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST;
@@ -2293,7 +2328,7 @@ struct WgReduce {
 template <int POL, int ROP, int DT, int KW, bool P32, bool RAGGED>
 DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_red, uint32_t tid) {
   using E = Elem<DT>;
-  using M = Mem<POL>;
+  using M = Mem<POL, false, true>;
   using RO = RowOp<ROP>;
   constexpr uint32_t V = E::V;
   constexpr bool MASK = ROP == GPUOS_IMPL_MASKED_SOFTMAX_LAST;
@@ -2421,7 +2456,7 @@ DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* 
 template <int POL, int DT, int NB, bool RAGGED>
 DEV void softmax_held(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
   using E = Elem<DT>;
-  using M = Mem<POL>;
+  using M = Mem<POL, false, true>;
   constexpr uint32_t V = E::V, U = 3, NR = NB * U, NL = 6;
   const uint32_t n = uni(r->red_n);
   const uint32_t chunk_bytes = (row_end - row_begin) * n * E::ES;
@@ -2574,7 +2609,7 @@ DEV void softmax_held(const Record* r, uint32_t row_begin, uint32_t row_end, flo
 template <int POL, int DT, bool RAGGED>
 DEV void masked_softmax_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
   using E = Elem<DT>;
-  using M = Mem<POL>;
+  using M = Mem<POL, false, true>;
   constexpr uint32_t V = E::V, U = 4;
   const uint32_t n = uni(r->red_n);
   const RowCut<V, RAGGED> cut(n);
@@ -2649,7 +2684,7 @@ DEV void masked_softmax_long(const Record* r, uint32_t row_begin, uint32_t row_e
 template <int POL, int DT, bool P32, bool RAGGED>
 DEV void layernorm_long(const Record* r, uint32_t row_begin, uint32_t row_end, float* s_v, uint32_t tid) {
   using E = Elem<DT>;
-  using M = Mem<POL>;
+  using M = Mem<POL, false, true>;
   constexpr uint32_t V = E::V;
   const uint32_t n = uni(r->red_n);
   const RowCut<V, RAGGED> cut(n);

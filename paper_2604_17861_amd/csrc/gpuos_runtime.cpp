@@ -403,6 +403,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
       }
       if (ok) { rec.path = PATH_ROW2D; rec.rflags |= RF_VEC; }
     }
+    if ((uint64_t)numel * dtype_size(ops[0].dtype) * (uint64_t)ar >= kStreamBytes) rec.rflags |= RF_STREAM;
     // Rows that are contiguous in every operand, or hold one scalar per row, under up to three outer
     // dims of any strides: 16-byte accesses whatever the row length and alignment are, as long as a
     // row holds a vector.  Operands of one dtype (a COPY may convert), scalars of any. 
@@ -598,6 +599,7 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   // the dispatcher holds it back until what it waits for is done.
   const uint64_t row_bytes = (uint64_t)n * dtype_size(ops[0].dtype), total = row_bytes * (uint64_t)rows;
   const uint64_t most = (uint64_t)chunk_elems * 24, spread = total / 128;
+  if (total >= kStreamBytes) rec.rflags |= RF_STREAM;
   uint64_t rpc = (spread < 32768 ? 32768 : (spread < most ? spread : most)) / row_bytes;
   if (chained && total <= kSmallTaskChunks * most) {
     const uint64_t quarter = ((uint64_t)rows + kSmallTaskChunks - 1) / kSmallTaskChunks;

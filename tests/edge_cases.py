@@ -132,6 +132,35 @@ def row_operation_edges(code):
     return b.stream("row_operation_edges_%d" % code)
 
 
+def every_second_element(code):
+    """Slices with a step of two, from the buffer's first element and from its second, that end with the buffer's last
+    element: fewer and more than a vector, than a round of the workgroup and than a chunk; alone, with contiguous
+    operands of any alignment and with each other; slices of matrices whose rows merge; every operator class."""
+    rng = np.random.default_rng(740 + code)
+    b = Builder()
+    V = 4 if code == S.F32 else 8
+    dt = np_dtype(code)
+    for i, n in enumerate((1, 2, V - 1, V, V + 1, 2 * V, 255 * V + 3, 1024, 1025, 2047, 4096, 8192, 8193, 16384, 40000 + V, 1 << 20, (1 << 20) + 2049, (1 << 21) + 5)):
+        first = i % 2
+
+        def second(k=first):
+            return b.pool(values(rng, 2 * n - 1 + k, code))[k::2]
+        lead = (0, 1, 3)[i % 3]
+        flat = b.pool(values(rng, n + lead, code))[lead:]
+
+        def out():
+            return b.pool(np.zeros(n + V, dt))[:n]
+        for name in ("SCALE", "RELU", "EXP", "GELU_ERF", "GELU_TANH")[i % 5:][:2]:
+            b.add(name, out(), [second()], alpha=0.75)
+        b.add(("ADD", "SUB", "MUL", "SUB_EXP", "DIV")[i % 5], out(), [second(), flat])
+        b.add(("SUB", "MUL", "DIV", "ADD")[i % 4], out(), [flat, second(1 - first)])
+        b.add("MUL", out(), [second(), second(1 - first)])
+        b.add("FMA", out(), [second(), flat, second()])
+    m = b.pool(values(rng, 30 * 58, code)).reshape(30, 58)                                    # x[:, ::2] * y, merged to one dim
+    b.add("MUL", b.pool(np.zeros((30, 29), dt)), [m[:, ::2], b.pool(values(rng, 30 * 29, code)).reshape(30, 29)])
+    return b.stream("every_second_element_%d" % code)
+
+
 def long_softmax_rows(code):
     """Softmax rows of which a workgroup keeps a part in registers and in LDS: either side of every length at
     which it keeps more, fits no more or reads another batch again, at every alignment of rows cut at blocks of memory (x

@@ -78,6 +78,12 @@ def test_softmax_rows_kept_in_part(code):
     print(stats, flush=True)
 
 
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_slices_with_a_step_of_two(code):
+    stats, _ = _run_and_check(E.every_second_element(code))
+    print(stats, flush=True)
+
+
 def test_gathers_larger_than_1024_regular_chunks():
     stats, _ = _run_and_check(E.large_gathers())
     print(stats, flush=True)
