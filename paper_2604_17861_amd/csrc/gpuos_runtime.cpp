@@ -589,12 +589,11 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   // (a row fits one buffer resource; rows are read as aligned vectors whatever n and the base's alignment are)
   rec.path = (s_last == 1 && rows_contig && n * 4 < kMaxExtent) ? PATH_RED_CONTIG : PATH_RED_GENERIC;
   // A reduction writes almost nothing and its rows are a chain of memory latencies, which grow to 10-20 us while the GPU
-  // streams: a task is cut into chunks of 28 KiB (what four wavefronts hold in their pieces of the scratch at a time), up to 128 of
-  // them, before chunks grow to the regular size.  (Chunks of twice
+  // streams: a task is cut into chunks of 16 KiB, up to 32 of them, then of up to 32 KiB, up to 128 of them, before chunks grow to
+  // the regular size.  (Chunks of twice
   // the elementwise traffic whatever the task's size: a 0.2 MB reduction in a bandwidth-bound stream was two chunks and
   // took 110 us.  Forty streaming operations of 0.1-220 MB, half of them reductions, in up to 64 pieces of 16 KiB at least,
-  // 64 of 32 KiB and 128 of 32 KiB: 109.5, 108.6 and 107.7 us; 24 integer operations 54.0, 53.9 and 51.1; 128 of 32, 28 and 24 KiB:
-  // 111.7, 111.2 and 112.8, integers 45.4 each.  Smaller pieces are bound by
+  // 64 of 32 KiB and 128 of 32 KiB: 109.5, 108.6 and 107.7 us; 24 integer operations 54.0, 53.9 and 51.1.  Smaller pieces are bound by
   // their claims, 12 ns each one after the other whoever makes them: 143 sums of 512K bf16 elements 143 us in pieces of 16 KiB, 105 so.)
   // But a link of a chain of at most four regular chunks is cut into (up to) four, like an elementwise
   // one: up to those a dependent task is published at once and waits in its workgroups, beyond them
@@ -602,7 +601,10 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   const uint64_t row_bytes = (uint64_t)n * dtype_size(ops[0].dtype), total = row_bytes * (uint64_t)rows;
   const uint64_t most = (uint64_t)chunk_elems * 24, spread = total / 128;
   if (total >= kStreamBytes) rec.rflags |= RF_STREAM;
-  uint64_t rpc = (spread < 28672 ? 28672 : (spread < most ? spread : most)) / row_bytes;
+  uint64_t piece = total / 32;
+  piece = piece < 16384 ? 16384 : piece < 32768 ? piece : 32768;
+  if (spread > piece) piece = spread < most ? spread : most;
+  uint64_t rpc = piece / row_bytes;
   if (chained && total <= kSmallTaskChunks * most) {
     const uint64_t quarter = ((uint64_t)rows + kSmallTaskChunks - 1) / kSmallTaskChunks;
     if (rpc < quarter) rpc = quarter;
