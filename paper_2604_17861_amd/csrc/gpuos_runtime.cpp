@@ -216,16 +216,23 @@ inline bool aligned16(uint64_t p) { return (p & 15u) == 0; }
 inline int packed(const Record& rec) { return rec.nchunks > kMaxChunksPerTask ? GPUOS_E_INVAL : GPUOS_OK; }
 
 // Validate `t` for implementation `impl` and pack it into *r, which holds something only if the result is GPUOS_OK.
-int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elems = kChunkElems, int program_arity = 0) {
+// CHECK_ONLY: what that result would be, and no record (r is not touched).
+template <bool CHECK_ONLY>
+int pack_or_check(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elems, int program_arity) {
   Record& rec = *r;
-  std::memset(&rec, 0, sizeof(rec));
-  rec.op_id = t.op_id;
-  rec.alpha = t.alpha;
-  rec.impl = impl;
-  rec.dep[0] = t.dep[0]; rec.dep[1] = t.dep[1]; rec.dep[2] = t.dep[2];
+  if constexpr (!CHECK_ONLY) {
+    std::memset(&rec, 0, sizeof(rec));
+    rec.op_id = t.op_id;
+    rec.alpha = t.alpha;
+    rec.impl = impl;
+    rec.dep[0] = t.dep[0]; rec.dep[1] = t.dep[1]; rec.dep[2] = t.dep[2];
+  }
   if (t.flags & ~(GPUOS_FLAG_FENCE | GPUOS_FLAG_KEEPDIM)) return GPUOS_E_INVAL;
-  if (t.flags & GPUOS_FLAG_FENCE) rec.rflags |= RF_FENCE;
+  if constexpr (!CHECK_ONLY) {
+    if (t.flags & GPUOS_FLAG_FENCE) rec.rflags |= RF_FENCE;
+  }
   if (impl == GPUOS_IMPL_FAIL) {                   // executes nothing; one unit reports it
+    if constexpr (CHECK_ONLY) return GPUOS_OK;
     rec.path = PATH_NOP;
     rec.nchunks = 1;
     return packed(rec);
@@ -268,6 +275,11 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
     same_dt = same_dt && ops[k].dtype == ops[ar].dtype;
   }
   if (any_int && (!all_int || !impl_takes_int(impl))) return GPUOS_E_INVAL;
+  if constexpr (CHECK_ONLY) {                       // (the last thing refused: a reduction of nothing into something)
+    bool any_row = true;
+    for (int d = 0; d + 1 < t.ndim; ++d) any_row = any_row && size[d] != 0;
+    return red && any_row && size[t.ndim - 1] == 0 ? GPUOS_E_INVAL : GPUOS_OK;
+  }
   if (all_int) rec.rflags |= RF_INT;
   rec.n_inputs = (uint8_t)ar;
   for (int k = 0; k < ar; ++k) { rec.dtype[k] = (uint8_t)ops[k].dtype; rec.ptr[k] = ops[k].ptr; }
@@ -617,6 +629,11 @@ int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elem
   rec.nchunks = (uint32_t)(((uint64_t)rows + rpc - 1) / rpc);
   return packed(rec);
 }
+
+int pack_task(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_elems = kChunkElems, int program_arity = 0) {
+  return pack_or_check<false>(t, impl, r, chunk_elems, program_arity);
+}
+int check_task(const gpuos_task& t, uint32_t impl, int program_arity) { return pack_or_check<true>(t, impl, nullptr, kChunkElems, program_arity); }
 
 // Runs: which tasks of one submit may be run by the workgroup that has just run the same chunk of the
 // task right before (RF_LINK; the dispatcher decides, the links inside one of its passes go with the
@@ -1708,6 +1725,72 @@ int gpuos_submit_flush(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, uint64
   return submit_impl(c, tasks, n, out_first_ticket, true);
 }
 namespace {
+// The implementation that an operator id is bound to (GPUOS_IMPL_NONE: none).
+inline uint32_t bound_impl(const gpuos_ctx* c, uint32_t op_id) {
+  return op_id < GPUOS_MAX_OPS && __atomic_load_n(&c->ops[op_id].version, __ATOMIC_ACQUIRE) != 0 ? __atomic_load_n(&c->ops[op_id].impl, __ATOMIC_RELAXED)
+                                                                                               : (uint32_t)GPUOS_IMPL_NONE;
+}
+// (a program's arity was stored before its id could be bound to any operator)
+inline int bound_arity(const gpuos_ctx* c, uint32_t impl) {
+  return impl >= GPUOS_IMPL_PROGRAM_BASE ? (int)c->prog_arity[(impl - GPUOS_IMPL_PROGRAM_BASE) % GPUOS_MAX_PROGRAMS] : 0;
+}
+
+// A large call that publishes, with no other producer about (the caller holds prod_mu): everything is checked first, and then each
+// batch of the dispatcher's is packed, written and published by itself, so that the device begins with the first when
+// that is packed.  Nothing is enqueued if one descriptor fails: what the check takes packing takes, under the lock that the
+// operator table changes under.  The line lies at two batches: of fewer there is little to overlap and the check costs 8 ns a task.
+// 1,000 adds in one call: 86.0 us when all were packed before the first was written, 76.1 so.  Calls of 128 are left as they were:
+// one function that checks and then packs, for both, took 2 ns a task more of them (24 calls: 228 us, 232).
+// A producer that finds the lock taken packs its tasks meanwhile, as before.
+int submit_in_batches(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, Record* records, uint64_t* out_first_ticket) {
+  uint64_t head = c->head.load(std::memory_order_relaxed);
+  for (uint32_t i = 0; i < n; ++i) {
+    const gpuos_task& t = tasks[i];
+    const uint32_t impl = bound_impl(c, t.op_id);
+    if (impl == GPUOS_IMPL_NONE && !c->cfg.defer_op_check) return GPUOS_E_BADOP;
+    const int rc = check_task(t, impl == GPUOS_IMPL_NONE ? (uint32_t)GPUOS_IMPL_FAIL : impl, bound_arity(c, impl));
+    if (rc != GPUOS_OK) return rc;
+    for (int k = 0; k < 3; ++k)
+      if (t.dep[k] >= c->cap) return GPUOS_E_INVAL;
+  }
+  for (uint32_t i = 0; i < n; ++i)
+    for (int k = 0; k < 3; ++k)
+      if (tasks[i].dep[k] > head + i) return GPUOS_E_INVAL;       // names a ticket before the first one
+  if (out_first_ticket) *out_first_ticket = head;
+  LinkRun run;
+  uint32_t summed = 0, written = 0;                   // records that are final (none of a run that is being built), and in the ring
+  for (uint32_t i = 0; i <= n; ++i) {
+    if (i < n) {
+      const uint32_t impl = bound_impl(c, tasks[i].op_id);
+      const int rc = pack_task(tasks[i], impl == GPUOS_IMPL_NONE ? (uint32_t)GPUOS_IMPL_FAIL : impl, &records[i], c->cfg.chunk_elems, bound_arity(c, impl));
+      if (rc != GPUOS_OK) return rc;
+      records[i].ticket = 0;
+      if (i == 0 || run.links(records[i - 1], records[i])) continue;
+    }
+    run.close(records + i);
+    for (; summed < i; ++summed) records[summed].check = weighted_sum(records[summed]);
+    if (i < n && summed < written + kDispatchBatch) continue;
+    const uint32_t end = i < n ? summed - (summed - written) % kDispatchBatch : n;
+    for (; written < end; ++written) {
+      if (head - c->floor.load(std::memory_order_acquire) >= c->cap) {
+        c->head.store(head, std::memory_order_release);
+        doorbell(c);                                  // publish so that the device can make room
+        const int rc = wait_floor(c, head - c->cap + 1, c->wait_ns);
+        if (rc != GPUOS_OK) return rc;
+      }
+      Record& rec = records[written];
+      rec.check = record_check_seed(head) - rec.check;
+      std::memcpy(&c->hring[head & c->mask], &rec, sizeof(Record));
+      ++head;
+      if ((written + 1) % kDispatchBatch == 0 || written + 1 == n) {
+        c->head.store(head, std::memory_order_release);
+        doorbell(c);
+      }
+    }
+  }
+  return GPUOS_OK;
+}
+
 int submit_impl(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, uint64_t* out_first_ticket, bool publish) {
   if (!c || (!tasks && n)) return GPUOS_E_INVAL;
   if (!c->worker_running || worker_exited(c)) return GPUOS_E_DEAD;
@@ -1725,6 +1808,10 @@ int submit_impl(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, uint64_t* out
     staged.resize(n);
   } catch (const std::bad_alloc&) {                             // no exception may cross the C boundary
     return GPUOS_E_NOMEM;
+  }
+  if (publish && n > 2 * kDispatchBatch && !c->cfg.nonblocking_submit && c->prod_mu.try_lock()) {
+    std::lock_guard<SpinMutex> lk(c->prod_mu, std::adopt_lock);
+    return submit_in_batches(c, tasks, n, staged.data(), out_first_ticket);
   }
   LinkRun run;
   uint32_t summed = 0;

@@ -232,11 +232,89 @@ static void runs_are_marked() {
   std::printf("ok: links of runs are marked, and nothing else\n");
 }
 
+// Calls of more than two batches are checked first and then packed batch by batch: whatever a descriptor is, such a call answers as
+// a single submit of it does, enqueues nothing if one is refused, and marks the same links.
+static void large_calls_answer_as_small_ones() {
+  gpuos_ctx* c = make(512);
+  const uint16_t impls[] = {GPUOS_IMPL_ADD, GPUOS_IMPL_RELU, GPUOS_IMPL_SUM_LAST, GPUOS_IMPL_MAX_LAST, GPUOS_IMPL_SOFTMAX_LAST, GPUOS_IMPL_LAYERNORM_LAST};
+  const int arity[] = {2, 1, 1, 1, 1, 3};
+  for (int k = 0; k < 6; ++k) CHECK(gpuos_register_op(c, (uint16_t)(20 + k), impls[k], nullptr) == GPUOS_OK);
+  uint32_t seed = 12345;
+  auto rnd = [&](uint32_t n) { seed = seed * 1664525u + 1013904223u; return (seed >> 8) % n; };
+  int refused = 0;
+  uint64_t head = 0;
+  for (int trial = 0; trial < 600; ++trial) {
+    const int k = (int)rnd(6);
+    gpuos_task t = add_task((uint16_t)(20 + k), 0);
+    t.n_inputs = (uint8_t)arity[k];
+    t.ndim = (uint8_t)(1 + rnd(GPUOS_MAX_DIMS));
+    const uint8_t dt = (uint8_t)rnd(4) ? GPUOS_F32 : GPUOS_BF16;
+    for (int d = 0; d < t.ndim; ++d) t.size[d] = rnd(12) ? 1 + rnd(9) : 0;
+    for (int j = 0; j < 4; ++j) {
+      auto& q = j < 3 ? t.in[j] : t.out;
+      q.ptr = (void*)(uintptr_t)(0x1000000 * (j + 1) + (rnd(3) ? 0 : 4));
+      q.dtype = dt;
+      int64_t s = 1;
+      for (int d = t.ndim - 1; d >= 0; --d) { q.stride[d] = s; s *= t.size[d] ? t.size[d] : 1; }
+      if (j < 3 && !rnd(4)) q.stride[rnd(t.ndim)] = 0;
+      if (j < 3 && t.ndim > 1 && !rnd(4)) std::swap(q.stride[0], q.stride[1]);
+    }
+    switch (rnd(24)) {                                    // one fault in half of them
+      case 0: t.n_inputs ^= 1; break;
+      case 1: t.ndim = 0; break;
+      case 2: t.ndim = GPUOS_MAX_DIMS + 1; break;
+      case 3: t.size[0] = -1; break;
+      case 4: t.size[0] = 1ll << 40; break;
+      case 5: t.in[0].ptr = nullptr; break;
+      case 6: t.out.dtype = GPUOS_I32; break;
+      case 7: t.in[0].dtype = 77; break;
+      case 8: t.out.stride[0] = 0; break;
+      case 9: t.op_id = 60; break;
+      case 10: t.flags = 0x80; break;
+      case 11: t.dep[1] = 512; break;
+      case 12: t.out.ptr = (void*)(uintptr_t)0x900001; break;
+      default: break;
+    }
+    uint64_t tk = 0;
+    const int one = gpuos_submit_flush(c, &t, 1, &tk);
+    if (one == GPUOS_OK) { CHECK(tk == head); ++head; }
+    else ++refused;
+    const uint32_t n = 129 + rnd(300);
+    std::vector<gpuos_task> v(n, add_task(7, 256));
+    v[rnd(n)] = t;
+    const int many = gpuos_submit_flush(c, v.data(), n, &tk);
+    CHECK(many == one);
+    if (many == GPUOS_OK) { CHECK(tk == head); head += n; }
+    gpuos_queue_state q;
+    CHECK(gpuos_peek_queue(c, &q) == GPUOS_OK && q.head_submitted == head);
+  }
+  CHECK(refused > 100 && refused < 500);
+  std::vector<gpuos_task> v(300, add_task(7, 256));
+  v[5].dep[0] = 511;                                      // one fault of each pass: the earlier pass answers
+  CHECK(head >= 511);
+  v[299].op_id = 60;
+  CHECK(gpuos_submit_flush(c, v.data(), 300, nullptr) == GPUOS_E_BADOP);
+  CHECK(gpuos_wait(c, GPUOS_ALL, 0) == GPUOS_OK);
+  for (uint32_t n : {129u, 191u, 192u, 193u, 450u}) {     // runs across the ends of batches, and tasks that are none
+    std::vector<gpuos_task> w(n, add_task(7, 1000, 1));
+    for (uint32_t i = 0; i < n; ++i) { w[i].in[0].ptr = w[i].out.ptr; if (rnd(40) == 0 || i == 0) w[i].dep[0] = 0; }
+    const uint64_t a = standin_links();
+    CHECK(gpuos_submit(c, w.data(), n, nullptr) == GPUOS_OK && gpuos_flush(c) == GPUOS_OK && gpuos_wait(c, GPUOS_ALL, 0) == GPUOS_OK);
+    const uint64_t b = standin_links();
+    CHECK(gpuos_submit_flush(c, w.data(), n, nullptr) == GPUOS_OK && gpuos_wait(c, GPUOS_ALL, 0) == GPUOS_OK);
+    CHECK(b > a && standin_links() - b == b - a);
+  }
+  CHECK(gpuos_shutdown(c) == GPUOS_OK);
+  CHECK(standin_errors() == 0);
+  std::printf("ok: large calls answer as small ones (%d of 600 refused)\n", refused);
+}
+
 int main() {
   check_word_rejects_mixtures();
   block_cuts_stay_below_the_offset_that_does_nothing();
   runs_are_marked();
   chunks_stay_addressable();
+  large_calls_answer_as_small_ones();
   // 1. many producers, tiny rings: every ticket exactly once, consecutive inside a call, in-order log
   for (uint32_t cap : {2u, 8u, 64u}) {
     for (int harv = 0; harv < 2; ++harv) {
