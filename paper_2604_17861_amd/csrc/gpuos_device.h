@@ -1171,7 +1171,8 @@ PATHFN void ew_staged(const Record* r_v, uint32_t begin_v, uint32_t end_v, float
 
 // PATH_STAGED under RF_PAIRS: contiguous output, inputs of its dtype that are contiguous or every second element of a buffer.  Both
 // halves of each pair are read and one is dropped: no LDS, no rounds, nothing to wait for but memory.  A lane makes 8 bytes of the output
-// from 16 of such an input, so that every access of a wavefront is one run of memory, and computes two of them together.  (Gathered through LDS the rounds are latencies in a row: products of 400 x 579 fp32 with every other column took 61 us
+// from 16 of such an input, so that every access of a wavefront is one run of memory, and computes two of them together.
+// (Gathered through LDS the rounds are latencies in a row: products of 400 x 579 fp32 with every other column took 61 us
 // for 147 MB, 1,238 x 2,359 bf16 93 us for 140 MB; 52 and 55 so.)  The tensor's last vector goes element by element: behind
 // its last element may be nothing to read.
 template <int POL, class OPER, int DT>
@@ -1329,7 +1330,7 @@ PATHFN void ew_rows(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint32_
   constexpr int V = EI::V > EO::V ? EI::V : EO::V;
   // A cast that widens gives each vector of eight elements to two lanes, four elements each, so that a wavefront's store is
   // one run of memory.  (One lane for both halves leaves every other 16 bytes to the next store, and memory takes each
-  // for itself: 24M elements from bf16 to fp32 took 98 us, 45 so.)
+  // for itself: 24M elements from bf16 to fp32 took 98 us, 45 so, 39 with plain stores.)
   constexpr int LN = EI::ES < EO::ES ? 2 : 1, VL = V / LN, NI = LN == 2 ? 1 : V / EI::V, NO = VL / EO::V;
   constexpr uint32_t kStep = kThreads / LN;
   constexpr int N = OPER::N;
@@ -2445,8 +2446,9 @@ DEV void rowop_wg(const Record* r, uint32_t row_begin, uint32_t row_end, float* 
 // The first keeps a running maximum and a sum relative to it per lane, rescaled once per
 // batch of vectors; the second writes.
 // A lane's first NB batches of three vectors stay in registers (up to eighteen, 72 of the 128: with twenty some went through scratch
-// memory) and the next six in LDS; the second pass reads only what is left, of a row of 32,003 fp32 elements eight of 32.  Bound by memory: 2 x 1,024 such rows took 175 us with twelve in registers, and as many of a caller's
-// saved and restored (525 MB read, 392 MB written, of 262 each).
+// memory) and the next six in LDS; the second pass reads only what is left, of a row of 32,003 fp32 elements eight of 32.  Bound
+// by memory: 2 x 1,024 such rows took 175 us with twelve in registers, and as many of a caller's saved and restored (525 MB
+// read, 392 MB written, of 262 each); 134 so, of which the plain loads are 5.
 // A row has more vectors a lane than stay in registers: those are whole and need no look at the row's end.
 // Ragged rows are cut where memory's 16-byte blocks begin, if x and the output lie alike in them: a block at
 // either end of a row is shared with its neighbour, every other access is a whole aligned one.  (The block
@@ -3020,7 +3022,8 @@ PATHFN void run_reductions(const Record* r_v, uint32_t impl_v, uint32_t chunk_v,
 }
 
 // The interpreter's executors, behind one call: in the worker's loop itself they were 44 of its 293 call sites, which cost
-// other operations' registers (softmax over rows of 32,003 fp32 elements: 180.4 us with them there, 175.9 so).  It ends in
+// other operations' registers (softmax over rows of 32,003 fp32 elements, then in that loop too: 180.4 us with them there, 175.9
+// so).  It ends in
 // jumps: where it made calls it had to keep for its caller all that its callees use, 376 bytes a lane, and
 // x / (1 + e^-x) over four tensors of 2,048 fp32 elements took 35.7 us instead of 16.0.
 template <int POL>
