@@ -44,14 +44,17 @@ namespace gpuos {
 //
 // The non-temporal hint (nt) keeps a line out of the memory-side cache (256 MB): what the next operation reads
 // is then in memory, and the parts of a line that two stores write each go there by themselves.  So:
-//   * elementwise operations and reductions store without it, and load with it where a task reads 8 MB or more
-//     (RF_STREAM), so that it leaves what is there in place;
+//   * elementwise operations and reductions store without it, and load with it where a task reads much (RF_STREAM: 4 MB, 1 MB
+//     where it goes by rows or pairs), so that it leaves what is there in place; of contiguous tensors, whose stores are
+//     whole lines, such a task stores with it too;
 //   * runs have it on nothing (each link's result is read by no one but may be, their inputs are the chain's);
 //   * row operations store with it and load without: the rows' readers are a matrix product away, and the inputs stay.
 // Measured against nt on every 16-byte access, three sets of buffers in turn / one set over and over: 24 chains of six
 // tasks 155.6 us, 134; masked softmax 38.4 and 32.3 / 37.9 and 32.4; layer norm 41.0 and 36.5; 24 layout changes 57.7 and 57.9 / 57.5 and 49.8
 // (rows of 363 bf16 copied into a wider matrix, 149 MB: 86 and 52); integers 51.5 and 45.6 / 51.4 and 44.3; softmax over 32,003
-// columns 139 and 134 / 139 and 117; forty streaming operations of 503 MB 110.3 and 111.6 / 110 and 95.7.
+// columns 139 and 134 / 139 and 117; forty streaming operations of 503 MB 110.3 and 111.6 / 110 and 95.7.  With the stores of large
+// contiguous tasks, and 4 MB and 1 MB in place of 8, those took 101.2 / 98.8, the layout changes 53.1 / 50.5, and 20,000 streaming
+// operations over 4 GB of inputs 55.5 ms instead of 57.7.  (From 2 MB on everywhere: 101.5 / 101.4, layout changes 55.7.)
 // ---------------------------------------------------------------------------
 enum { POL_PLAIN = 0, POL_COHERENT = 1 };
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -638,13 +641,13 @@ PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint3
           qc[u] = N > 2 ? ML::ld16(rc, (v + u * kThreads) * 16u) : qa[u];
         }
         typedef VecArg<DT, U> Arg;
-        ew_vectors<IMPL, DT, U>(Arg{qa}, Arg{qb}, Arg{qc}, alpha, [&](int u, const v4i& q) { M::st16(ro, (v + u * kThreads) * 16u, q); });
+        ew_vectors<IMPL, DT, U>(Arg{qa}, Arg{qb}, Arg{qc}, alpha, [&](int u, const v4i& q) { ML::st16(ro, (v + u * kThreads) * 16u, q); });
       }
     };
-    // (operators of many instructions are bound by those)
+    // (operators of many instructions are bound by those; of native programs, functors past the last id, nothing is known: a stream of them was 5 % slower without)
     constexpr bool SHORT = IMPL == GPUOS_IMPL_ADD || IMPL == GPUOS_IMPL_SUB || IMPL == GPUOS_IMPL_MUL || IMPL == GPUOS_IMPL_RELU ||
-                           IMPL == GPUOS_IMPL_SCALE || IMPL == GPUOS_IMPL_FMA || IMPL == GPUOS_IMPL_COPY;
-    if (SHORT && (uni(r->rflags) & RF_STREAM) != 0) batches(Mem<POL, SHORT>{});
+                           IMPL == GPUOS_IMPL_SCALE || IMPL == GPUOS_IMPL_FMA || IMPL == GPUOS_IMPL_COPY || IMPL > kImplProg3;
+    if (SHORT && (uni(r->rflags) & RF_STREAM) != 0) batches(Mem<POL, SHORT, SHORT>{});
     else batches(M{});
     for (; v < nvec; v += kThreads) {
       v4i qa[1], qb[1], qc[1];

@@ -51,7 +51,8 @@ enum OperandKind : uint8_t { K_FULL = 0, K_ROWVEC = 1, K_ROWSCALAR = 2, K_TRANSP
 
 constexpr uint32_t kMaxChunksPerTask = 1024;   // unit ring holds capacity * this entries
 constexpr uint32_t kChunkElems = 16384;        // minimum elements per chunk
-constexpr uint64_t kStreamBytes = 8ull << 20; // a contiguous task that reads this much reads it with the non-temporal hint
+constexpr uint64_t kStreamBytes = 4ull << 20;      // a contiguous task that reads this much goes past the memory-side cache ...
+constexpr uint64_t kStreamRowBytes = 1ull << 20;   // ... and one by rows or pairs reads so (both: the figures above POL_PLAIN)
 constexpr uint32_t kMostChunkElems = 1u << 24; // ... and the most a context may ask for: a chunk of any path is addressed through one buffer resource
 constexpr uint32_t kNoLoad = 0x7ffffff0u;      // a buffer offset past every resource: a load there returns 0 and a store does nothing
 constexpr uint32_t kSmallTaskChunks = 4;       // a dependent task of at most this many chunks is published at once and waits in its workgroups

@@ -415,7 +415,7 @@ int pack_or_check(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_
       }
       if (ok) { rec.path = PATH_ROW2D; rec.rflags |= RF_VEC; }
     }
-    if ((uint64_t)numel * dtype_size(ops[0].dtype) * (uint64_t)ar >= kStreamBytes) rec.rflags |= RF_STREAM;
+    if ((uint64_t)numel * dtype_size(ops[0].dtype) * (uint64_t)ar >= (rec.path == PATH_CONTIG && all_aligned ? kStreamBytes : kStreamRowBytes)) rec.rflags |= RF_STREAM;
     // Rows that are contiguous in every operand, or hold one scalar per row, under up to three outer
     // dims of any strides: 16-byte accesses whatever the row length and alignment are, as long as a
     // row holds a vector.  Operands of one dtype (a COPY may convert), scalars of any. 
