@@ -1748,6 +1748,8 @@ constexpr uint32_t kRedPieceVectors = 448; // ... and vectors of a wavefront's o
 // the wavefront reads them as they come: rows of 130 to 450 vectors take the same time either way, and longer ones no LDS holds.)
 constexpr uint32_t kRedLdsSpan = 128;
 
+// Rows of 1,024 vectors and more, a quarter of each row to a wavefront: four vectors a lane are worked on while the four behind them,
+// or the next row's first, are on their way.  (Eight at a time with nothing in flight meanwhile, forty streaming operations: 101.6 us, 100.6 so.)
 template <int POL, int RIMPL, int DT>
 PATHFN void red_rows_quarter(RedArgs a) {
   const RedRun run = red_run(a);
@@ -1758,32 +1760,55 @@ PATHFN void red_rows_quarter(RedArgs a) {
   using E = Elem<DT>;
   using A = typename RedAcc<DT>::T;
   using M = Mem<POL>;
-  constexpr uint32_t V = E::V;
-  constexpr int UN = 8;
-  const uint32_t lane = tid & 63u, wave = tid >> 6;
+  constexpr uint32_t V = E::V, U = 4;
+  const uint32_t lane = tid & 63u, wave = uni(tid >> 6);
   const uint32_t n = run.n;
-  for (uint32_t row = row_begin; row < row_end; ++row) {
-    const uint32_t lo = row * n + run.skew, hi = lo + n;
-    const uint32_t j0 = lo / V, j1 = (hi - 1) / V;
-    const uint32_t span = j1 - j0 + 1, sq = (span + 3u) / 4u;          // vectors per quarter
-    const uint32_t q_begin = j0 + wave * sq;
-    const uint32_t q_end = (q_begin + sq <= j1 + 1) ? q_begin + sq : j1 + 1;
-    A a0 = red_identity<RIMPL, A>(), a1 = a0;
-    for (uint32_t v = q_begin + lane; v < q_end; v += 64 * UN) {
-      v4i q[UN];
+  const bool stream = uni(a.stream) != 0;
+  struct At { uint32_t row, v, end; };                       // 4 x 64 vectors from v on, below end, of this wavefront's quarter of a row
+  auto quarter = [&](uint32_t row) {
+    const uint32_t j0 = (row * n + run.skew) / V, j1 = (row * n + run.skew + n - 1u) / V;
+    const uint32_t sq = (j1 - j0 + 4u) / 4u, v = j0 + wave * sq;
+    return At{row, v, v + sq <= j1 + 1u ? v + sq : j1 + 1u};
+  };
+  auto behind = [&](const At& at) { return at.v + 64u * U < at.end ? At{at.row, at.v + 64u * U, at.end} : quarter(at.row + 1u); };
+  auto fetch = [&](v4i (&q)[U], const At& at) {
+    const uint32_t end = at.row < row_end ? at.end : 0u;
+    if (stream) {
 #pragma unroll
-      for (int u = 0; u < UN; ++u) q[u] = M::ld16(run.rin, (v + u * 64 < q_end) ? (v + u * 64) * 16u : kNoLoad);
+      for (uint32_t u = 0; u < U; ++u) q[u] = Mem<POL, true>::ld16(run.rin, at.v + u * 64u + lane < end ? (at.v + u * 64u + lane) * 16u : kNoLoad);
+    } else {
 #pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const uint32_t j = v + u * 64;
-        if (j < q_end) {
-          if ((u & 1) == 0) a0 = red_vector<RIMPL, DT>(q[u], j * V, lo, hi, j == j0 || j == j1, a0);
-          else a1 = red_vector<RIMPL, DT>(q[u], j * V, lo, hi, j == j0 || j == j1, a1);
-        }
+      for (uint32_t u = 0; u < U; ++u) q[u] = M::ld16(run.rin, at.v + u * 64u + lane < end ? (at.v + u * 64u + lane) * 16u : kNoLoad);
+    }
+  };
+  A a0 = red_identity<RIMPL, A>(), a1 = a0;
+  auto take = [&](const v4i (&q)[U], const At& at, uint32_t next_row) {
+    const uint32_t lo = at.row * n + run.skew, hi = lo + n, j0 = lo / V, j1 = (hi - 1u) / V;
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t j = at.v + u * 64u + lane;
+      if (j < at.end) {
+        if ((u & 1) == 0) a0 = red_vector<RIMPL, DT>(q[u], j * V, lo, hi, j == j0 || j == j1, a0);
+        else a1 = red_vector<RIMPL, DT>(q[u], j * V, lo, hi, j == j0 || j == j1, a1);
       }
     }
+    if (next_row == at.row) return;
     const A t = wave_reduce<RIMPL>(red_finish<RIMPL>(red_combine<RIMPL>(a0, a1)), 64);
-    if (lane == 0) s_part[(row - row_begin) * 4 + wave] = __builtin_bit_cast(float, t);
+    if (lane == 0) s_part[(at.row - row_begin) * 4 + wave] = __builtin_bit_cast(float, t);
+    a0 = a1 = red_identity<RIMPL, A>();
+  };
+  v4i qa[U], qb[U];
+  At at = quarter(row_begin);
+  fetch(qa, at);
+  while (true) {
+    const At b = behind(at);
+    fetch(qb, b);
+    take(qa, at, b.row);
+    if (b.row >= row_end) break;
+    at = behind(b);
+    fetch(qa, at);
+    take(qb, b, at.row);
+    if (at.row >= row_end) break;
   }
   __syncthreads();
   const uint32_t nrows = row_end - row_begin;
