@@ -601,17 +601,19 @@ int pack_or_check(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_
   // (a row fits one buffer resource; rows are read as aligned vectors whatever n and the base's alignment are)
   rec.path = (s_last == 1 && rows_contig && n * 4 < kMaxExtent) ? PATH_RED_CONTIG : PATH_RED_GENERIC;
   // A reduction writes almost nothing and its rows are a chain of memory latencies, which grow to 10-20 us while the GPU
-  // streams: a task is cut into chunks of 16 KiB, up to 32 of them, then of up to 32 KiB, up to 128 of them, before chunks grow to
-  // the regular size.  (Chunks of twice
+  // streams: a task is cut into chunks of 16 KiB, up to 32 of them, then of up to 64 KiB, up to 128 of them, and from 8 MB on into
+  // 64, before chunks grow to the regular size.  (Chunks of twice
   // the elementwise traffic whatever the task's size: a 0.2 MB reduction in a bandwidth-bound stream was two chunks and
   // took 110 us.  Forty streaming operations of 0.1-220 MB, half of them reductions, in up to 64 pieces of 16 KiB at least,
   // 64 of 32 KiB and 128 of 32 KiB: 109.5, 108.6 and 107.7 us; 24 integer operations 54.0, 53.9 and 51.1.  Smaller pieces are bound by
-  // their claims, 12 ns each one after the other whoever makes them: 143 sums of 512K bf16 elements 143 us in pieces of 16 KiB, 105 so.)
+  // their claims, 12 ns each one after the other whoever makes them: 143 sums of 512K bf16 elements 143 us in pieces of 16 KiB, 105
+  // so.  And where the queue is never empty their number costs throughput: 20,000 streaming operations 55.2 ms in 128 pieces
+  // whatever the size, 54.3 so, 53.5 in 64; but in 64 the integer operations take 49.6 us instead of 45.5.)
   // But a link of a chain of at most four regular chunks is cut into (up to) four, like an elementwise
   // one: up to those a dependent task is published at once and waits in its workgroups, beyond them
   // the dispatcher holds it back until what it waits for is done.
   const uint64_t row_bytes = (uint64_t)n * dtype_size(ops[0].dtype), total = row_bytes * (uint64_t)rows;
-  const uint64_t most = (uint64_t)chunk_elems * 24, spread = total / 128;
+  const uint64_t most = (uint64_t)chunk_elems * 24, spread = total / (total < (8ull << 20) ? 128 : 64);
   if (total >= kStreamBytes) rec.rflags |= RF_STREAM;
   uint64_t piece = total / 32;
   piece = piece < 16384 ? 16384 : piece < 32768 ? piece : 32768;
