@@ -2551,7 +2551,7 @@ DEV void softmax_held(const Record* r, uint32_t row_begin, uint32_t row_end, flo
         part[u] = t[0];
         __builtin_amdgcn_sched_barrier(0);             // (a vector at a time: interleaved they need more registers than there are)
       }
-      sum = sum * __expf(m - ref) + ((part[0] + part[1]) + part[2]);
+      sum = __builtin_fmaf(sum, __expf(m - ref), (part[0] + part[1]) + part[2]);
       m = mb;
       __builtin_amdgcn_sched_barrier(0);
     };
