@@ -54,6 +54,26 @@ def reduction_shares(code):
     return b.stream("reduction_shares_%d" % code)
 
 
+def reduction_long_rows(code):
+    """Contiguous rows that wavefronts take a quarter each of, the next vectors or the next row's first on their way: quarters of
+    one group of 4 x 64 vectors and of many, of whole groups and not, the last one shorter; one row, a few, with and
+    without a lead; inputs on both sides of 4 MB, from which on they are read past the memory-side cache."""
+    rng = np.random.default_rng(725 + code)
+    b = Builder()
+    V = 4 if code in (S.F32, S.I32) else 8
+    odt = np.int32 if code == S.I32 else np.float32
+    for rows, n, lead in ((1, 1024 * V, 0), (5, 1024 * V, 0), (3, 1024 * V + 1, 1), (4, 1025 * V - 1, 2), (2, 2047 * V + 1, 0), (7, 2048 * V, 0),
+                          (3, 4096 * V, 0), (2, 4099 * V + 3, 1), (70, 1030 * V + 2, 0), (260, 1026 * V, 0), (29, 10000 * V + 1, 0)):
+        x = b.pool(values(rng, rows * n + lead, code))[lead:].reshape(rows, n)
+        if code != S.I32:
+            nan = to_dtype(np.array([np.nan], np.float32), code)[0]
+            x[1::7, -1] = nan
+            x[3::7, 0] = nan
+        for name in ("SUM_LAST", "MAX_LAST", "MIN_LAST"):
+            b.add(name, b.pool(np.zeros(rows, odt)), [x])
+    return b.stream("reduction_long_rows_%d" % code)
+
+
 def rows_edges(code):
     """Rows contiguous in every operand under outer dims of any strides: slices read and written, head
     splits, per-row scalars of any dtype, repeated rows, unaligned bases; rows of exactly one vector, of

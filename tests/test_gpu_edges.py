@@ -21,6 +21,12 @@ def test_reductions_of_shared_out_rows(code):
 
 
 @pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16, S.I32])
+def test_reductions_of_long_rows(code):
+    stats, _ = _run_and_check(E.reduction_long_rows(code))
+    print(stats, flush=True)
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16, S.I32])
 def test_rows_at_their_edges(code):
     stats, _ = _run_and_check(E.rows_edges(code))
     print(stats, flush=True)
