@@ -619,12 +619,13 @@ int pack_or_check(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_
   piece = piece < 16384 ? 16384 : piece < 32768 ? piece : 32768;
   if (spread > piece) piece = spread < most ? spread : most;
   uint64_t rpc = piece / row_bytes;
-  if (chained && total <= kSmallTaskChunks * most) {
-    const uint64_t quarter = ((uint64_t)rows + kSmallTaskChunks - 1) / kSmallTaskChunks;
-    if (rpc < quarter) rpc = quarter;
-  }
   if (rpc < 1) rpc = 1;
   if (rpc >= 4) rpc = rpc / 4 * 4;                    // the same share of rows for each wavefront
+  if (chained && total <= kSmallTaskChunks * most) {
+    uint64_t quarter = ((uint64_t)rows + kSmallTaskChunks - 1) / kSmallTaskChunks;
+    if (quarter >= 4) quarter = (quarter + 3) / 4 * 4;       // (up: a row less in each would be a fifth chunk)
+    if (rpc < quarter) rpc = quarter;
+  }
   const uint64_t min_rpc = ((uint64_t)rows + kMaxChunksPerTask - 1) / kMaxChunksPerTask;
   if (rpc < min_rpc) rpc = min_rpc;
   rec.chunk = (uint32_t)rpc;

@@ -6,6 +6,7 @@ import os
 import re
 
 import numpy as np
+import pytest
 
 import oracle
 from paper_2604_17861_amd import runtime as R
@@ -222,6 +223,26 @@ def test_small_links_of_a_chain_stay_within_four_chunks():
     # rows too long or too few for four pieces
     assert plan((3, 60000), 1)[1] == 3 and plan((1, 300000), 1)[1] == 1
     assert plan((5, 4096), 1, np.float32)[1] == 3
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_links_of_any_number_of_rows_stay_within_four_chunks(dtype):
+    """... whatever the number of rows: also where a quarter of them is no multiple of the four wavefronts."""
+    from helpers import Builder
+    most = 8192 * 24                                              # bytes of a regular chunk of a link
+    shapes = [(100, 512), (92, 256), (20, 4096), (50, 1024), (200, 300), (1000, 50), (23, 2048), (17, 5000), (13, 5000), (1999, 3)]
+    shapes += [(rows, n) for n in (64, 256, 1024) for rows in list(range(16, 320)) + list(range(321, 2000, 7))]
+    b = Builder()
+    buf, out = b.pool(np.zeros(4 * most // 2, dtype)), b.pool(np.zeros(2000, np.float32))
+    shapes = [(rows, n) for rows, n in shapes if rows * n * np.dtype(dtype).itemsize <= 4 * most]
+    assert len(shapes) > 500
+    for rows, n in shapes:
+        b.add("SUM_LAST", out[:rows], [buf[: rows * n].reshape(rows, n)], dep=(1, 0, 0))
+    s = b.stream()
+    tasks = HostPools(s).tasks
+    for i, (rows, n) in enumerate(shapes):
+        path, chunks, per, _ = R.task_plan(tasks, i, s.impl_for()[i])
+        assert path == "RED_CONTIG" and chunks <= 4 and (chunks - 1) * per < rows <= chunks * per, (rows, n, chunks, per)
 
 
 def test_task_plan_for_row_operations():
