@@ -836,7 +836,11 @@ struct gpuos_ctx {
   // producer state
   SpinMutex prod_mu;                         // producers: ticket reservation, ring writes, doorbell, table changes
   std::mutex harvest_mu;                     // one harvester at a time
-  std::atomic<uint64_t> head{0};             // tickets written (changed under prod_mu)
+  std::atomic<uint64_t> head{0};             // tickets handed out (changed under prod_mu)
+  std::atomic<uint64_t> ready{0};            // ... those written, and all before them (changed under prod_mu): what a doorbell publishes
+  std::atomic<bool> filling{false};          // a large call writes its records outside prod_mu, up to fill_end: ready lies before it (changed under prod_mu)
+  uint64_t fill_end = 0;                     // (under prod_mu)
+  std::atomic<uint32_t> need_room{0};        // calls that need more room than that one leaves: no other is begun before them
   std::atomic<uint64_t> published{0};        // tickets behind the doorbell
   std::atomic<uint64_t> floor{0};            // completed in order
   std::atomic<int32_t> first_error{0};
@@ -963,6 +967,20 @@ __attribute__((target("movdiri"))) void direct_store_u64(uint64_t* dst, uint64_t
   _directstoreu_u64(dst, v);
 }
 
+// The tickets before `head` are handed out, and their records written unless a large call still writes its own (it says so
+// when it is done).  Caller holds prod_mu.
+void handed_out(gpuos_ctx* c, uint64_t head) {
+  c->head.store(head, std::memory_order_release);
+  if (!c->filling.load(std::memory_order_relaxed)) c->ready.store(head, std::memory_order_release);
+}
+
+// What calls that have returned have submitted (a large call that still writes may give up, but not with a ticket behind its own).
+// Caller holds prod_mu.
+uint64_t submitted(const gpuos_ctx* c) {
+  const uint64_t head = c->head.load(std::memory_order_relaxed);
+  return c->filling.load(std::memory_order_relaxed) && head == c->fill_end ? c->ready.load(std::memory_order_relaxed) : head;
+}
+
 // Publish every written ticket: time-stamp, one store-release of the tail.  Caller holds prod_mu.
 // fence_first = false: the caller has just written ONE record and not pushed it out of the
 // write-combining buffers; record and doorbell then leave with one flush.  The doorbell may land
@@ -971,7 +989,7 @@ __attribute__((target("movdiri"))) void direct_store_u64(uint64_t* dst, uint64_t
 // doorbell did land first often enough to cost the small-task streams a fifth of their rate.)
 void doorbell(gpuos_ctx* c, bool fence_first = true, bool direct = false) {
   const uint64_t pub = c->published.load(std::memory_order_relaxed);
-  const uint64_t head = c->head.load(std::memory_order_relaxed);
+  const uint64_t head = c->ready.load(std::memory_order_relaxed);
   if (pub == head) return;
   const uint64_t t = now_ns();
   for (uint64_t i = pub; i < head; ++i) c->log[i & c->log_mask].t_submit_ns = t;
@@ -984,9 +1002,11 @@ void doorbell(gpuos_ctx* c, bool fence_first = true, bool direct = false) {
   __atomic_store_n(&c->bell->tail, head, __ATOMIC_RELEASE);     // the commit: one store-release
   if (c->push) _mm_sfence();                                    // ... and push the doorbell out of the write-combining buffer
 }
-void doorbell_locked(gpuos_ctx* c) {
+// ... and what has been submitted
+uint64_t doorbell_locked(gpuos_ctx* c) {
   std::lock_guard<SpinMutex> lk(c->prod_mu);
   doorbell(c);
+  return submitted(c);
 }
 
 void bump_epoch(gpuos_ctx* c, uint32_t op_hint, bool stop) {
@@ -1051,8 +1071,7 @@ int stop_worker(gpuos_ctx* c) {
   int rc = GPUOS_OK;
   if (c->worker_running) {
     if (!worker_exited(c)) {                                  // (one that left by itself is only joined)
-      doorbell_locked(c);
-      rc = wait_floor(c, c->head.load(), c->wait_ns);         // drain
+      rc = wait_floor(c, doorbell_locked(c), c->wait_ns);     // drain
     }
     {
       std::lock_guard<SpinMutex> lk(c->prod_mu);              // the epoch is the producers' (a swap may be running)
@@ -1456,7 +1475,7 @@ constexpr size_t kAuditKeep = 65536;
 void audit(gpuos_ctx* c, uint32_t kind, uint32_t op_id, uint32_t impl_id, uint32_t version) {
   gpuos_audit_record r{};
   r.t_ns = now_ns();
-  r.head_ticket = c->head.load(std::memory_order_relaxed);
+  r.head_ticket = c->ready.load(std::memory_order_relaxed);                  // (not published yet, so they see the change)
   r.kind = kind; r.op_id = op_id; r.impl_id = impl_id; r.version = version;
   if (impl_id >= GPUOS_IMPL_PROGRAM_BASE && impl_id - GPUOS_IMPL_PROGRAM_BASE < GPUOS_MAX_PROGRAMS) {
     const uint32_t k = impl_id - GPUOS_IMPL_PROGRAM_BASE;
@@ -1519,7 +1538,7 @@ int jit_retire(gpuos_ctx* c) {
   {
     jit_set_native(c, 0, true);
     std::lock_guard<SpinMutex> lk(c->prod_mu);
-    head0 = c->head.load(std::memory_order_relaxed);
+    head0 = c->ready.load(std::memory_order_relaxed);
     doorbell(c);
   }
   // tickets from head0 on were published after the flags went down and are interpreted; earlier ones
@@ -1712,7 +1731,7 @@ int gpuos_swap_op(gpuos_ctx* c, uint32_t op_id, uint32_t impl_id, uint32_t* out_
   bump_epoch(c, op_id, false);
   __atomic_store_n(&o.impl, impl_id, __ATOMIC_RELAXED);
   __atomic_store_n(&o.version, v, __ATOMIC_RELEASE);
-  o.prev_swap_head = c->head.load(std::memory_order_relaxed);
+  o.prev_swap_head = c->ready.load(std::memory_order_relaxed);               // (what is not written yet is published after the flip)
   audit(c, impl_id == GPUOS_IMPL_FAIL ? GPUOS_AUDIT_KILL : GPUOS_AUDIT_SWAP, op_id, impl_id, v);
   if (out_version) *out_version = v;
   return GPUOS_OK;
@@ -1738,35 +1757,57 @@ inline int bound_arity(const gpuos_ctx* c, uint32_t impl) {
   return impl >= GPUOS_IMPL_PROGRAM_BASE ? (int)c->prog_arity[(impl - GPUOS_IMPL_PROGRAM_BASE) % GPUOS_MAX_PROGRAMS] : 0;
 }
 
-// A large call that publishes, with no other producer about (the caller holds prod_mu): everything is checked first, and then each
-// batch of the dispatcher's is packed, written and published by itself, so that the device begins with the first when
-// that is packed.  Nothing is enqueued if one descriptor fails: what the check takes packing takes, under the lock that the
-// operator table changes under.  The line lies at two batches: of fewer there is little to overlap and the check costs 8 ns a task.
+// A large call that publishes: everything is checked, then n tickets are taken, and then each batch of the dispatcher's is
+// packed, written and published by itself, so that the device begins with the first when that is packed.  Nothing is enqueued if one
+// descriptor fails: what the check takes packing takes, under the implementation that the check saw.  The line lies at two
+// batches: of fewer there is little to overlap and the check costs 8 ns a task.
 // 1,000 adds in one call: 86.0 us when all were packed before the first was written, 76.1 so.  Calls of 128 are left as they were:
 // one function that checks and then packs, for both, took 2 ns a task more of them (24 calls: 228 us, 232).
-// A producer that finds the lock taken packs its tasks meanwhile, as before.
-int submit_in_batches(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, Record* records, uint64_t* out_first_ticket) {
-  uint64_t head = c->head.load(std::memory_order_relaxed);
+// The lock is held to take the tickets and, a batch at a time, to publish: whoever waits, flushes or swaps passes between, and a
+// producer that comes meanwhile and finds room writes its records behind these and returns; they are published with the last of
+// these.  There is room behind these only when there is room for all of these, so a call that has to wait for room, and may give up,
+// has nothing behind it.
+// false: not begun (another such call is under way, or one waits for room), nothing has been done.
+bool submit_in_batches(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, Record* records, uint64_t* out_first_ticket, int* result) {
+  if (c->filling.load(std::memory_order_relaxed)) return false;
   for (uint32_t i = 0; i < n; ++i) {
     const gpuos_task& t = tasks[i];
-    const uint32_t impl = bound_impl(c, t.op_id);
-    if (impl == GPUOS_IMPL_NONE && !c->cfg.defer_op_check) return GPUOS_E_BADOP;
-    const int rc = check_task(t, impl == GPUOS_IMPL_NONE ? (uint32_t)GPUOS_IMPL_FAIL : impl, bound_arity(c, impl));
-    if (rc != GPUOS_OK) return rc;
-    for (int k = 0; k < 3; ++k)
-      if (t.dep[k] >= c->cap) return GPUOS_E_INVAL;
+    const uint32_t bound = bound_impl(c, t.op_id), impl = bound == GPUOS_IMPL_NONE ? (uint32_t)GPUOS_IMPL_FAIL : bound;
+    *result = bound == GPUOS_IMPL_NONE && !c->cfg.defer_op_check ? (int)GPUOS_E_BADOP : check_task(t, impl, bound_arity(c, impl));
+    for (int k = 0; k < 3 && *result == GPUOS_OK; ++k)
+      if (t.dep[k] >= c->cap) *result = GPUOS_E_INVAL;
+    if (*result != GPUOS_OK) return true;
+    records[i].impl = impl;                           // (an operator may be swapped before its task is packed)
   }
-  for (uint32_t i = 0; i < n; ++i)
-    for (int k = 0; k < 3; ++k)
-      if (tasks[i].dep[k] > head + i) return GPUOS_E_INVAL;       // names a ticket before the first one
-  if (out_first_ticket) *out_first_ticket = head;
-  LinkRun run;
+  uint64_t head;
+  {
+    std::lock_guard<SpinMutex> lk(c->prod_mu);
+    if (c->filling.load(std::memory_order_relaxed) || c->need_room.load(std::memory_order_relaxed) != 0) return false;
+    head = c->head.load(std::memory_order_relaxed);
+    for (uint32_t i = 0; i < n; ++i)
+      for (int k = 0; k < 3; ++k)
+        if (tasks[i].dep[k] > head + i) { *result = GPUOS_E_INVAL; return true; }       // names a ticket before the first one
+    if (out_first_ticket) *out_first_ticket = head;
+    c->filling.store(true, std::memory_order_relaxed);
+    c->fill_end = head + n;
+    c->head.store(head + n, std::memory_order_release);
+  }
   uint32_t summed = 0, written = 0;                   // records that are final (none of a run that is being built), and in the ring
+  auto publish = [&](bool last) {
+    std::lock_guard<SpinMutex> lk(c->prod_mu);
+    if (last && written != n) c->head.store(head + written, std::memory_order_release);      // (nothing lies behind)
+    // (at the end with what others have written behind)
+    c->ready.store(last ? c->head.load(std::memory_order_relaxed) : head + written, std::memory_order_release);
+    if (last) c->filling.store(false, std::memory_order_relaxed);
+    doorbell(c);
+  };
+  LinkRun run;
   for (uint32_t i = 0; i <= n; ++i) {
     if (i < n) {
-      const uint32_t impl = bound_impl(c, tasks[i].op_id);
-      const int rc = pack_task(tasks[i], impl == GPUOS_IMPL_NONE ? (uint32_t)GPUOS_IMPL_FAIL : impl, &records[i], c->cfg.chunk_elems, bound_arity(c, impl));
-      if (rc != GPUOS_OK) return rc;
+      const uint32_t impl = records[i].impl;
+      // (it is not refused: see above; if it were, its ticket would report an error and run nothing)
+      if (pack_task(tasks[i], impl, &records[i], c->cfg.chunk_elems, bound_arity(c, impl)) != GPUOS_OK)
+        (void)pack_task(tasks[i], GPUOS_IMPL_FAIL, &records[i]);
       records[i].ticket = 0;
       if (i == 0 || run.links(records[i - 1], records[i])) continue;
     }
@@ -1774,24 +1815,22 @@ int submit_in_batches(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, Record*
     for (; summed < i; ++summed) records[summed].check = weighted_sum(records[summed]);
     if (i < n && summed < written + kDispatchBatch) continue;
     const uint32_t end = i < n ? summed - (summed - written) % kDispatchBatch : n;
-    for (; written < end; ++written) {
-      if (head - c->floor.load(std::memory_order_acquire) >= c->cap) {
-        c->head.store(head, std::memory_order_release);
-        doorbell(c);                                  // publish so that the device can make room
-        const int rc = wait_floor(c, head - c->cap + 1, c->wait_ns);
-        if (rc != GPUOS_OK) return rc;
+    while (written < end) {
+      const uint64_t ticket = head + written;
+      if (ticket - c->floor.load(std::memory_order_acquire) >= c->cap) {
+        publish(false);                               // so that the device can make room
+        *result = wait_floor(c, ticket - c->cap + 1, c->wait_ns);
+        if (*result != GPUOS_OK) { publish(true); return true; }
       }
       Record& rec = records[written];
-      rec.check = record_check_seed(head) - rec.check;
-      std::memcpy(&c->hring[head & c->mask], &rec, sizeof(Record));
-      ++head;
-      if ((written + 1) % kDispatchBatch == 0 || written + 1 == n) {
-        c->head.store(head, std::memory_order_release);
-        doorbell(c);
-      }
+      rec.check = record_check_seed(ticket) - rec.check;
+      std::memcpy(&c->hring[ticket & c->mask], &rec, sizeof(Record));
+      ++written;
+      if (written % kDispatchBatch == 0 || written == n) publish(written == n);
     }
   }
-  return GPUOS_OK;
+  *result = GPUOS_OK;
+  return true;
 }
 
 int submit_impl(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, uint64_t* out_first_ticket, bool publish) {
@@ -1812,9 +1851,9 @@ int submit_impl(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, uint64_t* out
   } catch (const std::bad_alloc&) {                             // no exception may cross the C boundary
     return GPUOS_E_NOMEM;
   }
-  if (publish && n > 2 * kDispatchBatch && !c->cfg.nonblocking_submit && c->prod_mu.try_lock()) {
-    std::lock_guard<SpinMutex> lk(c->prod_mu, std::adopt_lock);
-    return submit_in_batches(c, tasks, n, staged.data(), out_first_ticket);
+  if (publish && n > 2 * kDispatchBatch && !c->cfg.nonblocking_submit) {
+    int rc = GPUOS_OK;
+    if (submit_in_batches(c, tasks, n, staged.data(), out_first_ticket, &rc)) return rc;
   }
   LinkRun run;
   uint32_t summed = 0;
@@ -1846,20 +1885,32 @@ int submit_impl(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, uint64_t* out
   run.close(staged.data() + n);
   for (; summed < n; ++summed) staged[summed].check = weighted_sum(staged[summed]);
   // pass 2 (one producer at a time): reserve n consecutive tickets and write the records
-  std::lock_guard<SpinMutex> lk(c->prod_mu);
+  std::unique_lock<SpinMutex> lk(c->prod_mu);
+  auto no_room = [&] { return c->head.load(std::memory_order_relaxed) + n - c->floor.load(std::memory_order_acquire) > c->cap; };
+  if (c->filling.load(std::memory_order_relaxed) && !c->cfg.nonblocking_submit && no_room()) {
+    // Room comes from what a large call has yet to publish, under this lock: it goes first.
+    c->need_room.fetch_add(1, std::memory_order_relaxed);
+    while (c->filling.load(std::memory_order_relaxed) && no_room()) {
+      lk.unlock();
+      __builtin_ia32_pause();
+      lk.lock();
+    }
+    c->need_room.fetch_sub(1, std::memory_order_relaxed);
+  }
+  const bool behind = c->filling.load(std::memory_order_relaxed);      // a large call's records, not all written: it publishes these with its last
   uint64_t head = c->head.load(std::memory_order_relaxed);
   for (uint32_t i = 0; i < n; ++i)
     for (int k = 0; k < 3; ++k)
       if (tasks[i].dep[k] > head + i) return GPUOS_E_INVAL;       // names a ticket before the first one
   if (out_first_ticket) *out_first_ticket = head;
-  const bool direct = publish && n == 1 && c->direct_store;
+  const bool direct = publish && n == 1 && c->direct_store && !behind;
   if (c->cfg.nonblocking_submit) {
     if (!c->harvester_run.load(std::memory_order_relaxed)) harvest(c);
     if ((uint64_t)n > c->cap - (head - c->floor.load(std::memory_order_acquire))) return GPUOS_E_FULL;
   }
   for (uint32_t i = 0; i < n; ++i) {
     if (head - c->floor.load(std::memory_order_acquire) >= c->cap) {
-      c->head.store(head, std::memory_order_release);
+      handed_out(c, head);
       doorbell(c);                                                // publish so that the device can make room
       const int rc = wait_floor(c, head - c->cap + 1, c->wait_ns);
       if (rc != GPUOS_OK) return rc;
@@ -1871,22 +1922,22 @@ int submit_impl(gpuos_ctx* c, const gpuos_task* tasks, uint32_t n, uint64_t* out
     ++head;
     // A batch of the dispatcher's that is to be published leaves when it is written, not behind the last one.
     // (1,000 adds in one call: 106 us a pass when the first was published behind the last, 99 so.)
-    if (publish && (i + 1) % kDispatchBatch == 0 && i + 1 < n) {
-      c->head.store(head, std::memory_order_release);
+    if (publish && !behind && (i + 1) % kDispatchBatch == 0 && i + 1 < n) {
+      handed_out(c, head);
       doorbell(c);
     }
   }
-  if (publish) {
+  if (publish && !behind) {
     // a lone record and the doorbell leave this core with one flush of its write-combining buffers,
     // or, as direct stores, with none
-    c->head.store(head, std::memory_order_release);
+    handed_out(c, head);
     doorbell(c, n > 1, direct);
     return GPUOS_OK;
   }
   // Device-memory ring: the records sit in THIS core's write-combining buffers; push them out
   // before another producer thread can ring the doorbell over them.
   if (c->push) _mm_sfence();
-  c->head.store(head, std::memory_order_release);
+  handed_out(c, head);
   return GPUOS_OK;
 }
 }  // namespace
@@ -1901,11 +1952,12 @@ int gpuos_flush(gpuos_ctx* c) {
 int gpuos_wait(gpuos_ctx* c, uint64_t ticket, uint64_t timeout_ns) {
   if (!c) return GPUOS_E_INVAL;
   MarkerRange mr(c->cfg.markers != 0, ticket == GPUOS_ALL ? "gpuos_wait all" : "gpuos_wait ticket %llu", ticket);
-  if (c->worker_running) doorbell_locked(c);
+  uint64_t everything = c->head.load(std::memory_order_acquire);
+  if (c->worker_running) everything = doorbell_locked(c);
   const bool all = ticket == GPUOS_ALL;
   const uint64_t head = c->head.load(std::memory_order_acquire);
   if (!all && ticket >= head) return GPUOS_E_INVAL;
-  const uint64_t target = all ? head : ticket + 1;
+  const uint64_t target = all ? everything : ticket + 1;
   if (c->floor.load(std::memory_order_acquire) < target) {
     if (!c->worker_running) return GPUOS_E_DEAD;
     const int rc = wait_floor(c, target, timeout_ns ? timeout_ns : c->wait_ns);
@@ -1928,7 +1980,7 @@ int gpuos_get_completions(gpuos_ctx* c, uint64_t first, uint32_t n, gpuos_comple
 int gpuos_peek_queue(gpuos_ctx* c, gpuos_queue_state* out) {
   if (!c || !out) return GPUOS_E_INVAL;
   if (c->worker_running && !c->harvester_run.load(std::memory_order_relaxed)) harvest(c);
-  out->head_submitted = c->head.load(std::memory_order_acquire);
+  out->head_submitted = c->ready.load(std::memory_order_acquire);
   out->tail_published = c->published.load(std::memory_order_acquire);
   out->claimed = c->h ? __atomic_load_n(&c->h->dispatched, __ATOMIC_ACQUIRE) : 0;
   out->completed = c->floor.load(std::memory_order_acquire);

@@ -309,12 +309,165 @@ static void large_calls_answer_as_small_ones() {
   std::printf("ok: large calls answer as small ones (%d of 600 refused)\n", refused);
 }
 
+// A large call is packed and written while other threads wait, flush, swap and submit: nothing of theirs waits for it but what
+// needs the room that it takes.
+static void other_calls_pass_a_large_one() {
+  using clock = std::chrono::steady_clock;
+  auto ms_since = [](clock::time_point t) { return std::chrono::duration<double, std::milli>(clock::now() - t).count(); };
+  {                                                       // ... that waits for room on a device that is busy
+    gpuos_ctx* c = make(64);
+    std::vector<gpuos_task> many(200, add_task(7, 256));
+    uint64_t first = ~0ull;
+    std::atomic<bool> done{false};
+    standin_stall_ms(1500);
+    std::thread large([&] { CHECK(gpuos_submit_flush(c, many.data(), 200, &first) == GPUOS_OK); done.store(true); });
+    gpuos_queue_state q;
+    do CHECK(gpuos_peek_queue(c, &q) == GPUOS_OK); while (q.tail_published < 64);
+    std::this_thread::sleep_for(std::chrono::milliseconds(20));
+    const auto t0 = clock::now();
+    CHECK(gpuos_flush(c) == GPUOS_OK);
+    CHECK(gpuos_wait(c, 0, 30ull * 1000 * 1000) == GPUOS_E_TIMEOUT);
+    CHECK(gpuos_wait(c, GPUOS_ALL, 30ull * 1000 * 1000) == GPUOS_E_TIMEOUT);
+    CHECK(gpuos_swap_op(c, 9, GPUOS_IMPL_SUB, nullptr) == GPUOS_OK);
+    CHECK(ms_since(t0) < 700 && !done.load());
+    gpuos_task t = add_task(9, 256, 1);
+    uint64_t tk = 0;
+    CHECK(gpuos_submit_flush(c, &t, 1, &tk) == GPUOS_OK && tk == 200);       // (waits for its room)
+    large.join();
+    CHECK(first == 0 && gpuos_wait(c, GPUOS_ALL, 0) == GPUOS_OK);
+    std::vector<gpuos_completion> comp(201);
+    CHECK(gpuos_get_completions(c, 0, 201, comp.data()) == GPUOS_OK);
+    for (uint64_t i = 0; i <= 200; ++i) CHECK(comp[i].ticket == i && comp[i].status == 0 && comp[i].op_version == (i < 200 ? 1u : 2u));
+    CHECK(gpuos_shutdown(c) == GPUOS_OK);
+  }
+  {                                                       // ... that is being written: a call behind it returns first
+    gpuos_ctx* c = make(65536);
+    std::vector<gpuos_task> many(60000, add_task(7, 256));
+    uint64_t head = 0;
+    bool passed = false;
+    for (int trial = 0; trial < 20 && !passed; ++trial) {
+      std::atomic<bool> done{false};
+      std::thread large([&] { uint64_t tk = 0; CHECK(gpuos_submit_flush(c, many.data(), 60000, &tk) == GPUOS_OK && tk == head); done.store(true); });
+      gpuos_queue_state q;
+      do CHECK(gpuos_peek_queue(c, &q) == GPUOS_OK); while (q.head_submitted == head);
+      gpuos_task t[3] = {add_task(9, 256, 1), add_task(9, 256, 1), add_task(9, 256, 1)};
+      uint64_t tk = 0;
+      CHECK((trial & 1 ? gpuos_submit(c, t, 3, &tk) : gpuos_submit_flush(c, t, 3, &tk)) == GPUOS_OK && tk == head + 60000);
+      passed = !done.load();
+      CHECK(gpuos_wait(c, tk + 2, 0) == GPUOS_OK);
+      large.join();
+      head += 60003;
+    }
+    CHECK(passed);
+    CHECK(gpuos_wait(c, GPUOS_ALL, 0) == GPUOS_OK);
+    CHECK(gpuos_shutdown(c) == GPUOS_OK);
+  }
+  {                                                       // ... that gives up: what is written keeps its tickets
+    gpuos_config cfg;
+    gpuos_default_config(&cfg);
+    cfg.wait_timeout_ms = 400;
+    gpuos_ctx* c = nullptr;
+    CHECK(gpuos_init(&c, 64, &cfg) == GPUOS_OK);
+    CHECK(gpuos_register_op(c, 7, GPUOS_IMPL_ADD, nullptr) == GPUOS_OK);
+    std::vector<gpuos_task> many(200, add_task(7, 256));
+    uint64_t tk = ~0ull;
+    standin_stall_ms(1600);
+    CHECK(gpuos_submit_flush(c, many.data(), 200, &tk) == GPUOS_E_TIMEOUT && tk == 0);
+    gpuos_queue_state q;
+    CHECK(gpuos_peek_queue(c, &q) == GPUOS_OK && q.head_submitted == 64 && q.tail_published == 64);
+    CHECK(gpuos_wait(c, GPUOS_ALL, 5000ull * 1000 * 1000) == GPUOS_OK);
+    standin_leave_before(150);                            // (64 are done)
+    CHECK(gpuos_submit_flush(c, many.data(), 200, &tk) == GPUOS_E_DEAD && tk == 64);
+    CHECK(gpuos_peek_queue(c, &q) == GPUOS_OK && q.completed == 150 && q.head_submitted >= 150 && q.head_submitted <= 150 + 64);
+    CHECK(q.tail_published == q.head_submitted);
+    CHECK(gpuos_start_worker(c) == GPUOS_OK);
+    CHECK(gpuos_submit_flush(c, many.data(), 200, &tk) == GPUOS_OK && tk == q.head_submitted);
+    CHECK(gpuos_wait(c, GPUOS_ALL, 5000ull * 1000 * 1000) == GPUOS_OK);
+    CHECK(gpuos_shutdown(c) == GPUOS_OK);
+  }
+  CHECK(standin_errors() == 0);
+  std::printf("ok: other calls pass a large one\n");
+}
+
+// Producers of small and of large calls, waits and swaps beside them: every ticket once, in one piece per call, versions in order.
+static void large_and_small_producers() {
+  for (uint32_t cap : {64u, 512u, 4096u})
+    for (int harv = 0; harv < 2; ++harv) {
+      gpuos_ctx* c = make(cap, false, harv != 0);
+      const int n_threads = 4, per_thread = 6000;
+      std::vector<std::vector<std::pair<uint64_t, uint32_t>>> calls(n_threads);
+      std::vector<std::thread> th;
+      std::atomic<int> failures{0}, running{n_threads};
+      for (int k = 0; k < n_threads; ++k)
+        th.emplace_back([&, k] {
+          unsigned s = 71u * (unsigned)k + 5u;
+          uint32_t left = per_thread;
+          while (left > 0) {
+            s = s * 1664525u + 1013904223u;
+            uint32_t m = k % 2 ? 129 + (s >> 16) % 400u : 1 + (s >> 16) % 5u;
+            if (m > left) m = left;
+            std::vector<gpuos_task> v(m, add_task(9, 300 + (s >> 20), 1));
+            v[0].dep[0] = 0;
+            for (uint32_t i = 0; i < m; i += 1 + (s >> 28)) v[i].op_id = 7;
+            uint64_t first = ~0ull;
+            if (((s >> 4) % 3u ? gpuos_submit_flush(c, v.data(), m, &first) : gpuos_submit(c, v.data(), m, &first)) != GPUOS_OK) { failures++; break; }
+            calls[k].push_back({first, m});
+            if ((s >> 8) % 7u == 0 && gpuos_wait(c, first + m - 1, 0) != GPUOS_OK) { failures++; break; }
+            left -= m;
+          }
+          running--;
+        });
+      uint32_t v = 1;
+      std::vector<uint64_t> own;
+      while (running.load() > 0) {
+        CHECK(gpuos_swap_op(c, 7, v % 2 ? GPUOS_IMPL_SUB : GPUOS_IMPL_ADD, &v) == GPUOS_OK);
+        gpuos_task t = add_task(7, 256);
+        own.push_back(0);
+        CHECK(gpuos_submit_flush(c, &t, 1, &own.back()) == GPUOS_OK);
+        // (the stand-in has read this version then, and reads no entry while the next is written)
+        CHECK((v % 2 ? gpuos_wait(c, own.back(), 0) : gpuos_wait(c, GPUOS_ALL, 0)) == GPUOS_OK);
+      }
+      for (auto& t : th) t.join();
+      CHECK(failures.load() == 0);
+      CHECK(gpuos_wait(c, GPUOS_ALL, 0) == GPUOS_OK);
+      const uint64_t total = (uint64_t)n_threads * per_thread + own.size();
+      std::vector<int> seen(total, 0);
+      for (uint64_t t : own) { CHECK(t < total); seen[t]++; }
+      for (auto& q : calls) for (auto& f : q) for (uint64_t t = f.first; t < f.first + f.second; ++t) { CHECK(t < total); seen[t]++; }
+      for (uint64_t t = 0; t < total; ++t) CHECK(seen[t] == 1);
+      gpuos_queue_state q;
+      CHECK(gpuos_peek_queue(c, &q) == GPUOS_OK && q.head_submitted == total && q.tail_published == total && q.completed == total);
+      std::vector<gpuos_completion> comp(total);
+      CHECK(gpuos_get_completions(c, 0, (uint32_t)total, comp.data()) == GPUOS_OK);
+      uint32_t last = 1;
+      for (uint64_t t = 0; t < total; ++t) {
+        CHECK(comp[t].ticket == t && comp[t].status == 0 && comp[t].t_done_ns >= comp[t].t_submit_ns);
+        if (comp[t].op_version != 1) { CHECK(comp[t].op_version >= last); last = comp[t].op_version; }
+      }
+      uint64_t n_log = 0;
+      CHECK(gpuos_audit_log(c, 0, 0, nullptr, &n_log) == GPUOS_OK);
+      std::vector<gpuos_audit_record> log(n_log);
+      CHECK(gpuos_audit_log(c, 0, (uint32_t)n_log, log.data(), nullptr) == GPUOS_OK);
+      // (operator 9 keeps version 1; a task of operator 7 from a swap's ticket on has that version or a later one)
+      for (size_t i = 1; i < log.size(); ++i) {
+        CHECK(log[i].head_ticket >= log[i - 1].head_ticket);
+        if (log[i].kind == GPUOS_AUDIT_SWAP)
+          for (uint64_t t = log[i].head_ticket; t < total && t < log[i].head_ticket + 600; ++t) CHECK(comp[t].op_version == 1 || comp[t].op_version >= log[i].version);
+      }
+      CHECK(gpuos_shutdown(c) == GPUOS_OK);
+      CHECK(standin_errors() == 0);
+    }
+  std::printf("ok: producers of small and of large calls\n");
+}
+
 int main() {
   check_word_rejects_mixtures();
   block_cuts_stay_below_the_offset_that_does_nothing();
   runs_are_marked();
   chunks_stay_addressable();
   large_calls_answer_as_small_ones();
+  other_calls_pass_a_large_one();
+  large_and_small_producers();
   // 1. many producers, tiny rings: every ticket exactly once, consecutive inside a call, in-order log
   for (uint32_t cap : {2u, 8u, 64u}) {
     for (int harv = 0; harv < 2; ++harv) {
