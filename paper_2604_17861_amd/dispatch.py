@@ -55,6 +55,7 @@ from math import prod
 
 import numpy as np
 import torch
+from torch._prims_common import compute_elementwise_output_strides
 from torch.utils._python_dispatch import TorchDispatchMode
 
 from . import runtime as R
@@ -132,6 +133,7 @@ class GpuosMode(TorchDispatchMode):
         self._writer = {}                # storage address -> newest pending ticket that writes it
         self._inflight = deque()         # (ticket, tensors kept alive, storage addresses)
         self._seen = {}                  # context filter: signature -> sightings
+        self._layouts = {}               # (result shape, inputs' shapes and strides) -> layout of an elementwise result
         self._dirty = True               # PyTorch may have work in flight on its stream
         self.stats = dict(redirected=0, fallback_type=0, fallback_size=0, fallback_context=0, fallback_load=0,
                           fallback_paused=0, views=0, stream_syncs=0, host_waits=0, submits=0, pauses=0, resumes=0,
@@ -311,11 +313,31 @@ class GpuosMode(TorchDispatchMode):
             torch.cuda.current_stream(self.device).synchronize()
             self.stats["stream_syncs"] += 1
         self._dirty = False
-        out = torch.empty(p.out_shape, dtype=p.out_dtype, device=self.device)
-        self._stage(p, out)
+        layout = self._out_layout(p)
+        if layout is None:
+            out = torch.empty(p.out_shape, dtype=p.out_dtype, device=self.device)
+            self._stage(p, out, p.size, p.inputs, out)
+        else:                                            # described in the order of the result's dims in memory
+            stride, order = layout
+            out = torch.empty_strided(p.out_shape, stride, dtype=p.out_dtype, device=self.device)
+            self._stage(p, out, tuple(p.size[d] for d in order), [t.expand(p.size).permute(order) for t in p.inputs], out.permute(order))
         self.stats["redirected"] += 1
         self.stats["by_op"][p.impl] = self.stats["by_op"].get(p.impl, 0) + 1
         return out
+
+    def _out_layout(self, p):
+        """The strides PyTorch gives an elementwise result and the order of its dims in memory (None: contiguous, as it is of
+        contiguous operands).  What PyTorch does with it next, a matrix product say, then runs on the layout it would have had."""
+        if p.reduce or p.impl == "SOFTMAX_LAST" or all(t.is_contiguous() for t in p.inputs):
+            return None
+        key = (p.size, *((t.shape, t.stride()) for t in p.inputs))
+        if key not in self._layouts:                     # (65 us: kept by shape and strides)
+            if len(self._layouts) >= 4096:
+                self._layouts.clear()
+            stride = tuple(compute_elementwise_output_strides(*(t.expand(p.size) for t in p.inputs)))
+            order = sorted(range(len(stride)), key=lambda d: -stride[d])
+            self._layouts[key] = None if order == list(range(len(stride))) else (stride, order)
+        return self._layouts[key]
 
     def _room(self):
         if self._next is None:
@@ -346,15 +368,16 @@ class GpuosMode(TorchDispatchMode):
                 mask |= 1 << d
         return (ptr, *st, _DT[t.dtype], mask)
 
-    def _stage(self, p, out):
-        size = p.size if p.size else (1,)                  # a 0-dim tensor iterates as [1]
+    def _stage(self, p, out, size, inputs, result):
+        """p into `out`, as `result` from `inputs` over `size`: the same tensors, their dims in any order."""
+        size = size if size else (1,)                      # a 0-dim tensor iterates as [1]
         nd = len(size)
         if p.reduce and nd == 1:
             size, nd = (1,) + size, 2                      # a vector reduces as one row
         me = (self._next if self._next is not None else 0) + self._staged
         writer, touch, cap = self._writer, self._touch, self.capacity
         deps, ops, keys = [], [], []
-        for t in p.inputs:
+        for t in inputs:
             ptr = t.data_ptr()
             k = ptr - t.storage_offset() * _ITEMSIZE[t.dtype]                # the storage's address
             w = writer.get(k)
@@ -375,7 +398,7 @@ class GpuosMode(TorchDispatchMode):
                 acc *= size[d]
             o = (ko, *ost, _DT[out.dtype], 0)
         else:
-            o = self._operand(out, ko, size, nd)
+            o = self._operand(result, ko, size, nd)
         while len(ops) < 3:
             ops.append(_NO_TENSOR)
         while len(deps) < 3:

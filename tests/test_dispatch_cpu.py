@@ -360,3 +360,39 @@ def test_parameters_are_plain_tensors_and_autograd_still_works():
     with m:
         z = t + t
     assert m.stats["redirected"] == 0 and torch.equal(torch.Tensor(z), torch.Tensor(t) * 2)
+
+
+def test_results_are_laid_out_as_eager_lays_them_out():
+    """Strides of elementwise results: of transposed, permuted, sliced and broadcast operands, and what is computed from them."""
+    rng = random.Random(5)
+
+    def view(shape):
+        n = len(shape)
+        order = rng.sample(range(n), n)
+        kind = rng.randrange(4)
+        step = [rng.choice([1, 2]) if kind == 1 else 1 for _ in range(n)]
+        full = [1 if kind == 2 and rng.random() < 0.4 else shape[d] for d in range(n)]
+        t = torch.randn([full[d] * step[d] for d in order])
+        t = t.permute([order.index(d) for d in range(n)])[tuple(slice(None, None, k) for k in step)]
+        return t.expand(shape) if kind == 2 and rng.random() < 0.5 else t
+
+    def program(a, b):
+        y = a * b
+        z = torch.relu(a) - b.abs()
+        return y, z, z * 2.0, (y + z) / (b.abs() + 1.0), y.sum(-1)
+
+    kinds = set()
+    for trial in range(150):
+        shape = [rng.choice([1, 2, 3, 5, 8]) for _ in range(rng.randint(1, 4))]
+        a, b = view(shape), view(shape)
+        want = program(a, b)
+        m = mode(trial, batch=4)
+        with m:
+            got = program(a, b)
+        assert m.stats["fallback_type"] == 0
+        for g, w in zip(got[:-1], want[:-1]):
+            layout = [[st for st, n in zip(t.stride(), shape) if n > 1] for t in (g, w)]     # (of a dim of one element it means nothing)
+            assert layout[0] == layout[1] and torch.equal(g, w), (shape, a.stride(), b.stride(), g.stride(), w.stride())
+            kinds.add(w.is_contiguous())
+        torch.testing.assert_close(got[-1], want[-1])
+    assert kinds == {True, False}
