@@ -203,6 +203,28 @@ def long_softmax_rows(code):
     return b.stream("long_softmax_rows_%d" % code)
 
 
+def long_softmax_rows_whole_and_not(code):
+    """The same lengths, each with less, as many and more elements than its whole vectors hold, each at every alignment: rows of
+    whole aligned vectors among them at every length, with as many and with one vector more."""
+    rng = np.random.default_rng(760 + code)
+    b = Builder()
+    V = 4 if code == S.F32 else 8
+    dt = np_dtype(code)
+    lengths = [16 * 256, 21 * 256, 22 * 256, 24 * 256, 27 * 256] if code == S.F32 else [8 * 256, 12 * 256, 14 * 256, 15 * 256, 21 * 256, 24 * 256]
+    for vectors in lengths:
+        for more in (-1, 0, 1, V, 2 * V + 3):
+            for x_at, o_at in ((0, 0), (1, 1), (V - 1, V - 1), (0, 1)):
+                n = vectors * V + more
+                if n <= 16384:
+                    continue
+                x = b.pool(values(rng, 2 * n + x_at, code, 3.0))[x_at:].reshape(2, n)
+                if code != S.BF16:
+                    x[0, 0] = x[0, -1] = -np.inf
+                    x[1, : n // 2] = -np.inf
+                b.add("SOFTMAX_LAST", b.pool(np.zeros(2 * n + o_at, dt))[o_at:].reshape(2, n), [x])
+    return b.stream("long_softmax_rows_whole_and_not_%d" % code)
+
+
 def large_gathers():
     """Gathered tasks of more elements than 1,024 of the gather path's regular chunks hold: a product
     with every other column of a matrix, and a stride-2 slice of 16-bit elements.  (A chunk never run

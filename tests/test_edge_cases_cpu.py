@@ -193,3 +193,16 @@ def test_rows_up_to_the_last_addressable_byte(op):
             st = {"SOFTMAX_LAST": [[n, 1]], "MASKED_SOFTMAX_LAST": [[n, 1], [0, 1]], "LAYERNORM_LAST": [[n, 1], [0, 1], [0, 1]]}[op]
             path = plan_of(op, [rows, n], [(at[k], s, S.F32) for k, s in enumerate(st)], (at[3], [n, 1], S.F32), alpha=1.0)[0]
             assert path == want, (op, rows, n, path)
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_long_softmax_rows_are_whole_and_ragged_at_every_length(code):
+    s = E.long_softmax_rows_whole_and_not(code)
+    assert not stream_extent_violations(s)
+    V, longest = (4, 21 * 256) if code == S.F32 else (8, 15 * 256)       # vectors that registers and LDS hold with fewer batches
+    seen = {"ROW_FUSED": set(), "ROW_RAGGED": set()}
+    for (path, _, _, _), size in zip(plans(s), s.tasks["size"]):
+        seen[path].add(-(-int(size[1]) // V))
+    for vectors in seen.values():
+        assert min(vectors) <= longest < max(vectors) and {longest, longest + 1} <= vectors
+    run_oracle(s)

@@ -260,3 +260,10 @@ def test_long_softmax_rows_at_every_alignment(code):
     for k, first, count in outs:
         words = got[k].view(np.uint32 if code == S.F32 else np.uint16)
         assert not words[:first].any() and not words[first + count:].any()
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16])
+def test_long_softmax_rows_whole_and_not(code):
+    """Whole aligned rows on both sides of every length at which more is kept of a row, and the same lengths at other alignments."""
+    stats, _ = _run_and_check(E.long_softmax_rows_whole_and_not(code))
+    print(stats, flush=True)
