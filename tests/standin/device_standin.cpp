@@ -30,7 +30,7 @@ struct Worker {
 };
 std::mutex g_mu;
 std::map<void*, Worker*> g_workers;               // by stream
-std::atomic<uint64_t> g_errors{0}, g_records{0}, g_retries{0}, g_links{0};
+std::atomic<uint64_t> g_errors{0}, g_records{0}, g_retries{0}, g_links{0}, g_streams{0};
 std::atomic<uint64_t> g_alloc_calls{0};             // calls of the allocating / freeing / creating HIP entry points
 alignas(256) unsigned char g_scratch[gpuos::kStaticScratchBytes];   // stands in for the library's file-scope device array
 // Test hook: the consumer leaves "by itself" (exit code 2, as after an idle time-out) in front of this
@@ -90,6 +90,7 @@ void consumer(gpuos::WorkerArgs a, Worker* w) {
           if (table[rec.op_id].impl == GPUOS_IMPL_FAIL) status = GPUOS_E_BADOP;
           if (rec.nchunks == 0 || rec.nchunks > kMaxChunksPerTask) g_errors.fetch_add(1);
           if (rec.rflags & RF_LINK) g_links.fetch_add(1);
+          if (rec.rflags & RF_STREAM) g_streams.fetch_add(1);
           // a chunk's elements are addressed by 32-bit byte offsets below kNoLoad
           const uint64_t es = rec.dtype[3] == GPUOS_F32 || rec.dtype[3] == GPUOS_I32 ? 4 : 2;
           const uint64_t units = rec.chunk < rec.numel ? rec.chunk : rec.numel;
@@ -130,6 +131,7 @@ extern "C" {
 uint64_t standin_errors() { return g_errors.load(); }
 uint64_t standin_records() { return g_records.load(); }
 uint64_t standin_links() { return g_links.load(); }
+uint64_t standin_streams() { return g_streams.load(); }
 uint64_t standin_retries() { return g_retries.load(); }
 void standin_leave_before(uint64_t ticket) { g_leave_before.store(ticket); }
 void standin_stall_ms(uint32_t ms) { g_stall_ms.store(ms); }

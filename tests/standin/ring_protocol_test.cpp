@@ -19,6 +19,7 @@ extern "C" void standin_leave_before(uint64_t ticket);
 extern "C" void standin_stall_ms(uint32_t ms);
 extern "C" uint64_t standin_records();
 extern "C" uint64_t standin_links();
+extern "C" uint64_t standin_streams();
 extern "C" uint64_t standin_alloc_calls();
 extern "C" void standin_scratch_dirty();
 extern "C" uint64_t standin_scratch_nonzero(uint64_t n);
@@ -309,6 +310,54 @@ static void large_calls_answer_as_small_ones() {
   std::printf("ok: large calls answer as small ones (%d of 600 refused)\n", refused);
 }
 
+// What reads past the memory-side cache (RF_STREAM): by the bytes of each operand, in its own dtype, what is broadcast counted once.
+static void large_reads_are_marked() {
+  gpuos_ctx* c = make(64);
+  CHECK(gpuos_register_op(c, 40, GPUOS_IMPL_COPY, nullptr) == GPUOS_OK);
+  CHECK(gpuos_register_op(c, 41, GPUOS_IMPL_SUM_LAST, nullptr) == GPUOS_OK);
+  struct In { uint8_t dtype; int64_t s0, s1; uint64_t ptr; };
+  auto marked = [&](uint16_t op, int64_t rows, int64_t cols, std::vector<In> in, uint8_t out_dtype) {
+    gpuos_task t = add_task(op, 1);
+    t.ndim = 2; t.n_inputs = (uint8_t)in.size();
+    t.size[0] = rows; t.size[1] = cols;
+    for (size_t k = 0; k < in.size(); ++k) {
+      t.in[k].ptr = (void*)(uintptr_t)in[k].ptr; t.in[k].dtype = in[k].dtype;
+      t.in[k].stride[0] = in[k].s0; t.in[k].stride[1] = in[k].s1;
+    }
+    t.out.ptr = (void*)(uintptr_t)0x90000000; t.out.dtype = out_dtype;
+    t.out.stride[0] = op == 41 ? 1 : cols; t.out.stride[1] = op == 41 ? 0 : 1;
+    const uint64_t before = standin_streams();
+    uint64_t tk = 0;
+    CHECK(gpuos_submit_flush(c, &t, 1, &tk) == GPUOS_OK && gpuos_wait(c, tk, 0) == GPUOS_OK);
+    return standin_streams() != before;
+  };
+  const uint64_t A = 0x10000000, B = 0x30000000;
+  const int64_t M = 1 << 20;
+  // rows of 513: by rows, from 1 MB on
+  for (auto rows : {300, 600}) {                          // 0.6 and 1.2 MB of fp32
+    const bool big = rows == 600;
+    CHECK(marked(7, rows, 513, {{GPUOS_F32, 513, 1, A}, {GPUOS_F32, 0, 1, B}}, GPUOS_F32) == big);           // + a row vector
+    CHECK(marked(7, rows, 513, {{GPUOS_F32, 0, 1, B}, {GPUOS_F32, 513, 1, A}}, GPUOS_F32) == big);
+    CHECK(marked(7, rows, 513, {{GPUOS_F32, 513, 1, A}, {GPUOS_F32, 1, 0, B}}, GPUOS_F32) == big);           // + a scalar per row
+    CHECK(marked(7, 2 * rows, 513, {{GPUOS_BF16, 513, 1, A}, {GPUOS_F32, 1, 0, B}}, GPUOS_BF16) == big);
+    CHECK(marked(7, 2 * rows, 513, {{GPUOS_F32, 1, 0, B}, {GPUOS_BF16, 513, 1, A}}, GPUOS_BF16) == big);     // (the first input's dtype is not all there is)
+    CHECK(marked(7, rows, 513, {{GPUOS_F32, 513, 1, A + 4}, {GPUOS_F32, 513, 1, B}}, GPUOS_F32));            // two full operands, unaligned
+  }
+  // contiguous and aligned: from 4 MB on
+  CHECK(!marked(7, 1, M / 2 - 4, {{GPUOS_F32, M, 1, A}, {GPUOS_F32, M, 1, B}}, GPUOS_F32));
+  CHECK(marked(7, 1, M / 2, {{GPUOS_F32, M, 1, A}, {GPUOS_F32, M, 1, B}}, GPUOS_F32));
+  CHECK(!marked(41, 1024, 1020, {{GPUOS_F32, 1020, 1, A}}, GPUOS_F32));
+  CHECK(marked(41, 1024, 1024, {{GPUOS_F32, 1024, 1, A}}, GPUOS_F32));
+  // casts, by rows whatever their alignment: what is read counts
+  CHECK(!marked(40, 1, M / 4 - 8, {{GPUOS_F32, M, 1, A}}, GPUOS_BF16));
+  CHECK(marked(40, 1, M / 4, {{GPUOS_F32, M, 1, A}}, GPUOS_BF16));
+  CHECK(!marked(40, 1, M / 2 - 8, {{GPUOS_BF16, M, 1, A}}, GPUOS_F32));
+  CHECK(marked(40, 1, M / 2, {{GPUOS_BF16, M, 1, A}}, GPUOS_F32));
+  CHECK(gpuos_shutdown(c) == GPUOS_OK);
+  CHECK(standin_errors() == 0);
+  std::printf("ok: large reads are marked\n");
+}
+
 // A large call is packed and written while other threads wait, flush, swap and submit: nothing of theirs waits for it but what
 // needs the room that it takes.
 static void other_calls_pass_a_large_one() {
@@ -466,6 +515,7 @@ int main() {
   runs_are_marked();
   chunks_stay_addressable();
   large_calls_answer_as_small_ones();
+  large_reads_are_marked();
   other_calls_pass_a_large_one();
   large_and_small_producers();
   // 1. many producers, tiny rings: every ticket exactly once, consecutive inside a call, in-order log
