@@ -44,9 +44,13 @@ namespace gpuos {
 //
 // The non-temporal hint (nt) keeps a line out of the memory-side cache (256 MB): what the next operation reads
 // is then in memory, and the parts of a line that two stores write each go there by themselves.  So:
-//   * elementwise operations and reductions store without it, and load with it where a task reads much (RF_STREAM: 4 MB, 1 MB
-//     where it goes by rows or pairs), so that it leaves what is there in place; of contiguous tensors, whose stores are
-//     whole lines, such a task stores with it too;
+//   * contiguous aligned elementwise operations load and store with it (their stores are whole lines) where a task reads much
+//     (RF_STREAM: 4 MB; EXP, DIV and SUB_EXP 16 MB), so that it leaves what is there in place; both GELUs never, they are bound
+//     by their instructions;
+//   * those by rows or by pairs load with it from 1 MB on and store without; ROW2D, transposed tiles and the gather path have
+//     it on nothing;
+//   * reductions load with it from 4 MB on, of whole aligned rows of up to 64 vectors from 16 MB on, of rows that go by way of
+//     the LDS never;
 //   * runs have it on nothing (each link's result is read by no one but may be, their inputs are the chain's);
 //   * row operations store with it and load without: the rows' readers are a matrix product away, and the inputs stay.
 // Measured against nt on every 16-byte access, three sets of buffers in turn / one set over and over: 24 chains of six
@@ -55,6 +59,11 @@ namespace gpuos {
 // columns 139 and 134 / 139 and 117; forty streaming operations of 503 MB 110.3 and 111.6 / 110 and 95.7.  With the stores of large
 // contiguous tasks, and 4 MB and 1 MB in place of 8, those took 101.2 / 98.8, the layout changes 53.1 / 50.5, and 20,000 streaming
 // operations over 4 GB of inputs 55.5 ms instead of 57.7.  (From 2 MB on everywhere: 101.5 / 101.4, layout changes 55.7.)
+// Streams of one operation, 1-4 GB in tasks of 8M elements, without it and with it: DIV and SUB_EXP fp32 590 and 547 us, 16-bit 298 and
+// 282; EXP fp32 779 and 759; an interpreted addition 611 and 561; sums of 24 fp32 451 and 411, of 256 fp32 413 and 359, of 256 bf16 220 and
+// 189.  The 16 MB: on buffers used over and over EXP of 8 MB takes 22.5 us with it, 21.7 without, four of 16 MB 36.9 and
+// 37.9; DIV of 8 MB 21.2 and 20.7, of 64 MB 79.4 and 83.5.  ROW2D of 4 GB: 726 and 729 on every access, in tasks of 2 MB 487 and 479.
+// By rows, on stores too: rows of 2,049 fp32 less a scalar each 928 and 972, of 1,025 bf16 in tasks of 1 MB 378 and 371.
 // ---------------------------------------------------------------------------
 enum { POL_PLAIN = 0, POL_COHERENT = 1 };
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -644,9 +653,8 @@ PATHFN void ew_contig(const Record* r_v, uint32_t begin_v, uint32_t end_v, uint3
         ew_vectors<IMPL, DT, U>(Arg{qa}, Arg{qb}, Arg{qc}, alpha, [&](int u, const v4i& q) { ML::st16(ro, (v + u * kThreads) * 16u, q); });
       }
     };
-    // (operators of many instructions are bound by those; of native programs, functors past the last id, nothing is known: a stream of them was 5 % slower without)
-    constexpr bool SHORT = IMPL == GPUOS_IMPL_ADD || IMPL == GPUOS_IMPL_SUB || IMPL == GPUOS_IMPL_MUL || IMPL == GPUOS_IMPL_RELU ||
-                           IMPL == GPUOS_IMPL_SCALE || IMPL == GPUOS_IMPL_FMA || IMPL == GPUOS_IMPL_COPY || IMPL > kImplProg3;
+    // (both GELUs are bound by their instructions and take the same time either way)
+    constexpr bool SHORT = IMPL != GPUOS_IMPL_GELU_ERF && IMPL != GPUOS_IMPL_GELU_TANH;
     if (SHORT && (uni(r->rflags) & RF_STREAM) != 0) batches(Mem<POL, SHORT, SHORT>{});
     else batches(M{});
     for (; v < nvec; v += kThreads) {
@@ -1897,14 +1905,14 @@ PATHFN void red_rows_lds(RedArgs a) {
 // The same when every row is a whole number of vectors and starts on one (the attention shapes: rows
 // of 64 / 128 / 256 16-bit elements): no edges to mask and nothing to remember per pass but the
 // loaded vector, so eight passes stay in registers.
-template <int POL, int RIMPL, int DT>
+template <int POL, int RIMPL, int DT, bool LOADS_NT>
 PATHFN void red_rows_short_aligned(RedArgs a) {
   const RedRun run = red_run(a);
   const uint32_t tid = a.tid;
   const uint32_t odt = uni(a.odt), row_begin = uni(a.row_begin), row_end = uni(a.row_end), vpr = uni(a.max_span);
   using E = Elem<DT>;
   using A = typename RedAcc<DT>::T;
-  using M = Mem<POL>;
+  using M = Mem<POL, LOADS_NT>;
   constexpr uint32_t UP = 8;
   const uint32_t lane = tid & 63u, wave = uni(tid >> 6);
   uint32_t P = 1;                                     // lanes per row: power of two >= vectors per row
@@ -1971,7 +1979,8 @@ DEV void red_contig(const Record* r, uint32_t row_begin, uint32_t row_end, float
   a.stream = uni(r->rflags) & RF_STREAM; a.odt = uni(r->dtype[3]); a.row_begin = row_begin; a.row_end = row_end; a.s_part = s_part; a.tid = tid;
   const bool whole = n % V == 0 && a.lead == 0;       // every row is whole vectors
   a.max_span = whole ? n / V : (n + V - 2) / V + 1;
-  if (a.max_span <= 64u && whole) red_rows_short_aligned<POL, RIMPL, DT>(a);
+  // (an executor for either form of load: where one chose at each round of loads, rows of 24 bf16, 1.1 GB, took 322 us instead of 257)
+  if (a.max_span <= 64u && whole) { if (a.stream) red_rows_short_aligned<POL, RIMPL, DT, true>(a); else red_rows_short_aligned<POL, RIMPL, DT, false>(a); }
   else if (a.max_span <= kRedLdsSpan) red_rows_lds<POL, RIMPL, DT>(a);
   else if (a.max_span >= 1024u && row_end - row_begin <= kRedPartialRows) red_rows_quarter<POL, RIMPL, DT>(a);
   else red_rows_stream<POL, RIMPL, DT>(a);

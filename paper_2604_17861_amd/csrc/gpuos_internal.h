@@ -42,7 +42,7 @@ enum RecFlag : uint8_t {
   RF_INT = 4,            // all tensors are I32
   RF_DEPS_RESOLVED = 8,  // set by the dispatcher: published only after the dependencies completed
   RF_PAIRS = 32,         // PATH_STAGED: one dim, every operand of one dtype, inputs contiguous or every second element
-  RF_STREAM = 64,        // inputs too large to leave in the memory-side cache (kStreamBytes)
+  RF_STREAM = 64,        // reads so much that it goes past the memory-side cache (kStreamBytes and those after it)
   RF_LINK = 16           // may be run by the workgroup that has just run the same chunk of the ticket right before (see LinkRun)
 };
 
@@ -53,6 +53,7 @@ constexpr uint32_t kMaxChunksPerTask = 1024;   // unit ring holds capacity * thi
 constexpr uint32_t kChunkElems = 16384;        // minimum elements per chunk
 constexpr uint64_t kStreamBytes = 4ull << 20;      // a contiguous task that reads this much goes past the memory-side cache ...
 constexpr uint64_t kStreamRowBytes = 1ull << 20;   // ... and one by rows or pairs reads so (both: the figures above POL_PLAIN)
+constexpr uint64_t kStreamLargeBytes = 16ull << 20;   // ... EXP, DIV, SUB_EXP and reductions of rows of up to 1 KB from this on
 constexpr uint32_t kMostChunkElems = 1u << 24; // ... and the most a context may ask for: a chunk of any path is addressed through one buffer resource
 constexpr uint32_t kNoLoad = 0x7ffffff0u;      // a buffer offset past every resource: a load there returns 0 and a store does nothing
 constexpr uint32_t kSmallTaskChunks = 4;       // a dependent task of at most this many chunks is published at once and waits in its workgroups

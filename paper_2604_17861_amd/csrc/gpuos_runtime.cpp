@@ -421,7 +421,8 @@ int pack_or_check(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_
       for (int d = 0; d < nd; ++d) elements *= ops[k].stride[d] != 0 ? (uint64_t)size[d] : 1u;
       reads += elements * dtype_size(ops[k].dtype);
     }
-    if (reads >= (rec.path == PATH_CONTIG && all_aligned ? kStreamBytes : kStreamRowBytes)) rec.rflags |= RF_STREAM;
+    const bool late = impl == GPUOS_IMPL_EXP || impl == GPUOS_IMPL_DIV || impl == GPUOS_IMPL_SUB_EXP;
+    if (reads >= (rec.path != PATH_CONTIG || !all_aligned ? kStreamRowBytes : late ? kStreamLargeBytes : kStreamBytes)) rec.rflags |= RF_STREAM;
     // Rows that are contiguous in every operand, or hold one scalar per row, under up to three outer
     // dims of any strides: 16-byte accesses whatever the row length and alignment are, as long as a
     // row holds a vector.  Operands of one dtype (a COPY may convert), scalars of any. 
@@ -620,7 +621,7 @@ int pack_or_check(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_
   // the dispatcher holds it back until what it waits for is done.
   const uint64_t row_bytes = (uint64_t)n * dtype_size(ops[0].dtype), total = row_bytes * (uint64_t)rows;
   const uint64_t most = (uint64_t)chunk_elems * 24, spread = total / (total < (8ull << 20) ? 128 : 64);
-  if (total >= kStreamBytes) rec.rflags |= RF_STREAM;
+  if (total >= (row_bytes <= 1024u ? kStreamLargeBytes : kStreamBytes)) rec.rflags |= RF_STREAM;
   uint64_t piece = total / 32;
   piece = piece < 16384 ? 16384 : piece < 32768 ? piece : 32768;
   if (spread > piece) piece = spread < most ? spread : most;

@@ -225,6 +225,27 @@ def long_softmax_rows_whole_and_not(code):
     return b.stream("long_softmax_rows_whole_and_not_%d" % code)
 
 
+def past_the_cache(code):
+    """Tasks on both sides of the 16 MB of inputs from which on they are read past the memory-side cache: reductions of short rows,
+    whole aligned vectors and not, and operators of some instructions over contiguous tensors, whose last vector is not whole."""
+    rng = np.random.default_rng(770 + code)
+    b = Builder()
+    es = 4 if code in (S.F32, S.I32) else 2
+    V = 16 // es
+    for size in (15 << 20, 17 << 20):
+        x = b.pool(values(rng, size // es + (1 << 12), code))
+        for n, lead in ((3 * V, 0), (64 * V, 0), (25 * V + 1, 0), (127 * V, 1)):
+            rows = size // es // n + 1
+            for name in ("SUM_LAST", "MAX_LAST", "MIN_LAST")[: 2 if n == 3 * V else 1]:
+                b.add(name, b.pool(np.zeros(rows, np.int32 if code == S.I32 else np.float32)), [x[lead: lead + rows * n].reshape(rows, n)])
+        if code != S.I32:
+            one, half = size // es + 3, size // es // 2 + 5
+            b.add("EXP", b.pool(np.zeros(one, x.dtype)), [x[:one]])
+            for name in ("DIV", "SUB_EXP"):
+                b.add(name, b.pool(np.zeros(half, x.dtype)), [x[:half], x[8 * V: 8 * V + half]])
+    return b.stream("past_the_cache_%d" % code)
+
+
 def large_gathers():
     """Gathered tasks of more elements than 1,024 of the gather path's regular chunks hold: a product
     with every other column of a matrix, and a stride-2 slice of 16-bit elements.  (A chunk never run

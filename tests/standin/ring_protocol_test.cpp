@@ -315,6 +315,7 @@ static void large_reads_are_marked() {
   gpuos_ctx* c = make(64);
   CHECK(gpuos_register_op(c, 40, GPUOS_IMPL_COPY, nullptr) == GPUOS_OK);
   CHECK(gpuos_register_op(c, 41, GPUOS_IMPL_SUM_LAST, nullptr) == GPUOS_OK);
+  CHECK(gpuos_register_op(c, 42, GPUOS_IMPL_EXP, nullptr) == GPUOS_OK);
   struct In { uint8_t dtype; int64_t s0, s1; uint64_t ptr; };
   auto marked = [&](uint16_t op, int64_t rows, int64_t cols, std::vector<In> in, uint8_t out_dtype) {
     gpuos_task t = add_task(op, 1);
@@ -348,6 +349,9 @@ static void large_reads_are_marked() {
   CHECK(marked(7, 1, M / 2, {{GPUOS_F32, M, 1, A}, {GPUOS_F32, M, 1, B}}, GPUOS_F32));
   CHECK(!marked(41, 1024, 1020, {{GPUOS_F32, 1020, 1, A}}, GPUOS_F32));
   CHECK(marked(41, 1024, 1024, {{GPUOS_F32, 1024, 1, A}}, GPUOS_F32));
+  // EXP, DIV and SUB_EXP, and reductions of rows of up to 64 vectors: from 16 MB on
+  CHECK(!marked(42, 1, 4 * M - 4, {{GPUOS_F32, M, 1, A}}, GPUOS_F32) && marked(42, 1, 4 * M, {{GPUOS_F32, M, 1, A}}, GPUOS_F32));
+  CHECK(!marked(41, 16383, 256, {{GPUOS_F32, 256, 1, A}}, GPUOS_F32) && marked(41, 16384, 256, {{GPUOS_F32, 256, 1, A}}, GPUOS_F32));
   // casts, by rows whatever their alignment: what is read counts
   CHECK(!marked(40, 1, M / 4 - 8, {{GPUOS_F32, M, 1, A}}, GPUOS_BF16));
   CHECK(marked(40, 1, M / 4, {{GPUOS_F32, M, 1, A}}, GPUOS_BF16));

@@ -206,3 +206,13 @@ def test_long_softmax_rows_are_whole_and_ragged_at_every_length(code):
     for vectors in seen.values():
         assert min(vectors) <= longest < max(vectors) and {longest, longest + 1} <= vectors
     run_oracle(s)
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16, S.I32])
+def test_tasks_past_the_cache(code):
+    s = E.past_the_cache(code)
+    assert not stream_extent_violations(s)
+    assert {p[0] for p in plans(s)} == ({"RED_CONTIG"} if code == S.I32 else {"RED_CONTIG", "CONTIG"})
+    read = sorted({int(np.prod(t["size"][:t["ndim"]])) * int(t["n_inputs"]) * S.ELEM_SIZE[code] for t in s.tasks})
+    assert read[0] < 16 << 20 < read[-1] and read[-1] < 18 << 20
+    run_oracle(s)

@@ -267,3 +267,9 @@ def test_long_softmax_rows_whole_and_not(code):
     """Whole aligned rows on both sides of every length at which more is kept of a row, and the same lengths at other alignments."""
     stats, _ = _run_and_check(E.long_softmax_rows_whole_and_not(code))
     print(stats, flush=True)
+
+
+@pytest.mark.parametrize("code", [S.F32, S.F16, S.BF16, S.I32])
+def test_tasks_past_the_cache(code):
+    stats, _ = _run_and_check(E.past_the_cache(code))
+    print(stats, flush=True)
