@@ -415,14 +415,16 @@ int pack_or_check(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_
       }
       if (ok) { rec.path = PATH_ROW2D; rec.rflags |= RF_VEC; }
     }
-    uint64_t reads = 0;                              // bytes of memory, what is broadcast counted once
-    for (int k = 0; k < ar; ++k) {
-      uint64_t elements = 1;
-      for (int d = 0; d < nd; ++d) elements *= ops[k].stride[d] != 0 ? (uint64_t)size[d] : 1u;
-      reads += elements * dtype_size(ops[k].dtype);
+    if ((uint64_t)numel * 4u * (uint64_t)ar >= kStreamRowBytes) {      // (it may be much; of small tasks nothing is counted)
+      uint64_t reads = 0;                            // bytes of memory, what is broadcast counted once
+      for (int k = 0; k < ar; ++k) {
+        uint64_t elements = 1;
+        for (int d = 0; d < nd; ++d) elements *= ops[k].stride[d] != 0 ? (uint64_t)size[d] : 1u;
+        reads += elements * dtype_size(ops[k].dtype);
+      }
+      const bool late = impl == GPUOS_IMPL_EXP || impl == GPUOS_IMPL_DIV || impl == GPUOS_IMPL_SUB_EXP;
+      if (reads >= (rec.path != PATH_CONTIG || !all_aligned ? kStreamRowBytes : late ? kStreamLargeBytes : kStreamBytes)) rec.rflags |= RF_STREAM;
     }
-    const bool late = impl == GPUOS_IMPL_EXP || impl == GPUOS_IMPL_DIV || impl == GPUOS_IMPL_SUB_EXP;
-    if (reads >= (rec.path != PATH_CONTIG || !all_aligned ? kStreamRowBytes : late ? kStreamLargeBytes : kStreamBytes)) rec.rflags |= RF_STREAM;
     // Rows that are contiguous in every operand, or hold one scalar per row, under up to three outer
     // dims of any strides: 16-byte accesses whatever the row length and alignment are, as long as a
     // row holds a vector.  Operands of one dtype (a COPY may convert), scalars of any. 
