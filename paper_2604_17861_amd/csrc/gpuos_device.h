@@ -63,7 +63,8 @@ namespace gpuos {
 // 282; EXP fp32 779 and 759; an interpreted addition 611 and 561; sums of 24 fp32 451 and 411, of 256 fp32 413 and 359, of 256 bf16 220 and
 // 189.  The 16 MB: on buffers used over and over EXP of 8 MB takes 22.5 us with it, 21.7 without, four of 16 MB 36.9 and
 // 37.9; DIV of 8 MB 21.2 and 20.7, of 64 MB 79.4 and 83.5.  ROW2D of 4 GB: 726 and 729 on every access, in tasks of 2 MB 487 and 479.
-// By rows, on stores too: rows of 2,049 fp32 less a scalar each 928 and 972, of 1,025 bf16 in tasks of 1 MB 378 and 371.
+// By rows, on stores too: rows of 2,049 fp32 less a scalar each 928 and 972, of 1,025 bf16 in tasks of 1 MB 378 and 371.  Gathered, on
+// every access: products with every third fp32 element 504 and 530, bf16 438 and 443; the gather's rounds would need two executors for it.
 // ---------------------------------------------------------------------------
 enum { POL_PLAIN = 0, POL_COHERENT = 1 };
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -1674,7 +1675,8 @@ template <int RIMPL, int K> DEV float red_join(float acc, const float (&x)[K]) {
   }
 }
 
-// Rows of 65 to 1,023 vectors, whatever their alignment.  A wavefront takes a share of the chunk's rows, which is one
+// Rows of more vectors than go by way of the LDS, whatever their alignment (1,024 and more where a chunk has more than 64 rows; else
+// those go by quarters).  A wavefront takes a share of the chunk's rows, which is one
 // dense run of memory, and reads it in groups of 64 vectors, four of them while it works on the four before; a row ends where
 // it ends, within a group, and that group is looked at once for either row.  Bound by memory latency: what counts is
 // that four to eight loads a lane are always in flight.  (Row by row, four rows' or one row's eight loads at a time and then
@@ -1829,7 +1831,7 @@ PATHFN void red_rows_quarter(RedArgs a) {
   __syncthreads();
 }
 
-// Rows of up to 448 vectors that are not whole aligned vectors.  A wavefront takes a share of the chunk's rows and reads it
+// Rows of up to 128 vectors, but for whole aligned ones of up to 64.  A wavefront takes a share of the chunk's rows and reads it
 // densely, as many whole rows at a time as 448 vectors hold, puts them into its part of the LDS and
 // requests the next; from there rows have no edges: P lanes a row, element by element.  Bound by memory latency: seven
 // loads a lane are in flight throughout.  (P lanes a row straight from memory, masked element by element at either end, 64 lanes
@@ -2036,7 +2038,7 @@ PATHFN void red_generic(const Record* r_v, uint32_t begin_v, uint32_t end_v, uin
 //     Up to 256 vectors a row is read once into the registers of the P lanes that own it
 //     (P = 64 for rows over 64 vectors, else the power of two >= vectors per row, 64 / P rows
 //     per wavefront pass), reduced with xor butterflies over those lanes, and written once; longer
-//     rows belong to the workgroup (rowop_wg, softmax_long).
+//     rows belong to the workgroup (rowop_wg, softmax_held, masked_softmax_long, layernorm_long).
 //   PATH_ROW_GENERIC: any strides and dtypes; one wavefront per row, three passes over memory.
 // Arithmetic is fp32.  Lanes outside a row feed the identity (-inf to the softmax, 0 to the
 // sums).  The softmax maximum ignores NaN; a NaN still poisons its row through the sum.
@@ -3816,7 +3818,7 @@ DEV bool next_unit(const WorkerArgs& a, WorkShared* s, uint32_t gen, uint32_t wa
   }
 }
 
-// A chunk that has been executed, to the completion of its task.  All it goes by lies in LDS.
+// A chunk that has been executed, to the completion of its task.  It goes by what lies in LDS and by the kernel's arguments.
 template <int RING>
 DEV void complete_unit(const WorkerArgs& a, WorkShared* s, int32_t status, uint32_t tid) {
   const bool leader = tid == 0;

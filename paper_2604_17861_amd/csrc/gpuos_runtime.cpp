@@ -528,8 +528,9 @@ int pack_or_check(const gpuos_task& t, uint32_t impl, Record* r, uint32_t chunk_
           for (int k = 0; k < ar; ++k) rec.stride[k][d] = d < lead ? 0u : (uint32_t)ops[k].stride[d - lead];
           rec.stride[3][d] = d < lead ? 0u : (uint32_t)out.stride[d - lead];
         }
-        // (slices with a step of two merge to one dim, whatever their rank: 16-byte loads of both halves beat the gather at
-        // every size, 52 and 61 us for products of 147 MB of fp32, 9.8 and 10.9 for one of 2,048 elements)
+        // (slices with a step of two merge to one dim where a row begins two elements behind the last one of the row before: 16-byte
+        // loads of both halves beat the gather at every size, 52 and 61 us for products of 147 MB of fp32, 9.8 and 10.9 for one of
+        // 2,048 elements; slices of odd widths, of parts of rows and integers stay with the gather or the generic walk)
         bool pairs = nd == 1 && same_dt;
         for (int k = 0; k < ar && pairs; ++k) pairs = ops[k].stride[0] == 1 || ops[k].stride[0] == 2;
         if (pairs) rec.rflags |= RF_PAIRS;
