@@ -133,7 +133,8 @@ class GpuosMode(TorchDispatchMode):
         self._writer = {}                # storage address -> newest pending ticket that writes it
         self._inflight = deque()         # (ticket, tensors kept alive, storage addresses)
         self._seen = {}                  # context filter: signature -> sightings
-        self._layouts = {}               # (result shape, inputs' shapes and strides) -> layout of an elementwise result
+        self._strided = False            # a tensor looked at since the last layout was asked for is not contiguous
+        self._layouts = {}               # (result shape, inputs' shapes and strides) -> layout of an elementwise result (at most 4,096)
         self._dirty = True               # PyTorch may have work in flight on its stream
         self.stats = dict(redirected=0, fallback_type=0, fallback_size=0, fallback_context=0, fallback_load=0,
                           fallback_paused=0, views=0, stream_syncs=0, host_waits=0, submits=0, pauses=0, resumes=0,
@@ -163,6 +164,7 @@ class GpuosMode(TorchDispatchMode):
         n = t.numel()
         if n < _MAX_EXTENT and t.is_contiguous():
             return True
+        self._strided = True
         # the ring record holds 32-bit element offsets: a quick bound, then the extent of the view itself
         return (max(t.stride()) * n < _MAX_EXTENT
                 or sum((k - 1) * st for k, st in zip(t.shape, t.stride())) < _MAX_EXTENT)
@@ -313,31 +315,32 @@ class GpuosMode(TorchDispatchMode):
             torch.cuda.current_stream(self.device).synchronize()
             self.stats["stream_syncs"] += 1
         self._dirty = False
-        layout = self._out_layout(p)
-        if layout is None:
-            out = torch.empty(p.out_shape, dtype=p.out_dtype, device=self.device)
-            self._stage(p, out, p.size, p.inputs, out)
-        else:                                            # described in the order of the result's dims in memory
-            stride, order = layout
-            out = torch.empty_strided(p.out_shape, stride, dtype=p.out_dtype, device=self.device)
-            self._stage(p, out, tuple(p.size[d] for d in order), [t.expand(p.size).permute(order) for t in p.inputs], out.permute(order))
+        layout = self._out_layout(p) if self._strided else None           # (of contiguous operands the result is contiguous)
+        out = (torch.empty(p.out_shape, dtype=p.out_dtype, device=self.device) if layout is None
+               else torch.empty_strided(p.out_shape, layout[0], dtype=p.out_dtype, device=self.device))
+        self._stage(p, out, layout)
         self.stats["redirected"] += 1
         self.stats["by_op"][p.impl] = self.stats["by_op"].get(p.impl, 0) + 1
         return out
 
     def _out_layout(self, p):
-        """The strides PyTorch gives an elementwise result and the order of its dims in memory (None: contiguous, as it is of
-        contiguous operands).  What PyTorch does with it next, a matrix product say, then runs on the layout it would have had."""
-        if p.reduce or p.impl == "SOFTMAX_LAST" or all(t.is_contiguous() for t in p.inputs):
+        """The strides PyTorch gives an elementwise result, and the task in the order of that result's dims in memory: its
+        size, the inputs' strides and the result's (None: contiguous).  What PyTorch does with the result next, a matrix
+        product say, then runs on the layout it would have had."""
+        self._strided = False
+        if p.reduce or p.impl == "SOFTMAX_LAST" or all([t.is_contiguous() for t in p.inputs]):
             return None
-        key = (p.size, *((t.shape, t.stride()) for t in p.inputs))
-        if key not in self._layouts:                     # (65 us: kept by shape and strides)
-            if len(self._layouts) >= 4096:
-                self._layouts.clear()
-            stride = tuple(compute_elementwise_output_strides(*(t.expand(p.size) for t in p.inputs)))
+        key = (p.size, *[(t.shape, t.stride()) for t in p.inputs])
+        layouts = self._layouts
+        if key not in layouts:                           # (65 us: kept by shapes and strides)
+            if len(layouts) >= 4096:
+                layouts.clear()
+            views = [t.expand(p.size) for t in p.inputs]
+            stride = tuple(compute_elementwise_output_strides(*views))
             order = sorted(range(len(stride)), key=lambda d: -stride[d])
-            self._layouts[key] = None if order == list(range(len(stride))) else (stride, order)
-        return self._layouts[key]
+            ordered = [(*(st[d] for d in order), *_ZEROS[len(order):]) for st in (*(v.stride() for v in views), stride)]
+            layouts[key] = None if order == list(range(len(stride))) else (stride, tuple(p.size[d] for d in order), ordered)
+        return layouts[key]
 
     def _room(self):
         if self._next is None:
@@ -368,16 +371,15 @@ class GpuosMode(TorchDispatchMode):
                 mask |= 1 << d
         return (ptr, *st, _DT[t.dtype], mask)
 
-    def _stage(self, p, out, size, inputs, result):
-        """p into `out`, as `result` from `inputs` over `size`: the same tensors, their dims in any order."""
-        size = size if size else (1,)                      # a 0-dim tensor iterates as [1]
+    def _stage(self, p, out, layout):
+        size = layout[1] if layout else p.size if p.size else (1,)      # a 0-dim tensor iterates as [1]
         nd = len(size)
         if p.reduce and nd == 1:
             size, nd = (1,) + size, 2                      # a vector reduces as one row
         me = (self._next if self._next is not None else 0) + self._staged
         writer, touch, cap = self._writer, self._touch, self.capacity
         deps, ops, keys = [], [], []
-        for t in inputs:
+        for t in p.inputs:
             ptr = t.data_ptr()
             k = ptr - t.storage_offset() * _ITEMSIZE[t.dtype]                # the storage's address
             w = writer.get(k)
@@ -387,7 +389,7 @@ class GpuosMode(TorchDispatchMode):
                     deps.append(d)
             touch[k] = me
             keys.append(k)
-            ops.append(self._operand(t, ptr, size, nd))
+            ops.append((ptr, *layout[2][len(ops)], _DT[t.dtype], 0) if layout else self._operand(t, ptr, size, nd))
         ko = out.data_ptr()                                 # freshly allocated: offset 0
         if p.reduce:
             # the output walks the outer dims (size[:-1]); it is freshly allocated and contiguous
@@ -397,8 +399,10 @@ class GpuosMode(TorchDispatchMode):
                 ost[d] = acc
                 acc *= size[d]
             o = (ko, *ost, _DT[out.dtype], 0)
+        elif layout:
+            o = (ko, *layout[2][-1], _DT[out.dtype], 0)
         else:
-            o = self._operand(result, ko, size, nd)
+            o = self._operand(out, ko, size, nd)
         while len(ops) < 3:
             ops.append(_NO_TENSOR)
         while len(deps) < 3:
